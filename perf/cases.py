@@ -205,3 +205,78 @@ def tolerance(case):
     if case["what"] == "rbd":
         return {"rel": 1e-6, "max": 4e-6}
     return {"rel": 5e-6, "max": 2e-4} if case["dtype"] == "f32" else {"rel": 1.4e-2, "max": 0.3}
+
+
+def _act64(name, h):
+    """act(h) and its derivative."""
+    if name == "identity":
+        return h, torch.ones_like(h)
+    if name == "gelu":
+        phi = torch.exp(-0.5 * h * h) / math.sqrt(2.0 * math.pi)
+        cdf = 0.5 * torch.erfc(-h / math.sqrt(2.0))
+        return h * cdf, cdf + h * phi
+    sig = torch.sigmoid(h)
+    return h * sig, sig * (1.0 + h * (1.0 - sig))
+
+
+def exact(case, seed):
+    """What run() returns for these inputs, in float64 throughout (routing included: where two logits are closer than
+    float32 can tell, a token may go elsewhere than run() sends it).  Whole-number outputs are left out."""
+    s, c = prepare(case, seed), case
+    T, d, E, k = (c[n] for n in ("T", "d", "E", "k"))
+    keep = torch.float64 if c["dtype"] == "f32" else torch.float32      # bf16 results need no more
+    w, x = s["w"], s["x"].double()
+    logits = x @ w["w_router"].double()
+    if w["bias"] is not None:
+        logits += w["bias"].double()
+    p = torch.softmax(logits, dim=1)
+    idx = torch.sort(logits, dim=1, descending=True, stable=True).indices[:, :k]
+    topk_w = p.gather(1, idx)
+    flat_e, flat_w = idx.reshape(-1), topk_w.reshape(-1)
+    order = torch.sort(flat_e, stable=True).indices                     # rows: flat entries by expert, stable
+    if c["what"] == "rbd":
+        return [{"combine_weights": flat_w[order]}, None, None, None, None]
+    ends = torch.cumsum(torch.bincount(flat_e, minlength=E), 0).tolist()
+    train = c["what"] == "train"
+    out, dx, dw = torch.zeros_like(x), torch.zeros_like(x), torch.zeros_like(flat_w)
+    dout = s["dout"].double() if train else None
+    names = ("w1", "w2") if c["expert"] == "mlp2" else ("wg", "wu", "wd")
+    grads = {"d" + n: torch.zeros(w[n].shape, dtype=keep, device="cuda") for n in names} if train else {}
+    for e in range(E + (c["E_s"] if c["expert"] != "mlp2" else 0)):
+        if e < E:
+            slot = order[(ends[e - 1] if e else 0):ends[e]]
+            if c["capacity"] and len(slot) > c["capacity"]:              # the heaviest ones stay, ties: lower slot
+                slot = slot[torch.sort(flat_w[slot], descending=True, stable=True).indices[:c["capacity"]]]
+            tok, scale = slot // k, flat_w[slot][:, None]
+        else:
+            tok, scale = torch.arange(T, device="cuda"), torch.ones((T, 1), dtype=torch.float64, device="cuda")
+        if len(tok) == 0:
+            continue
+        X = x[tok]
+        m = [w[n][e].double() for n in names]
+        first = [X @ a for a in m[:-1]]
+        if c["expert"] == "mlp2":
+            A, slope = _act64(c["act"], first[0])
+        else:
+            silu, slope = _act64("silu", first[0])
+            A = silu * first[1]
+        Y = A @ m[-1]
+        out.index_add_(0, tok, scale * Y)
+        if not train:
+            continue
+        if e < E:
+            dw[slot] = (dout[tok] * Y).sum(1)
+        dY = scale * dout[tok]
+        dA = dY @ m[-1].t()
+        back = [dA * slope] if c["expert"] == "mlp2" else [dA * first[1] * slope, dA * silu]
+        grads["d" + names[-1]][e] = A.t() @ dY
+        for n, a, b in zip(names, m, back):
+            grads["d" + n][e] = X.t() @ b
+            dx.index_add_(0, tok, b @ a.t())
+    if not train:
+        return [out.to(keep), None, topk_w]
+    inner = torch.zeros_like(p).scatter_(1, idx, dw.reshape(T, k))
+    dlogits = p * (inner - (p * inner).sum(1, keepdim=True))
+    grads["dw_router"] = (x.t() @ dlogits).to(keep)
+    dx += dlogits @ w["w_router"].double().t()
+    return [out.to(keep), dx.to(keep), grads, None, topk_w]
