@@ -136,15 +136,15 @@ GEMM_WORK = {
     "ffn_wgrad_dma_kernel<false>": "wgrad_wd", "ffn_wgrad_dma_kernel<true>": "wgrad_wg_wu",
     "ffn_bwd_rest_dma_kernel": "bwd_rest",
 }
-for _fam in ("mfma", "simt"):
+for _fam in ("mfma",):
     for _k in ("gateup", "down", "dact", "dx", "wgrad"):
         GEMM_WORK[f"ffn_{_k}_{_fam}_kernel"] = _k
 # the two-matrix expert shares the down, dX and weight-gradient kernels (two launches of the latter per step)
 GEMM_WORK_MLP2 = {
     "mlp2_up_dma_kernel": "up", "ffn_rowgemm_dma_kernel<false>": "down", "mlp2_dact_dma_kernel": "dact",
     "ffn_dx_dma_kernel": "dx", "ffn_wgrad_dma_kernel<false>": "wgrad", "ffn_bwd_rest_dma_kernel": "bwd_rest",
-    "mlp2_up_simt_kernel": "up", "ffn_down_simt_kernel": "down", "mlp2_dact_simt_kernel": "dact",
-    "ffn_dx_simt_kernel": "dx", "ffn_wgrad_simt_kernel": "wgrad",
+    "mlp2_up_mfma_kernel": "up", "ffn_down_mfma_kernel": "down", "mlp2_dact_mfma_kernel": "dact",
+    "ffn_dx_mfma_kernel": "dx", "ffn_wgrad_mfma_kernel": "wgrad",
 }
 
 def load_measured_traffic(workload):

@@ -37,11 +37,11 @@ const char* const kKernelNames[K_COUNT] = {
     "tile_map_kernel",
     "row_grad_reduce_kernel",
     "combine_bwd_weights_kernel",
-    "ffn_gateup_simt_kernel",
-    "ffn_down_simt_kernel",
-    "ffn_dact_simt_kernel",
-    "ffn_dx_simt_kernel",
-    "ffn_wgrad_simt_kernel",
+    "ffn_gateup_mfma_kernel",
+    "ffn_down_mfma_kernel",
+    "ffn_dact_mfma_kernel",
+    "ffn_dx_mfma_kernel",
+    "ffn_wgrad_mfma_kernel",
     "ffn_gateup_dma_kernel",
     "ffn_rowgemm_dma_kernel<false>",
     "ffn_rowgemm_dma_kernel<true>",
@@ -49,8 +49,8 @@ const char* const kKernelNames[K_COUNT] = {
     "ffn_wgrad_dma_kernel<false>",
     "ffn_wgrad_dma_kernel<true>",
     "ffn_bwd_rest_dma_kernel",
-    "mlp2_up_simt_kernel",
-    "mlp2_dact_simt_kernel",
+    "mlp2_up_mfma_kernel",
+    "mlp2_dact_mfma_kernel",
     "mlp2_up_dma_kernel",
     "mlp2_dact_dma_kernel",
     "rbd_mark_kernel",

@@ -52,8 +52,8 @@ int launch_tile_map(const int32_t* off, int E, int tile_rows, int max_tiles, int
 // row_grad[i] = sum over p < parts of row_part[p * B + i], p ascending (fixed order: the result is reproducible)
 int launch_row_grad_reduce(const float* row_part, int parts, int B, float* row_grad, hipStream_t s);
 
-int ffn_fwd_simt(const FfnArgs& a, hipStream_t s);
-int ffn_bwd_simt(const FfnArgs& a, hipStream_t s);
+int ffn_fwd_tile(const FfnArgs& a, hipStream_t s);
+int ffn_bwd_tile(const FfnArgs& a, hipStream_t s);
 
 // bf16 MFMA family (needs d % 64 == 0, f % 64 == 0 and 16-byte aligned operands): 256x256 tiles, operands streamed
 // global -> LDS directly, transposing LDS reads
@@ -61,8 +61,8 @@ bool ffn_dma_supported(const FfnArgs& a);
 int ffn_fwd_dma(const FfnArgs& a, hipStream_t s);
 int ffn_bwd_dma(const FfnArgs& a, hipStream_t s);
 
-int mlp2_fwd_simt(const Mlp2Args& a, hipStream_t s);
-int mlp2_bwd_simt(const Mlp2Args& a, hipStream_t s);
+int mlp2_fwd_tile(const Mlp2Args& a, hipStream_t s);
+int mlp2_bwd_tile(const Mlp2Args& a, hipStream_t s);
 bool mlp2_dma_supported(const Mlp2Args& a);
 int mlp2_fwd_dma(const Mlp2Args& a, hipStream_t s);
 int mlp2_bwd_dma(const Mlp2Args& a, hipStream_t s);

@@ -1,6 +1,6 @@
 // Entry points of the expert MLP (paper: Listing 1 mlp(); Appendix B.4): argument checks, workspace carve-up,
 // and the choice between the bf16 MFMA kernels (bf16 storage, d and f multiples of 64, 16-byte aligned operands)
-// and the float32-ALU kernels (everything else).
+// and the general tile kernels (everything else).
 
 #include "xmoe_ffn.h"
 
@@ -44,7 +44,7 @@ int xmoe_expert_ffn_fwd(const void* xd, const int32_t* row_index, const int32_t*
     a.act = p;
     hipStream_t s = (hipStream_t)stream;
     if (ffn_dma_supported(a)) return ffn_fwd_dma(a, s);
-    return ffn_fwd_simt(a, s);
+    return ffn_fwd_tile(a, s);
 }
 
 int xmoe_expert_ffn_bwd(const void* xd, const int32_t* row_index, const void* g_save, const void* u_save,
@@ -83,7 +83,7 @@ int xmoe_expert_ffn_bwd(const void* xd, const int32_t* row_index, const void* g_
     a.row_part = (float*)p;   // the partial sums are always written (the matrix-core kernel has no branch for them)
     hipStream_t s = (hipStream_t)stream;
     if (ffn_dma_supported(a)) return ffn_bwd_dma(a, s);
-    return ffn_bwd_simt(a, s);
+    return ffn_bwd_tile(a, s);
 }
 
 int xmoe_expert_mlp2_fwd(const void* xd, const int32_t* row_index, const int32_t* expert_offsets, int B, int E,
@@ -110,7 +110,7 @@ int xmoe_expert_mlp2_fwd(const void* xd, const int32_t* row_index, const int32_t
     a.a_buf = p;
     hipStream_t s = (hipStream_t)stream;
     if (mlp2_dma_supported(a)) return mlp2_fwd_dma(a, s);
-    return mlp2_fwd_simt(a, s);
+    return mlp2_fwd_tile(a, s);
 }
 
 int xmoe_expert_mlp2_bwd(const void* xd, const int32_t* row_index, const void* h_save, const void* dy,
@@ -146,7 +146,7 @@ int xmoe_expert_mlp2_bwd(const void* xd, const int32_t* row_index, const void* h
     a.row_part = (float*)p;   // always written, as for the SwiGLU expert
     hipStream_t s = (hipStream_t)stream;
     if (mlp2_dma_supported(a)) return mlp2_bwd_dma(a, s);
-    return mlp2_bwd_simt(a, s);
+    return mlp2_bwd_tile(a, s);
 }
 
 }  // extern "C"

@@ -1,0 +1,545 @@
+// Expert MLP over ragged segments (paper: Listing 1 mlp(); Appendix B.4 "Sequential GeMM"), general version: serves
+// float32 workloads and every bf16 shape the direct-to-LDS kernels do not take, on the tiles of xmoe_tile_gemm.h.
+// One launch covers every expert: a tile map built on the device says which expert and which rows each row tile
+// belongs to, so there is no host round trip on tokens_per_expert and no per-expert launch.
+//
+// Measured (MI355X, one training step of the layer; before: 4 x 4 outputs per thread on the float32 ALUs, 22 to 26
+// TFLOP/s for either type, bound by their LDS reads):
+//   float32 T 2048 d 1024 f 704, 16 experts + 1 shared, k 4:   5330 -> 1665 us, the products at 81 to 96 TFLOP/s of 157
+//   bf16    T 3001 d 1000 f 712, 24 experts + 1 shared, k 3:   6720 ->  670 us, the products at 200 to 290 TFLOP/s
+//   float32 T 256 d 128 f 64, 8 experts, k 2 (launch-bound):    203 ->  125 us
+#include "xmoe_ffn.h"
+#include "xmoe_tile_gemm.h"
+
+namespace xmoe {
+
+// ---------------------------------------------------------------------------------------------------------
+// tile map: header {total tiles, 0, 0, 0} then (expert, first row) per row tile; unused entries have expert -1.
+// sched: the experts sorted by descending row count (ties: lower index first), then kSchedCounters zeroed counters
+// (the weight-gradient kernels hand out their tiles longest first from these).
+// ---------------------------------------------------------------------------------------------------------
+__global__ __launch_bounds__(512) void tile_map_kernel(const int32_t* __restrict__ off, int E, int tile_rows,
+                                                       int max_tiles, int32_t* __restrict__ map,
+                                                       int32_t* __restrict__ sched) {
+    __shared__ int start[XMOE_MAX_EXPERTS + 1];
+    __shared__ int count[XMOE_MAX_EXPERTS];
+    const int e = threadIdx.x;
+    int nt = 0, lo = 0, m = 0;
+    if (e < E) {
+        lo = off[e];
+        m = off[e + 1] - lo;
+        nt = m > 0 ? (m + tile_rows - 1) / tile_rows : 0;
+        start[e] = nt;
+        count[e] = m;
+    }
+    __syncthreads();
+    if (e < E) {
+        int rank = 0;
+        for (int i = 0; i < E; ++i) {
+            const int c = count[i];
+            rank += (c > m || (c == m && i < e)) ? 1 : 0;
+        }
+        sched[rank] = e;
+    }
+    if (threadIdx.x < kSchedCounters) sched[E + threadIdx.x] = 0;
+    if (threadIdx.x == 0) {
+        int run = 0;
+        for (int i = 0; i < E; ++i) {
+            int v = start[i];
+            start[i] = run;
+            run += v;
+        }
+        start[E] = run < max_tiles ? run : max_tiles;
+        map[0] = start[E];
+        map[1] = map[2] = map[3] = 0;
+    }
+    __syncthreads();
+    if (e < E) {
+        for (int i = 0; i < nt; ++i) {
+            int ti = start[e] + i;
+            if (ti < max_tiles) {
+                map[4 + 2 * ti] = e;
+                map[4 + 2 * ti + 1] = lo + i * tile_rows;
+            }
+        }
+    }
+    for (int ti = start[E] + threadIdx.x; ti < max_tiles; ti += 512) {
+        map[4 + 2 * ti] = -1;
+        map[4 + 2 * ti + 1] = 0;
+    }
+}
+
+int launch_tile_map(const int32_t* off, int E, int tile_rows, int max_tiles, int32_t* map, int32_t* sched,
+                    hipStream_t s) {
+    XMOE_LAUNCH(K_TILE_MAP, s, hipLaunchKernelGGL(tile_map_kernel, dim3(1), dim3(512), 0, s, off, E, tile_rows,
+                                                  max_tiles, map, sched));
+    return XMOE_OK;
+}
+
+// row_grad[i] = sum_p row_part[p * B + i], p ascending
+__global__ __launch_bounds__(256) void row_grad_reduce_kernel(const float* __restrict__ row_part, int parts, int B,
+                                                              float* __restrict__ row_grad) {
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i >= B) return;
+    float s = 0.f;
+    for (int p = 0; p < parts; ++p) s += row_part[(size_t)p * B + i];
+    row_grad[i] = s;
+}
+
+int launch_row_grad_reduce(const float* row_part, int parts, int B, float* row_grad, hipStream_t s) {
+    if (B <= 0) return XMOE_OK;
+    XMOE_LAUNCH(K_ROW_GRAD_REDUCE, s,
+                hipLaunchKernelGGL(row_grad_reduce_kernel, dim3((B + 255) / 256), dim3(256), 0, s, row_part, parts, B,
+                                   row_grad));
+    return XMOE_OK;
+}
+
+// A row GEMM's block: its expert and rows from the tile map (blockIdx.x), its first output column (blockIdx.y).
+struct RowTile {
+    int e, row0, rows;   // rows: valid rows of the tile, may exceed the tile
+    __device__ __forceinline__ bool init(const int32_t* __restrict__ off, const int32_t* __restrict__ map) {
+        e = map[4 + 2 * blockIdx.x];
+        if (e < 0) return false;
+        row0 = map[4 + 2 * blockIdx.x + 1];
+        rows = off[e + 1] - row0;
+        return true;
+    }
+};
+
+#define XMOE_TILE_BOUNDS __launch_bounds__(TileShape<BIG>::kThreads, 2)
+
+// ---------------------------------------------------------------------------------------------------------
+// forward 1: G = Xd Wg, U = Xd Wu, A = silu(G) * U          rows: ragged, K = d, N = f
+// A block computes the same kN/2 columns of G and of U, so the rows are fetched once for both and A needs no exchange.
+// ---------------------------------------------------------------------------------------------------------
+template <typename T, bool BIG>
+__global__ XMOE_TILE_BOUNDS void ffn_gateup_mfma_kernel(const T* __restrict__ xd,
+                                                        const int32_t* __restrict__ row_index,   // or NULL
+                                                        const int32_t* __restrict__ off,
+                                                        const int32_t* __restrict__ map, int d, int f,
+                                                        const T* __restrict__ wg, const T* __restrict__ wu,
+                                                        T* __restrict__ G, T* __restrict__ U, T* __restrict__ A) {
+    using S = TileShape<BIG>;
+    __shared__ __align__(16) char smem[S::kLds];
+    RowTile t;
+    if (!t.init(off, map)) return;
+    const int n0 = blockIdx.y * (S::kN / 2);
+    RowSrc<T, S::kThreads> a;
+    ColSrc<T, S::kThreads, false> b;
+    a.init(row_index ? xd : xd + (size_t)t.row0 * d, d, t.rows, row_index ? row_index + t.row0 : nullptr);
+    b.init(wg + (size_t)t.e * d * f + n0, wu + (size_t)t.e * d * f + n0, f, f - n0, nullptr, d);
+    tile_f32x16_t acc[S::kMI][2];
+    tile_zero<BIG>(acc);
+    tile_mainloop<T, BIG, true>(acc, d, t.rows, f - n0, a, b, smem);
+    const int n = n0 + tile_col<BIG, true>(0);
+    if (n >= f) return;
+#pragma unroll
+    for (int mi = 0; mi < S::kMI; ++mi)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            const int r = tile_row<BIG>(mi, v);
+            if (r < t.rows) {
+                const size_t ix = (size_t)(t.row0 + r) * f + n;
+                const float g = acc[mi][0][v], u = acc[mi][1][v];
+                G[ix] = from_float<T>(g);
+                U[ix] = from_float<T>(u);
+                A[ix] = from_float<T>(siluf_(g) * u);
+            }
+        }
+}
+
+// stores a block's tile: C[(row0 + r) * ld + n] for r < rows, n < N
+template <typename T, bool BIG>
+__device__ __forceinline__ void tile_store(const tile_f32x16_t (&acc)[TileShape<BIG>::kMI][2], T* __restrict__ C,
+                                           size_t ld, int rows, int cols) {
+#pragma unroll
+    for (int ni = 0; ni < 2; ++ni) {
+        const int n = tile_col<BIG, false>(ni);
+        if (n >= cols) continue;
+#pragma unroll
+        for (int mi = 0; mi < TileShape<BIG>::kMI; ++mi)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int r = tile_row<BIG>(mi, v);
+                if (r < rows) C[(size_t)r * ld + n] = from_float<T>(acc[mi][ni][v]);
+            }
+    }
+}
+
+// ---------------------------------------------------------------------------------------------------------
+// forward 2: Y = A Wd                                       rows: ragged, K = f, N = d
+// ---------------------------------------------------------------------------------------------------------
+template <typename T, bool BIG>
+__global__ XMOE_TILE_BOUNDS void ffn_down_mfma_kernel(const T* __restrict__ A, const int32_t* __restrict__ off,
+                                                      const int32_t* __restrict__ map, int d, int f,
+                                                      const T* __restrict__ wd, T* __restrict__ Y) {
+    using S = TileShape<BIG>;
+    __shared__ __align__(16) char smem[S::kLds];
+    RowTile t;
+    if (!t.init(off, map)) return;
+    const int n0 = blockIdx.y * S::kN;
+    RowSrc<T, S::kThreads> a;
+    ColSrc<T, S::kThreads, false> b;
+    a.init(A + (size_t)t.row0 * f, f, t.rows, nullptr);
+    b.init(wd + (size_t)t.e * f * d + n0, nullptr, d, d - n0, nullptr, f);
+    tile_f32x16_t acc[S::kMI][2];
+    tile_zero<BIG>(acc);
+    tile_mainloop<T, BIG, false>(acc, f, t.rows, d - n0, a, b, smem);
+    tile_store<T, BIG>(acc, Y + (size_t)t.row0 * d + n0, d, t.rows, d - n0);
+}
+
+// ---------------------------------------------------------------------------------------------------------
+// backward 1: dA = dY W^T (W = Wd or W2), K = d, N = f; row r of dY is dy_scale[r] * dY[dy_index[r]], the scale follows
+// in the epilogue.  EPI(i, ix, da, sc): the element ix of the [B,f] arrays from the unscaled da; it returns this
+// element's share of <unscaled dY row, Y row>, whose sum over the wave's 64 columns goes to row_part (one part per
+// 64 columns).
+// ---------------------------------------------------------------------------------------------------------
+template <typename T, bool BIG, class Prefetch, class Epi>
+__device__ __forceinline__ void dact_tile(const T* __restrict__ dY, const int32_t* __restrict__ dy_index,
+                                          const float* __restrict__ dy_scale, const int32_t* __restrict__ off,
+                                          const int32_t* __restrict__ map, int d, int f, const T* __restrict__ w,
+                                          float* __restrict__ row_part, int B, Prefetch prefetch, Epi epi) {
+    using S = TileShape<BIG>;
+    __shared__ __align__(16) char smem[S::kLds];
+    RowTile t;
+    if (!t.init(off, map)) return;
+    const int n0 = blockIdx.y * S::kN;
+    RowSrc<T, S::kThreads> a, b;
+    a.init(dy_index ? dY : dY + (size_t)t.row0 * d, d, t.rows, dy_index ? dy_index + t.row0 : nullptr);
+    b.init(w + ((size_t)t.e * f + n0) * d, d, f - n0, nullptr);
+    tile_f32x16_t acc[S::kMI][2];
+    tile_zero<BIG>(acc);
+    tile_mainloop<T, BIG, false>(acc, d, t.rows, f - n0, a, b, smem);
+    const bool scaled = dy_index && dy_scale;
+#pragma unroll
+    for (int mi = 0; mi < S::kMI; ++mi) {
+        float part[16], sc[16];
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            part[v] = 0.f;
+            const int r = tile_row<BIG>(mi, v);
+            sc[v] = scaled ? dy_scale[t.row0 + (r < t.rows ? r : t.rows - 1)] : 1.0f;
+        }
+#pragma unroll
+        for (int ni = 0; ni < 2; ++ni) {
+            const int n = n0 + tile_col<BIG, false>(ni);
+            const int nc = n < f ? n : f - 1;
+            // the 16 elements' inputs in one batch, at clamped addresses: no branch stands between the loads
+            float in0[16], in1[16];
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int r = tile_row<BIG>(mi, v);
+                prefetch((size_t)(t.row0 + (r < t.rows ? r : t.rows - 1)) * f + nc, in0[v], in1[v]);
+            }
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int r = tile_row<BIG>(mi, v);
+                if (r < t.rows && n < f)
+                    part[v] += epi((size_t)(t.row0 + r) * f + n, acc[mi][ni][v], sc[v], in0[v], in1[v]);
+            }
+        }
+        const float sum = tile_sum_over_cols(part);
+        const int lane = threadIdx.x & 63;
+        // the lane's v is not a compile-time constant here
+        const int r = tile_row<BIG>(mi, 0) + 8 * (((lane >> 1) & 15) >> 2) + (((lane >> 1) & 15) & 3);
+        const int p = blockIdx.y * (S::kN / 64) + tile_col_base<BIG, false>(0) / 64;
+        if (!(lane & 1) && r < t.rows && p * 64 < f) row_part[(size_t)p * B + t.row0 + r] = sum;
+    }
+}
+
+// dG = dA * U * silu'(G), dU = dA * silu(G), A = silu(G) * U
+template <typename T, bool BIG>
+__global__ XMOE_TILE_BOUNDS void ffn_dact_mfma_kernel(const T* __restrict__ dY,
+                                                      const int32_t* __restrict__ dy_index,   // or NULL
+                                                      const float* __restrict__ dy_scale,     // or NULL
+                                                      const int32_t* __restrict__ off,
+                                                      const int32_t* __restrict__ map, int d, int f,
+                                                      const T* __restrict__ wd, const T* __restrict__ G,
+                                                      const T* __restrict__ U, T* __restrict__ dG,
+                                                      T* __restrict__ dU, T* __restrict__ A,
+                                                      float* __restrict__ row_part, int B) {
+    dact_tile<T, BIG>(
+        dY, dy_index, dy_scale, off, map, d, f, wd, row_part, B,
+        [&](size_t ix, float& g, float& u) { g = to_float(G[ix]); u = to_float(U[ix]); },
+        [&](size_t ix, float da0, float sc, float g, float u) {
+            const float da = da0 * sc;
+            const float sg = sigmoidf_(g);
+            const float sl = g * sg;
+            dG[ix] = from_float<T>(da * u * (sg * (1.0f + g * (1.0f - sg))));
+            dU[ix] = from_float<T>(da * sl);
+            A[ix] = from_float<T>(sl * u * sc);   // scaled: the weight gradient multiplies it with unscaled rows
+            return da0 * (sl * u);
+        });
+}
+
+// two-matrix expert: dH = dA * act'(H), A = act(H)
+template <typename T, int ACT, bool BIG>
+__global__ XMOE_TILE_BOUNDS void mlp2_dact_mfma_kernel(const T* __restrict__ dY,
+                                                       const int32_t* __restrict__ dy_index,   // or NULL
+                                                       const float* __restrict__ dy_scale,     // or NULL
+                                                       const int32_t* __restrict__ off,
+                                                       const int32_t* __restrict__ map, int d, int f,
+                                                       const T* __restrict__ w2, const T* __restrict__ H,
+                                                       T* __restrict__ dH, T* __restrict__ A,
+                                                       float* __restrict__ row_part, int B) {
+    dact_tile<T, BIG>(
+        dY, dy_index, dy_scale, off, map, d, f, w2, row_part, B,
+        [&](size_t ix, float& h, float& unused) { h = to_float(H[ix]); unused = 0.f; },
+        [&](size_t ix, float da0, float sc, float h, float) {
+            float a, g;
+            act_fwd_grad<ACT>(h, a, g);
+            dH[ix] = from_float<T>(da0 * sc * g);
+            A[ix] = from_float<T>(a * sc);
+            return da0 * a;
+        });
+}
+
+// ---------------------------------------------------------------------------------------------------------
+// backward 2: dXd = dG Wg^T + dU Wu^T                        rows: ragged, K = f (twice), N = d
+// ---------------------------------------------------------------------------------------------------------
+template <typename T, bool BIG>
+__global__ XMOE_TILE_BOUNDS void ffn_dx_mfma_kernel(const T* __restrict__ dG, const T* __restrict__ dU,
+                                                    const int32_t* __restrict__ off,
+                                                    const int32_t* __restrict__ map, int d, int f,
+                                                    const T* __restrict__ wg, const T* __restrict__ wu,
+                                                    T* __restrict__ dXd) {
+    using S = TileShape<BIG>;
+    __shared__ __align__(16) char smem[S::kLds];
+    RowTile t;
+    if (!t.init(off, map)) return;
+    const int n0 = blockIdx.y * S::kN;
+    tile_f32x16_t acc[S::kMI][2];
+    tile_zero<BIG>(acc);
+    for (int set = 0; set < (dU ? 2 : 1); ++set) {   // the two-matrix expert has a single pair (dH, W1)
+        RowSrc<T, S::kThreads> a, b;
+        a.init((set ? dU : dG) + (size_t)t.row0 * f, f, t.rows, nullptr);
+        b.init((set ? wu : wg) + ((size_t)t.e * d + n0) * f, f, d - n0, nullptr);
+        tile_mainloop<T, BIG, false>(acc, f, t.rows, d - n0, a, b, smem);
+    }
+    tile_store<T, BIG>(acc, dXd + (size_t)t.row0 * d + n0, d, t.rows, d - n0);
+}
+
+// ---------------------------------------------------------------------------------------------------------
+// weight gradients: dW_e[m,n] = sum over the expert's rows r of P[r,m] * Q[r,n]   (K = ragged)
+//   dWd = A^T dY (M=f, N=d);  dWg = Xd^T dG, dWu = Xd^T dU (M=d, N=f).  Empty experts get zeros.
+// All of a call's weight gradients are one launch: blockIdx.x tile, blockIdx.y matrix, blockIdx.z expert, the experts
+// with the most rows first (sched), so the long sums start early and only one tail of idle CUs is left.
+// ---------------------------------------------------------------------------------------------------------
+template <typename T>
+struct WgradJob {
+    const T *P, *Q;
+    const int32_t *p_index, *q_index;   // or NULL
+    int M, N, tiles_m;
+    T* dW;
+};
+template <typename T>
+struct WgradJobs {
+    WgradJob<T> job[3];
+};
+
+template <typename T, bool BIG, bool GP, bool GQ>
+__device__ __forceinline__ void wgrad_tile(const WgradJob<T>& j, int e, int lo, int K, char* smem) {
+    using S = TileShape<BIG>;
+    const int m0 = (blockIdx.x % j.tiles_m) * S::kM, n0 = (blockIdx.x / j.tiles_m) * S::kN;
+    ColSrc<T, S::kThreads, GP> a;
+    ColSrc<T, S::kThreads, GQ> b;
+    a.init(j.P + m0 + (GP ? 0 : (size_t)lo * j.M), nullptr, j.M, j.M - m0, GP ? j.p_index + lo : nullptr, K);
+    b.init(j.Q + n0 + (GQ ? 0 : (size_t)lo * j.N), nullptr, j.N, j.N - n0, GQ ? j.q_index + lo : nullptr, K);
+    tile_f32x16_t acc[S::kMI][2];
+    tile_zero<BIG>(acc);
+    tile_mainloop<T, BIG, false>(acc, K, j.M - m0, j.N - n0, a, b, smem);
+    tile_store<T, BIG>(acc, j.dW + (size_t)e * j.M * j.N + (size_t)m0 * j.N + n0, j.N, j.M - m0, j.N - n0);
+}
+
+template <typename T, bool BIG>
+__global__ XMOE_TILE_BOUNDS void ffn_wgrad_mfma_kernel(WgradJobs<T> jobs, const int32_t* __restrict__ off,
+                                                       const int32_t* __restrict__ sched) {
+    __shared__ __align__(16) char smem[TileShape<BIG>::kLds];
+    const WgradJob<T> j = jobs.job[blockIdx.y];
+    const int e = sched[blockIdx.z];
+    const int lo = off[e], K = off[e + 1] - lo;
+    if (j.p_index)   // gathered rows on at most one side
+        wgrad_tile<T, BIG, true, false>(j, e, lo, K, smem);
+    else if (j.q_index)
+        wgrad_tile<T, BIG, false, true>(j, e, lo, K, smem);
+    else
+        wgrad_tile<T, BIG, false, false>(j, e, lo, K, smem);
+}
+
+// ---------------------------------------------------------------------------------------------------------
+// two-matrix expert, forward 1: H = Xd W1, A = act(H)         rows: ragged, K = d, N = f
+// ---------------------------------------------------------------------------------------------------------
+template <typename T, int ACT, bool BIG>
+__global__ XMOE_TILE_BOUNDS void mlp2_up_mfma_kernel(const T* __restrict__ xd,
+                                                     const int32_t* __restrict__ row_index,   // or NULL
+                                                     const int32_t* __restrict__ off,
+                                                     const int32_t* __restrict__ map, int d, int f,
+                                                     const T* __restrict__ w1, T* __restrict__ H,
+                                                     T* __restrict__ A) {
+    using S = TileShape<BIG>;
+    __shared__ __align__(16) char smem[S::kLds];
+    RowTile t;
+    if (!t.init(off, map)) return;
+    const int n0 = blockIdx.y * S::kN;
+    RowSrc<T, S::kThreads> a;
+    ColSrc<T, S::kThreads, false> b;
+    a.init(row_index ? xd : xd + (size_t)t.row0 * d, d, t.rows, row_index ? row_index + t.row0 : nullptr);
+    b.init(w1 + (size_t)t.e * d * f + n0, nullptr, f, f - n0, nullptr, d);
+    tile_f32x16_t acc[S::kMI][2];
+    tile_zero<BIG>(acc);
+    tile_mainloop<T, BIG, false>(acc, d, t.rows, f - n0, a, b, smem);
+#pragma unroll
+    for (int ni = 0; ni < 2; ++ni) {
+        const int n = n0 + tile_col<BIG, false>(ni);
+        if (n >= f) continue;
+#pragma unroll
+        for (int mi = 0; mi < S::kMI; ++mi)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int r = tile_row<BIG>(mi, v);
+                if (r < t.rows) {
+                    const size_t ix = (size_t)(t.row0 + r) * f + n;
+                    const float h = acc[mi][ni][v];
+                    H[ix] = from_float<T>(h);
+                    A[ix] = from_float<T>(act_fwd<ACT>(h));
+                }
+            }
+    }
+}
+
+// ---------------------------------------------------------------------------------------------------------
+// host-side drivers
+// ---------------------------------------------------------------------------------------------------------
+static inline int ceil_div(int a, int b) { return (a + b - 1) / b; }
+
+// Tile of a call's row GEMMs (the tile map is built for it): the big one when the experts' mean row count fills most of
+// it and there are enough blocks.  float32 wants a block for every CU, since its matrix products are long: whole steps
+// with the big | small tile at 96 blocks (T 512 d 1024 f 704 E 16+1) 780 | 681 us, at 264 blocks (T 4096 d 512 f 512
+// E 64) 1142 | 1231, at 480 (T 2048) 1665 | 1740.  bf16 gains from the big tile's fewer LDS and L2 reads earlier: 128
+// blocks (T 1024 d 1000 f 1000 E 8) 289 | 321, 192 blocks (T 1000 d 1000 f 712 E 24+1) 398 | 456, 564 blocks 664 | 1009.
+static inline bool big_tiles(int B, int E, int d, int f, int dt) {
+    const long long blocks = (long long)ceil_div(B, 128) * ceil_div(d < f ? d : f, 128);
+    return B >= 96 * E && blocks >= (dt == XMOE_F32 ? 256 : 96);
+}
+// Tile of the weight gradients: big when that still gives every CU two blocks (float32 and bf16: the steps above, whose
+// weight gradients have 450 to 3000 big tiles, and 384 | 1536 at T 3000 d 300 f 500 E 8: 448 | 416 us).
+static inline bool big_wgrad_tiles(int jobs, int E, int d, int f) {
+    return (long long)jobs * E * ceil_div(d, 128) * ceil_div(f, 128) >= 512;
+}
+
+template <typename T>
+static int launch_wgrad(WgradJobs<T> jobs, int n_jobs, int E, int d, int f, const int32_t* off, const int32_t* sched,
+                        hipStream_t s) {
+    const bool big = big_wgrad_tiles(n_jobs, E, d, f);
+    const int tile = big ? 128 : 64;
+    for (int i = 0; i < n_jobs; ++i) jobs.job[i].tiles_m = ceil_div(jobs.job[i].M, tile);
+    const dim3 grid(ceil_div(d, tile) * ceil_div(f, tile), n_jobs, E);
+    if (big)
+        XMOE_LAUNCH(K_FFN_WGRAD_MFMA, s, hipLaunchKernelGGL((ffn_wgrad_mfma_kernel<T, true>), grid, dim3(256), 0, s, jobs,
+                                                            off, sched));
+    else
+        XMOE_LAUNCH(K_FFN_WGRAD_MFMA, s, hipLaunchKernelGGL((ffn_wgrad_mfma_kernel<T, false>), grid, dim3(128), 0, s,
+                                                            jobs, off, sched));
+    return XMOE_OK;
+}
+
+template <typename T, bool BIG>
+static int fwd_tile(const FfnArgs& a, hipStream_t s) {
+    using S = TileShape<BIG>;
+    const int max_tiles = ffn_max_tiles(a.B, a.E, S::kM);
+    int st = launch_tile_map(a.off, a.E, S::kM, max_tiles, a.map, a.sched, s);
+    if (st != XMOE_OK) return st;
+    const dim3 g1(max_tiles, ceil_div(a.f, S::kN / 2)), g2(max_tiles, ceil_div(a.d, S::kN));
+    XMOE_LAUNCH(K_FFN_GATEUP_MFMA, s,
+                hipLaunchKernelGGL((ffn_gateup_mfma_kernel<T, BIG>), g1, dim3(S::kThreads), 0, s, (const T*)a.xd,
+                                   a.row_index, a.off, a.map, a.d, a.f, (const T*)a.wg, (const T*)a.wu, (T*)a.g,
+                                   (T*)a.u, (T*)a.act));
+    XMOE_LAUNCH(K_FFN_DOWN_MFMA, s,
+                hipLaunchKernelGGL((ffn_down_mfma_kernel<T, BIG>), g2, dim3(S::kThreads), 0, s, (const T*)a.act, a.off,
+                                   a.map, a.d, a.f, (const T*)a.wd, (T*)a.y));
+    return XMOE_OK;
+}
+
+template <typename T, bool BIG>
+static int bwd_tile(const FfnArgs& a, hipStream_t s) {
+    using S = TileShape<BIG>;
+    const int max_tiles = ffn_max_tiles(a.B, a.E, S::kM);
+    int st = launch_tile_map(a.off, a.E, S::kM, max_tiles, a.map, a.sched, s);
+    if (st != XMOE_OK) return st;
+    XMOE_LAUNCH(K_FFN_DACT_MFMA, s,
+                hipLaunchKernelGGL((ffn_dact_mfma_kernel<T, BIG>), dim3(max_tiles, ceil_div(a.f, S::kN)),
+                                   dim3(S::kThreads), 0, s, (const T*)a.dy, a.dy_index, a.dy_scale, a.off, a.map, a.d,
+                                   a.f, (const T*)a.wd, (const T*)a.g, (const T*)a.u, (T*)a.dg, (T*)a.du, (T*)a.act,
+                                   a.row_part, a.B));
+    if (a.row_grad) {
+        st = launch_row_grad_reduce(a.row_part, ceil_div(a.f, 64), a.B, a.row_grad, s);
+        if (st != XMOE_OK) return st;
+    }
+    XMOE_LAUNCH(K_FFN_DX_MFMA, s,
+                hipLaunchKernelGGL((ffn_dx_mfma_kernel<T, BIG>), dim3(max_tiles, ceil_div(a.d, S::kN)),
+                                   dim3(S::kThreads), 0, s, (const T*)a.dg, (const T*)a.du, a.off, a.map, a.d, a.f,
+                                   (const T*)a.wg, (const T*)a.wu, (T*)a.dxd));
+    WgradJobs<T> jobs = {{{(const T*)a.act, (const T*)a.dy, nullptr, a.dy_index, a.f, a.d, 0, (T*)a.dwd},
+                          {(const T*)a.xd, (const T*)a.dg, a.row_index, nullptr, a.d, a.f, 0, (T*)a.dwg},
+                          {(const T*)a.xd, (const T*)a.du, a.row_index, nullptr, a.d, a.f, 0, (T*)a.dwu}}};
+    return launch_wgrad<T>(jobs, 3, a.E, a.d, a.f, a.off, a.sched, s);
+}
+
+template <typename T, bool BIG>
+static int mlp2_fwd_tile(const Mlp2Args& a, hipStream_t s) {
+    using S = TileShape<BIG>;
+    const int max_tiles = ffn_max_tiles(a.B, a.E, S::kM);
+    int st = launch_tile_map(a.off, a.E, S::kM, max_tiles, a.map, a.sched, s);
+    if (st != XMOE_OK) return st;
+    const dim3 g1(max_tiles, ceil_div(a.f, S::kN)), g2(max_tiles, ceil_div(a.d, S::kN));
+#define XMOE_CALL(ACT)                                                                                               \
+    XMOE_LAUNCH(K_MLP2_UP_MFMA, s,                                                                                   \
+                hipLaunchKernelGGL((mlp2_up_mfma_kernel<T, ACT, BIG>), g1, dim3(S::kThreads), 0, s, (const T*)a.xd,  \
+                                   a.row_index, a.off, a.map, a.d, a.f, (const T*)a.w1, (T*)a.h, (T*)a.a_buf))
+    XMOE_DISPATCH_ACT(a.act, XMOE_CALL);
+#undef XMOE_CALL
+    XMOE_LAUNCH(K_FFN_DOWN_MFMA, s,
+                hipLaunchKernelGGL((ffn_down_mfma_kernel<T, BIG>), g2, dim3(S::kThreads), 0, s, (const T*)a.a_buf,
+                                   a.off, a.map, a.d, a.f, (const T*)a.w2, (T*)a.y));
+    return XMOE_OK;
+}
+
+template <typename T, bool BIG>
+static int mlp2_bwd_tile(const Mlp2Args& a, hipStream_t s) {
+    using S = TileShape<BIG>;
+    const int max_tiles = ffn_max_tiles(a.B, a.E, S::kM);
+    int st = launch_tile_map(a.off, a.E, S::kM, max_tiles, a.map, a.sched, s);
+    if (st != XMOE_OK) return st;
+    const dim3 g1(max_tiles, ceil_div(a.f, S::kN));
+#define XMOE_CALL(ACT)                                                                                                \
+    XMOE_LAUNCH(K_MLP2_DACT_MFMA, s,                                                                                  \
+                hipLaunchKernelGGL((mlp2_dact_mfma_kernel<T, ACT, BIG>), g1, dim3(S::kThreads), 0, s, (const T*)a.dy, \
+                                   a.dy_index, a.dy_scale, a.off, a.map, a.d, a.f, (const T*)a.w2, (const T*)a.h,     \
+                                   (T*)a.dh, (T*)a.a_buf, a.row_part, a.B))
+    XMOE_DISPATCH_ACT(a.act, XMOE_CALL);
+#undef XMOE_CALL
+    if (a.row_grad) {
+        st = launch_row_grad_reduce(a.row_part, ceil_div(a.f, 64), a.B, a.row_grad, s);
+        if (st != XMOE_OK) return st;
+    }
+    XMOE_LAUNCH(K_FFN_DX_MFMA, s,
+                hipLaunchKernelGGL((ffn_dx_mfma_kernel<T, BIG>), dim3(max_tiles, ceil_div(a.d, S::kN)),
+                                   dim3(S::kThreads), 0, s, (const T*)a.dh, (const T*)nullptr, a.off, a.map, a.d, a.f,
+                                   (const T*)a.w1, (const T*)nullptr, (T*)a.dxd));
+    WgradJobs<T> jobs = {{{(const T*)a.a_buf, (const T*)a.dy, nullptr, a.dy_index, a.f, a.d, 0, (T*)a.dw2},
+                          {(const T*)a.xd, (const T*)a.dh, a.row_index, nullptr, a.d, a.f, 0, (T*)a.dw1},
+                          {}}};
+    return launch_wgrad<T>(jobs, 2, a.E, a.d, a.f, a.off, a.sched, s);
+}
+
+// runs CALL<T, BIG>(a, s) for the call's element type and tile
+#define XMOE_TILE_CALL(CALL)                                                                       \
+    if (a.dt == XMOE_F32) return big_tiles(a.B, a.E, a.d, a.f, a.dt) ? CALL<float, true>(a, s) : CALL<float, false>(a, s); \
+    return big_tiles(a.B, a.E, a.d, a.f, a.dt) ? CALL<bf16_t, true>(a, s) : CALL<bf16_t, false>(a, s)
+
+int ffn_fwd_tile(const FfnArgs& a, hipStream_t s) { XMOE_TILE_CALL(fwd_tile); }
+int ffn_bwd_tile(const FfnArgs& a, hipStream_t s) { XMOE_TILE_CALL(bwd_tile); }
+int mlp2_fwd_tile(const Mlp2Args& a, hipStream_t s) { XMOE_TILE_CALL(mlp2_fwd_tile); }
+int mlp2_bwd_tile(const Mlp2Args& a, hipStream_t s) { XMOE_TILE_CALL(mlp2_bwd_tile); }
+
+}  // namespace xmoe

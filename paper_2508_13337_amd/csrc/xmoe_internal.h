@@ -29,11 +29,11 @@ enum KernelId : int {
     K_TILE_MAP,
     K_ROW_GRAD_REDUCE,
     K_COMBINE_BWD_W,
-    K_FFN_GATEUP_SIMT,
-    K_FFN_DOWN_SIMT,
-    K_FFN_DACT_SIMT,
-    K_FFN_DX_SIMT,
-    K_FFN_WGRAD_SIMT,
+    K_FFN_GATEUP_MFMA,
+    K_FFN_DOWN_MFMA,
+    K_FFN_DACT_MFMA,
+    K_FFN_DX_MFMA,
+    K_FFN_WGRAD_MFMA,
     K_FFN_GATEUP_DMA,
     K_FFN_DOWN_DMA,
     K_FFN_DACT_DMA,
@@ -41,8 +41,8 @@ enum KernelId : int {
     K_FFN_WGRAD_DMA,
     K_FFN_WGRAD_DUAL_DMA,
     K_FFN_BWD_REST_DMA,
-    K_MLP2_UP_SIMT,
-    K_MLP2_DACT_SIMT,
+    K_MLP2_UP_MFMA,
+    K_MLP2_DACT_MFMA,
     K_MLP2_UP_DMA,
     K_MLP2_DACT_DMA,
     K_RBD_MARK,

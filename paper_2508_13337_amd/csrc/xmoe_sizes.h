@@ -40,7 +40,7 @@ static inline size_t ffn_tilemap_bytes(int B, int E) {
 static inline size_t ffn_act_bytes(int B, int f, int dt) { return align_up((size_t)B * (size_t)f * dtype_size(dt), 256); }
 
 // partial sums of the per-row inner products <dY row, Y row> that the dAct kernels produce: one per row and per
-// 64 output columns of the matrix-core kernels' 256-column tiles (the float32-ALU kernels, 64-column tiles, use fewer)
+// 64 output columns of the matrix-core kernels' 256-column tiles (the general tiles use one per 64 columns of f)
 static inline int row_grad_parts(int f) { return (f + 255) / 256 * 4; }
 static inline size_t row_part_bytes(int B, int f) {
     return align_up((size_t)row_grad_parts(f) * (size_t)(B > 0 ? B : 1) * sizeof(float), 256);
