@@ -8,191 +8,204 @@ namespace xmoe {
 // =========================================================================================================
 // gate projection, fixed summation order
 // =========================================================================================================
-// One wave owns GT tokens x GE experts.  Lane l is partial sum l of the contract: it walks i = l, l+64, ...
-// and keeps GT*GE accumulators.  The 64 partials of every (token, expert) pair are then folded by halving
-// (lane l with lane l^32, then l^16, ...), which is the order the contract prescribes; the fold is done as a
-// transposing reduction so that lane v ends up with the finished sum of pair v.
-constexpr int kGT = 8;
-constexpr int kGE = 8;
-
-template <typename T>
-__device__ __forceinline__ void load_w8(const T* __restrict__ wrow, int e0, int E, bool vec, float (&wv)[kGE]);
-
+// The contract: partial l (0..63) of a (token, expert) pair absorbs i = l, l+64, ... in ascending order, one fused
+// multiply-add each; the 64 partials are folded by halving.  For one l that is a [tokens x d/64] x [d/64 x experts]
+// product whose terms are added one at a time, which is what the matrix instructions with K = 1 compute: one fused
+// multiply-add per output and instruction, with several independent blocks per instruction (v_mfma_f32_32x32x1_2b_f32,
+// v_mfma_f32_16x16x1_4b_f32).  The blocks take l, l+32 (TL = 32) or l, l+16, l+32, l+48 (TL = 16).  Same bits as the
+// plain loop, at four times the rate of the float32 ALUs without packed instructions.
+//
+//   block = 8 waves, TL tokens x TL experts.  Wave w owns the pairs l = 2(w%4) + {0, 1} + 8(w/4) (+ the blocks' offsets,
+//   + 16 for TL = 32), so that one LDS read of x serves two instructions; offsets 32 and 16 of the fold stay in
+//   registers, 8 to 1 go through LDS.  A stage is 32 KiB: 2 KiB of i per token and expert row, fetched one stage ahead
+//   through registers.  x past d reads +0 and w past d -0: their product -0 leaves every sum as it is, -0 included.
+//
+// Bound: TL = 32 by the matrix cores and the barriers between its stages (60 TFLOP/s), TL = 16 (few tokens) by the
+// latency of its stages.  Measured (MI355X, bf16, 64 experts, d 2048; before: float32 ALUs, operands staged through LDS
+// a 64-wide chunk at a time): T 8: 28 -> 9 us, T 509: 28 -> 11, T 8192: 50 -> 36, T 65536: 399 -> 287; d 1000, 24
+// experts, T 3001: 16 -> 9.
+typedef __attribute__((ext_vector_type(32))) float gate_f32x32_t;
+template <int TL>
+struct GateMma;
 template <>
-__device__ __forceinline__ void load_w8<float>(const float* __restrict__ wrow, int e0, int E, bool vec,
-                                               float (&wv)[kGE]) {
-    if (vec) {
-        const float4* p = reinterpret_cast<const float4*>(wrow + e0);
-        float4 a = p[0], b = p[1];
-        wv[0] = a.x; wv[1] = a.y; wv[2] = a.z; wv[3] = a.w;
-        wv[4] = b.x; wv[5] = b.y; wv[6] = b.z; wv[7] = b.w;
-    } else {
-#pragma unroll
-        for (int j = 0; j < kGE; ++j) wv[j] = (e0 + j < E) ? wrow[e0 + j] : 0.f;
+struct GateMma<32> {
+    typedef gate_f32x32_t Acc;
+    static __device__ __forceinline__ Acc mma(float a, float b, Acc c) {
+        return __builtin_amdgcn_mfma_f32_32x32x1f32(a, b, c, 0, 0, 0);
     }
-}
-
+    static __device__ __forceinline__ int row(int v) { return 8 * (v >> 2) + 4 * ((threadIdx.x >> 5) & 1) + (v & 3); }
+};
 template <>
-__device__ __forceinline__ void load_w8<bf16_t>(const bf16_t* __restrict__ wrow, int e0, int E, bool vec,
-                                                float (&wv)[kGE]) {
-    if (vec) {
-        uint4 q = *reinterpret_cast<const uint4*>(wrow + e0);
-        uint32_t u[4] = {q.x, q.y, q.z, q.w};
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            wv[2 * j] = __uint_as_float(u[j] << 16);
-            wv[2 * j + 1] = __uint_as_float(u[j] & 0xffff0000u);
-        }
-    } else {
-#pragma unroll
-        for (int j = 0; j < kGE; ++j) wv[j] = (e0 + j < E) ? to_float(wrow[e0 + j]) : 0.f;
+struct GateMma<16> {
+    typedef __attribute__((ext_vector_type(16))) float Acc;
+    static __device__ __forceinline__ Acc mma(float a, float b, Acc c) {
+        return __builtin_amdgcn_mfma_f32_16x16x1f32(a, b, c, 0, 0, 0);
     }
-}
+    static __device__ __forceinline__ int row(int v) { return 4 * ((threadIdx.x >> 4) & 3) + v; }
+};
 
+// 16 bytes from an address that is aligned to one element only
 template <typename T>
-__global__ __launch_bounds__(256) void gate_logits_kernel(const T* __restrict__ x, const T* __restrict__ w,
-                                                          const float* __restrict__ bias,
-                                                          float* __restrict__ logits, int Tn, int d, int E,
-                                                          int vec_w) {
-    const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
-    const int t0 = blockIdx.x * kGT;
-    const int e0 = (blockIdx.y * 4 + wave) * kGE;
-    if (e0 >= E) return;
-
-    float acc[kGT * kGE];
-#pragma unroll
-    for (int v = 0; v < kGT * kGE; ++v) acc[v] = 0.0f;
-
-    const T* xrow[kGT];
-#pragma unroll
-    for (int tt = 0; tt < kGT; ++tt) {
-        int t = t0 + tt;
-        t = t < Tn ? t : Tn - 1;
-        xrow[tt] = x + (size_t)t * d;
+struct __attribute__((packed, aligned(sizeof(T)))) GateVec {
+    uint32_t v[4];
+};
+__device__ __forceinline__ uint32_t gate_bits(float v) { return __float_as_uint(v); }
+__device__ __forceinline__ uint32_t gate_bits(bf16_t v) { return v.bits; }
+// the vector at p of which the first n elements exist; `fill` stands for the others
+template <typename T>
+__device__ __forceinline__ uint4 gate_load(const T* __restrict__ p, int n, uint32_t fill) {
+    constexpr int EV = 16 / sizeof(T);
+    if (n >= EV) {
+        const GateVec<T> q = *reinterpret_cast<const GateVec<T>*>(p);
+        return make_uint4(q.v[0], q.v[1], q.v[2], q.v[3]);
     }
-
-    for (int i = lane; i < d; i += 64) {
-        float wv[kGE];
-        load_w8<T>(w + (size_t)i * E, e0, E, vec_w != 0, wv);
-        float xv[kGT];
+    uint32_t s[4] = {0, 0, 0, 0};
 #pragma unroll
-        for (int tt = 0; tt < kGT; ++tt) xv[tt] = to_float(xrow[tt][i]);
-#pragma unroll
-        for (int tt = 0; tt < kGT; ++tt)
-#pragma unroll
-            for (int ee = 0; ee < kGE; ++ee) acc[tt * kGE + ee] = fmaf(xv[tt], wv[ee], acc[tt * kGE + ee]);
-    }
-
-    // fold the 64 lane partials of each of the 64 (token, expert) pairs: offsets 32, 16, 8, 4, 2, 1
-#pragma unroll
-    for (int width = 32; width >= 1; width >>= 1) {
-        const bool upper = (lane & width) != 0;
-#pragma unroll
-        for (int v = 0; v < width; ++v) {
-            float send = upper ? acc[v] : acc[v + width];
-            float keep = upper ? acc[v + width] : acc[v];
-            float recv = __shfl_xor(send, width, 64);
-            acc[v] = keep + recv;
-        }
-    }
-    // lane v now holds pair v = tt*kGE + ee
-    const int t = t0 + (lane / kGE);
-    const int e = e0 + (lane % kGE);
-    if (t < Tn && e < E) {
-        float v = acc[0];
-        if (bias) v = v + bias[e];
-        logits[(size_t)t * E + e] = v;
-    }
+    for (int j = 0; j < EV; ++j) s[j * 4 / EV] |= (j < n ? gate_bits(p[j]) : fill) << (EV == 8 ? 16 * (j & 1) : 0);
+    return make_uint4(s[0], s[1], s[2], s[3]);
 }
 
-// The same sums for bf16 operands whose rows are 16-byte aligned and d % 64 == 0, with the operands staged through
-// LDS.  In the kernel above a wave's load of w touches 64 different 128-byte lines for 1 KiB of data (lane l reads
-// 16 bytes of row l), four waves of a block do that side by side, and every wave fetches the same x values again: the
-// L1, not the float32 pipe, sets the pace.  Here the block fetches each 64-row chunk of w (its 32 experts: 64 bytes
-// per row) and of x (its 8 tokens) once, coalesced, a chunk ahead through registers, and a lane reads its row of w
-// and its 8 token values with two 16-byte LDS reads.  Work split, accumulation order and the fold are those of the
-// kernel above, so the results are the same bits.
-constexpr int kGWStride = 80;   // bytes per staged row of w: 4 x 16 bytes + 16 bytes of padding
+// what stands past d: +0 for x, -0 for w in bf16 and in float32
+__device__ __align__(16) const uint32_t kGatePad[12] = {0, 0, 0, 0, 0x80008000u, 0x80008000u, 0x80008000u, 0x80008000u,
+                                                        0x80000000u, 0x80000000u, 0x80000000u, 0x80000000u};
+// explicitly global, whichever of the two a lane reads: a flat load would count as an LDS access as well
+typedef const __attribute__((address_space(1))) char* gate_gptr;
+template <typename T>
+__device__ __forceinline__ uint4 gate_load16(gate_gptr p) {
+    const auto* q = reinterpret_cast<const __attribute__((address_space(1))) GateVec<T>*>(p);
+    return make_uint4(q->v[0], q->v[1], q->v[2], q->v[3]);
+}
 
-__global__ __launch_bounds__(256) void gate_logits_lds_kernel(const bf16_t* __restrict__ x,
-                                                              const bf16_t* __restrict__ w,
-                                                              const float* __restrict__ bias,
-                                                              float* __restrict__ logits, int Tn, int d, int E) {
-    __shared__ __align__(16) char sw[2][64 * kGWStride];   // [i][32 experts]
-    __shared__ __align__(16) char sx[2][64 * 16];          // [i][8 tokens]
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int t0 = blockIdx.x * kGT;
-    const int eb = blockIdx.y * 4 * kGE;
-    // staging roles: w row tid/4, 16-byte piece tid%4;  x token tid/32, elements 2*(tid%32) and the next
-    const int wr = tid >> 2, wpiece = tid & 3;
-    const bool w_ok = eb + kGE * wpiece < E;
-    const int xt = tid >> 5, xi = 2 * (tid & 31);
-    int tok = t0 + xt;
-    tok = tok < Tn ? tok : Tn - 1;
-    const bf16_t* xp = x + (size_t)tok * d + xi;
-    const bf16_t* wp = w + (size_t)wr * E + eb + kGE * wpiece;
-    uint4 wq = make_uint4(0, 0, 0, 0);
-    uint32_t xq;
+__device__ __forceinline__ void gate_pair(const bf16_t* p, float& a, float& b) {
+    const uint32_t u = *reinterpret_cast<const uint32_t*>(p);
+    a = __uint_as_float(u << 16);
+    b = __uint_as_float(u & 0xffff0000u);
+}
+__device__ __forceinline__ void gate_pair(const float* p, float& a, float& b) {
+    const float2 v = *reinterpret_cast<const float2*>(p);
+    a = v.x;
+    b = v.y;
+}
+
+// TL = 32 from this many of its blocks on: one per CU.  Below, tiles of a quarter of the size spread over more of the
+// chip, and a stage is twice as deep.
+constexpr long kGateBigBlocks = 256;
+
+template <typename T, int TL, bool VEC>
+__global__ __launch_bounds__(512, 2) void gate_logits_kernel(const T* __restrict__ x, const T* __restrict__ w,
+                                                             const float* __restrict__ bias,
+                                                             float* __restrict__ logits, int Tn, int d, int E) {
+    using M = GateMma<TL>;
+    constexpr int EV = 16 / sizeof(T);
+    constexpr int NBLK = 64 / TL, NJ = TL / 16;            // blocks per instruction; values of l per wave and parity
+    constexpr int CH = 16384 / (TL * 64 * (int)sizeof(T)); // 64-wide chunks of i per stage
+    constexpr int KI = CH * 64;
+    constexpr int VX = KI / EV, VW = TL / EV;              // vectors per row of x, of w
+    constexpr int XS = KI + EV;                            // elements per staged token
+    static_assert(TL * VX == 1024 && KI * VW == 1024, "two vectors of either operand per thread");
+    constexpr int kXBytes = TL * XS * (int)sizeof(T);
+    constexpr int kStage = kXBytes + 16384;
+    __shared__ __align__(16) char smem[2 * kStage];
+    static_assert(2 * kStage >= 16 * TL * TL * 4, "the fold reuses the stages");
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int t0 = blockIdx.x * TL, e0 = blockIdx.y * TL;
+    const int b = lane / TL, c = lane % TL;
+
+    uint4 rx[2], rw[2];
     auto fetch = [&](int i0) {
-        if (w_ok) wq = *reinterpret_cast<const uint4*>(wp + (size_t)i0 * E);
-        xq = *reinterpret_cast<const uint32_t*>(xp + i0);
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const int v = tid + 512 * q;
+            int t = t0 + v / VX;
+            t = t < Tn ? t : Tn - 1;      // rows past the last one repeat it; what they give is not stored
+            const int ix = i0 + (v % VX) * EV, iw = i0 + v / VW, e = e0 + (v % VW) * EV;
+            if (VEC) {   // no vector straddles an end: those past it come from the pad
+                const gate_gptr px = (gate_gptr)(const char*)(x + (size_t)t * d + ix);
+                const gate_gptr pw = (gate_gptr)(const char*)(w + (size_t)iw * E + (e < E ? e : 0));
+                rx[q] = gate_load16<T>(ix < d ? px : (gate_gptr)(const char*)kGatePad);
+                rw[q] = gate_load16<T>(iw < d ? pw : (gate_gptr)(const char*)(kGatePad + (sizeof(T) == 2 ? 4 : 8)));
+            } else {
+                rx[q] = gate_load(x + (size_t)t * d + ix, d - ix, 0u);
+                rw[q] = gate_load(w + (size_t)iw * E + e, iw < d ? E - e : 0, sizeof(T) == 2 ? 0x8000u : 0x80000000u);
+            }
+        }
     };
     auto stage = [&](int buf) {
-        *reinterpret_cast<uint4*>(sw[buf] + wr * kGWStride + wpiece * 16) = wq;
-        *reinterpret_cast<uint16_t*>(sx[buf] + xi * 16 + xt * 2) = (uint16_t)(xq & 0xffffu);
-        *reinterpret_cast<uint16_t*>(sx[buf] + (xi + 1) * 16 + xt * 2) = (uint16_t)(xq >> 16);
+        T* sx = reinterpret_cast<T*>(smem + buf * kStage);
+        T* sw = reinterpret_cast<T*>(smem + buf * kStage + kXBytes);
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const int v = tid + 512 * q;
+            *reinterpret_cast<uint4*>(sx + (v / VX) * XS + (v % VX) * EV) = rx[q];
+            *reinterpret_cast<uint4*>(sw + v * EV) = rw[q];
+        }
     };
 
-    float acc[kGT * kGE];
+    typename M::Acc acc[NJ][2];
 #pragma unroll
-    for (int v = 0; v < kGT * kGE; ++v) acc[v] = 0.0f;
+    for (int j = 0; j < NJ; ++j)
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+#pragma unroll
+            for (int v = 0; v < 16 * NJ; ++v) acc[j][s][v] = 0.f;
 
-    const int chunks = d / 64;
+    const int l0 = 2 * (wave & 3) + 8 * (wave >> 2);
+    auto multiply = [&](int g) {
+        const T* sx = reinterpret_cast<const T*>(smem + (g & 1) * kStage) + c * XS + TL * b + l0;
+        const T* sw = reinterpret_cast<const T*>(smem + (g & 1) * kStage + kXBytes) + (TL * b + l0) * TL + c;
+        auto chunk = [&](int q) {
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) {
+                float a[2];
+                gate_pair(sx + q * 64 + 16 * j, a[0], a[1]);
+#pragma unroll
+                for (int s = 0; s < 2; ++s)
+                    acc[j][s] = M::mma(a[s], to_float(sw[(q * 64 + 16 * j + s) * TL]), acc[j][s]);
+            }
+        };
+        // unrolled: the reads of later chunks run under the matrix instructions of earlier ones
+#pragma unroll
+        for (int q = 0; q < CH; ++q) chunk(q);
+    };
+    const int stages = (d + KI - 1) / KI;
     fetch(0);
     stage(0);
     __syncthreads();
-    for (int c = 0; c < chunks; ++c) {
-        const int buf = c & 1;
-        if (c + 1 < chunks) fetch((c + 1) * 64);
-        const uint4 wv4 = *reinterpret_cast<const uint4*>(sw[buf] + lane * kGWStride + wave * 16);
-        const uint4 xv4 = *reinterpret_cast<const uint4*>(sx[buf] + lane * 16);
-        const uint32_t wu[4] = {wv4.x, wv4.y, wv4.z, wv4.w}, xu[4] = {xv4.x, xv4.y, xv4.z, xv4.w};
-        float wv[kGE], xv[kGT];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            wv[2 * j] = __uint_as_float(wu[j] << 16);
-            wv[2 * j + 1] = __uint_as_float(wu[j] & 0xffff0000u);
-            xv[2 * j] = __uint_as_float(xu[j] << 16);
-            xv[2 * j + 1] = __uint_as_float(xu[j] & 0xffff0000u);
-        }
-#pragma unroll
-        for (int tt = 0; tt < kGT; ++tt)
-#pragma unroll
-            for (int ee = 0; ee < kGE; ++ee) acc[tt * kGE + ee] = fmaf(xv[tt], wv[ee], acc[tt * kGE + ee]);
-        if (c + 1 < chunks) stage(buf ^ 1);
-        // the chunk staged above is read after this barrier, and the buffer it went to was last read before the
-        // barrier of the previous round
+    for (int g = 0; g < stages; ++g) {
+        fetch((g + 1) * KI);   // past the last stage: nothing but pad
+        __builtin_amdgcn_sched_barrier(0);   // the loads stay in front of the matrix instructions they run under
+        multiply(g);
+        stage((g + 1) & 1);
+        // the stage written above is read after this barrier; its buffer was last read before the previous one
         __syncthreads();
     }
 
+    // fold: offset 32 between the blocks, 16 between the blocks (TL = 16) or the j (TL = 32), then 8, 4, 2, 1 over the
+    // waves' sums red[l][token][expert], l = 0..15
+    float* red = reinterpret_cast<float*>(smem);
+    constexpr int NV = TL * TL / 64;
 #pragma unroll
-    for (int width = 32; width >= 1; width >>= 1) {
-        const bool upper = (lane & width) != 0;
+    for (int s = 0; s < 2; ++s)
 #pragma unroll
-        for (int v = 0; v < width; ++v) {
-            float send = upper ? acc[v] : acc[v + width];
-            float keep = upper ? acc[v + width] : acc[v];
-            float recv = __shfl_xor(send, width, 64);
-            acc[v] = keep + recv;
+        for (int v = 0; v < NV; ++v) {
+            float p;
+            if (TL == 32)
+                p = (acc[0][s][v] + acc[0][s][NV + v]) + (acc[NJ - 1][s][v] + acc[NJ - 1][s][NV + v]);
+            else
+                p = (acc[0][s][v] + acc[0][s][2 * NV + v]) + (acc[0][s][NV + v] + acc[0][s][(3 * NV + v) & (16 * NJ - 1)]);
+            red[((l0 + s) * TL + M::row(v)) * TL + c] = p;
         }
-    }
-    const int t = t0 + (lane / kGE);
-    const int e = eb + wave * kGE + (lane % kGE);
-    if (t < Tn && e < E) {
-        float v = acc[0];
-        if (bias) v = v + bias[e];
-        logits[(size_t)t * E + e] = v;
+    __syncthreads();
+    for (int o = tid; o < TL * TL; o += 512) {
+        float p[16];
+#pragma unroll
+        for (int l = 0; l < 16; ++l) p[l] = red[l * TL * TL + o];
+#pragma unroll
+        for (int off = 8; off >= 1; off >>= 1)
+#pragma unroll
+            for (int l = 0; l < off; ++l) p[l] = p[l] + p[l + off];
+        const int t = t0 + o / TL, e = e0 + o % TL;
+        if (t < Tn && e < E) logits[(size_t)t * E + e] = bias ? p[0] + bias[e] : p[0];
     }
 }
 
@@ -771,17 +784,21 @@ __global__ __launch_bounds__(256) void gate_bwd_dx_mfma_kernel(const float* __re
 template <typename T>
 static int launch_gate_logits(const void* x, const void* w, const float* bias, float* logits, int Tn, int d,
                               int E, hipStream_t s) {
-    int vec = (E % kGE == 0) && aligned16(w) && ((E * sizeof(T)) % 16 == 0);
-    dim3 grid((Tn + kGT - 1) / kGT, (E + 4 * kGE - 1) / (4 * kGE));
-    if (sizeof(T) == 2 && vec && d % 64 == 0 && (reinterpret_cast<uintptr_t>(x) & 3u) == 0) {
-        XMOE_LAUNCH(K_GATE_LOGITS, s,
-                    hipLaunchKernelGGL(gate_logits_lds_kernel, grid, dim3(256), 0, s, (const bf16_t*)x,
-                                       (const bf16_t*)w, bias, logits, Tn, d, E));
-        return XMOE_OK;
+    const long blocks32 = (long)((Tn + 31) / 32) * ((E + 31) / 32);
+    // whole 16-byte vectors in either operand: no load needs a branch, and a stage's loads are in flight together
+    const bool vec = d % (16 / (int)sizeof(T)) == 0 && E % (16 / (int)sizeof(T)) == 0;
+#define XMOE_GATE(TL, VEC)                                                                                              \
+    XMOE_LAUNCH(K_GATE_LOGITS, s,                                                                                       \
+                hipLaunchKernelGGL((gate_logits_kernel<T, TL, VEC>), dim3((Tn + TL - 1) / TL, (E + TL - 1) / TL), dim3(512), \
+                                   0, s, (const T*)x, (const T*)w, bias, logits, Tn, d, E))
+    if (blocks32 >= kGateBigBlocks) {
+        if (vec) XMOE_GATE(32, true);
+        else XMOE_GATE(32, false);
+    } else {
+        if (vec) XMOE_GATE(16, true);
+        else XMOE_GATE(16, false);
     }
-    XMOE_LAUNCH(K_GATE_LOGITS, s,
-                hipLaunchKernelGGL(gate_logits_kernel<T>, grid, dim3(256), 0, s, (const T*)x, (const T*)w, bias,
-                                   logits, Tn, d, E, vec));
+#undef XMOE_GATE
     return XMOE_OK;
 }
 
