@@ -61,6 +61,11 @@ bool ffn_dma_supported(const FfnArgs& a);
 int ffn_fwd_dma(const FfnArgs& a, hipStream_t s);
 int ffn_bwd_dma(const FfnArgs& a, hipStream_t s);
 
+// forward products of experts with few rows (the same operands as the direct-to-LDS kernels)
+bool few_rows(int B, int E, int f);
+int ffn_fwd_few(const FfnArgs& a, hipStream_t s);
+int mlp2_fwd_few(const Mlp2Args& a, hipStream_t s);
+
 int mlp2_fwd_tile(const Mlp2Args& a, hipStream_t s);
 int mlp2_bwd_tile(const Mlp2Args& a, hipStream_t s);
 bool mlp2_dma_supported(const Mlp2Args& a);
