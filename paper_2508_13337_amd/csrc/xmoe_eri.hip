@@ -1,5 +1,6 @@
 // PFT construction (paper: Listing 1 PFT_construction() step 1 + histogram; Section 4.1.1 ERI-arrays):
-// a stable counting sort of the T*k flat entries by expert id, in three small kernels.
+// a stable counting sort of the T*k flat entries by expert id, in one kernel for up to kEriDirectChunks chunks of
+// entries (eri_direct_kernel) and in three small ones beyond:
 //   1. per-chunk histograms of expert ids            (chunk = 1024 consecutive flat entries)
 //   2. column scan over chunks + scan over experts   -> tokens_per_expert, expert_offsets, chunk bases
 //   3. per-chunk stable ranking and scatter          -> token_ids, expert_ids, combine_weights, row_of_slot
@@ -65,25 +66,11 @@ __global__ __launch_bounds__(512) void eri_scan_kernel(int32_t* __restrict__ chu
     }
 }
 
-// FLAT: the intermediate table of the token-dropping construction: token_ids receives the flat entry n itself,
-// expert_ids and row_of_slot are not written.
-template <bool FLAT>
-__global__ __launch_bounds__(256) void eri_scatter_kernel(const int32_t* __restrict__ topk_idx,
-                                                          const float* __restrict__ topk_w, int B, int E, int k,
-                                                          int ebits, const int32_t* __restrict__ chunk_prefix,
-                                                          const int32_t* __restrict__ expert_offsets,
-                                                          int32_t* __restrict__ token_ids,
-                                                          int32_t* __restrict__ expert_ids,
-                                                          float* __restrict__ combine_weights,
-                                                          int32_t* __restrict__ row_of_slot) {
-    // sub_count[s][e]: entries of expert e in sub-chunk s; turned into an exclusive prefix over s
-    extern __shared__ int sub_count[];
+// Rank of each of this thread's four entries among its 64-entry sub-chunk's entries of the same expert, and
+// sub_count[s][e] (zeroed before): entries of expert e in sub-chunk s.
+__device__ __forceinline__ void eri_rank(const int32_t* __restrict__ topk_idx, int base, int B, int E, int ebits,
+                                         int* sub_count, int (&my_e)[kSubPerChunk / 4], int (&my_rank)[kSubPerChunk / 4]) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    for (int i = threadIdx.x; i < kSubPerChunk * E; i += 256) sub_count[i] = 0;
-    __syncthreads();
-
-    const int base = blockIdx.x * kEriChunk;
-    int my_e[kSubPerChunk / 4], my_rank[kSubPerChunk / 4];
 #pragma unroll
     for (int r = 0; r < kSubPerChunk / 4; ++r) {
         const int sub = r * 4 + wave;
@@ -101,17 +88,27 @@ __global__ __launch_bounds__(256) void eri_scatter_kernel(const int32_t* __restr
         my_rank[r] = __popcll(same & below);
         if (ok && (same & below) == 0ull) sub_count[sub * E + e] = __popcll(same);   // first lane of its group
     }
-    __syncthreads();
-    for (int e = threadIdx.x; e < E; e += 256) {
-        int run = chunk_prefix[(size_t)blockIdx.x * E + e] + expert_offsets[e];
+}
+
+// sub_count[.][e] -> first row of every sub-chunk's entries of expert e
+__device__ __forceinline__ void eri_sub_prefix(int* sub_count, int e, int E, int run) {
 #pragma unroll
-        for (int s2 = 0; s2 < kSubPerChunk; ++s2) {
-            int v = sub_count[s2 * E + e];
-            sub_count[s2 * E + e] = run;
-            run += v;
-        }
+    for (int s2 = 0; s2 < kSubPerChunk; ++s2) {
+        int v = sub_count[s2 * E + e];
+        sub_count[s2 * E + e] = run;
+        run += v;
     }
-    __syncthreads();
+}
+
+// FLAT: the intermediate table of the token-dropping construction: token_ids receives the flat entry n itself,
+// expert_ids and row_of_slot are not written.
+template <bool FLAT>
+__device__ __forceinline__ void eri_write(const float* __restrict__ topk_w, int base, int B, int E, int k,
+                                          const int* sub_count, const int (&my_e)[kSubPerChunk / 4],
+                                          const int (&my_rank)[kSubPerChunk / 4], int32_t* __restrict__ token_ids,
+                                          int32_t* __restrict__ expert_ids, float* __restrict__ combine_weights,
+                                          int32_t* __restrict__ row_of_slot) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
     for (int r = 0; r < kSubPerChunk / 4; ++r) {
         const int sub = r * 4 + wave;
@@ -129,6 +126,103 @@ __global__ __launch_bounds__(256) void eri_scatter_kernel(const int32_t* __restr
             }
         }
     }
+}
+
+template <bool FLAT>
+__global__ __launch_bounds__(256) void eri_scatter_kernel(const int32_t* __restrict__ topk_idx,
+                                                          const float* __restrict__ topk_w, int B, int E, int k,
+                                                          int ebits, const int32_t* __restrict__ chunk_prefix,
+                                                          const int32_t* __restrict__ expert_offsets,
+                                                          int32_t* __restrict__ token_ids,
+                                                          int32_t* __restrict__ expert_ids,
+                                                          float* __restrict__ combine_weights,
+                                                          int32_t* __restrict__ row_of_slot) {
+    // sub_count[s][e]: entries of expert e in sub-chunk s; turned into an exclusive prefix over s
+    extern __shared__ int sub_count[];
+    for (int i = threadIdx.x; i < kSubPerChunk * E; i += 256) sub_count[i] = 0;
+    __syncthreads();
+    const int base = blockIdx.x * kEriChunk;
+    int my_e[kSubPerChunk / 4], my_rank[kSubPerChunk / 4];
+    eri_rank(topk_idx, base, B, E, ebits, sub_count, my_e, my_rank);
+    __syncthreads();
+    for (int e = threadIdx.x; e < E; e += 256)
+        eri_sub_prefix(sub_count, e, E, chunk_prefix[(size_t)blockIdx.x * E + e] + expert_offsets[e]);
+    __syncthreads();
+    eri_write<FLAT>(topk_w, base, B, E, k, sub_count, my_e, my_rank, token_ids, expert_ids, combine_weights,
+                    row_of_slot);
+}
+
+// The whole construction in one launch: a block counts the experts of all flat entries, and of those in front of its
+// chunk, by itself instead of taking them from two earlier launches, then ranks and writes its chunk as
+// eri_scatter_kernel does.  Block 0 writes tokens_per_expert and expert_offsets.  Bound by launch latency where a call
+// is small.  Measured (MI355X, sum of the kernels without the gaps between them, three launches | one): 1 chunk, 8 experts
+// 7.2 | 4.9 us; 3 chunks, 64 experts 15.2 | 7.7; 8 chunks, 16 experts 15.4 | 9.4; 9 chunks, 24 experts 15.5 | 10.4.  A
+// chunk more costs every block about 0.4 us, the three launches next to nothing, so the line is drawn at 16.
+constexpr int kEriDirectChunks = 16;
+
+__global__ __launch_bounds__(256) void eri_direct_kernel(const int32_t* __restrict__ topk_idx,
+                                                         const float* __restrict__ topk_w, int B, int E, int k,
+                                                         int ebits, int32_t* __restrict__ tokens_per_expert,
+                                                         int32_t* __restrict__ expert_offsets,
+                                                         int32_t* __restrict__ token_ids,
+                                                         int32_t* __restrict__ expert_ids,
+                                                         float* __restrict__ combine_weights,
+                                                         int32_t* __restrict__ row_of_slot) {
+    extern __shared__ int sub_count[];             // as in eri_scatter_kernel
+    __shared__ int total[XMOE_MAX_EXPERTS];        // entries of every expert, then their exclusive prefix
+    __shared__ int before[XMOE_MAX_EXPERTS];       // those in front of this block's chunk
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    for (int i = threadIdx.x; i < kSubPerChunk * E; i += 256) sub_count[i] = 0;
+    for (int i = threadIdx.x; i < XMOE_MAX_EXPERTS; i += 256) total[i] = before[i] = 0;
+    __syncthreads();
+    const int base = blockIdx.x * kEriChunk;
+    for (int n0 = 0; n0 < B; n0 += kEriChunk) {
+        int e[kEriChunk / 256];
+#pragma unroll
+        for (int r = 0; r < kEriChunk / 256; ++r) {
+            const int n = n0 + r * 256 + threadIdx.x;
+            e[r] = n < B ? topk_idx[n] : -1;
+        }
+#pragma unroll
+        for (int r = 0; r < kEriChunk / 256; ++r)
+            if ((unsigned)e[r] < (unsigned)E) atomicAdd(n0 < base ? &before[e[r]] : &total[e[r]], 1);
+    }
+    int my_e[kSubPerChunk / 4], my_rank[kSubPerChunk / 4];
+    eri_rank(topk_idx, base, B, E, ebits, sub_count, my_e, my_rank);
+    __syncthreads();
+    // `total` holds the entries from the chunk on; one wave adds those in front and scans
+    if (wave == 0) {
+        constexpr int kPer = XMOE_MAX_EXPERTS / 64;
+        int v[kPer], sum = 0;
+#pragma unroll
+        for (int j = 0; j < kPer; ++j) {
+            v[j] = total[lane * kPer + j] + before[lane * kPer + j];
+            sum += v[j];
+        }
+        int inc = sum;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const int up = __shfl_up(inc, o, 64);
+            if (lane >= o) inc += up;
+        }
+        int run = inc - sum;
+#pragma unroll
+        for (int j = 0; j < kPer; ++j) {
+            const int e = lane * kPer + j;
+            total[e] = run;
+            if (blockIdx.x == 0 && e < E) {
+                tokens_per_expert[e] = v[j];
+                expert_offsets[e] = run;
+            }
+            run += v[j];
+        }
+        if (blockIdx.x == 0 && lane == 63) expert_offsets[E] = run;   // experts from E on have no entries
+    }
+    __syncthreads();
+    for (int e = threadIdx.x; e < E; e += 256) eri_sub_prefix(sub_count, e, E, total[e] + before[e]);
+    __syncthreads();
+    eri_write<false>(topk_w, base, B, E, k, sub_count, my_e, my_rank, token_ids, expert_ids, combine_weights,
+                     row_of_slot);
 }
 
 // ---------------------------------------------------------------------------------------------------------
@@ -337,6 +431,14 @@ static int build_eri_launch(const int32_t* topk_idx, const float* topk_w, int T,
     const int nchunks = eri_num_chunks(B);
     int ebits = 0;
     while ((1 << ebits) < E) ++ebits;
+    if (nchunks > 0 && nchunks <= kEriDirectChunks) {
+        XMOE_LAUNCH(K_ERI_SCATTER, s,
+                    hipLaunchKernelGGL(eri_direct_kernel, dim3(nchunks), dim3(256),
+                                       (size_t)kSubPerChunk * E * sizeof(int), s, topk_idx, topk_w, B, E, k, ebits,
+                                       tokens_per_expert, expert_offsets, token_ids, expert_ids, combine_weights,
+                                       row_of_slot));
+        return XMOE_OK;
+    }
     if (nchunks > 0)
         XMOE_LAUNCH(K_ERI_HIST, s,
                     hipLaunchKernelGGL(eri_hist_kernel, dim3(nchunks), dim3(256), 0, s, topk_idx, B, E, counts));

@@ -1,0 +1,31 @@
+"""xmoe_build_eri on either side of the line between its one-launch and its three-launch construction (16 chunks of
+1024 flat entries), with chunks that are not full and expert counts up to the limit: bit-equal to a stable sort."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("T,E,k", [(1, 1, 1), (1, 512, 8), (170, 64, 6), (171, 64, 6), (2730, 64, 6), (2731, 64, 6),
+                                   (2048, 512, 8), (2049, 512, 8), (16384, 7, 1), (333, 96, 3)])
+def test_tables(T, E, k):
+    import paper_2508_13337_amd as m
+    g = torch.Generator().manual_seed(T + E + k)
+    idx = torch.rand((T, E), generator=g).argsort(1)[:, :k].int()
+    w = torch.rand((T, k), generator=g)
+    B = T * k
+    i32 = dict(dtype=torch.int32, device="cuda")
+    tpe, off = torch.full((E,), -9, **i32), torch.full((E + 1,), -9, **i32)
+    tok, exp, row = (torch.full((B,), -9, **i32) for _ in range(3))
+    cw = torch.empty(B, dtype=torch.float32, device="cuda")
+    ws = m.alloc_workspace(m.xmoe_workspace_bytes(m.WS_BUILD_ERI, T, 64, E, k, 0, m.XMOE_BF16))
+    m.xmoe_build_eri(idx.cuda(), w.cuda(), E, tpe, off, tok, exp, cw, row, ws)
+    flat = idx.reshape(-1).long()
+    order = torch.sort(flat, stable=True).indices
+    count = torch.bincount(flat, minlength=E)
+    inverse = torch.empty(B, dtype=torch.long)
+    inverse[order] = torch.arange(B)
+    for got, want in ((tpe, count), (off[1:], count.cumsum(0)), (tok, order // k), (exp, flat[order]), (row, inverse)):
+        assert torch.equal(got.cpu().long(), want)
+    assert int(off[0]) == 0
+    assert torch.equal(cw.cpu(), w.reshape(-1)[order])
