@@ -353,25 +353,39 @@ __global__ __launch_bounds__(256) void route_bwd_kernel(const float* __restrict_
 // D[row 8*(v/4) + 4*(l/32) + v%4][column l%32], v = 0..15.
 typedef __attribute__((ext_vector_type(16))) float gate_f32x16_t;
 
-// two consecutive elements of a row as float32; vec: one 4-byte (bf16) / 8-byte (float) load
-__device__ __forceinline__ void load_pair(const bf16_t* p, bool ok0, bool ok1, bool vec, float& a, float& b) {
-    if (vec) {
-        const uint32_t u = ok0 ? *reinterpret_cast<const uint32_t*>(p) : 0u;
+// An element, or two consecutive ones, of a row as float32, zero where !ok.  The address is what depends on ok: with a
+// branch around each load the compiler waits for one load before it issues the next.
+__device__ __forceinline__ float load_or_zero(const bf16_t* p, bool ok) {
+    const gate_gptr a = ok ? (gate_gptr)(const char*)p : (gate_gptr)(const char*)kGatePad;
+    return bf16_bits_to_float(*reinterpret_cast<const __attribute__((address_space(1))) uint16_t*>(a));
+}
+__device__ __forceinline__ float load_or_zero(const float* p, bool ok) {
+    const gate_gptr a = ok ? (gate_gptr)(const char*)p : (gate_gptr)(const char*)kGatePad;
+    return *reinterpret_cast<const __attribute__((address_space(1))) float*>(a);
+}
+// VEC: one 4-byte (bf16) / 8-byte (float) load, ok0 standing for both
+template <bool VEC>
+__device__ __forceinline__ void load_pair(const bf16_t* p, bool ok0, bool ok1, float& a, float& b) {
+    if (VEC) {
+        const gate_gptr q = ok0 ? (gate_gptr)(const char*)p : (gate_gptr)(const char*)kGatePad;
+        const uint32_t u = *reinterpret_cast<const __attribute__((address_space(1))) uint32_t*>(q);
         a = __uint_as_float(u << 16);
         b = __uint_as_float(u & 0xffff0000u);
     } else {
-        a = ok0 ? to_float(p[0]) : 0.f;
-        b = ok1 ? to_float(p[1]) : 0.f;
+        a = load_or_zero(p, ok0);
+        b = load_or_zero(p + 1, ok1);
     }
 }
-__device__ __forceinline__ void load_pair(const float* p, bool ok0, bool ok1, bool vec, float& a, float& b) {
-    if (vec) {
-        const float2 v = ok0 ? *reinterpret_cast<const float2*>(p) : make_float2(0.f, 0.f);
-        a = v.x;
-        b = v.y;
+template <bool VEC>
+__device__ __forceinline__ void load_pair(const float* p, bool ok0, bool ok1, float& a, float& b) {
+    if (VEC) {
+        const gate_gptr q = ok0 ? (gate_gptr)(const char*)p : (gate_gptr)(const char*)kGatePad;
+        const uint64_t u = *reinterpret_cast<const __attribute__((address_space(1))) uint64_t*>(q);
+        a = __uint_as_float((uint32_t)u);
+        b = __uint_as_float((uint32_t)(u >> 32));
     } else {
-        a = ok0 ? p[0] : 0.f;
-        b = ok1 ? p[1] : 0.f;
+        a = load_or_zero(p, ok0);
+        b = load_or_zero(p + 1, ok1);
     }
 }
 
@@ -382,11 +396,13 @@ __device__ __forceinline__ void load_pair(const float* p, bool ok0, bool ok1, bo
 // i0 + 2r + a, column c of block b is e0 + 2c + b), so that one 4-byte load of x and one 8-byte load of dlogits
 // per lane feed four instructions.  The block's four waves take interleaved runs of 16 tokens each (enough waves in
 // flight to hide the loads' latency), and their partial tiles are added through LDS in wave order.
-// grid = (ceil(d/64), ceil(E/64), splits).  vec_x / vec_e: the pairs may be fetched with one load.
-template <typename T>
+// Bound by the latency of its loads: all of a round's are issued before the first is waited for (with a branch around
+// each for the edges they were waited for one by one: T 256 d 128 E 8 16 -> 9 us, T 2048 d 1024 E 16 24 -> 10).
+// grid = (ceil(d/64), ceil(E/64), splits).  VEC: the pairs may be fetched with one load.
+template <typename T, bool VEC>
 __global__ __launch_bounds__(256) void gate_bwd_dw_kernel(const T* __restrict__ x, const float* __restrict__ dl,
                                                           float* __restrict__ partial, int Tn, int d, int E,
-                                                          int t_per_split, int vec_x, int vec_e) {
+                                                          int t_per_split) {
     __shared__ float red[4][32][64];   // [wave][accumulator register][lane], used once per row block a
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int i0 = blockIdx.x * 64, e0 = blockIdx.y * 64;
@@ -412,9 +428,10 @@ __global__ __launch_bounds__(256) void gate_bwd_dw_kernel(const T* __restrict__ 
         for (int u = 0; u < U; ++u) {
             const int t = t0 + 2 * u + h;
             const bool ok_t = t < te;
-            load_pair(xa + (size_t)(ok_t ? t : tb) * d, ok_t && ok_i0, ok_t && ok_i1, vec_x && ok_i1, av[u][0], av[u][1]);
-            load_pair(ba + (size_t)(ok_t ? t : tb) * E, ok_t && ok_e0, ok_t && ok_e1, vec_e && ok_e1, bv[u][0], bv[u][1]);
+            load_pair<VEC>(xa + (size_t)(ok_t ? t : tb) * d, ok_t && ok_i0, ok_t && ok_i1, av[u][0], av[u][1]);
+            load_pair<VEC>(ba + (size_t)(ok_t ? t : tb) * E, ok_t && ok_e0, ok_t && ok_e1, bv[u][0], bv[u][1]);
         }
+        __builtin_amdgcn_sched_barrier(0);   // all of them in flight before the first is waited for
 #pragma unroll
         for (int u = 0; u < U; ++u)
 #pragma unroll
@@ -460,7 +477,7 @@ __global__ __launch_bounds__(256) void gate_bwd_dw_reduce_kernel(const float* __
 // The summation index e is contiguous in both operands.  The instruction sums over its two k-slots and the loop
 // over its steps, so any assignment of experts to (step, slot) gives the same sum: slot h of step q takes expert
 // 32*h + q of a chunk of 64, and a lane then reads 32 consecutive experts of its row with 16-byte loads.
-// One wave: 32 tokens x kDxCols columns i; the token rows of dlogits stay in registers across the columns.
+// One wave: 32 tokens x up to kDxCols columns i; the token rows of dlogits stay in registers across the columns.
 constexpr int kDxCols = 256;
 
 template <typename T>
@@ -475,7 +492,7 @@ __device__ __forceinline__ void load_row32<float>(const float* __restrict__ p, i
         }
     } else {
 #pragma unroll
-        for (int q = 0; q < 32; ++q) v[q] = q < n_valid ? p[q] : 0.f;
+        for (int q = 0; q < 32; ++q) v[q] = load_or_zero(p + q, q < n_valid);
     }
 }
 template <>
@@ -494,20 +511,21 @@ __device__ __forceinline__ void load_row32<bf16_t>(const bf16_t* __restrict__ p,
         }
     } else {
 #pragma unroll
-        for (int q = 0; q < 32; ++q) v[q] = q < n_valid ? to_float(p[q]) : 0.f;
+        for (int q = 0; q < 32; ++q) v[q] = load_or_zero(p + q, q < n_valid);
     }
 }
 
 // vec: E % 64 == 0 and both operands 16-byte aligned
 template <typename T>
 __global__ __launch_bounds__(256) void gate_bwd_dx_kernel(const float* __restrict__ dl, const T* __restrict__ w,
-                                                          T* __restrict__ dxg, int Tn, int d, int E, int vec) {
+                                                          T* __restrict__ dxg, int Tn, int d, int E, int cols,
+                                                          int vec) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int t0 = (blockIdx.x * 4 + wave) * 32;
     if (t0 >= Tn) return;
     const int h = lane >> 5, c = lane & 31;
-    const int ibeg = blockIdx.y * kDxCols;
-    const int iend = ibeg + kDxCols < d ? ibeg + kDxCols : d;
+    const int ibeg = blockIdx.y * cols;
+    const int iend = ibeg + cols < d ? ibeg + cols : d;
     const bool ok_t = t0 + c < Tn;
     const float* arow = dl + (size_t)(ok_t ? t0 + c : 0) * E + 32 * h;
     const bool one_chunk = E <= 64;
@@ -830,20 +848,31 @@ static int launch_gate_bwd(const void* x, const void* w, const float* dl, int Tn
         }
         return XMOE_OK;
     }
-    const int vec_x = (d % 2 == 0) && ((reinterpret_cast<uintptr_t>(x) & (2 * sizeof(T) - 1)) == 0);
-    const int vec_e = (E % 2 == 0) && ((reinterpret_cast<uintptr_t>(dl) & 7u) == 0);
-    XMOE_LAUNCH(K_GATE_BWD_DW, s,
-                hipLaunchKernelGGL(gate_bwd_dw_kernel<T>, g1, dim3(256), 0, s, (const T*)x, dl, partial, Tn, d, E,
-                                   tps, vec_x, vec_e));
+    // d and E even: a pair lies in the matrix whole or not at all
+    const bool pairs = d % 2 == 0 && (reinterpret_cast<uintptr_t>(x) & (2 * sizeof(T) - 1)) == 0 && E % 2 == 0 &&
+                       (reinterpret_cast<uintptr_t>(dl) & 7u) == 0;
+    if (pairs)
+        XMOE_LAUNCH(K_GATE_BWD_DW, s,
+                    hipLaunchKernelGGL((gate_bwd_dw_kernel<T, true>), g1, dim3(256), 0, s, (const T*)x, dl, partial, Tn, d,
+                                       E, tps));
+    else
+        XMOE_LAUNCH(K_GATE_BWD_DW, s,
+                    hipLaunchKernelGGL((gate_bwd_dw_kernel<T, false>), g1, dim3(256), 0, s, (const T*)x, dl, partial, Tn, d,
+                                       E, tps));
     size_t n = (size_t)d * E;
     XMOE_LAUNCH(K_GATE_BWD_DW_REDUCE, s,
                 hipLaunchKernelGGL(gate_bwd_dw_reduce_kernel<T>, dim3((unsigned)((n + 255) / 256)), dim3(256), 0,
                                    s, partial, splits, n, (T*)dwr));
-    dim3 g2((Tn + 127) / 128, (d + kDxCols - 1) / kDxCols);
+    // columns per wave: fewer where that many would leave CUs without a block.  Fetching the rows of dlogits again costs
+    // less than the idle CUs (float32 T 256 d 128 E 8: 12 -> 5 us, T 2048 d 1024 E 16: 25 -> 9, bf16 T 3001 d 1000 E 24:
+    // 37 -> 18; part of it from fetching the elements of rows that are no whole vectors without branches)
+    int cols = kDxCols;
+    while (cols > 32 && (long)((Tn + 127) / 128) * ((d + cols - 1) / cols) < 512) cols /= 2;
+    dim3 g2((Tn + 127) / 128, (d + cols - 1) / cols);
     const int vec = (E % 64 == 0) && aligned16(dl) && aligned16(w);
     XMOE_LAUNCH(K_GATE_BWD_DX, s,
                 hipLaunchKernelGGL(gate_bwd_dx_kernel<T>, g2, dim3(256), 0, s, dl, (const T*)w, (T*)dxg, Tn, d, E,
-                                   vec));
+                                   cols, vec));
     return XMOE_OK;
 }
 
