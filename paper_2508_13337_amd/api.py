@@ -57,11 +57,12 @@ def _ptr(t: Optional[torch.Tensor], dtype=None, name="tensor"):
         raise ValueError(f"{name} must be contiguous")
     if dtype is not None and t.dtype != dtype:
         raise TypeError(f"{name} must be {dtype}, got {t.dtype}")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()   # an int: the argument types make it a pointer, without an object per tensor
 
 
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    # the raw handle, without a torch.cuda.Stream object per call
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def xmoe_version() -> str:
