@@ -64,6 +64,7 @@ def small_kernel_work(cfg):
         "eri_hist_kernel": B * 4 + chunks * E * 4,                    # expert ids read, chunk histograms written
         "eri_scan_kernel": 2 * chunks * E * 4 + (2 * E + 1) * 4,      # histograms -> chunk bases, counts, offsets
         "eri_scatter_kernel": B * 8 + chunks * E * 4 + B * 16,        # (expert, weight) read; 4 arrays of B written
+        "eri_direct_kernel": B * 8 + (2 * E + 1) * 4 + B * 16,        # all of it in one launch (few entries)
     }
     f32_flops = {"gate_logits_kernel": 2 * T * d * E, "gate_bwd_dw_kernel": 2 * T * d * E,
                  "gate_bwd_dx_kernel": 2 * T * d * E}
@@ -134,17 +135,19 @@ GEMM_WORK = {
     "ffn_gateup_dma_kernel": "gateup", "ffn_rowgemm_dma_kernel<false>": "down",
     "ffn_rowgemm_dma_kernel<true>": "dact", "ffn_dx_dma_kernel": "dx",
     "ffn_wgrad_dma_kernel<false>": "wgrad_wd", "ffn_wgrad_dma_kernel<true>": "wgrad_wg_wu",
-    "ffn_bwd_rest_dma_kernel": "bwd_rest",
+    "ffn_bwd_rest_dma_kernel": "bwd_rest", "ffn_gateup_few_kernel": "gateup", "ffn_down_few_kernel": "down",
 }
 for _fam in ("mfma",):
     for _k in ("gateup", "down", "dact", "dx", "wgrad"):
         GEMM_WORK[f"ffn_{_k}_{_fam}_kernel"] = _k
-# the two-matrix expert shares the down, dX and weight-gradient kernels (two launches of the latter per step)
+# the two-matrix expert shares the down, dX and weight-gradient kernels (both weight gradients are one launch, except
+# those of the direct-to-LDS family with XMOE_BWD_MERGE=0: two)
 GEMM_WORK_MLP2 = {
     "mlp2_up_dma_kernel": "up", "ffn_rowgemm_dma_kernel<false>": "down", "mlp2_dact_dma_kernel": "dact",
     "ffn_dx_dma_kernel": "dx", "ffn_wgrad_dma_kernel<false>": "wgrad", "ffn_bwd_rest_dma_kernel": "bwd_rest",
     "mlp2_up_mfma_kernel": "up", "ffn_down_mfma_kernel": "down", "mlp2_dact_mfma_kernel": "dact",
-    "ffn_dx_mfma_kernel": "dx", "ffn_wgrad_mfma_kernel": "wgrad",
+    "ffn_dx_mfma_kernel": "dx", "ffn_wgrad_mfma_kernel": "wgrad", "mlp2_up_few_kernel": "up",
+    "ffn_down_few_kernel": "down",
 }
 
 def load_measured_traffic(workload):

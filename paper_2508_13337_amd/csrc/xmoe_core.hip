@@ -60,6 +60,10 @@ const char* const kKernelNames[K_COUNT] = {
     "rbd_map_kernel",
     "rbd_absolute_kernel",
     "prof_copy_kernel",
+    "eri_direct_kernel",
+    "ffn_gateup_few_kernel",
+    "ffn_down_few_kernel",
+    "mlp2_up_few_kernel",
 };
 
 hipEvent_t get_event() {

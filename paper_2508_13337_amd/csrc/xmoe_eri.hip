@@ -432,7 +432,7 @@ static int build_eri_launch(const int32_t* topk_idx, const float* topk_w, int T,
     int ebits = 0;
     while ((1 << ebits) < E) ++ebits;
     if (nchunks > 0 && nchunks <= kEriDirectChunks) {
-        XMOE_LAUNCH(K_ERI_SCATTER, s,
+        XMOE_LAUNCH(K_ERI_DIRECT, s,
                     hipLaunchKernelGGL(eri_direct_kernel, dim3(nchunks), dim3(256),
                                        (size_t)kSubPerChunk * E * sizeof(int), s, topk_idx, topk_w, B, E, k, ebits,
                                        tokens_per_expert, expert_offsets, token_ids, expert_ids, combine_weights,

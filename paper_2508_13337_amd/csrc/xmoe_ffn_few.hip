@@ -176,12 +176,9 @@ __device__ __forceinline__ void few_tile(float* red, const bf16_t* w, size_t ldw
 
 // C[rows of the tile, n0 ..] = X W;  K x N weights per expert (w1: the second matrix of GATEUP)
 template <int MODE, int ACT>
-__global__ __launch_bounds__(256, 2) void ffn_few_rows_kernel(const bf16_t* __restrict__ x,
-                                                              const int32_t* __restrict__ row_index,   // or NULL
-                                                              const int32_t* __restrict__ off,
-                                                              const int32_t* __restrict__ map, int K, int N,
-                                                              const bf16_t* __restrict__ w0,
-                                                              const bf16_t* __restrict__ w1, FewOut out) {
+__device__ __forceinline__ void few_block(const bf16_t* __restrict__ x, const int32_t* __restrict__ row_index,   // or NULL
+                                          const int32_t* __restrict__ off, const int32_t* __restrict__ map, int K, int N,
+                                          const bf16_t* __restrict__ w0, const bf16_t* __restrict__ w1, FewOut out) {
     __shared__ __align__(16) float red[4 * 64 * 64];
     constexpr int kCols = MODE == FEW_GATEUP ? kFewCols / 2 : kFewCols;
     const int e = map[4 + 2 * blockIdx.y], n0 = blockIdx.x * kCols;
@@ -204,6 +201,29 @@ __global__ __launch_bounds__(256, 2) void ffn_few_rows_kernel(const bf16_t* __re
         few_tile<MODE, ACT, 2, 2>(red, w, N, x, K, row_index, row0, rows, p0 * kFewK, n, out, N, n0);
 }
 
+__global__ __launch_bounds__(256, 2) void ffn_gateup_few_kernel(const bf16_t* __restrict__ xd,
+                                                                const int32_t* __restrict__ row_index,
+                                                                const int32_t* __restrict__ off,
+                                                                const int32_t* __restrict__ map, int d, int f,
+                                                                const bf16_t* __restrict__ wg,
+                                                                const bf16_t* __restrict__ wu, FewOut out) {
+    few_block<FEW_GATEUP, XMOE_ACT_IDENTITY>(xd, row_index, off, map, d, f, wg, wu, out);
+}
+__global__ __launch_bounds__(256, 2) void ffn_down_few_kernel(const bf16_t* __restrict__ A,
+                                                              const int32_t* __restrict__ off,
+                                                              const int32_t* __restrict__ map, int f, int d,
+                                                              const bf16_t* __restrict__ w, FewOut out) {
+    few_block<FEW_PLAIN, XMOE_ACT_IDENTITY>(A, nullptr, off, map, f, d, w, nullptr, out);
+}
+template <int ACT>
+__global__ __launch_bounds__(256, 2) void mlp2_up_few_kernel(const bf16_t* __restrict__ xd,
+                                                             const int32_t* __restrict__ row_index,
+                                                             const int32_t* __restrict__ off,
+                                                             const int32_t* __restrict__ map, int d, int f,
+                                                             const bf16_t* __restrict__ w1, FewOut out) {
+    few_block<FEW_MLP2, ACT>(xd, row_index, off, map, d, f, w1, nullptr, out);
+}
+
 // columns padded to a multiple of the XCD count: the row tiles of an expert that read the same weights meet in one L2
 inline dim3 few_grid(int N, int cols, int max_tiles) { return dim3(((N + cols - 1) / cols + 7) / 8 * 8, max_tiles); }
 
@@ -222,14 +242,13 @@ int ffn_fwd_few(const FfnArgs& a, hipStream_t s) {
     int st = launch_tile_map(a.off, a.E, kFewRows, max_tiles, a.map, a.sched, s);
     if (st != XMOE_OK) return st;
     const FewOut o1 = {(bf16_t*)a.g, (bf16_t*)a.u, (bf16_t*)a.act}, o2 = {(bf16_t*)a.y, nullptr, nullptr};
-    XMOE_LAUNCH(K_FFN_GATEUP_DMA, s,
-                hipLaunchKernelGGL((ffn_few_rows_kernel<FEW_GATEUP, XMOE_ACT_IDENTITY>),
-                                   few_grid(a.f, kFewCols / 2, max_tiles), dim3(256), 0, s, (const bf16_t*)a.xd,
-                                   a.row_index, a.off, a.map, a.d, a.f, (const bf16_t*)a.wg, (const bf16_t*)a.wu, o1));
-    XMOE_LAUNCH(K_FFN_DOWN_DMA, s,
-                hipLaunchKernelGGL((ffn_few_rows_kernel<FEW_PLAIN, XMOE_ACT_IDENTITY>),
-                                   few_grid(a.d, kFewCols, max_tiles), dim3(256), 0, s, (const bf16_t*)a.act, nullptr,
-                                   a.off, a.map, a.f, a.d, (const bf16_t*)a.wd, (const bf16_t*)nullptr, o2));
+    XMOE_LAUNCH(K_FFN_GATEUP_FEW, s,
+                hipLaunchKernelGGL(ffn_gateup_few_kernel, few_grid(a.f, kFewCols / 2, max_tiles), dim3(256), 0, s,
+                                   (const bf16_t*)a.xd, a.row_index, a.off, a.map, a.d, a.f, (const bf16_t*)a.wg,
+                                   (const bf16_t*)a.wu, o1));
+    XMOE_LAUNCH(K_FFN_DOWN_FEW, s,
+                hipLaunchKernelGGL(ffn_down_few_kernel, few_grid(a.d, kFewCols, max_tiles), dim3(256), 0, s,
+                                   (const bf16_t*)a.act, a.off, a.map, a.f, a.d, (const bf16_t*)a.wd, o2));
     return XMOE_OK;
 }
 
@@ -239,16 +258,14 @@ int mlp2_fwd_few(const Mlp2Args& a, hipStream_t s) {
     if (st != XMOE_OK) return st;
     const FewOut o1 = {(bf16_t*)a.h, (bf16_t*)a.a_buf, nullptr}, o2 = {(bf16_t*)a.y, nullptr, nullptr};
 #define XMOE_CALL(ACT)                                                                                               \
-    XMOE_LAUNCH(K_MLP2_UP_DMA, s,                                                                                    \
-                hipLaunchKernelGGL((ffn_few_rows_kernel<FEW_MLP2, ACT>), few_grid(a.f, kFewCols, max_tiles), dim3(256), \
-                                   0, s, (const bf16_t*)a.xd, a.row_index, a.off, a.map, a.d, a.f,                   \
-                                   (const bf16_t*)a.w1, (const bf16_t*)nullptr, o1))
+    XMOE_LAUNCH(K_MLP2_UP_FEW, s,                                                                                    \
+                hipLaunchKernelGGL((mlp2_up_few_kernel<ACT>), few_grid(a.f, kFewCols, max_tiles), dim3(256), 0, s,    \
+                                   (const bf16_t*)a.xd, a.row_index, a.off, a.map, a.d, a.f, (const bf16_t*)a.w1, o1))
     XMOE_DISPATCH_ACT(a.act, XMOE_CALL);
 #undef XMOE_CALL
-    XMOE_LAUNCH(K_FFN_DOWN_DMA, s,
-                hipLaunchKernelGGL((ffn_few_rows_kernel<FEW_PLAIN, XMOE_ACT_IDENTITY>),
-                                   few_grid(a.d, kFewCols, max_tiles), dim3(256), 0, s, (const bf16_t*)a.a_buf, nullptr,
-                                   a.off, a.map, a.f, a.d, (const bf16_t*)a.w2, (const bf16_t*)nullptr, o2));
+    XMOE_LAUNCH(K_FFN_DOWN_FEW, s,
+                hipLaunchKernelGGL(ffn_down_few_kernel, few_grid(a.d, kFewCols, max_tiles), dim3(256), 0, s,
+                                   (const bf16_t*)a.a_buf, a.off, a.map, a.f, a.d, (const bf16_t*)a.w2, o2));
     return XMOE_OK;
 }
 

@@ -52,6 +52,10 @@ enum KernelId : int {
     K_RBD_MAP,
     K_RBD_ABS,
     K_PROF_COPY,
+    K_ERI_DIRECT,
+    K_FFN_GATEUP_FEW,
+    K_FFN_DOWN_FEW,
+    K_MLP2_UP_FEW,
     K_COUNT
 };
 

@@ -18,6 +18,19 @@ def to_dev(a, dtype_name: str) -> torch.Tensor:
     return t.to(torch_dtype(dtype_name)).cuda().contiguous()
 
 
+def launched(m, call) -> set:
+    """Names of the library's kernels that call() launches (m: the package)."""
+    m.xmoe_prof_reset()
+    m.xmoe_prof_enable(True)
+    try:
+        call()
+        torch.cuda.synchronize()
+        return set(m.xmoe_prof_read())
+    finally:
+        m.xmoe_prof_enable(False)
+        m.xmoe_prof_reset()
+
+
 def to_host(t: torch.Tensor) -> np.ndarray:
     return t.detach().float().cpu().numpy().astype(np.float64)
 

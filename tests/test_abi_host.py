@@ -43,6 +43,15 @@ def test_binding_has_same_names():
         assert callable(getattr(xm, n))
 
 
+def test_profiler_names_every_kernel_once(lib):
+    names = [lib.xmoe_prof_kernel_name(i).decode() for i in range(lib.xmoe_prof_num_kernels())]
+    assert len(set(names)) == len(names) and all(names)
+    # kernels without a clock sample of their own do not report another kernel's
+    ghz = ctypes.c_double(-1.0)
+    for n in ("ffn_gateup_few_kernel", "ffn_down_few_kernel", "mlp2_up_few_kernel", "eri_direct_kernel"):
+        assert lib.xmoe_prof_shader_clock(names.index(n), ctypes.byref(ghz)) == 0 and ghz.value == 0.0
+
+
 def test_status_strings(lib):
     assert lib.xmoe_status_string(0) == b"XMOE_OK"
     for s in range(1, 5):

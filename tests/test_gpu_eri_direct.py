@@ -3,6 +3,8 @@
 import pytest
 import torch
 
+from gpu_util import launched
+
 pytestmark = pytest.mark.gpu
 
 
@@ -19,7 +21,9 @@ def test_tables(T, E, k):
     tok, exp, row = (torch.full((B,), -9, **i32) for _ in range(3))
     cw = torch.empty(B, dtype=torch.float32, device="cuda")
     ws = m.alloc_workspace(m.xmoe_workspace_bytes(m.WS_BUILD_ERI, T, 64, E, k, 0, m.XMOE_BF16))
-    m.xmoe_build_eri(idx.cuda(), w.cuda(), E, tpe, off, tok, exp, cw, row, ws)
+    kernels = launched(m, lambda: m.xmoe_build_eri(idx.cuda(), w.cuda(), E, tpe, off, tok, exp, cw, row, ws))
+    assert kernels == ({"eri_direct_kernel"} if B <= 16 * 1024 else
+                       {"eri_hist_kernel", "eri_scan_kernel", "eri_scatter_kernel"}), kernels
     flat = idx.reshape(-1).long()
     order = torch.sort(flat, stable=True).indices
     count = torch.bincount(flat, minlength=E)
