@@ -1,16 +1,20 @@
-"""Forward products of experts with few rows (at most 64 on average): segments at the edges of a 32- and a 64-row block,
-widths that fill a 128-column tile and widths that do not, K that splits unevenly over a block's four waves.
+"""Forward products of experts with few rows (xmoe_ffn_few.hip, taken up to 16 rows per expert on average): segments at
+the edges of a 32- and a 64-row block, several row tiles per expert, empty experts, widths that fill a 128-column
+tile and that do not, K that splits unevenly over a block's four waves.  Every test asserts the kernels that ran.
 
 Tolerance: G, U, H and the activations are one float32-accumulated product rounded to bf16 (2^-9 relative) against a
 float64 product of the same operands; an element that cancels to below the RMS is held to that share of the RMS."""
 import pytest
 import torch
 
+from gpu_util import launched
+
 pytestmark = pytest.mark.gpu
 
+# the empty experts behind each list keep the mean within the rule
 ROWS = {
-    "edges": [0, 1, 31, 32, 33, 63, 64, 65, 0],
-    "one long": [1, 0, 200, 0, 3, 0],      # 204 rows, 34 on average: four row tiles of one expert
+    "edges": [0, 1, 31, 32, 33, 63, 64, 65, 0] + [0] * 10,      # 289 rows, 19 experts
+    "one long": [1, 0, 200, 0, 3, 0] + [0] * 7,                 # 204 rows, 13 experts: four row tiles of one expert
     "single": [1],
 }
 WIDTHS = [(64, 64), (128, 192), (320, 64), (192, 448), (1024, 704)]   # d, f
@@ -34,51 +38,65 @@ def inputs(rows, d, f, gathered, matrices):
     return x, xs, index, off, w
 
 
+def swiglu(m, x, off, w, B, index=None):
+    """(G, U, Y, kernels) of one call; a marked row behind each output has to stand."""
+    E, d, f = w[0].shape
+    act = dict(dtype=torch.bfloat16, device="cuda")
+    o = [torch.full((B + 1, n), 7.0, **act) for n in (f, f, d)]
+    ws = m.alloc_workspace(m.xmoe_workspace_bytes(m.WS_FFN_FWD, B, d, E, 1, f, m.XMOE_BF16))
+    args = (x.cuda(), off.cuda(), *(a.cuda() for a in w), *(t[:B] for t in o), ws)
+    kernels = launched(m, lambda: m.xmoe_expert_ffn_fwd(*args, row_index=None if index is None else index.cuda()))
+    o = [t.cpu() for t in o]
+    assert all(bool((t[B] == 7.0).all()) for t in o)
+    return [t[:B] for t in o] + [kernels]
+
+
+def mlp2(m, x, off, w, act, B, index=None):
+    E, d, f = w[0].shape
+    o = [torch.full((B + 1, n), 7.0, dtype=torch.bfloat16, device="cuda") for n in (f, d)]
+    ws = m.alloc_workspace(m.xmoe_workspace_bytes(m.WS_MLP2_FWD, B, d, E, 1, f, m.XMOE_BF16))
+    args = (x.cuda(), off.cuda(), *(a.cuda() for a in w), act, *(t[:B] for t in o), ws)
+    kernels = launched(m, lambda: m.xmoe_expert_mlp2_fwd(*args, row_index=None if index is None else index.cuda()))
+    o = [t.cpu() for t in o]
+    assert all(bool((t[B] == 7.0).all()) for t in o)
+    return [t[:B] for t in o] + [kernels]
+
+
 @pytest.mark.parametrize("gathered", [False, True])
 @pytest.mark.parametrize("d,f", WIDTHS)
 @pytest.mark.parametrize("rows", ROWS, ids=list(ROWS))
 def test_swiglu(rows, d, f, gathered):
     import paper_2508_13337_amd as m
     rows = ROWS[rows]
-    x, xs, index, off, (wg, wu, wd) = inputs(rows, d, f, gathered, 3)
-    E, B = len(rows), sum(rows)
-    act = dict(dtype=torch.bfloat16, device="cuda")
-    G, U, Y = torch.full((B + 1, f), 7.0, **act), torch.full((B + 1, f), 7.0, **act), torch.full((B + 1, d), 7.0, **act)
-    ws = m.alloc_workspace(m.xmoe_workspace_bytes(m.WS_FFN_FWD, B, d, E, 1, f, m.XMOE_BF16))
-    m.xmoe_expert_ffn_fwd(x.cuda(), off.cuda(), wg.cuda(), wu.cuda(), wd.cuda(), G[:B], U[:B], Y[:B], ws,
-                          row_index=None if index is None else index.cuda())
-    G, U, Y = G.cpu(), U.cpu(), Y.cpu()
-    for o in (G, U, Y):
-        assert bool((o[B] == 7.0).all())
-    for e in range(E):
+    x, xs, index, off, w = inputs(rows, d, f, gathered, 3)
+    G, U, Y, kernels = swiglu(m, x, off, w, sum(rows), index)
+    assert kernels == {"tile_map_kernel", "ffn_gateup_few_kernel", "ffn_down_few_kernel"}, kernels
+    for e in range(len(rows)):
         s = slice(int(off[e]), int(off[e + 1]))
         if rows[e] == 0:
             continue
-        g64, u64 = xs[s].double() @ wg[e].double(), xs[s].double() @ wu[e].double()
+        g64, u64 = xs[s].double() @ w[0][e].double(), xs[s].double() @ w[1][e].double()
         close(G[s], g64)
         close(U[s], u64)
         a = g64 * torch.sigmoid(g64) * u64
         # A is rounded to bf16 in between: one rounding more, averaged over f terms
-        close(Y[s], a.bfloat16().double() @ wd[e].double(), 2.0 ** -6)
+        close(Y[s], a.bfloat16().double() @ w[2][e].double(), 2.0 ** -6)
 
 
 @pytest.mark.parametrize("act", ["identity", "gelu", "silu"])
 @pytest.mark.parametrize("d,f", [(64, 64), (192, 448)])
-def test_two_matrix(d, f, act):
+@pytest.mark.parametrize("rows", ["edges", "one long"])
+def test_two_matrix(rows, d, f, act):
     import paper_2508_13337_amd as m
-    rows = ROWS["edges"]
-    x, xs, index, off, (w1, w2) = inputs(rows, d, f, True, 2)
-    E, B = len(rows), sum(rows)
-    t = dict(dtype=torch.bfloat16, device="cuda")
-    H, Y = torch.empty((B, f), **t), torch.empty((B, d), **t)
-    ws = m.alloc_workspace(m.xmoe_workspace_bytes(m.WS_MLP2_FWD, B, d, E, 1, f, m.XMOE_BF16))
-    m.xmoe_expert_mlp2_fwd(x.cuda(), off.cuda(), w1.cuda(), w2.cuda(), act, H, Y, ws, row_index=index.cuda())
-    H, Y = H.cpu(), Y.cpu()
-    for e in range(E):
+    rows = ROWS[rows]
+    x, xs, index, off, w = inputs(rows, d, f, True, 2)
+    H, Y, kernels = mlp2(m, x, off, w, act, sum(rows), index)
+    assert kernels == {"tile_map_kernel", "mlp2_up_few_kernel", "ffn_down_few_kernel"}, kernels
+    for e in range(len(rows)):
         s = slice(int(off[e]), int(off[e + 1]))
         if rows[e] == 0:
             continue
-        h = xs[s].double() @ w1[e].double()
+        h = xs[s].double() @ w[0][e].double()
         close(H[s], h)
         a = {"identity": h, "gelu": torch.nn.functional.gelu(h), "silu": h * torch.sigmoid(h)}[act]
-        close(Y[s], a.bfloat16().double() @ w2[e].double(), 2.0 ** -6)
+        close(Y[s], a.bfloat16().double() @ w[1][e].double(), 2.0 ** -6)
