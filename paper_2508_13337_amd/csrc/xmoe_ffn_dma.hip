@@ -861,12 +861,6 @@ __device__ __forceinline__ void mainloop(f32x16_t (&acc)[4][2], const Operand& o
     mainloop2<A_COL, B_COL, DUAL, false, A_GATHER, B_GATHER>(acc, oa, ob, K, oa, ob, 0, mi_count, smem);
 }
 
-// sigmoid with the hardware exp2 and reciprocal (each good to about 1 ulp): the results are rounded to bf16, and
-// the library-grade expf and IEEE division cost as much as a quarter of a tile's main loop in the fused epilogues.
-__device__ __forceinline__ float fast_sigmoid(float g) {
-    return __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.44269504088896341f * g));
-}
-
 __device__ __forceinline__ void zero_acc(f32x16_t (&acc)[4][2]) {
 #pragma unroll
     for (int mi = 0; mi < 4; ++mi)
@@ -1475,30 +1469,6 @@ __global__ __launch_bounds__(512) void ffn_dx_dma_kernel(const bf16_t* __restric
 // =========================================================================================================
 // two-matrix expert, forward 1: H = Xd W1, A = act(H)      (K = d, N = f, weights "in x out" -> col tile)
 // =========================================================================================================
-// activation of the matrix-core epilogues: silu takes the hardware exp2 / reciprocal like the SwiGLU epilogues
-// and gelu takes the error function from the rational approximation 7.1.26 of Abramowitz and Stegun
-//   erf(x) = 1 - (a1 t + a2 t^2 + a3 t^3 + a4 t^4 + a5 t^5) exp(-x^2),  t = 1 / (1 + p x),  x >= 0,  |error| <= 1.5e-7,
-// far below half a bf16 unit of the stored result; its exp(-x^2) with x = h / sqrt(2) is also the Gaussian density
-// that the derivative needs.
-__device__ __forceinline__ void fast_gelu_parts(float h, float& Phi, float& phi) {
-    const float x = fabsf(h) * 0.70710678118654752f;
-    const float t = __builtin_amdgcn_rcpf(1.0f + 0.3275911f * x);
-    const float e = __builtin_amdgcn_exp2f(-1.44269504088896341f * x * x);
-    const float poly = t * (0.254829592f + t * (-0.284496736f + t * (1.421413741f + t * (-1.453152027f + t * 1.061405429f))));
-    const float erf_abs = 1.0f - poly * e;
-    Phi = 0.5f * (1.0f + copysignf(erf_abs, h));
-    phi = 0.39894228040143268f * e;
-}
-template <int ACT>
-__device__ __forceinline__ float act_fast(float h) {
-    if (ACT == XMOE_ACT_SILU) return h * fast_sigmoid(h);
-    if (ACT == XMOE_ACT_GELU) {
-        float Phi, phi;
-        fast_gelu_parts(h, Phi, phi);
-        return h * Phi;
-    }
-    return h;
-}
 template <int ACT>
 __device__ __forceinline__ void act_fast_grad(float h, float& a, float& g) {
     if (ACT == XMOE_ACT_SILU) {

@@ -1,21 +1,21 @@
 // Forward products of the expert MLP where the experts have few rows (bf16, d and f multiples of 64, 16-byte aligned
 // operands): a decoding step, the prompt of one request, a small micro-batch.  The weights of every expert with rows
-// have to come from memory once and that is the bound; the 256 x 256 tiles of the direct-to-LDS kernels leave one
-// block and at most three 16 KiB pieces of weights in flight per CU, and cut the work into so few tiles that the last
-// wave of them is nearly empty (the down product of 36 experts at d 2048: 288 tiles for 256 CUs).
+// have to come from memory once and that is the bound; the 256 x 256 tiles of the direct-to-LDS kernels keep at most
+// three 16 KiB pieces of weights in flight per CU, and cut the work into so few tiles that the last wave of them is nearly
+// empty (the down product of 36 experts at d 2048: 288 tiles for 256 CUs).
 //
-//   block = 4 waves = 64 rows x 128 columns (gate/up: the same 64 columns of both matrices), two blocks per CU.  The
-//   waves split K, 32 at a time, and their sums are added through LDS in a fixed order at the end, so a wave streams its
-//   part of the weights into registers with no barrier: 8 KiB of loads per wave and piece of K, one piece ahead (two
-//   where the tile holds at most 32 rows).
+//   block = 4 waves = 64 rows x 128 columns (gate/up: the same 64 columns of both matrices), two blocks per CU.  A ring
+//   of kFewStages stages of 32 k (8 KiB of weights, 4 KiB of rows) is filled by direct-to-LDS loads, three per wave and
+//   stage, so a block keeps all but one stage in flight; one barrier per stage.  A wave owns 32 columns over all of K.
 //
-// A lane fetches 8 bytes (4 columns) of 8 consecutive k-rows, which is after 16 byte permutes its share of four matrix
-// instructions (v_mfma_f32_32x32x16_bf16, weights first): instruction j multiplies the columns 4c + j, c = 0..31.  So
-// every load covers 256 contiguous bytes of a weight row, nothing passes through LDS on the way in, and a lane ends up
-// with runs of consecutive columns of one row.
+// Measured (MI355X, d 2048, f 1408, 64 experts + 2 shared, one decoding step of 8 tokens with 36 experts active, 256-row
+// tiles | these): gate/up 96 | 85 us (4.9 TB/s), down 63 | 46 (4.5 TB/s); 8 experts with 8 rows each 70 | 18 and 48 | 12.
+// Four stages and three blocks per CU: 2 to 8 % faster for narrow f, 15 % slower for a Zipf load on 32 experts of
+// d 4096; twelve stages and one block: 3 to 15 % slower.
 //
-// Measured (MI355X, d 2048, f 1408, 64 experts + 2 shared, one decoding step of 8 tokens with 36 experts active): gate/up
-// 95 -> 87 us (4.8 TB/s), down 64 -> 44 (4.7 TB/s); 8 experts with 8 rows each: both together 119 -> 36.
+// Every output is one accumulator that takes K in ascending steps of 16, as in the 256 x 256 kernels, with the same
+// operands in the same slots of the same instruction and the same activation: a row's result has the same bits whichever
+// of the two families a call's row count selects.
 #include "xmoe_ffn.h"
 
 namespace xmoe {
@@ -23,19 +23,14 @@ namespace {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 few_bf16x8_t;
 typedef __attribute__((ext_vector_type(16))) float few_f32x16_t;
-typedef __attribute__((ext_vector_type(2))) uint32_t few_u32x2_t;
-typedef __attribute__((ext_vector_type(4))) uint32_t few_u32x4_t;
+typedef __attribute__((ext_vector_type(4))) short few_s16x4_t;
+typedef __attribute__((ext_vector_type(8))) short few_s16x8_t;
 
-constexpr int kFewRows = 64, kFewCols = 128, kFewK = 32;
+constexpr int kFewRows = 64, kFewCols = 128, kFewK = 32, kFewStages = 6;
+constexpr int kFewWBytes = kFewK * kFewCols * 2;              // [32 k][128 columns]
+constexpr int kFewStageBytes = kFewWBytes + kFewRows * kFewK * 2;   // and [64 rows][32 k]
+constexpr int kFewLoads = 3;                                  // per wave and stage: two of weights, one of rows
 __device__ __align__(16) const unsigned int kFewZero[4] = {0u, 0u, 0u, 0u};
-
-// Explicitly global addresses: through a pointer that may be the block of zeros the compiler makes flat loads, which
-// count as LDS accesses too and are waited for all at once.
-typedef const __attribute__((address_space(1))) char* few_gptr;
-template <typename V>
-__device__ __forceinline__ V few_load(few_gptr p) {
-    return *reinterpret_cast<const __attribute__((address_space(1))) V*>(p);
-}
 
 // what becomes of a product
 enum FewMode { FEW_PLAIN = 0, FEW_GATEUP = 1, FEW_MLP2 = 2 };
@@ -44,161 +39,160 @@ struct FewOut {
     bf16_t *o0, *o1, *o2;   // PLAIN: C; GATEUP: G, U, A; MLP2: H, A
 };
 
-// the operands of one piece of K in flight
-template <int MB>
-struct FewPiece {
-    few_u32x2_t w[2][8];
-    few_u32x4_t x[MB][2];
-};
-
-// MB 32-row blocks of rows; w: this lane's columns of k-row 0 of the wave's K range, x: its rows at k 0 of it
-template <int MB, int NB>
-__device__ __forceinline__ void few_mainloop(few_f32x16_t (&acc)[MB][4], const bf16_t* w, size_t ldw,
-                                             const bf16_t* const (&x)[MB], int n) {
-    FewPiece<MB> p[NB];
-    const few_gptr zero = (few_gptr)(const char*)kFewZero;
-    const few_gptr wl = (few_gptr)(const char*)(w + 8 * ((threadIdx.x >> 5) & 1) * ldw);
-    auto load = [&](FewPiece<MB>& q, int c) {   // past the end: zeros, so that no load depends on a branch
-        const bool in = c < n;
-        const size_t ld = in ? 2 * ldw : 0;
-        const few_gptr wp = in ? wl + (size_t)c * kFewK * ld : zero;
-#pragma unroll
-        for (int st = 0; st < 2; ++st)
-#pragma unroll
-            for (int k = 0; k < 8; ++k) q.w[st][k] = few_load<few_u32x2_t>(wp + (16 * st + k) * ld);
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb) {
-            const few_gptr xl = in ? (few_gptr)(const char*)x[mb] + c * kFewK * 2 : zero;
-#pragma unroll
-            for (int st = 0; st < 2; ++st) q.x[mb][st] = few_load<few_u32x4_t>(xl + (in ? 32 * st : 0));
-        }
-    };
-    auto multiply = [&](const FewPiece<MB>& q) {
-#pragma unroll
-        for (int st = 0; st < 2; ++st)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                uint32_t f[4];
-#pragma unroll
-                for (int a = 0; a < 4; ++a) {   // the low (even column) or high halves of k-rows 2a and 2a+1
-                    const few_u32x2_t lo = q.w[st][2 * a], hi = q.w[st][2 * a + 1];
-                    f[a] = __builtin_amdgcn_perm(j < 2 ? hi.x : hi.y, j < 2 ? lo.x : lo.y,
-                                                 (j & 1) ? 0x07060302u : 0x05040100u);
-                }
-                const few_bf16x8_t wf = __builtin_bit_cast(few_bf16x8_t, make_uint4(f[0], f[1], f[2], f[3]));
-#pragma unroll
-                for (int mb = 0; mb < MB; ++mb)
-                    acc[mb][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                        wf, __builtin_bit_cast(few_bf16x8_t, q.x[mb][st]), acc[mb][j], 0, 0, 0);
-            }
-    };
-#pragma unroll
-    for (int b = 0; b < NB - 1; ++b) load(p[b], b);
-    for (int c = 0; c < n; c += NB)
-#pragma unroll
-        for (int b = 0; b < NB; ++b) {
-            load(p[(b + NB - 1) % NB], c + b + NB - 1);
-            multiply(p[b]);
-        }
+__device__ __forceinline__ void few_load16(const bf16_t* p, char* lds) {
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)p,
+                                     (__attribute__((address_space(3))) void*)lds, 16, 0, 0);
 }
 
-// red: 64 KiB.  Lane (h, r) of wave w adds up, for row r, the columns it stores: PLAIN, MLP2 16 consecutive ones
-// (registers 4w .. 4w+3 of the four accumulators), GATEUP 8 of either matrix (registers 2w, 2w+1 and 8 above them).
-template <int MODE, int ACT, int MB, int NB>
-__device__ __forceinline__ void few_tile(float* red, const bf16_t* w, size_t ldw, const bf16_t* x, size_t ldx,
-                                         const int32_t* row_index, int row0, int rows, int k0, int n, FewOut out, int N,
-                                         int n0) {
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int h = lane >> 5, r = lane & 31;
-    const bf16_t* xp[MB];
-#pragma unroll
-    for (int mb = 0; mb < MB; ++mb) {   // rows past the last one repeat it; what they give is not stored
-        int rr = mb * 32 + r;
-        rr = row0 + (rr < rows ? rr : rows - 1);
-        xp[mb] = x + (size_t)(row_index ? row_index[rr] : rr) * ldx + k0 + 8 * h;
+// A lane's share of the loads: 16 bytes of k-rows kr and kr + 4 of the weights and of one row of X per stage.
+struct FewLoader {
+    const bf16_t *w[2], *x;   // of the stage issued next
+    size_t step;              // elements between the weights of two stages
+    int left;                 // stages of K not yet issued; behind them the block of zeros, so that the counts stay uniform
+    __device__ __forceinline__ void issue(char* __restrict__ stage) {
+        const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        const bool in = left > 0;
+        const bf16_t* z = reinterpret_cast<const bf16_t*>(kFewZero);
+        few_load16(in ? w[0] : z, stage + wave * 2048);
+        few_load16(in ? w[1] : z, stage + wave * 2048 + 1024);
+        few_load16(in ? x : z, stage + kFewWBytes + wave * 1024);
+        w[0] += step;
+        w[1] += step;
+        x += kFewK;
+        --left;
     }
-    few_f32x16_t acc[MB][4];
+};
+
+// LDS layout: k-rows of 256 bytes whose 16-byte pieces are XOR-swizzled with 4 * (k-row % 4), rows of X of 64 bytes with
+// pieces XOR-swizzled with (row / 4) % 4: the fragment reads fall on all banks.
+// Columns of the wave, 8 k (16 ks + 8 (lane/32) ..): in a group of 16 lanes, lane s addresses 4 consecutive columns (s%4)
+// of k-row s/4, and the transposing read hands every lane one column with 4 consecutive k.
+template <int MODE>
+__device__ __forceinline__ few_bf16x8_t few_frag_w(const char* stage, int ks) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, G = lane >> 4, s = lane & 15;
+    const int col = (MODE == FEW_GATEUP ? 64 * (G & 1) + 16 * wave : 32 * wave + 16 * (G & 1)) + 4 * (s & 3);
+    few_s16x4_t h[2];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        const int kr = 16 * ks + 8 * (G >> 1) + (s >> 2) + 4 * q;
+        const char* a = stage + kr * 256 + (((col >> 3) ^ ((kr & 3) << 2)) << 4) + (col & 7) * 2;
+        h[q] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) few_s16x4_t*)(
+            (__attribute__((address_space(3))) void*)a));
+    }
+    const few_s16x8_t v = {h[0][0], h[0][1], h[0][2], h[0][3], h[1][0], h[1][1], h[1][2], h[1][3]};
+    return __builtin_bit_cast(few_bf16x8_t, v);
+}
+__device__ __forceinline__ few_bf16x8_t few_frag_x(const char* stage, int mb, int ks) {
+    const int lane = threadIdx.x & 63, r = mb * 32 + (lane & 31), c = 2 * ks + (lane >> 5);
+    return *reinterpret_cast<const few_bf16x8_t*>(stage + kFewWBytes + r * 64 + ((c ^ ((r >> 2) & 3)) << 4));
+}
+
+// Refills the stage read before the last barrier and multiplies `cur`.  The two are distinct, and saying so matters: an
+// LDS read that may observe a direct-to-LDS load in flight makes the compiler wait for all of them.
+template <int MODE, int MB>
+__device__ __forceinline__ void few_step(few_f32x16_t (&acc)[MB], FewLoader& ld, char* __restrict__ next,
+                                         const char* __restrict__ cur) {
+    ld.issue(next);
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+        const few_bf16x8_t w = few_frag_w<MODE>(cur, ks);
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb)
+            acc[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w, few_frag_x(cur, mb, ks), acc[mb], 0, 0, 0);
+    }
+}
+
+// One tile: rows [row0, row0 + min(rows, 32 MB)), the block's columns.
+template <int MODE, int ACT, int MB>
+__device__ __forceinline__ void few_tile(FewLoader& ld, char* smem, int n, int row0, int rows, FewOut out, int N, int n0) {
+    few_f32x16_t acc[MB];
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
+        for (int v = 0; v < 16; ++v) acc[mb][v] = 0.f;
 #pragma unroll
-            for (int v = 0; v < 16; ++v) acc[mb][j][v] = 0.f;
-    few_mainloop<MB, NB>(acc, w + (size_t)k0 * ldw, ldw, xp, n);
+    for (int s = 0; s < kFewStages - 1; ++s) ld.issue(smem + s * kFewStageBytes);
+    int cur = 0, next = kFewStages - 1;
+    for (int i = 0; i < n; ++i) {
+        // stage i has landed for every thread, and every wave is done with stage i - 1, which is refilled now
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(kFewLoads * (kFewStages - 2)) : "memory");
+        few_step<MODE, MB>(acc, ld, smem + next * kFewStageBytes, smem + cur * kFewStageBytes);
+        next = cur;
+        cur = cur + 1 < kFewStages ? cur + 1 : 0;
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // nothing may land in this LDS once the block has left it
+    // accumulator register v of row r: column 8 (v/4) + 4 (lane/32) + v%4 of the wave's 32 (GATEUP: 16 gate, then 16 up)
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, r = lane & 31;
+    const int col = n0 + (MODE == FEW_GATEUP ? 16 : 32) * wave + 4 * (lane >> 5);
+    if (col >= N) return;
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb) {
-        if (mb) __syncthreads();
-#pragma unroll
-        for (int v = 0; v < 16; ++v)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) red[((wave * 16 + v) * 4 + j) * 64 + lane] = acc[mb][j][v];
-        __syncthreads();
-        float s[16];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int v = MODE == FEW_GATEUP ? 2 * wave + (q & 1) + 8 * (q >> 1) : 4 * wave + q;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const float* p = red + (v * 4 + j) * 64 + lane;
-                s[q * 4 + j] = ((p[0] + p[4096]) + p[8192]) + p[12288];
-            }
-        }
         if (mb * 32 + r >= rows) continue;
-        // accumulator register v holds c = 8 (v/4) + 4 h + v%4, columns 4c .. 4c+3 (GATEUP: c < 16 gate, then up)
-        const int c = MODE == FEW_GATEUP ? 8 * (wave >> 1) + 4 * h + 2 * (wave & 1) : 8 * wave + 4 * h;
-        const int col = n0 + 4 * c;
-        if (col >= N) continue;
         const size_t ix = (size_t)(row0 + mb * 32 + r) * N + col;
-        auto store8 = [&](bf16_t* o, const float* t) {
-            *reinterpret_cast<uint4*>(o + ix) = make_uint4(pack_bf16x2(t[0], t[1]), pack_bf16x2(t[2], t[3]),
-                                                           pack_bf16x2(t[4], t[5]), pack_bf16x2(t[6], t[7]));
+        auto store4 = [&](bf16_t* o, int q, float a, float b, float c, float d) {
+            *reinterpret_cast<uint2*>(o + ix + 8 * q) = make_uint2(pack_bf16x2(a, b), pack_bf16x2(c, d));
         };
-        if (MODE == FEW_GATEUP) {
-            float a[8];
 #pragma unroll
-            for (int i = 0; i < 8; ++i) a[i] = siluf_(s[i]) * s[8 + i];
-            store8(out.o0, s);
-            store8(out.o1, s + 8);
-            store8(out.o2, a);
-        } else {
-            store8(out.o0, s);
-            store8(out.o0 + 8, s + 8);
+        for (int q = 0; q < (MODE == FEW_GATEUP ? 2 : 4); ++q) {
+            float s[4], a[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) s[i] = acc[mb][4 * q + i];
+            store4(out.o0, q, s[0], s[1], s[2], s[3]);
+            if (MODE == FEW_GATEUP) {
+                float u[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    u[i] = acc[mb][8 + ((4 * q + i) & 7)];
+                    a[i] = s[i] * fast_sigmoid(s[i]) * u[i];
+                }
+                store4(out.o1, q, u[0], u[1], u[2], u[3]);
+                store4(out.o2, q, a[0], a[1], a[2], a[3]);
+            }
             if (MODE == FEW_MLP2) {
-                float a[16];
 #pragma unroll
-                for (int i = 0; i < 16; ++i) a[i] = act_fwd<ACT>(s[i]);
-                store8(out.o1, a);
-                store8(out.o1 + 8, a + 8);
+                for (int i = 0; i < 4; ++i) a[i] = act_fast<ACT>(s[i]);
+                store4(out.o1, q, a[0], a[1], a[2], a[3]);
             }
         }
     }
 }
 
-// C[rows of the tile, n0 ..] = X W;  K x N weights per expert (w1: the second matrix of GATEUP)
+// C[rows of the tile, n0 ..] = X W;  K x N weights per expert (w1: the second matrix of GATEUP).
+// The tiles (row tile, then column tile) are dealt to the XCDs in eight runs of equal length, workgroup L going to XCD
+// L % 8: every XCD gets its share whatever the number of column tiles, and row tiles that read the same weights meet in
+// one L2.
 template <int MODE, int ACT>
 __device__ __forceinline__ void few_block(const bf16_t* __restrict__ x, const int32_t* __restrict__ row_index,   // or NULL
                                           const int32_t* __restrict__ off, const int32_t* __restrict__ map, int K, int N,
                                           const bf16_t* __restrict__ w0, const bf16_t* __restrict__ w1, FewOut out) {
-    __shared__ __align__(16) float red[4 * 64 * 64];
+    __shared__ __align__(16) char smem[kFewStages * kFewStageBytes];
     constexpr int kCols = MODE == FEW_GATEUP ? kFewCols / 2 : kFewCols;
-    const int e = map[4 + 2 * blockIdx.y], n0 = blockIdx.x * kCols;
-    if (e < 0 || n0 >= N) return;
-    const int row0 = map[4 + 2 * blockIdx.y + 1], rows = off[e + 1] - row0;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int c = threadIdx.x & 31;
-    const bf16_t* w = w0;
-    int col = n0 + 4 * c;
-    if (MODE == FEW_GATEUP && c >= 16) {
-        w = w1;
-        col -= 64;
+    const int nt = (N + kCols - 1) / kCols, total = map[0] * nt, run = (total + 7) / 8;
+    const int slot = blockIdx.x >> 3, t = (blockIdx.x & 7) * run + slot;
+    if (slot >= run || t >= total) return;
+    const int tile = t / nt, n0 = (t - tile * nt) * kCols;
+    const int e = map[4 + 2 * tile], row0 = map[4 + 2 * tile + 1], rows = off[e + 1] - row0;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    FewLoader ld;
+    {
+        int r = wave * 16 + (lane >> 2);   // rows past the last one repeat it; what they give is not stored
+        const int c = (lane & 3) ^ ((r >> 2) & 3);
+        r = row0 + (r < rows ? r : rows - 1);
+        ld.x = x + (size_t)(row_index ? row_index[r] : r) * K + 8 * c;
     }
+    const int c = (lane & 15) ^ ((lane >> 4) << 2);
+    const bf16_t* w = MODE == FEW_GATEUP && c >= 8 ? w1 : w0;
+    int col = n0 + 8 * (MODE == FEW_GATEUP ? c & 7 : c);
     if (col >= N) col = n0;   // the second half of a tile at the edge: not stored
-    w += (size_t)e * K * N + col;
-    const int pieces = K / kFewK, p0 = pieces * wave / 4, n = pieces * (wave + 1) / 4 - p0;
+    w += ((size_t)e * K + wave * 8 + (lane >> 4)) * N + col;
+    ld.w[0] = w;
+    ld.w[1] = w + (size_t)4 * N;
+    ld.step = (size_t)kFewK * N;
+    ld.left = K / kFewK;
     if (rows <= 32)
-        few_tile<MODE, ACT, 1, 3>(red, w, N, x, K, row_index, row0, rows, p0 * kFewK, n, out, N, n0);
+        few_tile<MODE, ACT, 1>(ld, smem, K / kFewK, row0, rows, out, N, n0);
     else
-        few_tile<MODE, ACT, 2, 2>(red, w, N, x, K, row_index, row0, rows, p0 * kFewK, n, out, N, n0);
+        few_tile<MODE, ACT, 2>(ld, smem, K / kFewK, row0, rows, out, N, n0);
 }
 
 __global__ __launch_bounds__(256, 2) void ffn_gateup_few_kernel(const bf16_t* __restrict__ xd,
@@ -224,8 +218,10 @@ __global__ __launch_bounds__(256, 2) void mlp2_up_few_kernel(const bf16_t* __res
     few_block<FEW_MLP2, ACT>(xd, row_index, off, map, d, f, w1, nullptr, out);
 }
 
-// columns padded to a multiple of the XCD count: the row tiles of an expert that read the same weights meet in one L2
-inline dim3 few_grid(int N, int cols, int max_tiles) { return dim3(((N + cols - 1) / cols + 7) / 8 * 8, max_tiles); }
+inline dim3 few_grid(int N, int cols, int max_tiles) {
+    const long long tiles = (long long)max_tiles * ((N + cols - 1) / cols);
+    return dim3((unsigned)((tiles + 7) / 8 * 8));
+}
 
 }  // namespace
 

@@ -1,6 +1,6 @@
 """Forward products of experts with few rows (xmoe_ffn_few.hip, taken up to 16 rows per expert on average): segments at
-the edges of a 32- and a 64-row block, several row tiles per expert, empty experts, widths that fill a 128-column
-tile and that do not, K that splits unevenly over a block's four waves.  Every test asserts the kernels that ran.
+the edges of a 32- and a 64-row block, several row tiles per expert, empty experts, widths of one and of several
+64-column tiles.  Every test asserts the kernels that ran.
 
 Tolerance: G, U, H and the activations are one float32-accumulated product rounded to bf16 (2^-9 relative) against a
 float64 product of the same operands; an element that cancels to below the RMS is held to that share of the RMS."""
@@ -100,3 +100,26 @@ def test_two_matrix(rows, d, f, act):
         close(H[s], h)
         a = {"identity": h, "gelu": torch.nn.functional.gelu(h), "silu": h * torch.sigmoid(h)}[act]
         close(Y[s], a.bfloat16().double() @ w[1][e].double(), 2.0 ** -6)
+
+
+@pytest.mark.parametrize("expert", ["swiglu", "identity", "gelu", "silu"])
+@pytest.mark.parametrize("d,f", [(64, 64), (320, 192), (2048, 1408)])
+def test_a_rows_bits_do_not_depend_on_the_row_count(d, f, expert):
+    """The same tokens in a call with few rows and among many others (a decoding step, and a prompt, of one sequence):
+    the direct-to-LDS kernels and these give the same bits, since both add K's products in one ascending order."""
+    import paper_2508_13337_amd as m
+    few, extra = [1, 0, 33, 64, 7] + [0] * 8, [40, 3, 300, 70, 1] + [100] * 8
+    x, _, index, off, w = inputs(few, d, f, True, 3 if expert == "swiglu" else 2)
+    g = torch.Generator().manual_seed(d)
+    many = [a + b for a, b in zip(few, extra)]
+    parts = []
+    for e, n in enumerate(extra):     # every expert's rows of the small call, then others
+        parts += [index[int(off[e]):int(off[e + 1])], torch.randint(0, 37, (n,), generator=g, dtype=torch.int32)]
+    off2 = torch.tensor([0] + list(torch.tensor(many).cumsum(0)), dtype=torch.int32)
+    call = (lambda *a: swiglu(m, *a)) if expert == "swiglu" else (lambda x, o, w, B, i: mlp2(m, x, o, w, expert, B, i))
+    a = call(x, off, w, sum(few), index)
+    b = call(x, off2, w, sum(many), torch.cat(parts))
+    assert any("_few_" in k for k in a[-1]) and not any("_few_" in k for k in b[-1]), (a[-1], b[-1])
+    for p, q in zip(a[:-1], b[:-1]):
+        for e, n in enumerate(few):
+            assert torch.equal(p[int(off[e]):int(off[e]) + n], q[int(off2[e]):int(off2[e]) + n]), (expert, e)
