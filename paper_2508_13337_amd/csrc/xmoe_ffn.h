@@ -92,7 +92,7 @@ int ffn_fwd_dma(const FfnArgs& a, hipStream_t s);
 int ffn_bwd_dma(const FfnArgs& a, hipStream_t s);
 
 // forward products of experts with few rows (the same operands as the direct-to-LDS kernels)
-bool few_rows(int B, int E, int f);
+bool few_rows(int B, int E);
 int ffn_fwd_few(const FfnArgs& a, hipStream_t s);
 int mlp2_fwd_few(const Mlp2Args& a, hipStream_t s);
 

@@ -43,7 +43,7 @@ int xmoe_expert_ffn_fwd(const void* xd, const int32_t* row_index, const int32_t*
     p += ffn_tilemap_bytes(B, E);
     a.act = p;
     hipStream_t s = (hipStream_t)stream;
-    if (ffn_dma_supported(a)) return few_rows(B, E, f) ? ffn_fwd_few(a, s) : ffn_fwd_dma(a, s);
+    if (ffn_dma_supported(a)) return few_rows(B, E) ? ffn_fwd_few(a, s) : ffn_fwd_dma(a, s);
     return ffn_fwd_tile(a, s);
 }
 
@@ -109,7 +109,7 @@ int xmoe_expert_mlp2_fwd(const void* xd, const int32_t* row_index, const int32_t
     p += ffn_tilemap_bytes(B, E);
     a.a_buf = p;
     hipStream_t s = (hipStream_t)stream;
-    if (mlp2_dma_supported(a)) return few_rows(B, E, f) ? mlp2_fwd_few(a, s) : mlp2_fwd_dma(a, s);
+    if (mlp2_dma_supported(a)) return few_rows(B, E) ? mlp2_fwd_few(a, s) : mlp2_fwd_dma(a, s);
     return mlp2_fwd_tile(a, s);
 }
 

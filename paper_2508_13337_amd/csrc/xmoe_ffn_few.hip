@@ -225,13 +225,21 @@ inline dim3 few_grid(int N, int cols, int max_tiles) {
 
 }  // namespace
 
-// Where these kernels are the faster ones (gate/up and down together, us, 256-row tiles | these): mean rows 1: 173 | 154,
-// 8: 228 | 212, 16: 231 | 221, 32: 236 | 248 (64 experts, d 2048, f 1408); 8: 181 | 164, 32: 177 | 183 (32 experts,
-// d 4096, f 1024).  Fewer 256-row tiles than CUs leave most of the chip idle, and the line lies higher: mean rows 8:
-// 119 | 36, 32: 120 | 43 (8 experts, d 2048, f 1408); 32: 247 | 115 (4 experts, d 7168, f 2048).
-bool few_rows(int B, int E, int f) {
-    return B <= 16ll * E || (B <= 32ll * E && (long long)E * ((f + 127) / 128) < 256);
-}
+// Where these kernels are the faster ones: up to 32 rows per expert on average.  Measured (MI355X, gate/up and down
+// together, us, 256-row tiles | these; Zipf: the experts' loads follow rank^-1.2):
+//     mean rows                         1           8          16          32          48          64
+//     64 experts, d 2048, f 1408    240 | 203   234 | 211   241 | 224   247 | 239   251 | 255   254 | 270
+//       Zipf                                    222 | 202   241 | 225   258 | 258   280 | 281   306 | 314
+//     256 experts, d 2048, f 512    347 | 295   342 | 317   360 | 336   367 | 359   377 | 391   388 | 404
+//     32 experts, d 4096, f 1024    183 | 165   179 | 165   183 | 168   181 | 174   183 | 184   185 | 191
+//       Zipf                                    182 | 174   188 | 177   244 | 193   237 | 230   269 | 244
+//     512 experts, d 1024, f 256    228 | 172   229 | 186   238 | 199   246 | 218   257 | 229   262 | 249
+//     64 experts, d 7168, f 256     207 | 146   202 | 153   195 | 158   200 | 175
+//     8 experts, d 2048, f 1408     117 | 29    118 | 29    118 | 30    116 | 30
+// With all rows on one expert they are the faster ones too (64 experts, d 2048, f 1408, mean 16: 96 | 51), but for 8192
+// rows and more (256 experts, d 2048, f 512, mean 32: 106 | 112).  Above 32 rows the 64-row tiles read the weights more
+// often than the 256-row ones wait for them.
+bool few_rows(int B, int E) { return B <= 32ll * E; }
 
 int ffn_fwd_few(const FfnArgs& a, hipStream_t s) {
     const int max_tiles = ffn_max_tiles(a.B, a.E, kFewRows);

@@ -1,4 +1,4 @@
-"""Forward products of experts with few rows (xmoe_ffn_few.hip, taken up to 16 rows per expert on average): segments at
+"""Forward products of experts with few rows (xmoe_ffn_few.hip, taken up to 32 rows per expert on average): segments at
 the edges of a 32- and a 64-row block, several row tiles per expert, empty experts, widths of one and of several
 64-column tiles.  Every test asserts the kernels that ran.
 
@@ -123,3 +123,16 @@ def test_a_rows_bits_do_not_depend_on_the_row_count(d, f, expert):
     for p, q in zip(a[:-1], b[:-1]):
         for e, n in enumerate(few):
             assert torch.equal(p[int(off[e]):int(off[e]) + n], q[int(off2[e]):int(off2[e]) + n]), (expert, e)
+
+
+@pytest.mark.parametrize("E,f,rows,few", [(256, 64, 8192, True), (256, 64, 8193, False), (4, 192, 128, True),
+                                          (4, 192, 129, False)])
+def test_both_sides_of_the_rule(E, f, rows, few):
+    import paper_2508_13337_amd as m
+    d = 64
+    count = [rows // E + (e < rows % E) for e in range(E)]
+    x, xs, index, off, w = inputs(count, d, f, True, 2)
+    H, Y, kernels = mlp2(m, x, off, w, "identity", rows, index)
+    assert ("mlp2_up_few_kernel" in kernels) == few and ("mlp2_up_dma_kernel" in kernels) != few, kernels
+    e = torch.repeat_interleave(torch.arange(E), torch.tensor(count))
+    close(H, torch.bmm(xs.float().unsqueeze(1), w[0].float()[e]).squeeze(1).double())
