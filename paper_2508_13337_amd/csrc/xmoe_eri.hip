@@ -155,11 +155,20 @@ __global__ __launch_bounds__(256) void eri_scatter_kernel(const int32_t* __restr
 // The whole construction in one launch: a block counts the experts of all flat entries, and of those in front of its
 // chunk, by itself instead of taking them from two earlier launches, then ranks and writes its chunk as
 // eri_scatter_kernel does.  Block 0 writes tokens_per_expert and expert_offsets.  Bound by launch latency where a call
-// is small.  Measured (MI355X, sum of the kernels without the gaps between them, three launches | one): 1 chunk, 8 experts
-// 7.2 | 4.9 us; 3 chunks, 64 experts 15.2 | 7.7; 8 chunks, 16 experts 15.4 | 9.4; 9 chunks, 24 experts 15.5 | 10.4.  A
-// chunk more costs every block about 0.4 us, the three launches next to nothing, so the line is drawn at 16.
+// is small.  Measured (MI355X, replayed from a graph, three launches | one, us):
+//     chunks            1             4             8            16       16, every entry on one expert
+//     8 experts     8.0 | 5.4     8.8 | 6.4     9.0 | 7.4     9.2 | 9.2      9.0 | 8.9
+//    64 experts     9.5 | 6.4    10.4 | 7.5    10.5 | 8.4    10.9 | 10.2    10.4 | 9.7
+//   512 experts    15.7 | 8.1    17.0 | 9.4    17.6 | 10.8   18.0 | 12.8    17.3 | 11.7
+// A chunk more costs every block 0.2 to 0.3 us, the three launches next to nothing: 8 experts break even at 16 chunks,
+// and the line is drawn there.
+// COPIES (from 5 chunks on): every expert has kEriCopies counters, chosen by the lane, so that a load that falls on few
+// experts does not send a whole wave to one address (one counter each: 18.5, 19.1 and 20.8 us in the last column); up to
+// 4 chunks adding them up costs more than it saves.
 constexpr int kEriDirectChunks = 16;
+constexpr int kEriPlainChunks = 4, kEriCopies = 4;
 
+template <bool COPIES>
 __global__ __launch_bounds__(256) void eri_direct_kernel(const int32_t* __restrict__ topk_idx,
                                                          const float* __restrict__ topk_w, int B, int E, int k,
                                                          int ebits, int32_t* __restrict__ tokens_per_expert,
@@ -171,25 +180,49 @@ __global__ __launch_bounds__(256) void eri_direct_kernel(const int32_t* __restri
     extern __shared__ int sub_count[];             // as in eri_scatter_kernel
     __shared__ int total[XMOE_MAX_EXPERTS];        // entries of every expert, then their exclusive prefix
     __shared__ int before[XMOE_MAX_EXPERTS];       // those in front of this block's chunk
+    __shared__ int total_c[COPIES ? XMOE_MAX_EXPERTS * kEriCopies : 1], before_c[COPIES ? XMOE_MAX_EXPERTS * kEriCopies : 1];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     for (int i = threadIdx.x; i < kSubPerChunk * E; i += 256) sub_count[i] = 0;
     for (int i = threadIdx.x; i < XMOE_MAX_EXPERTS; i += 256) total[i] = before[i] = 0;
+    if (COPIES)
+        for (int i = threadIdx.x; i < kEriCopies * E; i += 256) total_c[i] = before_c[i] = 0;
     __syncthreads();
     const int base = blockIdx.x * kEriChunk;
-    for (int n0 = 0; n0 < B; n0 += kEriChunk) {
-        int e[kEriChunk / 256];
+    constexpr int kR = (COPIES ? 4 : 1) * kEriChunk / 256;   // entries per thread that are fetched together
+    for (int n0 = 0; n0 < B; n0 += kR * 256) {
+        int e[kR];
 #pragma unroll
-        for (int r = 0; r < kEriChunk / 256; ++r) {
+        for (int r = 0; r < kR; ++r) {
             const int n = n0 + r * 256 + threadIdx.x;
-            e[r] = n < B ? topk_idx[n] : -1;
+            e[r] = topk_idx[n < B ? n : B - 1];
         }
 #pragma unroll
-        for (int r = 0; r < kEriChunk / 256; ++r)
-            if ((unsigned)e[r] < (unsigned)E) atomicAdd(n0 < base ? &before[e[r]] : &total[e[r]], 1);
+        for (int r = 0; r < kR; ++r) {
+            const int n = n0 + r * 256 + threadIdx.x;
+            if (n >= B || (unsigned)e[r] >= (unsigned)E) continue;
+            const bool front = n0 + r * 256 < base;
+            if (COPIES)
+                atomicAdd((front ? before_c : total_c) + e[r] * kEriCopies + (lane & (kEriCopies - 1)), 1);
+            else
+                atomicAdd((front ? before : total) + e[r], 1);
+        }
     }
     int my_e[kSubPerChunk / 4], my_rank[kSubPerChunk / 4];
     eri_rank(topk_idx, base, B, E, ebits, sub_count, my_e, my_rank);
     __syncthreads();
+    if (COPIES) {
+        for (int e = threadIdx.x; e < E; e += 256) {
+            int a = 0, b = 0;
+#pragma unroll
+            for (int c = 0; c < kEriCopies; ++c) {
+                a += total_c[e * kEriCopies + c];
+                b += before_c[e * kEriCopies + c];
+            }
+            total[e] = a;
+            before[e] = b;
+        }
+        __syncthreads();
+    }
     // `total` holds the entries from the chunk on; one wave adds those in front and scans
     if (wave == 0) {
         constexpr int kPer = XMOE_MAX_EXPERTS / 64;
@@ -432,11 +465,17 @@ static int build_eri_launch(const int32_t* topk_idx, const float* topk_w, int T,
     int ebits = 0;
     while ((1 << ebits) < E) ++ebits;
     if (nchunks > 0 && nchunks <= kEriDirectChunks) {
-        XMOE_LAUNCH(K_ERI_DIRECT, s,
-                    hipLaunchKernelGGL(eri_direct_kernel, dim3(nchunks), dim3(256),
-                                       (size_t)kSubPerChunk * E * sizeof(int), s, topk_idx, topk_w, B, E, k, ebits,
-                                       tokens_per_expert, expert_offsets, token_ids, expert_ids, combine_weights,
-                                       row_of_slot));
+#define XMOE_CALL(COPIES)                                                                                             \
+    XMOE_LAUNCH(K_ERI_DIRECT, s,                                                                                      \
+                hipLaunchKernelGGL(eri_direct_kernel<COPIES>, dim3(nchunks), dim3(256),                               \
+                                   (size_t)kSubPerChunk * E * sizeof(int), s, topk_idx, topk_w, B, E, k, ebits,       \
+                                   tokens_per_expert, expert_offsets, token_ids, expert_ids, combine_weights,         \
+                                   row_of_slot))
+        if (nchunks <= kEriPlainChunks)
+            XMOE_CALL(false);
+        else
+            XMOE_CALL(true);
+#undef XMOE_CALL
         return XMOE_OK;
     }
     if (nchunks > 0)

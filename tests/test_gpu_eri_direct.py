@@ -1,5 +1,6 @@
 """xmoe_build_eri on either side of the line between its one-launch and its three-launch construction (16 chunks of
-1024 flat entries), with chunks that are not full and expert counts up to the limit: bit-equal to a stable sort."""
+1024 flat entries), with chunks that are not full, expert counts up to the limit and loads that all fall on the same
+few experts (the counters are kept in several copies from 5 chunks on): bit-equal to a stable sort."""
 import pytest
 import torch
 
@@ -8,12 +9,16 @@ from gpu_util import launched
 pytestmark = pytest.mark.gpu
 
 
+@pytest.mark.parametrize("load", ["even", "same experts"])
 @pytest.mark.parametrize("T,E,k", [(1, 1, 1), (1, 512, 8), (170, 64, 6), (171, 64, 6), (2730, 64, 6), (2731, 64, 6),
-                                   (2048, 512, 8), (2049, 512, 8), (16384, 7, 1), (333, 96, 3)])
-def test_tables(T, E, k):
+                                   (2048, 512, 8), (2049, 512, 8), (16384, 7, 1), (333, 96, 3), (4096, 130, 1),
+                                   (4097, 128, 1), (1366, 129, 3), (1400, 257, 6)])
+def test_tables(T, E, k, load):
     import paper_2508_13337_amd as m
     g = torch.Generator().manual_seed(T + E + k)
-    idx = torch.rand((T, E), generator=g).argsort(1)[:, :k].int()
+    idx = torch.rand((T, E), generator=g).argsort(1)[:, :k].int().contiguous()
+    if load == "same experts":
+        idx = idx[:1].repeat(T, 1)
     w = torch.rand((T, k), generator=g)
     B = T * k
     i32 = dict(dtype=torch.int32, device="cuda")
