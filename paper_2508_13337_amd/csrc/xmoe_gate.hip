@@ -13,17 +13,18 @@ namespace xmoe {
 // product whose terms are added one at a time, which is what the matrix instructions with K = 1 compute: one fused
 // multiply-add per output and instruction, with several independent blocks per instruction (v_mfma_f32_32x32x1_2b_f32,
 // v_mfma_f32_16x16x1_4b_f32).  The blocks take l, l+32 (TL = 32) or l, l+16, l+32, l+48 (TL = 16).  Same bits as the
-// plain loop, at four times the rate of the float32 ALUs without packed instructions.
+// plain loop, at twice the rate of the float32 ALUs without packed instructions.
 //
 //   block = 8 waves, TL tokens x TL experts.  Wave w owns the pairs l = 2(w%4) + {0, 1} + 8(w/4) (+ the blocks' offsets,
 //   + 16 for TL = 32), so that one LDS read of x serves two instructions; offsets 32 and 16 of the fold stay in
-//   registers, 8 to 1 go through LDS.  A stage is 32 KiB: 2 KiB of i per token and expert row, fetched one stage ahead
-//   through registers.  x past d reads +0 and w past d -0: their product -0 leaves every sum as it is, -0 included.
+//   registers, 8 to 1 go through LDS.  A stage is 16 KiB of either operand, 512 bytes (TL = 32) or 1 KiB (TL = 16) of
+//   i per token, fetched one stage ahead through registers.  x past d reads +0 and w past d -0: their product -0 leaves
+//   every sum as it is, -0 included.
 //
-// Bound: TL = 32 by the matrix cores and the barriers between its stages (60 TFLOP/s), TL = 16 (few tokens) by the
-// latency of its stages.  Measured (MI355X, bf16, 64 experts, d 2048; before: float32 ALUs, operands staged through LDS
-// a 64-wide chunk at a time): T 8: 28 -> 9 us, T 509: 28 -> 11, T 8192: 50 -> 36, T 65536: 399 -> 287; d 1000, 24
-// experts, T 3001: 16 -> 9.
+// Bound: TL = 32 by the barriers between its stages: about 180 registers leave one block of 8 waves per CU, and nothing
+// runs over them (61 to 72 TFLOP/s); TL = 16 (few tokens) by the latency of its stages.  Measured (MI355X, bf16, 64
+// experts, d 2048; float32 ALUs, operands staged through LDS a 64-wide chunk at a time | this): T 8: 19 | 9 us, T 509:
+// 19 | 10, T 8192: 52 | 35, T 65536: 334 | 238; d 1000, 24 experts, T 3001: 12 | 8.
 typedef __attribute__((ext_vector_type(32))) float gate_f32x32_t;
 template <int TL>
 struct GateMma;
@@ -87,11 +88,13 @@ __device__ __forceinline__ void gate_pair(const float* p, float& a, float& b) {
     b = v.y;
 }
 
-// TL = 32 from this many of its blocks on: one per CU.  Below, tiles of a quarter of the size spread over more of the
-// chip, and a stage is twice as deep.
+// TL = 32 from this many of its blocks on (one per CU) and from 17 experts on.  Below, tiles of a quarter of the size
+// spread over more of the chip, and a stage is twice as deep; up to 16 experts the larger tile would spend half of its
+// matrix work or more on columns that do not exist (bf16 d 2048, T 8192 | 32768, us at TL = 32, at 16: 8 experts 18 | 62,
+// 12 | 39; 4 experts d 512, T 32768: 33, 18).
 constexpr long kGateBigBlocks = 256;
 
-template <typename T, int TL, bool VEC>
+template <typename T, int TL, bool VECX, bool VECW>
 __global__ __launch_bounds__(512, 2) void gate_logits_kernel(const T* __restrict__ x, const T* __restrict__ w,
                                                              const float* __restrict__ bias,
                                                              float* __restrict__ logits, int Tn, int d, int E) {
@@ -119,13 +122,16 @@ __global__ __launch_bounds__(512, 2) void gate_logits_kernel(const T* __restrict
             int t = t0 + v / VX;
             t = t < Tn ? t : Tn - 1;      // rows past the last one repeat it; what they give is not stored
             const int ix = i0 + (v % VX) * EV, iw = i0 + v / VW, e = e0 + (v % VW) * EV;
-            if (VEC) {   // no vector straddles an end: those past it come from the pad
+            if (VECX) {   // no vector straddles an end: those past it come from the pad
                 const gate_gptr px = (gate_gptr)(const char*)(x + (size_t)t * d + ix);
-                const gate_gptr pw = (gate_gptr)(const char*)(w + (size_t)iw * E + (e < E ? e : 0));
                 rx[q] = gate_load16<T>(ix < d ? px : (gate_gptr)(const char*)kGatePad);
-                rw[q] = gate_load16<T>(iw < d ? pw : (gate_gptr)(const char*)(kGatePad + (sizeof(T) == 2 ? 4 : 8)));
             } else {
                 rx[q] = gate_load(x + (size_t)t * d + ix, d - ix, 0u);
+            }
+            if (VECW) {
+                const gate_gptr pw = (gate_gptr)(const char*)(w + (size_t)iw * E + (e < E ? e : 0));
+                rw[q] = gate_load16<T>(iw < d ? pw : (gate_gptr)(const char*)(kGatePad + (sizeof(T) == 2 ? 4 : 8)));
+            } else {
                 rw[q] = gate_load(w + (size_t)iw * E + e, iw < d ? E - e : 0, sizeof(T) == 2 ? 0x8000u : 0x80000000u);
             }
         }
@@ -171,14 +177,16 @@ __global__ __launch_bounds__(512, 2) void gate_logits_kernel(const T* __restrict
     fetch(0);
     stage(0);
     __syncthreads();
-    for (int g = 0; g < stages; ++g) {
-        fetch((g + 1) * KI);   // past the last stage: nothing but pad
+    for (int g = 0; g + 1 < stages; ++g) {
+        fetch((g + 1) * KI);
         __builtin_amdgcn_sched_barrier(0);   // the loads stay in front of the matrix instructions they run under
         multiply(g);
         stage((g + 1) & 1);
         // the stage written above is read after this barrier; its buffer was last read before the previous one
         __syncthreads();
     }
+    multiply(stages - 1);
+    __syncthreads();
 
     // fold: offset 32 between the blocks, 16 between the blocks (TL = 16) or the j (TL = 32), then 8, 4, 2, 1 over the
     // waves' sums red[l][token][expert], l = 0..15
@@ -803,20 +811,25 @@ template <typename T>
 static int launch_gate_logits(const void* x, const void* w, const float* bias, float* logits, int Tn, int d,
                               int E, hipStream_t s) {
     const long blocks32 = (long)((Tn + 31) / 32) * ((E + 31) / 32);
-    // whole 16-byte vectors in either operand: no load needs a branch, and a stage's loads are in flight together
-    const bool vec = d % (16 / (int)sizeof(T)) == 0 && E % (16 / (int)sizeof(T)) == 0;
-#define XMOE_GATE(TL, VEC)                                                                                              \
+    // whole 16-byte vectors in an operand: none of its loads needs a branch, and a stage's are in flight together
+    const bool vx = d % (16 / (int)sizeof(T)) == 0, vw = E % (16 / (int)sizeof(T)) == 0;
+#define XMOE_GATE_V(TL, VX, VW)                                                                                         \
     XMOE_LAUNCH(K_GATE_LOGITS, s,                                                                                       \
-                hipLaunchKernelGGL((gate_logits_kernel<T, TL, VEC>), dim3((Tn + TL - 1) / TL, (E + TL - 1) / TL), dim3(512), \
-                                   0, s, (const T*)x, (const T*)w, bias, logits, Tn, d, E))
-    if (blocks32 >= kGateBigBlocks) {
-        if (vec) XMOE_GATE(32, true);
-        else XMOE_GATE(32, false);
-    } else {
-        if (vec) XMOE_GATE(16, true);
-        else XMOE_GATE(16, false);
-    }
+                hipLaunchKernelGGL((gate_logits_kernel<T, TL, VX, VW>), dim3((Tn + TL - 1) / TL, (E + TL - 1) / TL),    \
+                                   dim3(512), 0, s, (const T*)x, (const T*)w, bias, logits, Tn, d, E))
+#define XMOE_GATE(TL)                                  \
+    do {                                               \
+        if (vx && vw) XMOE_GATE_V(TL, true, true);     \
+        else if (vx) XMOE_GATE_V(TL, true, false);     \
+        else if (vw) XMOE_GATE_V(TL, false, true);     \
+        else XMOE_GATE_V(TL, false, false);            \
+    } while (0)
+    if (E > 16 && blocks32 >= kGateBigBlocks)
+        XMOE_GATE(32);
+    else
+        XMOE_GATE(16);
 #undef XMOE_GATE
+#undef XMOE_GATE_V
     return XMOE_OK;
 }
 

@@ -1,5 +1,5 @@
 """xmoe_gate_logits on the K = 1 matrix instructions: the same bits as the oracle's loop, at the edges of its two tile
-sizes (16 x 16 and 32 x 32, the larger from 256 of its blocks on), of its stages and of 16-byte vectors."""
+sizes (16 x 16 up to 16 experts, and below 256 blocks of 32 x 32), of its stages and of 16-byte vectors in either operand."""
 import numpy as np
 import pytest
 import torch
@@ -11,6 +11,7 @@ pytestmark = pytest.mark.gpu
 SHAPES = [  # T, d, E
     (1, 1, 1), (1, 64, 3), (15, 63, 7), (16, 65, 16), (17, 512, 17), (33, 1000, 64), (8, 2048, 64), (3, 129, 512),
     (4096, 64, 64), (4095, 130, 63), (8161, 257, 1), (513, 384, 512), (1100, 77, 250),
+    (8200, 136, 4), (8193, 513, 16), (8200, 256, 17), (8200, 250, 24), (9000, 1032, 20),
 ]
 
 
