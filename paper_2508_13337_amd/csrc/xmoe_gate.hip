@@ -1,5 +1,7 @@
 // Gating of the padding-free MoE layer (paper: Listing 1 gating(); Appendix B.3 "Padding-free Gating"):
 // gate projection in a fixed float32 order, softmax + top-k routing, and their backward.
+#include <type_traits>
+
 #include "xmoe_internal.h"
 #include "xmoe_sizes.h"
 
@@ -397,6 +399,21 @@ __device__ __forceinline__ void load_pair(const float* p, bool ok0, bool ok1, fl
     }
 }
 
+// The same from an address that is always readable (p[0] and p[o1]); IN: both elements are known to exist.
+template <bool VEC, bool IN, typename T>
+__device__ __forceinline__ void take_pair(const T* p, int o1, bool ok0, bool ok1, float& a, float& b) {
+    if (VEC) {
+        gate_pair(p, a, b);
+    } else {
+        a = to_float(p[0]);
+        b = to_float(p[IN ? 1 : o1]);
+    }
+    if (!IN) {
+        a = ok0 ? a : 0.f;
+        b = ok1 ? b : 0.f;
+    }
+}
+
 // partial[s][i][e] = sum over the s-th slice of tokens of x[t,i] * dlogits[t,e]
 // The summation index is the token, and both operands are stored token-major, so a half-wave reads consecutive
 // elements of one token's row: no transposition.  A block owns 64 rows i x 64 columns e of one slice.  The rows and
@@ -404,11 +421,20 @@ __device__ __forceinline__ void load_pair(const float* p, bool ok0, bool ok1, fl
 // i0 + 2r + a, column c of block b is e0 + 2c + b), so that one 4-byte load of x and one 8-byte load of dlogits
 // per lane feed four instructions.  The block's four waves take interleaved runs of 16 tokens each (enough waves in
 // flight to hide the loads' latency), and their partial tiles are added through LDS in wave order.
-// Bound by the latency of its loads: all of a round's are issued before the first is waited for (with a branch around
-// each for the edges they were waited for one by one: T 256 d 128 E 8 16 -> 9 us, T 2048 d 1024 E 16 24 -> 10).
-// grid = (ceil(d/64), ceil(E/64), splits).  VEC: the pairs may be fetched with one load.
-template <typename T, bool VEC>
-__global__ __launch_bounds__(256) void gate_bwd_dw_kernel(const T* __restrict__ x, const float* __restrict__ dl,
+// Bound by the latency of its loads where the blocks are few: all of a round's are issued before the first is waited for
+// (with a branch around each for the edges they were waited for one by one: float32 T 256 d 128 E 8 15 -> 11 us, T 2048
+// d 1024 E 16 16 -> 12).  Rounds whose tokens all exist fetch without a choice of address; columns past the end of d or E
+// read an element that exists and are cleared.
+// grid = (ceil(d/64), ceil(E/64), splits).  VECX, VECE: the pairs of x, of dlogits may be fetched with one load.
+// MODE:
+//   DW_FREE   whole rounds in the compiler's own order: other waves hide the latency, and loads sunk between the matrix
+//             instructions take fewer registers.  float32 from 512 blocks on, us without | with it: T 16384 d 1000 E 256
+//             173 | 111, T 3001 36 | 27, T 16384 d 2048 E 64 85 | 62 (1024 blocks); below: T 3001 d 1000 E 64 (192
+//             blocks) 12 | 17, T 65536 d 128 E 64 (64) 44 | 107.  bf16: 115 | 117 at d 1000 E 256, 32 | 52 at E 64.
+//   DW_TAIL   no slice has a whole round (T < 16): the code for them is left out (0.7 us of 7.5)
+enum DwMode { DW_BATCH = 0, DW_FREE = 1, DW_TAIL = 2 };
+template <typename T, bool VECX, bool VECE, int MODE>
+__global__ __launch_bounds__(256, MODE == DW_FREE ? 4 : 1) void gate_bwd_dw_kernel(const T* __restrict__ x, const float* __restrict__ dl,
                                                           float* __restrict__ partial, int Tn, int d, int E,
                                                           int t_per_split) {
     __shared__ float red[4][32][64];   // [wave][accumulator register][lane], used once per row block a
@@ -430,16 +456,26 @@ __global__ __launch_bounds__(256) void gate_bwd_dw_kernel(const T* __restrict__ 
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[a][b][v] = 0.f;
     constexpr int U = 8;   // instructions' worth of operands fetched before the first is used
-    for (int t0 = tb + wave * 2 * U; t0 < te; t0 += 4 * 2 * U) {
+    const int o_i = ok_i1 ? 1 : 0, o_e = ok_e1 ? 1 : 0;
+    // t_in: all of the round's tokens exist; x_in, e_in: so do all of the block's rows i (columns e)
+    auto round = [&](auto t_in, auto x_in, auto e_in, int t0) {
         float av[U][2], bv[U][2];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int t = t0 + 2 * u + h;
-            const bool ok_t = t < te;
-            load_pair<VEC>(xa + (size_t)(ok_t ? t : tb) * d, ok_t && ok_i0, ok_t && ok_i1, av[u][0], av[u][1]);
-            load_pair<VEC>(ba + (size_t)(ok_t ? t : tb) * E, ok_t && ok_e0, ok_t && ok_e1, bv[u][0], bv[u][1]);
+            const bool ok_t = decltype(t_in)::value || t < te;
+            const T* px = xa + (size_t)(ok_t ? t : tb) * d;
+            const float* pb = ba + (size_t)(ok_t ? t : tb) * E;
+            if (decltype(t_in)::value) {
+                take_pair<VECX, decltype(x_in)::value>(px, o_i, ok_i0, ok_i1, av[u][0], av[u][1]);
+                take_pair<VECE, decltype(e_in)::value>(pb, o_e, ok_e0, ok_e1, bv[u][0], bv[u][1]);
+            } else {
+                load_pair<VECX>(px, ok_t && ok_i0, ok_t && ok_i1, av[u][0], av[u][1]);
+                load_pair<VECE>(pb, ok_t && ok_e0, ok_t && ok_e1, bv[u][0], bv[u][1]);
+            }
         }
-        __builtin_amdgcn_sched_barrier(0);   // all of them in flight before the first is waited for
+        // all of them in flight before the first is waited for
+        if (MODE != DW_FREE || !decltype(x_in)::value || !decltype(e_in)::value) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int u = 0; u < U; ++u)
 #pragma unroll
@@ -447,7 +483,20 @@ __global__ __launch_bounds__(256) void gate_bwd_dw_kernel(const T* __restrict__ 
 #pragma unroll
                 for (int b = 0; b < 2; ++b)
                     acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[u][a], bv[u][b], acc[a][b], 0, 0, 0);
+    };
+    int t0 = tb + wave * 2 * U;
+    auto full_rounds = [&](auto x_in, auto e_in) {
+        for (; t0 + 2 * U <= te; t0 += 4 * 2 * U) round(std::true_type{}, x_in, e_in, t0);
+    };
+    if (MODE != DW_TAIL) {
+        if (i0 + 64 <= d && e0 + 64 <= E)
+            full_rounds(std::true_type{}, std::true_type{});
+        else if (i0 + 64 <= d)
+            full_rounds(std::true_type{}, std::false_type{});
+        else
+            full_rounds(std::false_type{}, std::false_type{});
     }
+    for (; t0 < te; t0 += 4 * 2 * U) round(std::false_type{}, std::false_type{}, std::false_type{}, t0);
     float* out = partial + (size_t)blockIdx.z * d * E;
 #pragma unroll
     for (int a = 0; a < 2; ++a) {
@@ -488,15 +537,18 @@ __global__ __launch_bounds__(256) void gate_bwd_dw_reduce_kernel(const float* __
 // One wave: 32 tokens x up to kDxCols columns i; the token rows of dlogits stay in registers across the columns.
 constexpr int kDxCols = 256;
 
+// full: all 32 exist, whatever the alignment of the row (wave-uniform)
 template <typename T>
-__device__ __forceinline__ void load_row32(const T* __restrict__ p, int n_valid, bool vec, float (&v)[32]);
+__device__ __forceinline__ void load_row32(const T* __restrict__ p, int n_valid, bool full, float (&v)[32]);
 template <>
-__device__ __forceinline__ void load_row32<float>(const float* __restrict__ p, int n_valid, bool vec, float (&v)[32]) {
-    if (vec) {
+__device__ __forceinline__ void load_row32<float>(const float* __restrict__ p, int n_valid, bool full,
+                                                  float (&v)[32]) {
+    if (full) {
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
-            const float4 f = reinterpret_cast<const float4*>(p)[q];
-            v[4 * q] = f.x; v[4 * q + 1] = f.y; v[4 * q + 2] = f.z; v[4 * q + 3] = f.w;
+            const GateVec<float> f = reinterpret_cast<const GateVec<float>*>(p)[q];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) v[4 * q + j] = __uint_as_float(f.v[j]);
         }
     } else {
 #pragma unroll
@@ -504,17 +556,16 @@ __device__ __forceinline__ void load_row32<float>(const float* __restrict__ p, i
     }
 }
 template <>
-__device__ __forceinline__ void load_row32<bf16_t>(const bf16_t* __restrict__ p, int n_valid, bool vec,
+__device__ __forceinline__ void load_row32<bf16_t>(const bf16_t* __restrict__ p, int n_valid, bool full,
                                                    float (&v)[32]) {
-    if (vec) {
+    if (full) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            const uint4 u4 = reinterpret_cast<const uint4*>(p)[q];
-            const uint32_t u[4] = {u4.x, u4.y, u4.z, u4.w};
+            const GateVec<bf16_t> f = reinterpret_cast<const GateVec<bf16_t>*>(p)[q];
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                v[8 * q + 2 * j] = __uint_as_float(u[j] << 16);
-                v[8 * q + 2 * j + 1] = __uint_as_float(u[j] & 0xffff0000u);
+                v[8 * q + 2 * j] = __uint_as_float(f.v[j] << 16);
+                v[8 * q + 2 * j + 1] = __uint_as_float(f.v[j] & 0xffff0000u);
             }
         }
     } else {
@@ -523,11 +574,11 @@ __device__ __forceinline__ void load_row32<bf16_t>(const bf16_t* __restrict__ p,
     }
 }
 
-// vec: E % 64 == 0 and both operands 16-byte aligned
-template <typename T>
+// FEW: E < 64, no run of 32 is known to be complete (the code for complete ones left out: bf16 T 65536 d 2048 E 8
+// 335 -> 247 us)
+template <typename T, bool FEW>
 __global__ __launch_bounds__(256) void gate_bwd_dx_kernel(const float* __restrict__ dl, const T* __restrict__ w,
-                                                          T* __restrict__ dxg, int Tn, int d, int E, int cols,
-                                                          int vec) {
+                                                          T* __restrict__ dxg, int Tn, int d, int E, int cols) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int t0 = (blockIdx.x * 4 + wave) * 32;
     if (t0 >= Tn) return;
@@ -536,9 +587,10 @@ __global__ __launch_bounds__(256) void gate_bwd_dx_kernel(const float* __restric
     const int iend = ibeg + cols < d ? ibeg + cols : d;
     const bool ok_t = t0 + c < Tn;
     const float* arow = dl + (size_t)(ok_t ? t0 + c : 0) * E + 32 * h;
-    const bool one_chunk = E <= 64;
+    const bool one_chunk = FEW || E <= 64;
     float av[32];
-    if (one_chunk) load_row32<float>(arow, ok_t ? E - 32 * h : 0, vec && ok_t, av);
+    // (full: rows past the last one read row 0 and are cleared)
+    if (one_chunk) load_row32<float>(arow, ok_t ? E - 32 * h : 0, !FEW && E == 64, av);
     if (one_chunk && !ok_t) {
 #pragma unroll
         for (int q = 0; q < 32; ++q) av[q] = 0.f;
@@ -553,13 +605,13 @@ __global__ __launch_bounds__(256) void gate_bwd_dx_kernel(const float* __restric
             float bv[32];
             const int n_valid = E - e0 - 32 * h;   // experts left in this lane's run of 32
             if (!one_chunk) {
-                load_row32<float>(arow + e0, ok_t ? n_valid : 0, vec && ok_t, av);
+                load_row32<float>(arow + e0, ok_t ? n_valid : 0, !FEW && E - e0 >= 64, av);
                 if (!ok_t) {
 #pragma unroll
                     for (int q = 0; q < 32; ++q) av[q] = 0.f;
                 }
             }
-            load_row32<T>(brow + e0, ok_i ? n_valid : 0, vec && ok_i, bv);
+            load_row32<T>(brow + e0, ok_i ? n_valid : 0, !FEW && E - e0 >= 64, bv);
             if (!ok_i) {
 #pragma unroll
                 for (int q = 0; q < 32; ++q) bv[q] = 0.f;
@@ -861,31 +913,44 @@ static int launch_gate_bwd(const void* x, const void* w, const float* dl, int Tn
         }
         return XMOE_OK;
     }
-    // d and E even: a pair lies in the matrix whole or not at all
-    const bool pairs = d % 2 == 0 && (reinterpret_cast<uintptr_t>(x) & (2 * sizeof(T) - 1)) == 0 && E % 2 == 0 &&
-                       (reinterpret_cast<uintptr_t>(dl) & 7u) == 0;
-    if (pairs)
-        XMOE_LAUNCH(K_GATE_BWD_DW, s,
-                    hipLaunchKernelGGL((gate_bwd_dw_kernel<T, true>), g1, dim3(256), 0, s, (const T*)x, dl, partial, Tn, d,
-                                       E, tps));
-    else
-        XMOE_LAUNCH(K_GATE_BWD_DW, s,
-                    hipLaunchKernelGGL((gate_bwd_dw_kernel<T, false>), g1, dim3(256), 0, s, (const T*)x, dl, partial, Tn, d,
-                                       E, tps));
+    // d (E) even: a pair lies in a row of x (dlogits) whole or not at all
+    const bool px = d % 2 == 0 && (reinterpret_cast<uintptr_t>(x) & (2 * sizeof(T) - 1)) == 0;
+    const bool pe = E % 2 == 0 && (reinterpret_cast<uintptr_t>(dl) & 7u) == 0;
+#define XMOE_GATE_DW_M(VX, VE, MODE)                                                                                    \
+    XMOE_LAUNCH(K_GATE_BWD_DW, s,                                                                                       \
+                hipLaunchKernelGGL((gate_bwd_dw_kernel<T, VX, VE, MODE>), g1, dim3(256), 0, s, (const T*)x, dl,         \
+                                   partial, Tn, d, E, tps))
+#define XMOE_GATE_DW(VX, VE)                                                           \
+    do {                                                                               \
+        if (tps < 16) XMOE_GATE_DW_M(VX, VE, DW_TAIL);                                 \
+        else if (batch) XMOE_GATE_DW_M(VX, VE, DW_BATCH);                              \
+        else XMOE_GATE_DW_M(VX, VE, (sizeof(T) == 2 ? (int)DW_BATCH : (int)DW_FREE));  \
+    } while (0)
+    const bool batch = sizeof(T) == 2 || (long)g1.x * g1.y * g1.z < 512;
+    if (px && pe) XMOE_GATE_DW(true, true);
+    else if (px) XMOE_GATE_DW(true, false);
+    else if (pe) XMOE_GATE_DW(false, true);
+    else XMOE_GATE_DW(false, false);
+#undef XMOE_GATE_DW
+#undef XMOE_GATE_DW_M
     size_t n = (size_t)d * E;
     XMOE_LAUNCH(K_GATE_BWD_DW_REDUCE, s,
                 hipLaunchKernelGGL(gate_bwd_dw_reduce_kernel<T>, dim3((unsigned)((n + 255) / 256)), dim3(256), 0,
                                    s, partial, splits, n, (T*)dwr));
     // columns per wave: fewer where that many would leave CUs without a block.  Fetching the rows of dlogits again costs
-    // less than the idle CUs (float32 T 256 d 128 E 8: 12 -> 5 us, T 2048 d 1024 E 16: 25 -> 9, bf16 T 3001 d 1000 E 24:
-    // 37 -> 18; part of it from fetching the elements of rows that are no whole vectors without branches)
+    // less than the idle CUs (float32 T 256 d 128 E 8: 14 -> 7 us, T 2048 d 1024 E 16: 26 -> 11, bf16 T 3001 d 1000 E 24:
+    // 34 -> 19; part of it from fetching the elements of rows that are no whole vectors without branches)
     int cols = kDxCols;
     while (cols > 32 && (long)((Tn + 127) / 128) * ((d + cols - 1) / cols) < 512) cols /= 2;
     dim3 g2((Tn + 127) / 128, (d + cols - 1) / cols);
-    const int vec = (E % 64 == 0) && aligned16(dl) && aligned16(w);
-    XMOE_LAUNCH(K_GATE_BWD_DX, s,
-                hipLaunchKernelGGL(gate_bwd_dx_kernel<T>, g2, dim3(256), 0, s, dl, (const T*)w, (T*)dxg, Tn, d, E,
-                                   cols, vec));
+    if (E < 64)
+        XMOE_LAUNCH(K_GATE_BWD_DX, s,
+                    hipLaunchKernelGGL((gate_bwd_dx_kernel<T, true>), g2, dim3(256), 0, s, dl, (const T*)w, (T*)dxg, Tn, d,
+                                       E, cols));
+    else
+        XMOE_LAUNCH(K_GATE_BWD_DX, s,
+                    hipLaunchKernelGGL((gate_bwd_dx_kernel<T, false>), g2, dim3(256), 0, s, dl, (const T*)w, (T*)dxg, Tn,
+                                       d, E, cols));
     return XMOE_OK;
 }
 

@@ -1,5 +1,6 @@
 """xmoe_gate_logits on the K = 1 matrix instructions: the same bits as the oracle's loop, at the edges of its two tile
-sizes (16 x 16 up to 16 experts, and below 256 blocks of 32 x 32), of its stages and of 16-byte vectors in either operand."""
+sizes (16 x 16 up to 16 experts, and below 256 blocks of 32 x 32), of its stages and of 16-byte vectors in either operand.
+xmoe_gate_logits_bwd in float32, and in bf16 where an operand's rows are no whole vectors, against float64."""
 import numpy as np
 import pytest
 import torch
@@ -50,3 +51,32 @@ def test_special_values(T, E, special):
     logits = torch.empty((T, E), dtype=torch.float32, device="cuda")
     m.xmoe_gate_logits(x.cuda(), w.cuda(), None, logits)
     np.testing.assert_array_equal(logits.cpu().numpy().view(np.uint32), want.view(np.uint32))
+
+
+# dx takes 32, 64, 128 or 256 columns per wave (the more the blocks): 585, 520 (d no multiple of the columns) and 516
+# blocks at the last three; E on both sides of a 64-expert chunk; odd and even d and E
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("shift", [0, 1])
+@pytest.mark.parametrize("T,d,E", [(1, 1, 1), (16, 63, 2), (17, 64, 3), (257, 130, 65), (300, 129, 128), (700, 66, 63),
+                                   (8197, 520, 9), (16500, 501, 24), (16500, 1001, 66)])
+def test_backward_any_shape(T, d, E, shift, dtype):
+    import paper_2508_13337_amd as m
+    g = torch.Generator().manual_seed(T * 31 + d * 7 + E)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    x, w = (torch.randn(s, generator=g).to(dt) for s in ((T, d), (d, E)))
+    dl = torch.randn((T, E), generator=g)
+    # shift: operands that start one element into their storage
+    xs, ws, ds = (torch.empty(t.numel() + 1, dtype=t.dtype, device="cuda")[shift:shift + t.numel()].view(t.shape).copy_(t)
+                  for t in (x, w, dl))
+    dw, dx = torch.full((d + 1, E), 5.0, dtype=dt, device="cuda"), torch.full((T + 1, d), 5.0, dtype=dt, device="cuda")
+    tmp = m.alloc_workspace(m.xmoe_workspace_bytes(m.WS_GATE_BWD, T, d, E, 1, 0, m.dtype_code(dt)))
+    m.xmoe_gate_logits_bwd(xs, ws, ds, dw[:d], dx[:T], tmp)
+    assert bool((dw[d] == 5.0).all()) and bool((dx[T] == 5.0).all())
+    x64, w64, dl64 = x.double().cuda(), w.double().cuda(), dl.double().cuda()
+    # products of n terms summed in float32: n 2^-24 of the sum of the magnitudes; the bf16 kernels drop 2^-17 of every
+    # dlogits element; one rounding of the result
+    u, split = (2.0 ** -24, 0.0) if dtype == "f32" else (2.0 ** -8, 2.0 ** -16)
+    for got, a, b, n in ((dw[:d], x64.t(), dl64, T), (dx[:T], dl64, w64.t(), E)):
+        want, mag = a @ b, a.abs() @ b.abs()
+        over = (got.double() - want).abs() - ((n + 8) * 2.0 ** -24 + split) * mag * 1.01 - u * want.abs() - 1e-30
+        assert bool((over <= 0).all()), float(over.max())
