@@ -354,19 +354,23 @@ __device__ __forceinline__ void tile_zero(tile_f32x16_t (&acc)[TileShape<BIG>::k
 }
 
 // Sums part[v] over the 32 lanes of each half-wave by halving (a fixed order); lane l then holds the sum of
-// v = (l/2) % 16.
-__device__ __forceinline__ float tile_sum_over_cols(float (&part)[16]) {
-    const int lane = threadIdx.x & 63;
+// v = (l/2) % 16.  One call per step: a loop over the halving width is left rolled by the compiler, and its indexing
+// puts the array in memory (16 KiB of LDS per 256-thread block).
+template <int W>
+__device__ __forceinline__ void tile_fold(float (&part)[16]) {
+    const bool upper = (threadIdx.x & (2 * W)) != 0;
 #pragma unroll
-    for (int w = 8; w >= 1; w >>= 1) {
-        const bool upper = (lane & (2 * w)) != 0;
-#pragma unroll
-        for (int v = 0; v < w; ++v) {
-            const float send = upper ? part[v] : part[v + w];
-            const float keep = upper ? part[v + w] : part[v];
-            part[v] = keep + __shfl_xor(send, 2 * w, 64);
-        }
+    for (int v = 0; v < W; ++v) {
+        const float send = upper ? part[v] : part[v + W];
+        const float keep = upper ? part[v + W] : part[v];
+        part[v] = keep + __shfl_xor(send, 2 * W, 64);
     }
+}
+__device__ __forceinline__ float tile_sum_over_cols(float (&part)[16]) {
+    tile_fold<8>(part);
+    tile_fold<4>(part);
+    tile_fold<2>(part);
+    tile_fold<1>(part);
     return part[0] + __shfl_xor(part[0], 1, 64);
 }
 
