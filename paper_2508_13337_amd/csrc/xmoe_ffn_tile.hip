@@ -130,7 +130,7 @@ __global__ XMOE_TILE_BOUNDS void ffn_gateup_mfma_kernel(const T* __restrict__ xd
     b.init(wg + (size_t)t.e * d * f + n0, wu + (size_t)t.e * d * f + n0, f, f - n0, nullptr, d);
     tile_f32x16_t acc[S::kMI][2];
     tile_zero<BIG>(acc);
-    tile_mainloop<T, BIG, true>(acc, d, t.rows, f - n0, a, b, smem);
+    tile_mainloop<T, BIG, true, false>(acc, d, t.rows, f - n0, a, b, smem);
     const int n = n0 + tile_col<BIG, true>(0);
     if (n >= f) return;
 #pragma unroll
@@ -184,7 +184,7 @@ __global__ XMOE_TILE_BOUNDS void ffn_down_mfma_kernel(const T* __restrict__ A, c
     b.init(wd + (size_t)t.e * f * d + n0, nullptr, d, d - n0, nullptr, f);
     tile_f32x16_t acc[S::kMI][2];
     tile_zero<BIG>(acc);
-    tile_mainloop<T, BIG, false>(acc, f, t.rows, d - n0, a, b, smem);
+    tile_mainloop<T, BIG, false, false>(acc, f, t.rows, d - n0, a, b, smem);
     tile_store<T, BIG>(acc, Y + (size_t)t.row0 * d + n0, d, t.rows, d - n0);
 }
 
@@ -209,7 +209,7 @@ __device__ __forceinline__ void dact_tile(const T* __restrict__ dY, const int32_
     b.init(w + ((size_t)t.e * f + n0) * d, d, f - n0, nullptr);
     tile_f32x16_t acc[S::kMI][2];
     tile_zero<BIG>(acc);
-    tile_mainloop<T, BIG, false>(acc, d, t.rows, f - n0, a, b, smem);
+    tile_mainloop<T, BIG, false, false>(acc, d, t.rows, f - n0, a, b, smem);
     const bool scaled = dy_index && dy_scale;
 #pragma unroll
     for (int mi = 0; mi < S::kMI; ++mi) {
@@ -314,7 +314,7 @@ __global__ XMOE_TILE_BOUNDS void ffn_dx_mfma_kernel(const T* __restrict__ dG, co
         RowSrc<T, S::kThreads> a, b;
         a.init((set ? dU : dG) + (size_t)t.row0 * f, f, t.rows, nullptr);
         b.init((set ? wu : wg) + ((size_t)t.e * d + n0) * f, f, d - n0, nullptr);
-        tile_mainloop<T, BIG, false>(acc, f, t.rows, d - n0, a, b, smem);
+        tile_mainloop<T, BIG, false, false>(acc, f, t.rows, d - n0, a, b, smem);
     }
     tile_store<T, BIG>(acc, dXd + (size_t)t.row0 * d + n0, d, t.rows, d - n0);
 }
@@ -347,7 +347,7 @@ __device__ __forceinline__ void wgrad_tile(const WgradJob<T>& j, int e, int lo, 
     b.init(j.Q + n0 + (GQ ? 0 : (size_t)lo * j.N), nullptr, j.N, j.N - n0, GQ ? j.q_index + lo : nullptr, K);
     tile_f32x16_t acc[S::kMI][2];
     tile_zero<BIG>(acc);
-    tile_mainloop<T, BIG, false>(acc, K, j.M - m0, j.N - n0, a, b, smem);
+    tile_mainloop<T, BIG, false, true>(acc, K, j.M - m0, j.N - n0, a, b, smem);
     tile_store<T, BIG>(acc, j.dW + (size_t)e * j.M * j.N + (size_t)m0 * j.N + n0, j.N, j.M - m0, j.N - n0);
 }
 
@@ -387,7 +387,7 @@ __global__ XMOE_TILE_BOUNDS void mlp2_up_mfma_kernel(const T* __restrict__ xd,
     b.init(w1 + (size_t)t.e * d * f + n0, nullptr, f, f - n0, nullptr, d);
     tile_f32x16_t acc[S::kMI][2];
     tile_zero<BIG>(acc);
-    tile_mainloop<T, BIG, false>(acc, d, t.rows, f - n0, a, b, smem);
+    tile_mainloop<T, BIG, false, false>(acc, d, t.rows, f - n0, a, b, smem);
 #pragma unroll
     for (int ni = 0; ni < 2; ++ni) {
         const int n = n0 + tile_col<BIG, false>(ni);
