@@ -1,7 +1,8 @@
 """The entry point that allocates nothing (xmoe_build_eri_static: the scratch is a static device array inside the
 library) against the existing entry point (xmoe_build_eri with a caller-provided workspace): every output array bit
-for bit, on two calls in a row, the second on a smaller input, so that whatever the first call left in the shared
-array must not leak into the second."""
+for bit, on calls in a row, the second on a smaller input that still uses the array (more than 16 chunks of 1024
+entries), so that whatever the first call left in it must not leak into the second; the third is small enough for the
+one-launch construction, which does not touch the array, and the fourth uses it again."""
 import numpy as np
 import pytest
 import torch
@@ -31,10 +32,11 @@ def _run(m, idx, w, E, static):
     return out
 
 
-def test_build_eri_static_matches_build_eri_twice_in_a_row():
+def test_build_eri_static_matches_build_eri_in_a_row():
     import paper_2508_13337_amd as m
-    # first a large, skewed table (many chunks, every expert count differs), then a smaller one with other sizes
-    for T, E, k, seed, skew in ((8192, 64, 6, 11, 1.5), (1000, 40, 3, 12, 0.0)):
+    # first a large, skewed table (many chunks, every expert count differs), then smaller ones with other sizes
+    for T, E, k, seed, skew in ((8192, 64, 6, 11, 1.5), (6000, 40, 3, 13, 0.0), (1000, 40, 3, 12, 0.0),
+                                (5800, 24, 3, 14, 0.7)):
         print(f"case T={T} E={E} k={k} seed={seed}", flush=True)
         logits = xi.make_logits(T, E, seed=seed)
         if skew:
