@@ -210,7 +210,8 @@ int xmoe_dispatch(const void* x, const int32_t* token_ids, int T, int B, int d, 
  *   G = Xd_e Wg_e,  U = Xd_e Wu_e,  A = silu(G) * U,  Y_e = A Wd_e          (SwiGLU, no biases)
  * xd [B,d]; wg, wu [E,d,f]; wd [E,f,d] ("in x out"); expert_offsets [E+1] int32 on the device with
  * offsets[0] = 0 and offsets[E] = B.  Outputs: y [B,d]; g_save, u_save [B,f] (kept for backward).
- * An expert with no rows reads no weights.
+ * An expert with no rows reads no weights.  For one dt, d, f and operand alignment the bits of a row's results do not
+ * depend on how many other rows its expert or the call has.
  * row_index: NULL, or the gather of dispatch fused into the operand load (Section 3.2 / Table 2 names the dispatched copy
  * as one of the two activation tensors worth removing): xd is then the token matrix x [T,d] itself, row_index [B]
  * int32 holds token ids (token_ids of the ERI-arrays), and row i of the expert input is x[row_index[i]]; no [B,d]

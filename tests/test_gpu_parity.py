@@ -63,9 +63,8 @@ def test_gate_logits_bit_exact(name):
 @pytest.mark.parametrize("T,d,E,bias", [(13, 64, 8, False), (9, 64, 24, True), (257, 128, 40, True),
                                          (100, 192, 72, False), (64, 1024, 256, True), (8, 4096, 32, False)])
 def test_gate_logits_staged_kernel_edge_shapes(T, d, E, bias):
-    """bf16 operands with d % 64 == 0 and E % 8 == 0 take the kernel that stages its operands through LDS: token counts
-    that are not a multiple of a wave's 8, expert counts that do not fill a block's 32 (or need several blocks), one
-    chunk and many chunks of d - against the contract, bit for bit."""
+    """bf16 operands whose rows are whole 16-byte vectors, the loads without a branch: token and expert counts that do not
+    fill a block's 16 (or need several blocks), one stage and many stages of d - against the contract, bit for bit."""
     rng = np.random.default_rng(T * 1000 + d + E)
     x = xi.round_to_storage(rng.standard_normal((T, d)).astype(np.float32), "bf16")
     w = xi.round_to_storage((rng.standard_normal((d, E)) / np.sqrt(d)).astype(np.float32), "bf16")

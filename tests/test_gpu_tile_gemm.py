@@ -198,3 +198,27 @@ def test_expert_mlp2_any_width(d, f, rows, dtype, act):
         within("dw2", got["dw2"][e], dw2[e], eS.T @ D + (n + h) * eps * ((c * ka).T @ D))
         within("row_grad", rg[s], (dA0 * act_h).sum(1),
                (e0 * ka + np.abs(dA0) * sa).sum(1) + (f + h) * eps * (np.abs(dA0) * ka).sum(1))
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_a_rows_bits_do_not_depend_on_the_row_count(dtype):
+    """The same tokens in a call that takes the small tiles and among enough others for the large ones."""
+    import paper_2508_13337_amd as m
+    T, d, f, few, many = 400, 300, 200, (1, 33, 0, 64), (4000, 4300, 90, 8500)
+    g = torch.Generator().manual_seed(7)
+    tdt = torch_dtype(dtype)
+    x, wg, wu, wd = (torch.randn(s, generator=g).to(tdt).cuda() * 0.1
+                     for s in ((T, d), (4, d, f), (4, d, f), (4, f, d)))
+    more = [torch.randint(0, T, (n,), generator=g, dtype=torch.int32) for n in many]
+    runs = []
+    for rows, index in ((few, [i[:n] for i, n in zip(more, few)]), (many, more)):
+        off = torch.tensor([0] + list(torch.tensor(rows).cumsum(0)), dtype=torch.int32).cuda()
+        B = sum(rows)
+        out = [torch.empty((B, n), dtype=tdt, device="cuda") for n in (f, f, d)]
+        ws = m.alloc_workspace(m.xmoe_workspace_bytes(m.WS_FFN_FWD, B, d, 4, 1, f, m.dtype_code(tdt)))
+        m.xmoe_expert_ffn_fwd(x, off, wg, wu, wd, *out, ws, row_index=torch.cat(index).cuda())
+        runs.append((off.tolist(), [o.cpu() for o in out]))
+    (o1, a), (o2, b) = runs
+    for p, q in zip(a, b):
+        for e, n in enumerate(few):
+            assert torch.equal(p[o1[e]:o1[e] + n], q[o2[e]:o2[e] + n]), e
