@@ -5,9 +5,9 @@
 //
 // Measured (MI355X, one training step of the layer; before: 4 x 4 outputs per thread on the float32 ALUs, 22 to 26
 // TFLOP/s for either type, bound by their LDS reads):
-//   float32 T 2048 d 1024 f 704, 16 experts + 1 shared, k 4:   5330 -> 1665 us, the products at 81 to 96 TFLOP/s of 157
-//   bf16    T 3001 d 1000 f 712, 24 experts + 1 shared, k 3:   6720 ->  670 us, the products at 200 to 290 TFLOP/s
-//   float32 T 256 d 128 f 64, 8 experts, k 2 (launch-bound):    203 ->  125 us
+//   float32 T 2048 d 1024 f 704, 16 experts + 1 shared, k 4:   5295 -> 1615 us, the products at 63 to 102 TFLOP/s of 157
+//   bf16    T 3001 d 1000 f 712, 24 experts + 1 shared, k 3:   6735 ->  624 us, the products at 155 to 305 TFLOP/s
+//   float32 T 256 d 128 f 64, 8 experts, k 2 (launch-bound):    203 ->   97 us
 #include "xmoe_ffn.h"
 #include "xmoe_tile_gemm.h"
 

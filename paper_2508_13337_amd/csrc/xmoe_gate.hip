@@ -24,9 +24,9 @@ namespace xmoe {
 //   every sum as it is, -0 included.
 //
 // Bound: TL = 32 by the barriers between its stages: about 180 registers leave one block of 8 waves per CU, and nothing
-// runs over them (61 to 72 TFLOP/s); TL = 16 (few tokens) by the latency of its stages.  Measured (MI355X, bf16, 64
-// experts, d 2048; float32 ALUs, operands staged through LDS a 64-wide chunk at a time | this): T 8: 19 | 9 us, T 509:
-// 19 | 10, T 8192: 52 | 35, T 65536: 334 | 238; d 1000, 24 experts, T 3001: 12 | 8.
+// runs over them (61 to 72 TFLOP/s, the matrix cores busy 36 %); TL = 16 (few tokens) by the latency of its stages.
+// Measured (MI355X, bf16, 64 experts, d 2048; float32 ALUs, operands staged through LDS a 64-wide chunk at a time | this):
+// T 8: 19 | 9 us, T 509: 19 | 10, T 8192: 52 | 35, T 65536: 334 | 238; d 1000, 24 experts, T 3001: 12 | 8.
 typedef __attribute__((ext_vector_type(32))) float gate_f32x32_t;
 template <int TL>
 struct GateMma;
