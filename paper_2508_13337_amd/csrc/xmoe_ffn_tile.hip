@@ -94,17 +94,24 @@ int launch_row_grad_reduce(const float* row_part, int parts, int B, float* row_g
     return XMOE_OK;
 }
 
-// A row GEMM's block: its expert and rows from the tile map (blockIdx.x), its first output column (blockIdx.y).
+// A row GEMM's block: its row tile (expert and rows from the tile map) and column tile.  Blocks go to the XCDs in turn
+// (block b to XCD b % 8); each XCD takes an eighth of the tiles there are, in one run, columns fastest, so that its L2
+// fetches the rows of a tile once for all columns and an expert's weights once for all its row tiles.
 struct RowTile {
-    int e, row0, rows;   // rows: valid rows of the tile, may exceed the tile
-    __device__ __forceinline__ bool init(const int32_t* __restrict__ off, const int32_t* __restrict__ map) {
-        e = map[4 + 2 * blockIdx.x];
-        if (e < 0) return false;
-        row0 = map[4 + 2 * blockIdx.x + 1];
+    int e, row0, rows, col;   // rows: valid rows of the tile, may exceed the tile
+    __device__ __forceinline__ bool init(const int32_t* __restrict__ off, const int32_t* __restrict__ map, int cols) {
+        const int total = map[0] * cols, per = (total + 7) / 8, s = blockIdx.x >> 3;
+        const int t = (blockIdx.x & 7) * per + s;
+        if (s >= per || t >= total) return false;
+        const int i = t / cols;
+        col = t - i * cols;
+        e = map[4 + 2 * i];
+        row0 = map[4 + 2 * i + 1];
         rows = off[e + 1] - row0;
         return true;
     }
 };
+static inline dim3 row_grid(int max_tiles, int cols) { return dim3(((long long)max_tiles * cols + 7) / 8 * 8); }
 
 #define XMOE_TILE_BOUNDS __launch_bounds__(TileShape<BIG>::kThreads, 2)
 
@@ -122,8 +129,8 @@ __global__ XMOE_TILE_BOUNDS void ffn_gateup_mfma_kernel(const T* __restrict__ xd
     using S = TileShape<BIG>;
     __shared__ __align__(16) char smem[S::kLds];
     RowTile t;
-    if (!t.init(off, map)) return;
-    const int n0 = blockIdx.y * (S::kN / 2);
+    if (!t.init(off, map, (f + S::kN / 2 - 1) / (S::kN / 2))) return;
+    const int n0 = t.col * (S::kN / 2);
     RowSrc<T, S::kThreads> a;
     ColSrc<T, S::kThreads, false> b;
     a.init(row_index ? xd : xd + (size_t)t.row0 * d, d, t.rows, row_index ? row_index + t.row0 : nullptr);
@@ -176,8 +183,8 @@ __global__ XMOE_TILE_BOUNDS void ffn_down_mfma_kernel(const T* __restrict__ A, c
     using S = TileShape<BIG>;
     __shared__ __align__(16) char smem[S::kLds];
     RowTile t;
-    if (!t.init(off, map)) return;
-    const int n0 = blockIdx.y * S::kN;
+    if (!t.init(off, map, (d + S::kN - 1) / S::kN)) return;
+    const int n0 = t.col * S::kN;
     RowSrc<T, S::kThreads> a;
     ColSrc<T, S::kThreads, false> b;
     a.init(A + (size_t)t.row0 * f, f, t.rows, nullptr);
@@ -202,8 +209,8 @@ __device__ __forceinline__ void dact_tile(const T* __restrict__ dY, const int32_
     using S = TileShape<BIG>;
     __shared__ __align__(16) char smem[S::kLds];
     RowTile t;
-    if (!t.init(off, map)) return;
-    const int n0 = blockIdx.y * S::kN;
+    if (!t.init(off, map, (f + S::kN - 1) / S::kN)) return;
+    const int n0 = t.col * S::kN;
     RowSrc<T, S::kThreads> a, b;
     a.init(dy_index ? dY : dY + (size_t)t.row0 * d, d, t.rows, dy_index ? dy_index + t.row0 : nullptr);
     b.init(w + ((size_t)t.e * f + n0) * d, d, f - n0, nullptr);
@@ -242,7 +249,7 @@ __device__ __forceinline__ void dact_tile(const T* __restrict__ dY, const int32_
         const int lane = threadIdx.x & 63;
         // the lane's v is not a compile-time constant here
         const int r = tile_row<BIG>(mi, 0) + 8 * (((lane >> 1) & 15) >> 2) + (((lane >> 1) & 15) & 3);
-        const int p = blockIdx.y * (S::kN / 64) + tile_col_base<BIG, false>(0) / 64;
+        const int p = t.col * (S::kN / 64) + tile_col_base<BIG, false>(0) / 64;
         if (!(lane & 1) && r < t.rows && p * 64 < f) row_part[(size_t)p * B + t.row0 + r] = sum;
     }
 }
@@ -306,8 +313,8 @@ __global__ XMOE_TILE_BOUNDS void ffn_dx_mfma_kernel(const T* __restrict__ dG, co
     using S = TileShape<BIG>;
     __shared__ __align__(16) char smem[S::kLds];
     RowTile t;
-    if (!t.init(off, map)) return;
-    const int n0 = blockIdx.y * S::kN;
+    if (!t.init(off, map, (d + S::kN - 1) / S::kN)) return;
+    const int n0 = t.col * S::kN;
     tile_f32x16_t acc[S::kMI][2];
     tile_zero<BIG>(acc);
     for (int set = 0; set < (dU ? 2 : 1); ++set) {   // the two-matrix expert has a single pair (dH, W1)
@@ -322,8 +329,9 @@ __global__ XMOE_TILE_BOUNDS void ffn_dx_mfma_kernel(const T* __restrict__ dG, co
 // ---------------------------------------------------------------------------------------------------------
 // weight gradients: dW_e[m,n] = sum over the expert's rows r of P[r,m] * Q[r,n]   (K = ragged)
 //   dWd = A^T dY (M=f, N=d);  dWg = Xd^T dG, dWu = Xd^T dU (M=d, N=f).  Empty experts get zeros.
-// All of a call's weight gradients are one launch: blockIdx.x tile, blockIdx.y matrix, blockIdx.z expert, the experts
-// with the most rows first (sched), so the long sums start early and only one tail of idle CUs is left.
+// All of a call's weight gradients are one launch, the experts with the most rows first (sched), so the long sums start
+// early and only one tail of idle CUs is left.  A matrix's tiles are cut into at most eight runs, dealt to the XCDs in turn
+// (block b runs on XCD b % 8): the tiles of a run share operand panels in one L2.
 // ---------------------------------------------------------------------------------------------------------
 template <typename T>
 struct WgradJob {
@@ -335,12 +343,13 @@ struct WgradJob {
 template <typename T>
 struct WgradJobs {
     WgradJob<T> job[3];
+    int n_jobs, tiles, run, runs;   // tiles of a matrix, tiles of a run, runs of a matrix
 };
 
 template <typename T, bool BIG, bool GP, bool GQ>
-__device__ __forceinline__ void wgrad_tile(const WgradJob<T>& j, int e, int lo, int K, char* smem) {
+__device__ __forceinline__ void wgrad_tile(const WgradJob<T>& j, int u, int e, int lo, int K, char* smem) {
     using S = TileShape<BIG>;
-    const int m0 = (blockIdx.x % j.tiles_m) * S::kM, n0 = (blockIdx.x / j.tiles_m) * S::kN;
+    const int m0 = (u % j.tiles_m) * S::kM, n0 = (u / j.tiles_m) * S::kN;
     ColSrc<T, S::kThreads, GP> a;
     ColSrc<T, S::kThreads, GQ> b;
     a.init(j.P + m0 + (GP ? 0 : (size_t)lo * j.M), nullptr, j.M, j.M - m0, GP ? j.p_index + lo : nullptr, K);
@@ -352,18 +361,21 @@ __device__ __forceinline__ void wgrad_tile(const WgradJob<T>& j, int e, int lo, 
 }
 
 template <typename T, bool BIG>
-__global__ XMOE_TILE_BOUNDS void ffn_wgrad_mfma_kernel(WgradJobs<T> jobs, const int32_t* __restrict__ off,
+__global__ XMOE_TILE_BOUNDS void ffn_wgrad_mfma_kernel(WgradJobs<T> jobs, int E, const int32_t* __restrict__ off,
                                                        const int32_t* __restrict__ sched) {
     __shared__ __align__(16) char smem[TileShape<BIG>::kLds];
-    const WgradJob<T> j = jobs.job[blockIdx.y];
-    const int e = sched[blockIdx.z];
+    const int s = blockIdx.x >> 3, r = (s / jobs.run) * 8 + (blockIdx.x & 7);   // run r of all
+    const int m = r / jobs.runs, u = (r - m * jobs.runs) * jobs.run + s % jobs.run;
+    if (m >= jobs.n_jobs * E || u >= jobs.tiles) return;
+    const WgradJob<T> j = jobs.job[m % jobs.n_jobs];
+    const int e = sched[m / jobs.n_jobs];
     const int lo = off[e], K = off[e + 1] - lo;
     if (j.p_index)   // gathered rows on at most one side
-        wgrad_tile<T, BIG, true, false>(j, e, lo, K, smem);
+        wgrad_tile<T, BIG, true, false>(j, u, e, lo, K, smem);
     else if (j.q_index)
-        wgrad_tile<T, BIG, false, true>(j, e, lo, K, smem);
+        wgrad_tile<T, BIG, false, true>(j, u, e, lo, K, smem);
     else
-        wgrad_tile<T, BIG, false, false>(j, e, lo, K, smem);
+        wgrad_tile<T, BIG, false, false>(j, u, e, lo, K, smem);
 }
 
 // ---------------------------------------------------------------------------------------------------------
@@ -379,8 +391,8 @@ __global__ XMOE_TILE_BOUNDS void mlp2_up_mfma_kernel(const T* __restrict__ xd,
     using S = TileShape<BIG>;
     __shared__ __align__(16) char smem[S::kLds];
     RowTile t;
-    if (!t.init(off, map)) return;
-    const int n0 = blockIdx.y * S::kN;
+    if (!t.init(off, map, (f + S::kN - 1) / S::kN)) return;
+    const int n0 = t.col * S::kN;
     RowSrc<T, S::kThreads> a;
     ColSrc<T, S::kThreads, false> b;
     a.init(row_index ? xd : xd + (size_t)t.row0 * d, d, t.rows, row_index ? row_index + t.row0 : nullptr);
@@ -433,13 +445,17 @@ static int launch_wgrad(WgradJobs<T> jobs, int n_jobs, int E, int d, int f, cons
     const bool big = big_wgrad_tiles(n_jobs, E, d, f);
     const int tile = big ? 128 : 64;
     for (int i = 0; i < n_jobs; ++i) jobs.job[i].tiles_m = ceil_div(jobs.job[i].M, tile);
-    const dim3 grid(ceil_div(d, tile) * ceil_div(f, tile), n_jobs, E);
+    jobs.n_jobs = n_jobs;
+    jobs.tiles = ceil_div(d, tile) * ceil_div(f, tile);
+    jobs.run = ceil_div(jobs.tiles, 8);
+    jobs.runs = ceil_div(jobs.tiles, jobs.run);
+    const dim3 grid(((long long)n_jobs * E * jobs.runs + 7) / 8 * 8 * jobs.run);
     if (big)
         XMOE_LAUNCH(K_FFN_WGRAD_MFMA, s, hipLaunchKernelGGL((ffn_wgrad_mfma_kernel<T, true>), grid, dim3(256), 0, s, jobs,
-                                                            off, sched));
+                                                            E, off, sched));
     else
         XMOE_LAUNCH(K_FFN_WGRAD_MFMA, s, hipLaunchKernelGGL((ffn_wgrad_mfma_kernel<T, false>), grid, dim3(128), 0, s,
-                                                            jobs, off, sched));
+                                                            jobs, E, off, sched));
     return XMOE_OK;
 }
 
@@ -449,7 +465,7 @@ static int fwd_tile(const FfnArgs& a, hipStream_t s) {
     const int max_tiles = ffn_max_tiles(a.B, a.E, S::kM);
     int st = launch_tile_map(a.off, a.E, S::kM, max_tiles, a.map, a.sched, s);
     if (st != XMOE_OK) return st;
-    const dim3 g1(max_tiles, ceil_div(a.f, S::kN / 2)), g2(max_tiles, ceil_div(a.d, S::kN));
+    const dim3 g1 = row_grid(max_tiles, ceil_div(a.f, S::kN / 2)), g2 = row_grid(max_tiles, ceil_div(a.d, S::kN));
     XMOE_LAUNCH(K_FFN_GATEUP_MFMA, s,
                 hipLaunchKernelGGL((ffn_gateup_mfma_kernel<T, BIG>), g1, dim3(S::kThreads), 0, s, (const T*)a.xd,
                                    a.row_index, a.off, a.map, a.d, a.f, (const T*)a.wg, (const T*)a.wu, (T*)a.g,
@@ -467,7 +483,7 @@ static int bwd_tile(const FfnArgs& a, hipStream_t s) {
     int st = launch_tile_map(a.off, a.E, S::kM, max_tiles, a.map, a.sched, s);
     if (st != XMOE_OK) return st;
     XMOE_LAUNCH(K_FFN_DACT_MFMA, s,
-                hipLaunchKernelGGL((ffn_dact_mfma_kernel<T, BIG>), dim3(max_tiles, ceil_div(a.f, S::kN)),
+                hipLaunchKernelGGL((ffn_dact_mfma_kernel<T, BIG>), row_grid(max_tiles, ceil_div(a.f, S::kN)),
                                    dim3(S::kThreads), 0, s, (const T*)a.dy, a.dy_index, a.dy_scale, a.off, a.map, a.d,
                                    a.f, (const T*)a.wd, (const T*)a.g, (const T*)a.u, (T*)a.dg, (T*)a.du, (T*)a.act,
                                    a.row_part, a.B));
@@ -476,7 +492,7 @@ static int bwd_tile(const FfnArgs& a, hipStream_t s) {
         if (st != XMOE_OK) return st;
     }
     XMOE_LAUNCH(K_FFN_DX_MFMA, s,
-                hipLaunchKernelGGL((ffn_dx_mfma_kernel<T, BIG>), dim3(max_tiles, ceil_div(a.d, S::kN)),
+                hipLaunchKernelGGL((ffn_dx_mfma_kernel<T, BIG>), row_grid(max_tiles, ceil_div(a.d, S::kN)),
                                    dim3(S::kThreads), 0, s, (const T*)a.dg, (const T*)a.du, a.off, a.map, a.d, a.f,
                                    (const T*)a.wg, (const T*)a.wu, (T*)a.dxd));
     WgradJobs<T> jobs = {{{(const T*)a.act, (const T*)a.dy, nullptr, a.dy_index, a.f, a.d, 0, (T*)a.dwd},
@@ -491,7 +507,7 @@ static int mlp2_fwd_tile(const Mlp2Args& a, hipStream_t s) {
     const int max_tiles = ffn_max_tiles(a.B, a.E, S::kM);
     int st = launch_tile_map(a.off, a.E, S::kM, max_tiles, a.map, a.sched, s);
     if (st != XMOE_OK) return st;
-    const dim3 g1(max_tiles, ceil_div(a.f, S::kN)), g2(max_tiles, ceil_div(a.d, S::kN));
+    const dim3 g1 = row_grid(max_tiles, ceil_div(a.f, S::kN)), g2 = row_grid(max_tiles, ceil_div(a.d, S::kN));
 #define XMOE_CALL(ACT)                                                                                               \
     XMOE_LAUNCH(K_MLP2_UP_MFMA, s,                                                                                   \
                 hipLaunchKernelGGL((mlp2_up_mfma_kernel<T, ACT, BIG>), g1, dim3(S::kThreads), 0, s, (const T*)a.xd,  \
@@ -510,7 +526,7 @@ static int mlp2_bwd_tile(const Mlp2Args& a, hipStream_t s) {
     const int max_tiles = ffn_max_tiles(a.B, a.E, S::kM);
     int st = launch_tile_map(a.off, a.E, S::kM, max_tiles, a.map, a.sched, s);
     if (st != XMOE_OK) return st;
-    const dim3 g1(max_tiles, ceil_div(a.f, S::kN));
+    const dim3 g1 = row_grid(max_tiles, ceil_div(a.f, S::kN));
 #define XMOE_CALL(ACT)                                                                                                \
     XMOE_LAUNCH(K_MLP2_DACT_MFMA, s,                                                                                  \
                 hipLaunchKernelGGL((mlp2_dact_mfma_kernel<T, ACT, BIG>), g1, dim3(S::kThreads), 0, s, (const T*)a.dy, \
@@ -523,7 +539,7 @@ static int mlp2_bwd_tile(const Mlp2Args& a, hipStream_t s) {
         if (st != XMOE_OK) return st;
     }
     XMOE_LAUNCH(K_FFN_DX_MFMA, s,
-                hipLaunchKernelGGL((ffn_dx_mfma_kernel<T, BIG>), dim3(max_tiles, ceil_div(a.d, S::kN)),
+                hipLaunchKernelGGL((ffn_dx_mfma_kernel<T, BIG>), row_grid(max_tiles, ceil_div(a.d, S::kN)),
                                    dim3(S::kThreads), 0, s, (const T*)a.dh, (const T*)nullptr, a.off, a.map, a.d, a.f,
                                    (const T*)a.w1, (const T*)nullptr, (T*)a.dxd));
     WgradJobs<T> jobs = {{{(const T*)a.a_buf, (const T*)a.dy, nullptr, a.dy_index, a.f, a.d, 0, (T*)a.dw2},
