@@ -3,11 +3,10 @@
 // One launch covers every expert: a tile map built on the device says which expert and which rows each row tile
 // belongs to, so there is no host round trip on tokens_per_expert and no per-expert launch.
 //
-// Measured (MI355X, one training step of the layer; before: 4 x 4 outputs per thread on the float32 ALUs, 22 to 26
-// TFLOP/s for either type, bound by their LDS reads):
-//   float32 T 2048 d 1024 f 704, 16 experts + 1 shared, k 4:   5295 -> 1615 us, the products at 63 to 102 TFLOP/s of 157
-//   bf16    T 3001 d 1000 f 712, 24 experts + 1 shared, k 3:   6735 ->  624 us, the products at 155 to 305 TFLOP/s
-//   float32 T 256 d 128 f 64, 8 experts, k 2 (launch-bound):    203 ->   97 us
+// Measured (MI355X, one training step of the layer; float32: with the float32 matrix instruction -> now; both: row tiles
+// numbered down the segments -> runs of neighbouring tiles per XCD):
+//   float32 T 2048 d 1024 f 704, 16 experts + 1 shared, k 4:   1602 -> 1130 us, the products at 85 to 156 TFLOP/s
+//   bf16    T 3001 d 1000 f 712, 24 experts + 1 shared, k 3:    627 ->  558 us, the products at 200 to 435 TFLOP/s
 #include "xmoe_ffn.h"
 #include "xmoe_tile_gemm.h"
 

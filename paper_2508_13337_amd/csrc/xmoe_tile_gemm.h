@@ -1,25 +1,33 @@
-// A GEMM tile on the matrix cores for any shape, stride and alignment, in float32 (v_mfma_f32_32x32x2_f32: float32
-// products and sums, nothing is split or rounded to fewer bits) and in bf16 (v_mfma_f32_32x32x16_bf16, float32
-// accumulators).  It serves the float32 workloads and the bf16 shapes whose d or f is no multiple of 64, for which
-// the direct-to-LDS kernels have no loads.
+// A GEMM tile on the matrix cores for any shape, stride and alignment, in float32 and in bf16, with float32 accumulators.
+// It serves the float32 workloads and the bf16 shapes whose d or f is no multiple of 64, for which the direct-to-LDS
+// kernels have no loads.
 //
 //   BIG:   128 x 128 outputs, 256 threads = 4 waves (2 x 2), wave tile 64 x 64, 64 KiB of LDS: two blocks per CU
 //   small:  64 x  64 outputs, 128 threads = 2 waves (2 x 1), wave tile 32 x 64, 32 KiB of LDS
 //
-// K is stepped by 128 bytes (32 floats or 64 bf16).  Both operand tiles lie in LDS as [row or column][128 bytes of k],
-// so one 16-byte LDS read is a fragment for either type: four consecutive k for four float32 MFMAs, eight for one
-// bf16 MFMA.  The next step's operands travel global -> registers while the matrix instructions run and are written to
-// the other half of the LDS buffer behind them, one barrier per step.  An operand that is K-strided in memory is
-// transposed in registers on the way (4 x 4 floats are renamed, 8 x 4 bf16 take 16 byte permutes).  Loads are declared
-// with the alignment of one element; the hardware takes unaligned 16-byte loads at the rate of aligned ones but for the
-// lines they straddle, so an odd leading dimension costs no scalar path.  Only a vector that crosses the end of K or
-// of the columns is fetched element by element.
+// The matrix instruction is v_mfma_f32_32x32x16_bf16 for both types.  A float is the exact sum of three bf16 numbers (hi +
+// mid + lo, 8 bits each), a product of two floats the sum of nine products of bf16 numbers, each exact in float32; the six
+// of them that reach 2^-24 of the whole are taken: 192 clocks of the matrix cores per 16 k, where the float32 instruction
+// (v_mfma_f32_32x32x2_f32) takes 512.  The largest product left out is 2^-23 of the whole at worst and 2^-26 on average,
+// below what one float32 addition of the sum rounds off, and a sum has six roundings per 16 k instead of eight: against
+// float64 the results are nearer than those of the float32 instruction (training step, f32 cases: 1.2e-6 -> 1.0e-6 and
+// 3.9e-7 -> 3.5e-7).  A non-finite input gives NaN in the results it reaches (an infinity has no finite parts).
 //
-// Bound: float32 by the matrix cores (a K-step is 4096 clocks of them per wave, against about 2000 for the latency of
-// its loads), busy 52 to 64 % of a launch whose blocks fill 1.2 to 1.7 of two waves per SIMD on average (dAct, with the
-// activation's loads and stores behind it, 39 %); bf16 by that latency (512 clocks of matrix work per step and wave): 39 to
-// 53 % of a wave's time is waits, the matrix cores are busy 9 to 15 %.
+// K is stepped by 64 bf16 (both operand tiles lie in LDS as [row or column][128 bytes of k]) or 16 floats ([row or
+// column][three parts of 32 bytes]), so that one 16-byte LDS read is a fragment of a matrix instruction.  The operands
+// travel global -> registers, two steps ahead for float32 and one for bf16 (whose steps are four times as many
+// registers), while the matrix instructions run, and are written to the other half of the LDS buffer behind them (float32:
+// split on the way, once per element of the tile), one barrier per step.  An operand that is K-strided in memory is
+// transposed in registers on the way.  Loads are declared with the alignment of one element; the hardware takes unaligned
+// 16-byte loads at the rate of aligned ones but for the lines they straddle, so an odd leading dimension costs no scalar
+// path.  Only a vector that crosses the end of K or of the columns is fetched element by element.
+//
+// Bound: float32 by the matrix cores and the split's vector instructions between them (gate/up of T 2048, d 1024, f 704, 16
+// experts + 1: 344 -> 189 us, the matrix cores busy 45 % of it); bf16 by latency (512 clocks of matrix work per step and
+// wave, 44 % of a wave's time is waits, the matrix cores are busy 15 %).
 #pragma once
+
+#include <type_traits>
 
 #include "xmoe_internal.h"
 
@@ -33,19 +41,24 @@ struct TileShape {
     static constexpr int kM = BIG ? 128 : 64, kN = BIG ? 128 : 64;
     static constexpr int kThreads = BIG ? 256 : 128;
     static constexpr int kMI = BIG ? 2 : 1;                     // 32-row blocks per wave
-    static constexpr int kBufBytes = (kM + kN) * 128;
-    static constexpr int kLds = 2 * kBufBytes;
+    static constexpr int kLds = 2 * (kM + kN) * 128;
 };
 
 template <typename T>
 struct TileElem;
 template <>
 struct TileElem<float> {
-    static constexpr int kV = 4, kK = 32;                       // elements per 16 bytes, k per step
+    static constexpr int kV = 4, kK = 16;                       // elements per 16 bytes, k per step
+    static constexpr int kRowBytes = 96;                        // of a tile row in LDS
+    static constexpr int kColK = 4, kColN = 2;                  // a thread's k-rows and columns of a K-strided operand
+    static constexpr int kSets = 2;                             // steps on their way in registers
 };
 template <>
 struct TileElem<bf16_t> {
     static constexpr int kV = 8, kK = 64;
+    static constexpr int kRowBytes = 128;
+    static constexpr int kColK = 8, kColN = 4;
+    static constexpr int kSets = 1;
 };
 
 // 16 (8) bytes from an address that is aligned to one element only
@@ -61,84 +74,132 @@ struct __attribute__((packed, aligned(sizeof(T)))) Packed8 {
 __device__ __forceinline__ uint32_t elem_bits(const float* p) { return __float_as_uint(*p); }
 __device__ __forceinline__ uint32_t elem_bits(const bf16_t* p) { return p->bits; }
 
-// byte address of 16-byte chunk c (0..7) of row (or column) r in a tile: eight consecutive rows at one chunk and eight
-// rows four apart at one chunk (the fragment reads, and the writes of a transposed operand) fall on all banks
+// bf16: byte address of 16-byte chunk c (0..7) of row (or column) r in a tile: eight consecutive rows at one chunk and
+// eight rows four apart at one chunk (the fragment reads, and the writes of a transposed operand) fall on all banks
 __device__ __forceinline__ int tile_addr(int r, int c) { return r * 128 + ((c ^ ((r ^ (r >> 3)) & 7)) << 4); }
+// float32: byte address of chunk c (0..1: eight k) of part p (0..2) of row r
+__device__ __forceinline__ int split_addr(int r, int p, int c) {
+    return r * 96 + p * 32 + ((c ^ (((r >> 2) ^ (r >> 3)) & 1)) << 4);
+}
+
+// The three bf16 parts of four floats, x = hi + mid + lo exactly (8 bits each; hi is cut off, so that the largest
+// finite floats stay finite, mid and lo are rounded to nearest)
+__device__ __forceinline__ void split4(const uint32_t (&x)[4], uint2 (&part)[3]) {
+    uint32_t h[2], m[2], l[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const uint32_t a = x[2 * i], b = x[2 * i + 1];
+        h[i] = __builtin_amdgcn_perm(b, a, 0x07060302u);
+        const float ra = __uint_as_float(a) - __uint_as_float(a & 0xffff0000u);
+        const float rb = __uint_as_float(b) - __uint_as_float(b & 0xffff0000u);
+        m[i] = pack_bf16x2(ra, rb);
+        l[i] = pack_bf16x2(ra - __uint_as_float(m[i] << 16), rb - __uint_as_float(m[i] & 0xffff0000u));
+    }
+    part[0] = make_uint2(h[0], h[1]);
+    part[1] = make_uint2(m[0], m[1]);
+    part[2] = make_uint2(l[0], l[1]);
+}
 
 // ---- K-contiguous operand: element (r, k) at base + row(r)*ld + k; rows past the last valid one repeat it (the outputs
-// they feed are never stored), k past K reads zero
+// they feed are never stored), k past K reads zero.  Two sets of registers: two steps of the operand are on their way.
 template <typename T, int NT>
 struct RowSrc {
     static constexpr int kV = TileElem<T>::kV, kK = TileElem<T>::kK;
-    const T* p[4];
-    uint32_t s[4][4];
+    static constexpr int kC = kK / kV;                           // chunks of a row
+    static constexpr int kP = (NT == 256 ? 128 : 64) * kC / NT;  // rows per thread
+    const T* p[kP];
+    uint32_t s[TileElem<T>::kSets][kP][4];
     // n_valid >= 1 rows; index: row r of the tile is row index[r] of the matrix (index points at the tile's first row)
     __device__ __forceinline__ void init(const T* base, size_t ld, int n_valid, const int32_t* index) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            int r = (int)(threadIdx.x >> 3) + (NT / 8) * i;
+        for (int i = 0; i < kP; ++i) {
+            int r = (int)(threadIdx.x / kC) + (NT / kC) * i;
             r = r < n_valid ? r : n_valid - 1;
             if (index) r = index[r];
-            p[i] = base + (size_t)r * ld + (threadIdx.x & 7) * kV;
+            p[i] = base + (size_t)r * ld + (threadIdx.x % kC) * kV;
         }
     }
     __device__ __forceinline__ bool wide() const { return true; }
-    __device__ __forceinline__ void load_full(int k0, int) {
+    __device__ __forceinline__ void advance(int, int) {}
+    template <int S>
+    __device__ __forceinline__ void load_full(int k0) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < kP; ++i) {
             const Packed16<T> q = *reinterpret_cast<const Packed16<T>*>(p[i] + k0);
 #pragma unroll
-            for (int j = 0; j < 4; ++j) s[i][j] = q.v[j];
+            for (int j = 0; j < 4; ++j) s[S][i][j] = q.v[j];
         }
     }
+    template <int S>
     __device__ __forceinline__ void load_tail(int k0, int K) {
-        const int n = K - k0 - (int)(threadIdx.x & 7) * kV;   // valid elements of this thread's chunks
+        const int n = K - k0 - (int)(threadIdx.x % kC) * kV;   // valid elements of this thread's chunks
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < kP; ++i) {
 #pragma unroll
-            for (int j = 0; j < 4; ++j) s[i][j] = 0;
+            for (int j = 0; j < 4; ++j) s[S][i][j] = 0;
             if (n >= kV) {
                 const Packed16<T> q = *reinterpret_cast<const Packed16<T>*>(p[i] + k0);
 #pragma unroll
-                for (int j = 0; j < 4; ++j) s[i][j] = q.v[j];
+                for (int j = 0; j < 4; ++j) s[S][i][j] = q.v[j];
             } else {
 #pragma unroll
                 for (int j = 0; j < kV - 1; ++j)
-                    if (j < n) s[i][j * 4 / kV] |= elem_bits(p[i] + k0 + j) << (kV == 8 ? 16 * (j & 1) : 0);
+                    if (j < n) s[S][i][j * 4 / kV] |= elem_bits(p[i] + k0 + j) << (kV == 8 ? 16 * (j & 1) : 0);
             }
         }
     }
-    __device__ __forceinline__ void store(char* tile) const {
+    template <int S>
+    __device__ __forceinline__ void store(char* tile) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int r = (threadIdx.x >> 3) + (NT / 8) * i;
-            *reinterpret_cast<uint4*>(tile + tile_addr(r, threadIdx.x & 7)) =
-                make_uint4(s[i][0], s[i][1], s[i][2], s[i][3]);
+        for (int i = 0; i < kP; ++i) {
+            const int r = threadIdx.x / kC + (NT / kC) * i, c = threadIdx.x % kC;
+            if (kV == 8) {
+                *reinterpret_cast<uint4*>(tile + tile_addr(r, c)) =
+                    make_uint4(s[S][i][0], s[S][i][1], s[S][i][2], s[S][i][3]);
+            } else {
+                uint2 part[3];
+                split4(s[S][i], part);
+#pragma unroll
+                for (int q = 0; q < 3; ++q)
+                    *reinterpret_cast<uint2*>(tile + split_addr(r, q, c >> 1) + (c & 1) * 8) = part[q];
+            }
         }
     }
 };
 
-// ---- K-strided operand: element (k, n) at base + row(k)*ld + n, ld columns in all.  A thread owns kV k-rows x 4
-// columns; k past K reads zero.  Columns past the last one feed outputs that are never stored, so what they read only
-// has to lie in the matrix: a thread whose four columns straddle the end reads the last four and moves them down before
-// they go to LDS, one that lies past it reads the tile's first columns.
+// ---- K-strided operand: element (k, n) at base + row(k)*ld + n, ld columns in all.  A thread owns kColK k-rows x kColN
+// columns (8 bytes of a row); k past K reads zero.  Columns past the last one feed outputs that are never stored, so what
+// they read only has to lie in the matrix: a thread whose columns straddle the end reads the last kColN and moves them
+// down before they go to LDS, one that lies past it reads the tile's first columns.
 template <typename T, int NT, bool GATHER>
 struct ColSrc {
-    static constexpr int kV = TileElem<T>::kV, kK = TileElem<T>::kK;
-    static constexpr int kNB = NT == 256 ? 32 : 16;   // 4-column blocks of the tile
+    static constexpr int kQ = TileElem<T>::kColK, kC = TileElem<T>::kColN, kK = TileElem<T>::kK;
+    static constexpr int kNB = (NT == 256 ? 128 : 64) / kC;   // column blocks of the tile
     const T* base;       // already at this thread's columns
     size_t ld;
     const int32_t* index;   // GATHER: k-row k is row index[k] of the matrix
-    int shift;           // columns the loaded four lie before the thread's own
-    int n_valid;         // of this thread's four columns (used where ld < 4 only)
-    int row[GATHER ? kV : 1];   // GATHER: the source rows of the next load
-    uint32_t s[16];
+    int shift;           // columns the loaded ones lie before the thread's own
+    int n_valid;         // of this thread's columns (used where ld < kC only)
+    int row[GATHER ? kQ : 1], next_row[GATHER ? kQ : 1];   // GATHER: the source rows of this load and of the next one
+    uint32_t s[TileElem<T>::kSets][2 * kQ];
+    // The thread's column block and group of k-rows.  bf16: consecutive threads take consecutive blocks.  float32: the
+    // two groups of a 16-byte chunk alternate between eight blocks, so that 16 lanes' 8-byte writes fall on all banks.
+    static __device__ __forceinline__ int block() {
+        const int t = threadIdx.x;
+        if (kC == 4) return t % kNB;
+        return (t & 7) | (t >> 1 & (kNB - 8));
+    }
+    static __device__ __forceinline__ int group() {
+        const int t = threadIdx.x;
+        if (kC == 4) return t / kNB;
+        return (t >> 3 & 1) | (t / (2 * kNB)) << 1;
+    }
     // cols >= 1: columns from p0 on.  Two matrices side by side (p1 != NULL): columns [0, TN/2) from p0, the others from p1
     __device__ __forceinline__ void init(const T* p0, const T* p1, size_t ld_, int cols, const int32_t* index_, int K) {
-        int n = (int)(threadIdx.x % kNB) * 4;
+        int n = block() * kC;
         base = p0;
-        if (p1 && n >= 2 * kNB) {
-            n -= 2 * kNB;
+        if (p1 && n >= kNB * kC / 2) {
+            n -= kNB * kC / 2;
             base = p1;
         }
         n_valid = cols - n;
@@ -147,119 +208,94 @@ struct ColSrc {
             n = 0;
             n_valid = cols;
         }
-        shift = n_valid < 4 && wide() ? 4 - n_valid : 0;
+        shift = n_valid < kC && wide() ? kC - n_valid : 0;
         base += n - shift;
         index = index_;
         if (GATHER && K > 0) fetch_rows(0, K);
     }
-    __device__ __forceinline__ bool wide() const { return ld >= 4; }   // block-uniform
-    __device__ __forceinline__ void fetch_rows(int k0, int K) {
-        const int k = k0 + (int)(threadIdx.x / kNB) * kV;
+    // before the load of the step at k0: its source rows have arrived, the next step's are requested, ahead of the step's
+    // own loads (the next step then waits for these and no newer ones before it forms its addresses)
+    __device__ __forceinline__ void advance(int k0, int K) {
+        if (!GATHER) return;
 #pragma unroll
-        for (int q = 0; q < kV; ++q) row[q] = index[k + q < K ? k + q : K - 1];
+        for (int q = 0; q < kQ; ++q) row[GATHER ? q : 0] = next_row[GATHER ? q : 0];
+        fetch_rows(k0 + kK, K);
     }
-    __device__ __forceinline__ void load4(int q, const T* p) {
-        if (kV == 4) {
-            const Packed16<T> v = *reinterpret_cast<const Packed16<T>*>(p);
+    __device__ __forceinline__ bool wide() const { return ld >= kC; }   // block-uniform
+    __device__ __forceinline__ void fetch_rows(int k0, int K) {
+        const int k = k0 + group() * kQ;
 #pragma unroll
-            for (int c = 0; c < 4; ++c) s[q * 4 + c] = v.v[c];
-        } else {
-            const Packed8<T> v = *reinterpret_cast<const Packed8<T>*>(p);
-            s[q * 2] = v.v[0];
-            s[q * 2 + 1] = v.v[1];
-        }
+        for (int q = 0; q < kQ; ++q) next_row[GATHER ? q : 0] = index[k + q < K ? k + q : K - 1];
+    }
+    template <int S>
+    __device__ __forceinline__ void load_row(int q, const T* p) {
+        const Packed8<T> v = *reinterpret_cast<const Packed8<T>*>(p);
+        s[S][q * 2] = v.v[0];
+        s[S][q * 2 + 1] = v.v[1];
     }
     // a whole step of a wide matrix: no branch, so all of a step's loads are in flight together
-    __device__ __forceinline__ void load_full(int k0, int K) {
-        const T* p = base + (size_t)(k0 + (int)(threadIdx.x / kNB) * kV) * ld;
+    template <int S>
+    __device__ __forceinline__ void load_full(int k0) {
+        const T* p = base + (size_t)(k0 + group() * kQ) * ld;
 #pragma unroll
-        for (int q = 0; q < kV; ++q) load4(q, GATHER ? base + (size_t)row[GATHER ? q : 0] * ld : p + q * ld);
-        if (GATHER) fetch_rows(k0 + kK, K);
+        for (int q = 0; q < kQ; ++q) load_row<S>(q, GATHER ? base + (size_t)row[GATHER ? q : 0] * ld : p + q * ld);
     }
+    template <int S>
     __device__ __forceinline__ void load_tail(int k0, int K) {
-        const int k = k0 + (int)(threadIdx.x / kNB) * kV;
+        const int k = k0 + group() * kQ;
         const T* p = base + (size_t)k * ld;
 #pragma unroll
-        for (int j = 0; j < 16; ++j) s[j] = 0;
+        for (int j = 0; j < 2 * kQ; ++j) s[S][j] = 0;
 #pragma unroll
-        for (int q = 0; q < kV; ++q) {
+        for (int q = 0; q < kQ; ++q) {
             if (k + q >= K) continue;
             const T* pr = GATHER ? base + (size_t)row[GATHER ? q : 0] * ld : p + q * ld;
             if (wide()) {
-                load4(q, pr);
+                load_row<S>(q, pr);
             } else {
 #pragma unroll
-                for (int c = 0; c < 3; ++c)
-                    if (c < n_valid)
-                        s[kV == 4 ? q * 4 + c : q * 2 + (c >> 1)] |= elem_bits(pr + c) << (kV == 8 ? 16 * (c & 1) : 0);
-            }
-        }
-        if (GATHER) fetch_rows(k0 + kK, K);
-    }
-    __device__ __forceinline__ void unshift() {
-        if (shift == 0) return;
-        // two steps of constant moves: a choice by `shift` itself would index the registers and put them in memory
-        const bool by1 = shift & 1, by2 = shift & 2;
-#pragma unroll
-        for (int q = 0; q < kV; ++q) {
-            if (kV == 4) {
-                s[q * 4] = by1 ? s[q * 4 + 1] : s[q * 4];
-                s[q * 4 + 1] = by1 ? s[q * 4 + 2] : s[q * 4 + 1];
-                s[q * 4 + 2] = by1 ? s[q * 4 + 3] : s[q * 4 + 2];
-                s[q * 4] = by2 ? s[q * 4 + 2] : s[q * 4];
-                s[q * 4 + 1] = by2 ? s[q * 4 + 3] : s[q * 4 + 1];
-            } else {
-                const uint64_t v = (((uint64_t)s[q * 2 + 1] << 32) | s[q * 2]) >> (16 * shift);
-                s[q * 2] = (uint32_t)v;
-                s[q * 2 + 1] = (uint32_t)(v >> 32);
+                for (int c = 0; c < kC - 1; ++c)
+                    if (c < n_valid) s[S][q * 2 + c * 2 / kC] |= elem_bits(pr + c) << (kC == 4 ? 16 * (c & 1) : 0);
             }
         }
     }
+    template <int S>
     __device__ __forceinline__ void store(char* tile) {
-        unshift();
-        const int c = threadIdx.x / kNB, n = (threadIdx.x % kNB) * 4;
+        if (shift != 0) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            uint32_t v[4];
-#pragma unroll
-            for (int a = 0; a < 4; ++a) {
-                if (kV == 4)
-                    v[a] = s[a * 4 + j];
-                else   // the low (even column) or high halves of k-rows 2a and 2a+1
-                    v[a] = __builtin_amdgcn_perm(s[(2 * a + 1) * 2 + (j >> 1)], s[2 * a * 2 + (j >> 1)],
-                                                 (j & 1) ? 0x07060302u : 0x05040100u);
+            for (int q = 0; q < kQ; ++q) {
+                const uint64_t v = (((uint64_t)s[S][q * 2 + 1] << 32) | s[S][q * 2]) >> (8 * sizeof(T) * shift);
+                s[S][q * 2] = (uint32_t)v;
+                s[S][q * 2 + 1] = (uint32_t)(v >> 32);
             }
-            *reinterpret_cast<uint4*>(tile + tile_addr(n + j, c)) = make_uint4(v[0], v[1], v[2], v[3]);
+        }
+        const int c = group(), n = block() * kC;
+#pragma unroll
+        for (int j = 0; j < kC; ++j) {
+            uint32_t v[4];
+            if (kC == 4) {   // the low (even column) or high halves of k-rows 2a and 2a+1
+#pragma unroll
+                for (int a = 0; a < 4; ++a)
+                    v[a] = __builtin_amdgcn_perm(s[S][((2 * a + 1) * 2 + (j >> 1)) % (2 * kQ)],
+                                                 s[S][(2 * a * 2 + (j >> 1)) % (2 * kQ)],
+                                                 (j & 1) ? 0x07060302u : 0x05040100u);
+                *reinterpret_cast<uint4*>(tile + tile_addr(n + j, c)) = make_uint4(v[0], v[1], v[2], v[3]);
+            } else {
+#pragma unroll
+                for (int a = 0; a < 4; ++a) v[a] = s[S][a * 2 + j];
+                uint2 part[3];
+                split4(v, part);
+#pragma unroll
+                for (int q = 0; q < 3; ++q)
+                    *reinterpret_cast<uint2*>(tile + split_addr(n + j, q, c >> 1) + (c & 1) * 8) = part[q];
+            }
         }
     }
 };
 
-// acc[mi][ni] += a[mi] b[ni] over the fragments' k.  Consecutive matrix instructions go to different accumulators.
-template <int MI, int N>
-__device__ __forceinline__ void tile_mma(tile_f32x16_t (&acc)[N][2], const uint4 (&a)[MI], const uint4 (&b)[2],
-                                         const float*) {
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
-        for (int mi = 0; mi < MI; ++mi)
-#pragma unroll
-            for (int ni = 0; ni < 2; ++ni) {
-                const uint32_t av[4] = {a[mi].x, a[mi].y, a[mi].z, a[mi].w};
-                const uint32_t bv[4] = {b[ni].x, b[ni].y, b[ni].z, b[ni].w};
-                acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(av[j]), __uint_as_float(bv[j]),
-                                                                   acc[mi][ni], 0, 0, 0);
-            }
-}
-template <int MI, int N>
-__device__ __forceinline__ void tile_mma(tile_f32x16_t (&acc)[N][2], const uint4 (&a)[MI], const uint4 (&b)[2],
-                                         const bf16_t*) {
-#pragma unroll
-    for (int mi = 0; mi < MI; ++mi)
-#pragma unroll
-        for (int ni = 0; ni < 2; ++ni)
-            acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(tile_bf16x8_t, a[mi]),
-                                                                  __builtin_bit_cast(tile_bf16x8_t, b[ni]),
-                                                                  acc[mi][ni], 0, 0, 0);
+__device__ __forceinline__ tile_f32x16_t tile_mfma(const uint4& a, const uint4& b, const tile_f32x16_t& c) {
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(tile_bf16x8_t, a),
+                                                   __builtin_bit_cast(tile_bf16x8_t, b), c, 0, 0, 0);
 }
 
 // Where a lane's accumulators lie: acc[mi][ni][v] is output (tile_row(mi, v), tile_col(ni)) of the block's tile.
@@ -277,15 +313,16 @@ __device__ __forceinline__ int tile_col_base(int ni) {
 template <bool BIG, bool DUAL>
 __device__ __forceinline__ int tile_col(int ni) { return tile_col_base<BIG, DUAL>(ni) + (int)(threadIdx.x & 31); }
 
-// one K-step of the first MI 32-row blocks of the wave; k: valid k of the step, behind which there are zeros only
-template <typename T, bool BIG, bool DUAL, int MI, int N>
-__device__ __forceinline__ void tile_compute(tile_f32x16_t (&acc)[N][2], const char* ta, const char* tb,
-                                             int k = TileElem<T>::kK) {
+// One K-step of the first MI 32-row blocks of the wave; k: valid k of the step, behind which there are zeros only.
+// Consecutive matrix instructions go to different accumulators.
+template <bool BIG, bool DUAL, int MI, int N>
+__device__ __forceinline__ void tile_compute(tile_f32x16_t (&acc)[N][2], const char* ta, const char* tb, int k,
+                                             const bf16_t*) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int ra = (BIG ? (wave >> 1) * 64 : wave * 32) + (lane & 31);
 #pragma unroll
     for (int st = 0; st < 4; ++st) {
-        if (st * 2 * TileElem<T>::kV >= k) break;
+        if (st * 16 >= k) break;
         const int c = 2 * st + (lane >> 5);
         uint4 fa[MI], fb[2];
 #pragma unroll
@@ -293,60 +330,111 @@ __device__ __forceinline__ void tile_compute(tile_f32x16_t (&acc)[N][2], const c
 #pragma unroll
         for (int ni = 0; ni < 2; ++ni)
             fb[ni] = *reinterpret_cast<const uint4*>(tb + tile_addr(tile_col<BIG, DUAL>(ni), c));
-        tile_mma<MI, N>(acc, fa, fb, (const T*)nullptr);
+#pragma unroll
+        for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+            for (int ni = 0; ni < 2; ++ni) acc[mi][ni] = tile_mfma(fa[mi], fb[ni], acc[mi][ni]);
     }
+}
+// float32: the six products of the parts that reach 2^-24 of the whole, the smallest first
+template <bool BIG, bool DUAL, int MI, int N>
+__device__ __forceinline__ void tile_compute(tile_f32x16_t (&acc)[N][2], const char* ta, const char* tb, int,
+                                             const float*) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, c = lane >> 5;
+    const int ra = (BIG ? (wave >> 1) * 64 : wave * 32) + (lane & 31);
+    uint4 fa[MI][3], fb[2][3];
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+#pragma unroll
+        for (int mi = 0; mi < MI; ++mi)
+            fa[mi][p] = *reinterpret_cast<const uint4*>(ta + split_addr(ra + mi * 32, p, c));
+#pragma unroll
+        for (int ni = 0; ni < 2; ++ni)
+            fb[ni][p] = *reinterpret_cast<const uint4*>(tb + split_addr(tile_col<BIG, DUAL>(ni), p, c));
+    }
+    constexpr int kPa[6] = {0, 2, 1, 0, 1, 0}, kPb[6] = {2, 0, 1, 1, 0, 0};
+#pragma unroll
+    for (int t = 0; t < 6; ++t)
+#pragma unroll
+        for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+            for (int ni = 0; ni < 2; ++ni) acc[mi][ni] = tile_mfma(fa[mi][kPa[t]], fb[ni][kPb[t]], acc[mi][ni]);
 }
 
 // acc += A B over K; smem holds TileShape<BIG>::kLds bytes; rows, cols: valid ones of the tile (may exceed it).  Every
 // thread of the block calls it.  A wave multiplies only its 32-row blocks that hold a valid row, and nothing if no
 // column of its is valid: a partly filled tile then costs the matrix cores what it holds.  RAGGED: K is a row count, and
-// the last step multiplies only what there is of it (float32, 1 row per expert, d 1024 f 704 E 17: the whole backward
-// 149 -> 138 us; the row products, whose K is a width, are 1 to 2 % slower with it).
+// the last step multiplies only what there is of it.
 template <typename T, bool BIG, bool DUAL, bool RAGGED, class SrcA, class SrcB>
 __device__ __forceinline__ void tile_mainloop(tile_f32x16_t (&acc)[TileShape<BIG>::kMI][2], int K, int rows, int cols,
                                               SrcA& a, SrcB& b, char* smem) {
-    constexpr int MI = TileShape<BIG>::kMI, kK = TileElem<T>::kK, kBuf = TileShape<BIG>::kBufBytes;
-    constexpr int kBOff = TileShape<BIG>::kM * 128;
+    constexpr int MI = TileShape<BIG>::kMI, kK = TileElem<T>::kK;
+    constexpr int kBOff = TileShape<BIG>::kM * TileElem<T>::kRowBytes;
+    constexpr int kBuf = kBOff + TileShape<BIG>::kN * TileElem<T>::kRowBytes;
+    static_assert(2 * kBuf <= TileShape<BIG>::kLds, "two buffers");
     if (K <= 0) return;   // block-uniform
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wcol = BIG ? (wave & 1) * (DUAL ? 32 : 64) : 0;
     const int mi_n = cols > wcol ? (rows - (BIG ? (wave >> 1) * 64 : wave * 32) + 31) / 32 : 0;
-    auto compute = [&](int i, int k) {
-        const char* t = smem + (i & 1) * kBuf;
+    const int n = (K + kK - 1) / kK, n_full = a.wide() && b.wide() ? K / kK : 0;
+    auto compute = [&](auto P, int k) {
+        const char* t = smem + P.value * kBuf;
         if (mi_n >= MI)
-            tile_compute<T, BIG, DUAL, MI>(acc, t, t + kBOff, k);
+            tile_compute<BIG, DUAL, MI>(acc, t, t + kBOff, k, (const T*)nullptr);
         else if (MI == 2 && mi_n == 1)
-            tile_compute<T, BIG, DUAL, 1>(acc, t, t + kBOff, k);
+            tile_compute<BIG, DUAL, 1>(acc, t, t + kBOff, k, (const T*)nullptr);
     };
-    auto store = [&](int i) {   // into the half that was last read before the previous step's barrier
-        a.store(smem + (i & 1) * kBuf);
-        b.store(smem + (i & 1) * kBuf + kBOff);
+    auto load_whole = [&](auto S, int i) {
+        a.advance(i * kK, K);
+        b.advance(i * kK, K);
+        a.template load_full<S.value>(i * kK);
+        b.template load_full<S.value>(i * kK);
+    };
+    auto load = [&](auto P, int i) {
+        a.advance(i * kK, K);
+        b.advance(i * kK, K);
+        if (i < n_full) {
+            a.template load_full<P.value>(i * kK);
+            b.template load_full<P.value>(i * kK);
+        } else {
+            a.template load_tail<P.value>(i * kK, K);
+            b.template load_tail<P.value>(i * kK, K);
+        }
+    };
+    // register set S into buffer P, which was last read before the barrier of the step before
+    auto store = [&](auto S, auto P) {
+        a.template store<S.value>(smem + P.value * kBuf);
+        b.template store<S.value>(smem + P.value * kBuf + kBOff);
         __syncthreads();
     };
-    const int n = (K + kK - 1) / kK, n_full = a.wide() && b.wide() ? K / kK : 0;
-    if (n_full > 0) {
-        a.load_full(0, K);
-        b.load_full(0, K);
-    } else {
-        a.load_tail(0, K);
-        b.load_tail(0, K);
-    }
-    __syncthreads();      // a previous loop's last reads of the buffer
-    store(0);
+    constexpr int kS1 = TileElem<T>::kSets - 1;   // the odd steps' register set
+    constexpr std::integral_constant<int, 0> P0{};
+    constexpr std::integral_constant<int, 1> P1{};
+    constexpr std::integral_constant<int, kS1> S1{};
+    load(P0, 0);
+    if (kS1 && n > 1) load(S1, 1);
+    __syncthreads();      // a previous loop's last reads of the buffers
+    store(P0, P0);
     int i = 0;
-    for (; i + 1 < n_full; ++i) {
-        a.load_full((i + 1) * kK, K);
-        b.load_full((i + 1) * kK, K);
-        compute(i, kK);
-        store(i + 1);
+    // Before step i its operands lie in buffer i % 2; with two sets those of step i + 1 are on their way to registers.
+    // The loop over whole steps has no branch: the compiler then waits for the older of the two sets only.
+    for (; i + 2 + kS1 < n_full; i += 2) {
+        load_whole(P0, i + 1 + kS1);
+        compute(P0, kK);
+        store(S1, P1);
+        load_whole(S1, i + 2 + kS1);
+        compute(P1, kK);
+        store(P0, P0);
     }
-    for (; i + 1 < n; ++i) {
-        a.load_tail((i + 1) * kK, K);
-        b.load_tail((i + 1) * kK, K);
-        compute(i, kK);
-        store(i + 1);
+    for (; i < n; i += 2) {
+        if (i + 1 + kS1 < n) load(P0, i + 1 + kS1);
+        compute(P0, RAGGED ? K - i * kK : kK);
+        if (i + 1 >= n) break;
+        store(S1, P1);
+        if (i + 2 + kS1 < n) load(S1, i + 2 + kS1);
+        compute(P1, RAGGED ? K - (i + 1) * kK : kK);
+        if (i + 2 < n) store(P0, P0);
     }
-    compute(i, RAGGED ? K - i * kK : kK);
 }
 
 template <bool BIG>
