@@ -64,6 +64,12 @@ const char* const kKernelNames[K_COUNT] = {
     "ffn_gateup_few_kernel",
     "ffn_down_few_kernel",
     "mlp2_up_few_kernel",
+    "ffn_gateup_direct_kernel",
+    "ffn_down_direct_kernel",
+    "ffn_dact_direct_kernel",
+    "ffn_dx_direct_kernel",
+    "mlp2_up_direct_kernel",
+    "mlp2_dact_direct_kernel",
 };
 
 hipEvent_t get_event() {

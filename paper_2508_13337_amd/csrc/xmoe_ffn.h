@@ -76,6 +76,23 @@ __device__ __forceinline__ float act_fast(float h) {
     }
     return h;
 }
+template <int ACT>
+__device__ __forceinline__ void act_fast_grad(float h, float& a, float& g) {
+    if (ACT == XMOE_ACT_SILU) {
+        const float sg = fast_sigmoid(h);
+        a = h * sg;
+        g = sg * (1.0f + h * (1.0f - sg));
+    } else if (ACT == XMOE_ACT_GELU) {
+        float Phi, phi;
+        fast_gelu_parts(h, Phi, phi);
+        a = h * Phi;
+        g = Phi + h * phi;
+    } else {
+        a = h;
+        g = 1.0f;
+    }
+}
+
 int launch_tile_map(const int32_t* off, int E, int tile_rows, int max_tiles, int32_t* map, int32_t* sched,
                     hipStream_t s);
 
@@ -90,16 +107,29 @@ int ffn_bwd_tile(const FfnArgs& a, hipStream_t s);
 bool ffn_dma_supported(const FfnArgs& a);
 int ffn_fwd_dma(const FfnArgs& a, hipStream_t s);
 int ffn_bwd_dma(const FfnArgs& a, hipStream_t s);
+int ffn_bwd_wgrads_dma(const FfnArgs& a, hipStream_t s);   // the weight gradients only, once dG, dU and A exist
 
 // forward products of experts with few rows (the same operands as the direct-to-LDS kernels)
 bool few_rows(int B, int E);
 int ffn_fwd_few(const FfnArgs& a, hipStream_t s);
 int mlp2_fwd_few(const Mlp2Args& a, hipStream_t s);
 
+// 128-row tiles with direct-to-LDS loads (bf16, d % 8 == 0, f % 8 == 0 and 16-byte aligned operands): the whole forward, and
+// the backward's row products (tile map, dAct with the row scales' gradient, dX) without the weight gradients
+bool direct_fwd(int B, int E, int d, int f);   // whether they take a call's row products from the 256-row kernels
+bool direct_bwd(int B, int E, int d, int f);
+bool direct_supported(const FfnArgs& a);
+bool direct_supported(const Mlp2Args& a);
+int ffn_fwd_direct(const FfnArgs& a, hipStream_t s);
+int ffn_bwd_rows_direct(const FfnArgs& a, hipStream_t s);
+int mlp2_fwd_direct(const Mlp2Args& a, hipStream_t s);
+int mlp2_bwd_rows_direct(const Mlp2Args& a, hipStream_t s);
+
 int mlp2_fwd_tile(const Mlp2Args& a, hipStream_t s);
 int mlp2_bwd_tile(const Mlp2Args& a, hipStream_t s);
 bool mlp2_dma_supported(const Mlp2Args& a);
 int mlp2_fwd_dma(const Mlp2Args& a, hipStream_t s);
 int mlp2_bwd_dma(const Mlp2Args& a, hipStream_t s);
+int mlp2_bwd_wgrads_dma(const Mlp2Args& a, hipStream_t s);
 
 }  // namespace xmoe

@@ -1,6 +1,7 @@
 // Entry points of the expert MLP (paper: Listing 1 mlp(); Appendix B.4): argument checks, workspace carve-up,
-// and the choice between the bf16 MFMA kernels (bf16 storage, d and f multiples of 64, 16-byte aligned operands; forward
-// products of experts with few rows take their own kernels) and the general tile kernels (everything else).
+// and the choice between the 256-row bf16 kernels (bf16 storage, d and f multiples of 64, 16-byte aligned operands), their
+// smaller siblings (forward products of experts with few rows; 128-row tiles where the 256-row ones leave the chip empty)
+// and the general tile kernels (everything else).
 
 #include "xmoe_ffn.h"
 
@@ -43,8 +44,9 @@ int xmoe_expert_ffn_fwd(const void* xd, const int32_t* row_index, const int32_t*
     p += ffn_tilemap_bytes(B, E);
     a.act = p;
     hipStream_t s = (hipStream_t)stream;
-    if (ffn_dma_supported(a)) return few_rows(B, E) ? ffn_fwd_few(a, s) : ffn_fwd_dma(a, s);
-    return ffn_fwd_tile(a, s);
+    if (!ffn_dma_supported(a)) return ffn_fwd_tile(a, s);
+    if (few_rows(B, E)) return ffn_fwd_few(a, s);
+    return direct_fwd(B, E, d, f) ? ffn_fwd_direct(a, s) : ffn_fwd_dma(a, s);
 }
 
 int xmoe_expert_ffn_bwd(const void* xd, const int32_t* row_index, const void* g_save, const void* u_save,
@@ -82,8 +84,10 @@ int xmoe_expert_ffn_bwd(const void* xd, const int32_t* row_index, const void* g_
     a.row_grad = dy_row_scale_grad;
     a.row_part = (float*)p;   // the partial sums are always written (the matrix-core kernel has no branch for them)
     hipStream_t s = (hipStream_t)stream;
-    if (ffn_dma_supported(a)) return ffn_bwd_dma(a, s);
-    return ffn_bwd_tile(a, s);
+    if (!ffn_dma_supported(a)) return ffn_bwd_tile(a, s);
+    if (!direct_bwd(B, E, d, f)) return ffn_bwd_dma(a, s);
+    st = ffn_bwd_rows_direct(a, s);
+    return st != XMOE_OK ? st : ffn_bwd_wgrads_dma(a, s);
 }
 
 int xmoe_expert_mlp2_fwd(const void* xd, const int32_t* row_index, const int32_t* expert_offsets, int B, int E,
@@ -109,8 +113,9 @@ int xmoe_expert_mlp2_fwd(const void* xd, const int32_t* row_index, const int32_t
     p += ffn_tilemap_bytes(B, E);
     a.a_buf = p;
     hipStream_t s = (hipStream_t)stream;
-    if (mlp2_dma_supported(a)) return few_rows(B, E) ? mlp2_fwd_few(a, s) : mlp2_fwd_dma(a, s);
-    return mlp2_fwd_tile(a, s);
+    if (!mlp2_dma_supported(a)) return mlp2_fwd_tile(a, s);
+    if (few_rows(B, E)) return mlp2_fwd_few(a, s);
+    return direct_fwd(B, E, d, f) ? mlp2_fwd_direct(a, s) : mlp2_fwd_dma(a, s);
 }
 
 int xmoe_expert_mlp2_bwd(const void* xd, const int32_t* row_index, const void* h_save, const void* dy,
@@ -145,8 +150,10 @@ int xmoe_expert_mlp2_bwd(const void* xd, const int32_t* row_index, const void* h
     a.row_grad = dy_row_scale_grad;
     a.row_part = (float*)p;   // always written, as for the SwiGLU expert
     hipStream_t s = (hipStream_t)stream;
-    if (mlp2_dma_supported(a)) return mlp2_bwd_dma(a, s);
-    return mlp2_bwd_tile(a, s);
+    if (!mlp2_dma_supported(a)) return mlp2_bwd_tile(a, s);
+    if (!direct_bwd(B, E, d, f)) return mlp2_bwd_dma(a, s);
+    st = mlp2_bwd_rows_direct(a, s);
+    return st != XMOE_OK ? st : mlp2_bwd_wgrads_dma(a, s);
 }
 
 }  // extern "C"

@@ -1,0 +1,389 @@
+// Row products of the expert MLP on 128 x 128 bf16 tiles with direct-to-LDS loads (xmoe_tile_direct.h):
+//   - widths that are multiples of 8 but not of 64, in place of the register-staged tiles (the launch profiler counts them
+//     under those tiles' names);
+//   - widths that are multiples of 64 where the 256 x 256 tiles of the direct-to-LDS kernels are too few for the chip, or
+//     half empty (direct_fwd, direct_bwd below).
+//
+// Measured (MI355X): T 3001 d 1000 f 712, 24 experts + 1 shared, register-staged | these: gate/up 96 | 72 us, dAct 82 | 58,
+// down 51 | 47, dX 78 | 75; 509 tokens, 64 experts + 2 shared, d 2048 f 1408, 256-row tiles | these: gate/up 180 | 172,
+// down 120 | 86; 8 experts of 200 rows, d 2048 f 1408: forward 119 | 57, backward 215 | 166.
+//
+// Bound: a 128 x 128 tile takes in 64 bytes per clock and CU at the full rate of the matrix cores, about what a CU's load
+// path delivers at best; they reach 15 to 30 % of it where K is long, a third less than the 256 x 256 tiles, which is why
+// those keep every call that fills the chip with them.
+#include "xmoe_ffn.h"
+#include "xmoe_tile_direct.h"
+
+namespace xmoe {
+namespace {
+
+#define XMOE_DIRECT_KERNEL __global__ __launch_bounds__(256, 2) void
+
+// FAST (widths that are multiples of 64): the activations of the 256-row kernels, so that a row's result does not depend on
+// which of the two a call's row count selects; otherwise those of the register-staged tiles, for the same reason.
+template <bool FAST>
+__device__ __forceinline__ float dir_sigmoid(float g) { return FAST ? fast_sigmoid(g) : sigmoidf_(g); }
+
+// G = Xd Wg, U = Xd Wu, A = silu(G) * U: 64 columns of both matrices
+template <bool FAST>
+XMOE_DIRECT_KERNEL ffn_gateup_direct_kernel(const bf16_t* __restrict__ xd, const int32_t* __restrict__ row_index,   // or NULL
+                                            const int32_t* __restrict__ off, const int32_t* __restrict__ map, int d, int f,
+                                            const bf16_t* __restrict__ wg, const bf16_t* __restrict__ wu,
+                                            bf16_t* __restrict__ G, bf16_t* __restrict__ U, bf16_t* __restrict__ A) {
+    __shared__ __align__(16) char smem[kDirLds];
+    RowTile t;
+    if (!t.init(off, map, (f + 63) / 64, 128)) return;
+    const int n0 = t.col * 64;
+    DirRows<false> a;
+    DirCols b;
+    a.init(row_index ? xd : xd + (size_t)t.row0 * d, nullptr, d, t.rows, row_index ? row_index + t.row0 : nullptr, d);
+    b.init(wg + (size_t)t.e * d * f + n0, wu + (size_t)t.e * d * f + n0, f, f - n0, d);
+    tile_f32x16_t acc[2][2];
+    tile_zero<true>(acc);
+    dir_mainloop_rc<true>(acc, a, b, d, t.rows, f - n0, smem);
+    char* strip = dir_strip(smem);
+    const int wm = threadIdx.x >> 7, wn = (threadIdx.x >> 6) & 1, cols = f - n0 - wn * 32;
+#pragma unroll
+    for (int mi = 0; mi < 2; ++mi) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            float g[4], u[4], s[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                g[j] = acc[mi][0][4 * q + j];
+                u[j] = acc[mi][1][4 * q + j];
+                s[j] = g[j] * dir_sigmoid<FAST>(g[j]) * u[j];
+            }
+            dir_put4(strip, 0, q, g[0], g[1], g[2], g[3]);
+            dir_put4(strip, 16, q, u[0], u[1], u[2], u[3]);
+            dir_put4(strip, 32, q, s[0], s[1], s[2], s[3]);
+        }
+        dir_strip_sync();
+        const int r0 = wm * 64 + mi * 32;
+        const size_t ix = (size_t)(t.row0 + r0) * f + n0 + wn * 32;
+        dir_flush<32, true, false>(strip, 0, G + ix, f, t.rows - r0, cols);
+        dir_flush<32, true, false>(strip, 16, U + ix, f, t.rows - r0, cols);
+        dir_flush<32, true, false>(strip, 32, A + ix, f, t.rows - r0, cols);
+        dir_strip_sync();
+    }
+}
+
+// Y = A Wd
+XMOE_DIRECT_KERNEL ffn_down_direct_kernel(const bf16_t* __restrict__ A, const int32_t* __restrict__ off,
+                                          const int32_t* __restrict__ map, int d, int f, const bf16_t* __restrict__ wd,
+                                          bf16_t* __restrict__ Y) {
+    __shared__ __align__(16) char smem[kDirLds];
+    RowTile t;
+    if (!t.init(off, map, (d + 127) / 128, 128)) return;
+    const int n0 = t.col * 128;
+    DirRows<false> a;
+    DirCols b;
+    a.init(A + (size_t)t.row0 * f, nullptr, f, t.rows, nullptr, f);
+    b.init(wd + (size_t)t.e * f * d + n0, nullptr, d, d - n0, f);
+    tile_f32x16_t acc[2][2];
+    tile_zero<true>(acc);
+    dir_mainloop_rc<false>(acc, a, b, f, t.rows, d - n0, smem);
+    dir_store(acc, smem, Y + (size_t)t.row0 * d + n0, d, t.rows, d - n0);
+}
+
+// two-matrix expert: H = Xd W1, A = act(H)
+template <int ACT, bool FAST>
+XMOE_DIRECT_KERNEL mlp2_up_direct_kernel(const bf16_t* __restrict__ xd, const int32_t* __restrict__ row_index,   // or NULL
+                                         const int32_t* __restrict__ off, const int32_t* __restrict__ map, int d, int f,
+                                         const bf16_t* __restrict__ w1, bf16_t* __restrict__ H, bf16_t* __restrict__ A) {
+    __shared__ __align__(16) char smem[kDirLds];
+    RowTile t;
+    if (!t.init(off, map, (f + 127) / 128, 128)) return;
+    const int n0 = t.col * 128;
+    DirRows<false> a;
+    DirCols b;
+    a.init(row_index ? xd : xd + (size_t)t.row0 * d, nullptr, d, t.rows, row_index ? row_index + t.row0 : nullptr, d);
+    b.init(w1 + (size_t)t.e * d * f + n0, nullptr, f, f - n0, d);
+    tile_f32x16_t acc[2][2];
+    tile_zero<true>(acc);
+    dir_mainloop_rc<false>(acc, a, b, d, t.rows, f - n0, smem);
+    char* strip = dir_strip(smem);
+    const int wm = threadIdx.x >> 7, wn = (threadIdx.x >> 6) & 1, cols = f - n0 - wn * 64;
+#pragma unroll
+    for (int mi = 0; mi < 2; ++mi) {
+#pragma unroll
+        for (int ni = 0; ni < 2; ++ni)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                float h[4], s[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    h[j] = acc[mi][ni][4 * q + j];
+                    s[j] = FAST ? act_fast<ACT>(h[j]) : act_fwd<ACT>(h[j]);
+                }
+                dir_put4(strip, 8 * ni, q, h[0], h[1], h[2], h[3]);
+                dir_put4(strip, 16 + 8 * ni, q, s[0], s[1], s[2], s[3]);
+            }
+        dir_strip_sync();
+        const int r0 = wm * 64 + mi * 32;
+        const size_t ix = (size_t)(t.row0 + r0) * f + n0 + wn * 64;
+        dir_flush<64, true, false>(strip, 0, H + ix, f, t.rows - r0, cols);
+        dir_flush<64, true, false>(strip, 16, A + ix, f, t.rows - r0, cols);
+        dir_strip_sync();
+    }
+}
+
+// dA = dY W^T (W = Wd or W2) and what follows from it; in, out: arrays [B, f], EPI as in dir_dact_rounds
+template <int NIN, int NOUT, class Epi>
+__device__ __forceinline__ void dact_direct(const bf16_t* __restrict__ dY, const int32_t* __restrict__ dy_index,
+                                            const float* __restrict__ dy_scale, const int32_t* __restrict__ off,
+                                            const int32_t* __restrict__ map, int d, int f, const bf16_t* __restrict__ w,
+                                            float* __restrict__ row_part, int B, const bf16_t* const (&in)[NIN],
+                                            bf16_t* const (&out)[NOUT], Epi epi) {
+    __shared__ __align__(16) char smem[kDirLds];
+    RowTile t;
+    if (!t.init(off, map, (f + 127) / 128, 128)) return;
+    const int n0 = t.col * 128;
+    DirRows<false> a, b;
+    a.init(dy_index ? dY : dY + (size_t)t.row0 * d, nullptr, d, t.rows, dy_index ? dy_index + t.row0 : nullptr, d);
+    b.init(w + ((size_t)t.e * f + n0) * d, nullptr, d, f - n0, nullptr, d);
+    tile_f32x16_t acc[2][2];
+    tile_zero<true>(acc);
+    dir_mainloop_rr<false>(acc, a, b, d, t.rows, f - n0, smem);
+    const size_t base = (size_t)t.row0 * f + n0;
+    const bf16_t* tin[NIN];
+    bf16_t* tout[NOUT];
+#pragma unroll
+    for (int i = 0; i < NIN; ++i) tin[i] = in[i] + base;
+#pragma unroll
+    for (int i = 0; i < NOUT; ++i) tout[i] = out[i] + base;
+    const int wm = threadIdx.x >> 7, wn = (threadIdx.x >> 6) & 1;
+    float* part = row_part + (size_t)(t.col * 2 + wn) * B + t.row0;
+    const float* scale = dy_index && dy_scale ? dy_scale + t.row0 : nullptr;
+    if (t.rows >= wm * 64 + 64 && f - n0 >= wn * 64 + 64)
+        dir_dact_rounds<true, NIN, NOUT>(acc, smem, tin, tout, f, scale, part, t.rows, f - n0, epi);
+    else
+        dir_dact_rounds<false, NIN, NOUT>(acc, smem, tin, tout, f, scale, part, t.rows, f - n0, epi);
+}
+
+// dG = dA * U * silu'(G), dU = dA * silu(G), A = silu(G) * U
+template <bool FAST>
+XMOE_DIRECT_KERNEL ffn_dact_direct_kernel(const bf16_t* __restrict__ dY, const int32_t* __restrict__ dy_index,   // or NULL
+                                          const float* __restrict__ dy_scale,                                   // or NULL
+                                          const int32_t* __restrict__ off, const int32_t* __restrict__ map, int d, int f,
+                                          const bf16_t* __restrict__ wd, const bf16_t* __restrict__ G,
+                                          const bf16_t* __restrict__ U, bf16_t* __restrict__ dG, bf16_t* __restrict__ dU,
+                                          bf16_t* __restrict__ A, float* __restrict__ row_part, int B) {
+    const bf16_t* in[2] = {G, U};
+    bf16_t* out[3] = {dG, dU, A};
+    dact_direct<2, 3>(dY, dy_index, dy_scale, off, map, d, f, wd, row_part, B, in, out,
+                      [](float da0, float sc, const float(&x)[2], float(&y)[3]) {
+                          const float g = x[0], u = x[1], da = da0 * sc, sg = dir_sigmoid<FAST>(g), sl = g * sg;
+                          const float a1 = sl * u;
+                          y[0] = da * u * (sg * (1.0f + g * (1.0f - sg)));
+                          y[1] = da * sl;
+                          y[2] = a1 * sc;   // scaled: the weight gradient multiplies it with unscaled rows
+                          return a1;
+                      });
+}
+
+// two-matrix expert: dH = dA * act'(H), A = act(H)
+template <int ACT, bool FAST>
+XMOE_DIRECT_KERNEL mlp2_dact_direct_kernel(const bf16_t* __restrict__ dY, const int32_t* __restrict__ dy_index,   // or NULL
+                                           const float* __restrict__ dy_scale,                                   // or NULL
+                                           const int32_t* __restrict__ off, const int32_t* __restrict__ map, int d, int f,
+                                           const bf16_t* __restrict__ w2, const bf16_t* __restrict__ H,
+                                           bf16_t* __restrict__ dH, bf16_t* __restrict__ A, float* __restrict__ row_part,
+                                           int B) {
+    const bf16_t* in[1] = {H};
+    bf16_t* out[2] = {dH, A};
+    dact_direct<1, 2>(dY, dy_index, dy_scale, off, map, d, f, w2, row_part, B, in, out,
+                      [](float da0, float sc, const float(&x)[1], float(&y)[2]) {
+                          float a, g;
+                          if (FAST)
+                              act_fast_grad<ACT>(x[0], a, g);
+                          else
+                              act_fwd_grad<ACT>(x[0], a, g);
+                          y[0] = da0 * sc * g;
+                          y[1] = a * sc;
+                          return a;
+                      });
+}
+
+// dXd = dG Wg^T + dU Wu^T; TWO = false: a single pair (the two-matrix expert: dXd = dH W1^T)
+template <bool TWO>
+XMOE_DIRECT_KERNEL ffn_dx_direct_kernel(const bf16_t* __restrict__ dG, const bf16_t* __restrict__ dU,
+                                        const int32_t* __restrict__ off, const int32_t* __restrict__ map, int d, int f,
+                                        const bf16_t* __restrict__ wg, const bf16_t* __restrict__ wu,
+                                        bf16_t* __restrict__ dXd) {
+    __shared__ __align__(16) char smem[kDirLds];
+    RowTile t;
+    if (!t.init(off, map, (d + 127) / 128, 128)) return;
+    const int n0 = t.col * 128;
+    DirRows<TWO> a, b;
+    const size_t r = (size_t)t.row0 * f, c = ((size_t)t.e * d + n0) * f;
+    a.init(dG + r, TWO ? dU + r : nullptr, f, t.rows, nullptr, f);
+    b.init(wg + c, TWO ? wu + c : nullptr, f, d - n0, nullptr, f);
+    tile_f32x16_t acc[2][2];
+    tile_zero<true>(acc);
+    dir_mainloop_rr<TWO>(acc, a, b, f, t.rows, d - n0, smem);
+    dir_store(acc, smem, dXd + (size_t)t.row0 * d + n0, d, t.rows, d - n0);
+}
+
+template <class Args>
+inline int tile_map_direct(const Args& a, hipStream_t s) {
+    return launch_tile_map(a.off, a.E, 128, ffn_max_tiles(a.B, a.E, 128), a.map, a.sched, s);
+}
+template <class Args>
+inline dim3 grid_direct(const Args& a, int n, int cols) {
+    return row_grid(ffn_max_tiles(a.B, a.E, 128), (n + cols - 1) / cols);
+}
+inline bool fast_act(int d, int f) { return d % 64 == 0 && f % 64 == 0; }
+
+}  // namespace
+
+// Where these are faster than the 256-row kernels.  Measured (MI355X, gate/up and down together, us, 256-row | these; the
+// tiles are those of the 256-row kernels for both products):
+//   few tiles (a launch of up to one or two rounds of 256 CUs runs as long as its longest tile, whatever it holds):
+//     rows per expert         100          400          800          1600         3200
+//     4 experts, 2048 x 1408  117 | 43     121 | 58     136 | 93     185 | 146    262 | 268     (304, 532, 988 tiles from 800)
+//     8 experts, 2048 x 1408   92 | 45     144 | 87     158 | 148    264 | 268    472 | 539     (304, 608, 1064 from 400)
+//     8 experts, 4096 x 1024  147 | 56     143 | 113    188 | 204    354 | 386                  (384, 768 from 400)
+//    16 experts, 1024 x 704    65 | 30      95 | 53     102 | 88     161 | 157                  (320, 640, 1120 from 400)
+//    32 experts, 2048 x 704   103 | 78     185 | 183    294 | 318                               (896, 1792 from 400)
+//   one half-empty tile per expert:
+//     rows per expert         33-40        64           96           128
+//    64 experts, 1024 x 704    97 | 64      93 | 70      97 | 77
+//    96 experts, 2048 x 704   216 | 177    212 | 189    220 | 205
+//   512 experts, 1024 x 256   243 | 210    255 | 222    269 | 241    288 | 278
+//    32 experts, 4096 x 1024  183 | 175    180 | 180    186 | 189    196 | 242     (Zipf 64: 240 | 194)
+//    64 experts, 2048 x 1408  244 | 232    247 | 242    259 | 260    268 | 313     (Zipf 64: 293 | 267)
+//    32 experts, 2048 x 2560  223 | 219    226 | 234    236 | 247
+//   256 experts, 2048 x 512   353 | 359    368 | 374    390 | 400    424 | 475
+//   128 experts, 5120 x 1536 1143 | 1216  1166 | 1289  1214 | 1383  1367 | 1600
+// Many large weights keep the chip full and their stream long, and then the larger tile's fewer requests count.  Below 256
+// columns the products are launch-bound either way.
+bool direct_fwd(int B, int E, int d, int f) {
+    if (d < 256 || f < 256) return false;
+    const long long row_tiles = E * ((B + 256ll * E - 1) / (256ll * E)), weights = (long long)E * d * f;
+    if (row_tiles * ((f + 127) / 128 + (d + 255) / 256) <= 640) return true;
+    return (B <= 96ll * E && weights <= 160000000) || (B <= 72ll * E && weights <= 200000000 && (long long)d * f <= 1 << 22);
+}
+// The backward's dAct and dX (the weight gradients stay a launch of the 256-row kernels, which without dX of their own is
+// longer at its end).  Whole backward, us, 256-row | these:
+//   few tiles: rows per expert       40           200          400          800          1600
+//     4 experts, 2048 x 1408        167 | 141    198 | 146    212 | 162    250 | 208    340 | 347    (24, 24, 48, 96, 168 of dAct)
+//     8 experts, 2048 x 1408        172 | 146    215 | 166    205 | 214    327 | 320    535 | 579    (48, 48, 96, 192, 336)
+//     8 experts, 4096 x 1024        233 | 162    293 | 201    368 | 273    401 | 435                 (32, 32, 64, 128)
+//     8 experts, 1024 x 704         139 | 112    155 | 120    163 | 130    175 | 144    237 | 232    (24, 24, 48, 96, 168)
+//    16 experts, 1024 x 704         146 | 126    164 | 130    134 | 147    219 | 209    335 | 344    (48, 48, 96, 192, 336)
+//   half-empty tiles: rows            4           32           64           96
+//    16 experts, 2048 x 1408        228 | 186    219 | 186    225 | 190    192 | 202
+//    64 experts, 1024 x 704         197 | 166    202 | 165    224 | 187    204 | 194
+//    64 experts, 2048 x 1408        504 | 471    530 | 505    562 | 541    601 | 589   (96 of routed and 2 x 1021 rows: 679 | 757)
+//    32 experts, 4096 x 1024        372 | 364    379 | 370    406 | 399    430 | 428   (1 row: 320 | 330)
+//    32 experts, 7168 x 2048       1070 | 1002  1124 | 1042  1203 | 1136  1297 | 1246
+//   256 experts, 2048 x 512         695 | 680    776 | 770    852 | 845    907 | 902
+bool direct_bwd(int B, int E, int d, int f) {
+    if (d < 256 || f < 256) return false;
+    const long long row_tiles = E * ((B + 256ll * E - 1) / (256ll * E));
+    return B <= 80ll * E || row_tiles * ((f + 255) / 256) <= 64;
+}
+
+bool direct_supported(const FfnArgs& a) {
+    if (a.dt != XMOE_BF16 || a.d % 8 != 0 || a.f % 8 != 0) return false;
+    const void* ptrs[] = {a.xd, a.wg, a.wu, a.wd, a.g, a.u, a.y, a.dy, a.dxd, a.dwg, a.dwu, a.dwd, a.act, a.dg, a.du};
+    for (const void* p : ptrs)
+        if (!aligned16(p)) return false;
+    return true;
+}
+bool direct_supported(const Mlp2Args& a) {
+    if (a.dt != XMOE_BF16 || a.d % 8 != 0 || a.f % 8 != 0) return false;
+    const void* ptrs[] = {a.xd, a.w1, a.w2, a.h, a.y, a.dy, a.dxd, a.dw1, a.dw2, a.a_buf, a.dh};
+    for (const void* p : ptrs)
+        if (!aligned16(p)) return false;
+    return true;
+}
+
+template <bool FAST>
+static int fwd_direct(const FfnArgs& a, hipStream_t s) {
+    int st = tile_map_direct(a, s);
+    if (st != XMOE_OK) return st;
+    XMOE_LAUNCH(FAST ? K_FFN_GATEUP_DIRECT : K_FFN_GATEUP_MFMA, s,
+                hipLaunchKernelGGL((ffn_gateup_direct_kernel<FAST>), grid_direct(a, a.f, 64), dim3(256), 0, s,
+                                   (const bf16_t*)a.xd, a.row_index, a.off, a.map, a.d, a.f, (const bf16_t*)a.wg,
+                                   (const bf16_t*)a.wu, (bf16_t*)a.g, (bf16_t*)a.u, (bf16_t*)a.act));
+    XMOE_LAUNCH(FAST ? K_FFN_DOWN_DIRECT : K_FFN_DOWN_MFMA, s,
+                hipLaunchKernelGGL(ffn_down_direct_kernel, grid_direct(a, a.d, 128), dim3(256), 0, s, (const bf16_t*)a.act,
+                                   a.off, a.map, a.d, a.f, (const bf16_t*)a.wd, (bf16_t*)a.y));
+    return XMOE_OK;
+}
+int ffn_fwd_direct(const FfnArgs& a, hipStream_t s) {
+    return fast_act(a.d, a.f) ? fwd_direct<true>(a, s) : fwd_direct<false>(a, s);
+}
+
+template <bool FAST>
+static int bwd_rows_direct(const FfnArgs& a, hipStream_t s) {
+    int st = tile_map_direct(a, s);
+    if (st != XMOE_OK) return st;
+    XMOE_LAUNCH(FAST ? K_FFN_DACT_DIRECT : K_FFN_DACT_MFMA, s,
+                hipLaunchKernelGGL((ffn_dact_direct_kernel<FAST>), grid_direct(a, a.f, 128), dim3(256), 0, s,
+                                   (const bf16_t*)a.dy, a.dy_index, a.dy_scale, a.off, a.map, a.d, a.f, (const bf16_t*)a.wd,
+                                   (const bf16_t*)a.g, (const bf16_t*)a.u, (bf16_t*)a.dg, (bf16_t*)a.du, (bf16_t*)a.act,
+                                   a.row_part, a.B));
+    if (a.row_grad) {
+        st = launch_row_grad_reduce(a.row_part, (a.f + 63) / 64, a.B, a.row_grad, s);
+        if (st != XMOE_OK) return st;
+    }
+    XMOE_LAUNCH(FAST ? K_FFN_DX_DIRECT : K_FFN_DX_MFMA, s,
+                hipLaunchKernelGGL((ffn_dx_direct_kernel<true>), grid_direct(a, a.d, 128), dim3(256), 0, s,
+                                   (const bf16_t*)a.dg, (const bf16_t*)a.du, a.off, a.map, a.d, a.f, (const bf16_t*)a.wg,
+                                   (const bf16_t*)a.wu, (bf16_t*)a.dxd));
+    return XMOE_OK;
+}
+int ffn_bwd_rows_direct(const FfnArgs& a, hipStream_t s) {
+    return fast_act(a.d, a.f) ? bwd_rows_direct<true>(a, s) : bwd_rows_direct<false>(a, s);
+}
+
+template <bool FAST>
+static int mlp2_fwd_direct_as(const Mlp2Args& a, hipStream_t s) {
+    int st = tile_map_direct(a, s);
+    if (st != XMOE_OK) return st;
+#define XMOE_CALL(ACT)                                                                                                    \
+    XMOE_LAUNCH(FAST ? K_MLP2_UP_DIRECT : K_MLP2_UP_MFMA, s,                                                              \
+                hipLaunchKernelGGL((mlp2_up_direct_kernel<ACT, FAST>), grid_direct(a, a.f, 128), dim3(256), 0, s,          \
+                                   (const bf16_t*)a.xd, a.row_index, a.off, a.map, a.d, a.f, (const bf16_t*)a.w1,          \
+                                   (bf16_t*)a.h, (bf16_t*)a.a_buf))
+    XMOE_DISPATCH_ACT(a.act, XMOE_CALL);
+#undef XMOE_CALL
+    XMOE_LAUNCH(FAST ? K_FFN_DOWN_DIRECT : K_FFN_DOWN_MFMA, s,
+                hipLaunchKernelGGL(ffn_down_direct_kernel, grid_direct(a, a.d, 128), dim3(256), 0, s,
+                                   (const bf16_t*)a.a_buf, a.off, a.map, a.d, a.f, (const bf16_t*)a.w2, (bf16_t*)a.y));
+    return XMOE_OK;
+}
+int mlp2_fwd_direct(const Mlp2Args& a, hipStream_t s) {
+    return fast_act(a.d, a.f) ? mlp2_fwd_direct_as<true>(a, s) : mlp2_fwd_direct_as<false>(a, s);
+}
+
+template <bool FAST>
+static int mlp2_bwd_rows_direct_as(const Mlp2Args& a, hipStream_t s) {
+    int st = tile_map_direct(a, s);
+    if (st != XMOE_OK) return st;
+#define XMOE_CALL(ACT)                                                                                                    \
+    XMOE_LAUNCH(FAST ? K_MLP2_DACT_DIRECT : K_MLP2_DACT_MFMA, s,                                                          \
+                hipLaunchKernelGGL((mlp2_dact_direct_kernel<ACT, FAST>), grid_direct(a, a.f, 128), dim3(256), 0, s,        \
+                                   (const bf16_t*)a.dy, a.dy_index, a.dy_scale, a.off, a.map, a.d, a.f,                    \
+                                   (const bf16_t*)a.w2, (const bf16_t*)a.h, (bf16_t*)a.dh, (bf16_t*)a.a_buf, a.row_part,   \
+                                   a.B))
+    XMOE_DISPATCH_ACT(a.act, XMOE_CALL);
+#undef XMOE_CALL
+    if (a.row_grad) {
+        st = launch_row_grad_reduce(a.row_part, (a.f + 63) / 64, a.B, a.row_grad, s);
+        if (st != XMOE_OK) return st;
+    }
+    XMOE_LAUNCH(FAST ? K_FFN_DX_DIRECT : K_FFN_DX_MFMA, s,
+                hipLaunchKernelGGL((ffn_dx_direct_kernel<false>), grid_direct(a, a.d, 128), dim3(256), 0, s,
+                                   (const bf16_t*)a.dh, (const bf16_t*)nullptr, a.off, a.map, a.d, a.f,
+                                   (const bf16_t*)a.w1, (const bf16_t*)nullptr, (bf16_t*)a.dxd));
+    return XMOE_OK;
+}
+int mlp2_bwd_rows_direct(const Mlp2Args& a, hipStream_t s) {
+    return fast_act(a.d, a.f) ? mlp2_bwd_rows_direct_as<true>(a, s) : mlp2_bwd_rows_direct_as<false>(a, s);
+}
+
+}  // namespace xmoe

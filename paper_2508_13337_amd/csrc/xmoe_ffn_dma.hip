@@ -1469,23 +1469,6 @@ __global__ __launch_bounds__(512) void ffn_dx_dma_kernel(const bf16_t* __restric
 // =========================================================================================================
 // two-matrix expert, forward 1: H = Xd W1, A = act(H)      (K = d, N = f, weights "in x out" -> col tile)
 // =========================================================================================================
-template <int ACT>
-__device__ __forceinline__ void act_fast_grad(float h, float& a, float& g) {
-    if (ACT == XMOE_ACT_SILU) {
-        const float sg = fast_sigmoid(h);
-        a = h * sg;
-        g = sg * (1.0f + h * (1.0f - sg));
-    } else if (ACT == XMOE_ACT_GELU) {
-        float Phi, phi;
-        fast_gelu_parts(h, Phi, phi);
-        a = h * Phi;
-        g = Phi + h * phi;
-    } else {
-        a = h;
-        g = 1.0f;
-    }
-}
-
 template <bool GATHER, int ACT>
 __global__ __launch_bounds__(512) void mlp2_up_dma_kernel(const bf16_t* __restrict__ xd,
                                                           const int32_t* __restrict__ row_index,
@@ -1806,7 +1789,8 @@ __global__ __launch_bounds__(512) void ffn_wgrad_dma_kernel(const bf16_t* __rest
 // as a launch of its own, so each keeps the register allocation of its own kernel.
 // =========================================================================================================
 // SWIGLU = false: the two-matrix expert (dXd = dH W1^T, dW2 = A^T dY, dW1 = Xd^T dH; dG stands for dH, wg for W1,
-// dWg for dW1; dU, wu and dWu are not used)
+// dWg for dW1; dU, wu and dWu are not used).  dXd NULL: the weight gradients only (dXd comes from elsewhere, and the tile
+// map is not of 256-row tiles)
 template <bool SWIGLU, bool GATHER, bool DY_GATHER>
 __global__ __launch_bounds__(512) void ffn_bwd_rest_dma_kernel(
     const bf16_t* __restrict__ dG, const bf16_t* __restrict__ dU, const bf16_t* __restrict__ act,
@@ -1820,7 +1804,7 @@ __global__ __launch_bounds__(512) void ffn_bwd_rest_dma_kernel(
     extern __shared__ __align__(16) char smem[];
     clock_note(clk, 0);
     TileWalker tw;
-    for (int t = tw.start(cnt_dx, map[0] * ((d + TN - 1) / TN), smem); t >= 0; t = tw.next()) {
+    for (int t = tw.start(cnt_dx, dXd ? map[0] * ((d + TN - 1) / TN) : 0, smem); t >= 0; t = tw.next()) {
         tw.draw();
         dx_tile<SWIGLU>(t, tw, smem, dG, dU, off, map, d, f, wg, wu, dXd);
     }
@@ -1998,32 +1982,11 @@ int ffn_fwd_dma(const FfnArgs& a, hipStream_t s) {
     return XMOE_OK;
 }
 
-int ffn_bwd_dma(const FfnArgs& a, hipStream_t s) {
-    int st = init_device();
-    if (st != XMOE_OK) return st;
-    const int max_tiles = ffn_max_tiles(a.B, a.E, TM);
-    st = launch_tile_map(a.off, a.E, TM, max_tiles, a.map, a.sched, s);
-    if (st != XMOE_OK) return st;
-    const bf16_t *xd = (const bf16_t*)a.xd, *wg = (const bf16_t*)a.wg, *wu = (const bf16_t*)a.wu,
-                 *wd = (const bf16_t*)a.wd, *dy = (const bf16_t*)a.dy;
+// dXd (unless a.dxd is NULL), dWd and dWg | dWu, once dG, dU and A exist
+static int bwd_rest(const FfnArgs& a, int max_tiles, hipStream_t s) {
+    const bf16_t *xd = (const bf16_t*)a.xd, *wg = (const bf16_t*)a.wg, *wu = (const bf16_t*)a.wu, *dy = (const bf16_t*)a.dy;
     bf16_t *dg = (bf16_t*)a.dg, *du = (bf16_t*)a.du, *act = (bf16_t*)a.act;
-    const int ntf = (a.f + TN - 1) / TN, ntd = (a.d + TN - 1) / TN;
-    if (a.dy_index)
-        XMOE_LAUNCH(K_FFN_DACT_DMA, s,
-                    hipLaunchKernelGGL((ffn_rowgemm_dma_kernel<true, true>), dim3(round_up8((long)max_tiles * ntf)),
-                                       dim3(512), kLdsBytes, s, dy, a.dy_index, a.dy_scale, a.off, a.map, a.d, a.f, wd,
-                                       nullptr, (const bf16_t*)a.g, (const bf16_t*)a.u, dg, du, act,
-                                       a.row_part, (long)a.B, row_counters(a.sched, a.E, 0), clock_slot(CS_DACT)));
-    else
-        XMOE_LAUNCH(K_FFN_DACT_DMA, s,
-                    hipLaunchKernelGGL((ffn_rowgemm_dma_kernel<true, false>), dim3(round_up8((long)max_tiles * ntf)),
-                                       dim3(512), kLdsBytes, s, dy, nullptr, nullptr, a.off, a.map, a.d, a.f, wd,
-                                       nullptr, (const bf16_t*)a.g, (const bf16_t*)a.u, dg, du, act,
-                                       a.row_part, (long)a.B, row_counters(a.sched, a.E, 0), clock_slot(CS_DACT)));
-    if (a.row_grad) {
-        st = launch_row_grad_reduce(a.row_part, 4 * ntf, a.B, a.row_grad, s);
-        if (st != XMOE_OK) return st;
-    }
+    const int ntd = (a.d + TN - 1) / TN;
     const int mtf = (a.f + TM - 1) / TM, mtd = (a.d + TM - 1) / TM;
     const int ntf2 = (a.f + 127) / 128;
     if (bwd_merged()) {
@@ -2044,7 +2007,7 @@ int ffn_bwd_dma(const FfnArgs& a, hipStream_t s) {
 #undef XMOE_REST
         return XMOE_OK;
     }
-    XMOE_LAUNCH(K_FFN_DX_DMA, s,
+    if (a.dxd) XMOE_LAUNCH(K_FFN_DX_DMA, s,
                 hipLaunchKernelGGL(ffn_dx_dma_kernel<true>, dim3(round_up8((long)max_tiles * ntd)), dim3(512), kLdsBytes, s, dg,
                                    du, a.off, a.map, a.d, a.f, wg, wu, (bf16_t*)a.dxd, row_counters(a.sched, a.E, 1), clock_slot(CS_DX)));
     // dWd [f, d] = A^T dY
@@ -2074,6 +2037,41 @@ int ffn_bwd_dma(const FfnArgs& a, hipStream_t s) {
                                        dim3(512), kLdsBytes, s, xd, nullptr, dg, du, nullptr, nullptr, nullptr, a.off, a.sched,
                                        a.sched + a.E + kNumXcd, a.E, wgrad_one_xcd(a), a.d, a.f, (bf16_t*)a.dwg, (bf16_t*)a.dwu, clock_slot(CS_WGRAD_DUAL)));
     return XMOE_OK;
+}
+
+int ffn_bwd_dma(const FfnArgs& a, hipStream_t s) {
+    int st = init_device();
+    if (st != XMOE_OK) return st;
+    const int max_tiles = ffn_max_tiles(a.B, a.E, TM);
+    st = launch_tile_map(a.off, a.E, TM, max_tiles, a.map, a.sched, s);
+    if (st != XMOE_OK) return st;
+    const bf16_t *wd = (const bf16_t*)a.wd, *dy = (const bf16_t*)a.dy;
+    bf16_t *dg = (bf16_t*)a.dg, *du = (bf16_t*)a.du, *act = (bf16_t*)a.act;
+    const int ntf = (a.f + TN - 1) / TN;
+    if (a.dy_index)
+        XMOE_LAUNCH(K_FFN_DACT_DMA, s,
+                    hipLaunchKernelGGL((ffn_rowgemm_dma_kernel<true, true>), dim3(round_up8((long)max_tiles * ntf)),
+                                       dim3(512), kLdsBytes, s, dy, a.dy_index, a.dy_scale, a.off, a.map, a.d, a.f, wd,
+                                       nullptr, (const bf16_t*)a.g, (const bf16_t*)a.u, dg, du, act,
+                                       a.row_part, (long)a.B, row_counters(a.sched, a.E, 0), clock_slot(CS_DACT)));
+    else
+        XMOE_LAUNCH(K_FFN_DACT_DMA, s,
+                    hipLaunchKernelGGL((ffn_rowgemm_dma_kernel<true, false>), dim3(round_up8((long)max_tiles * ntf)),
+                                       dim3(512), kLdsBytes, s, dy, nullptr, nullptr, a.off, a.map, a.d, a.f, wd,
+                                       nullptr, (const bf16_t*)a.g, (const bf16_t*)a.u, dg, du, act,
+                                       a.row_part, (long)a.B, row_counters(a.sched, a.E, 0), clock_slot(CS_DACT)));
+    if (a.row_grad) {
+        st = launch_row_grad_reduce(a.row_part, 4 * ntf, a.B, a.row_grad, s);
+        if (st != XMOE_OK) return st;
+    }
+    return bwd_rest(a, max_tiles, s);
+}
+
+int ffn_bwd_wgrads_dma(const FfnArgs& a, hipStream_t s) {
+    FfnArgs w = a;
+    w.dxd = nullptr;
+    const int st = init_device();
+    return st != XMOE_OK ? st : bwd_rest(w, 0, s);
 }
 
 bool mlp2_dma_supported(const Mlp2Args& a) {
@@ -2119,38 +2117,11 @@ int mlp2_fwd_dma(const Mlp2Args& a, hipStream_t s) {
     return XMOE_OK;
 }
 
-int mlp2_bwd_dma(const Mlp2Args& a, hipStream_t s) {
-    int st = init_device();
-    if (st != XMOE_OK) return st;
-    const int max_tiles = ffn_max_tiles(a.B, a.E, TM);
-    st = launch_tile_map(a.off, a.E, TM, max_tiles, a.map, a.sched, s);
-    if (st != XMOE_OK) return st;
-    const bf16_t *xd = (const bf16_t*)a.xd, *w1 = (const bf16_t*)a.w1, *w2 = (const bf16_t*)a.w2,
-                 *dy = (const bf16_t*)a.dy;
+// dXd (unless a.dxd is NULL), dW2 and dW1, once dH and A exist
+static int bwd_rest(const Mlp2Args& a, int max_tiles, hipStream_t s) {
+    const bf16_t *xd = (const bf16_t*)a.xd, *w1 = (const bf16_t*)a.w1, *dy = (const bf16_t*)a.dy;
     bf16_t *dh = (bf16_t*)a.dh, *act = (bf16_t*)a.a_buf;
     const int ntf = (a.f + TN - 1) / TN, ntd = (a.d + TN - 1) / TN;
-    const dim3 grid(round_up8((long)max_tiles * ntf));
-    if (a.dy_index) {
-#define XMOE_CALL(ACT)                                                                                              \
-    XMOE_LAUNCH(K_MLP2_DACT_DMA, s,                                                                                 \
-                hipLaunchKernelGGL((mlp2_dact_dma_kernel<ACT, true>), grid, dim3(512), kLdsBytes, s, dy, a.dy_index, \
-                                   a.dy_scale, a.off, a.map, a.d, a.f, w2, (const bf16_t*)a.h, dh, act,            \
-                                   a.row_part, (long)a.B, row_counters(a.sched, a.E, 0), clock_slot(CS_MLP2_DACT)))
-        XMOE_DISPATCH_ACT(a.act, XMOE_CALL);
-#undef XMOE_CALL
-    } else {
-#define XMOE_CALL(ACT)                                                                                              \
-    XMOE_LAUNCH(K_MLP2_DACT_DMA, s,                                                                                 \
-                hipLaunchKernelGGL((mlp2_dact_dma_kernel<ACT, false>), grid, dim3(512), kLdsBytes, s, dy, nullptr,  \
-                                   nullptr, a.off, a.map, a.d, a.f, w2, (const bf16_t*)a.h, dh, act,               \
-                                   a.row_part, (long)a.B, row_counters(a.sched, a.E, 0), clock_slot(CS_MLP2_DACT)))
-        XMOE_DISPATCH_ACT(a.act, XMOE_CALL);
-#undef XMOE_CALL
-    }
-    if (a.row_grad) {
-        st = launch_row_grad_reduce(a.row_part, 4 * ntf, a.B, a.row_grad, s);
-        if (st != XMOE_OK) return st;
-    }
     const int mtf = (a.f + TM - 1) / TM, mtd = (a.d + TM - 1) / TM;
     if (bwd_merged()) {
         // dXd, dW2, dW1: one launch
@@ -2171,7 +2142,7 @@ int mlp2_bwd_dma(const Mlp2Args& a, hipStream_t s) {
 #undef XMOE_REST
         return XMOE_OK;
     }
-    XMOE_LAUNCH(K_FFN_DX_DMA, s,
+    if (a.dxd) XMOE_LAUNCH(K_FFN_DX_DMA, s,
                 hipLaunchKernelGGL(ffn_dx_dma_kernel<false>, dim3(round_up8((long)max_tiles * ntd)), dim3(512),
                                    kLdsBytes, s, dh, nullptr, a.off, a.map, a.d, a.f, w1, nullptr, (bf16_t*)a.dxd,
                                    row_counters(a.sched, a.E, 1), clock_slot(CS_DX)));
@@ -2203,6 +2174,47 @@ int mlp2_bwd_dma(const Mlp2Args& a, hipStream_t s) {
                                        a.sched,
                                        a.sched + a.E + kNumXcd, a.E, wgrad_one_xcd(a), a.d, a.f, (bf16_t*)a.dw1, nullptr, clock_slot(CS_WGRAD)));
     return XMOE_OK;
+}
+
+int mlp2_bwd_dma(const Mlp2Args& a, hipStream_t s) {
+    int st = init_device();
+    if (st != XMOE_OK) return st;
+    const int max_tiles = ffn_max_tiles(a.B, a.E, TM);
+    st = launch_tile_map(a.off, a.E, TM, max_tiles, a.map, a.sched, s);
+    if (st != XMOE_OK) return st;
+    const bf16_t *w2 = (const bf16_t*)a.w2, *dy = (const bf16_t*)a.dy;
+    bf16_t *dh = (bf16_t*)a.dh, *act = (bf16_t*)a.a_buf;
+    const int ntf = (a.f + TN - 1) / TN;
+    const dim3 grid(round_up8((long)max_tiles * ntf));
+    if (a.dy_index) {
+#define XMOE_CALL(ACT)                                                                                              \
+    XMOE_LAUNCH(K_MLP2_DACT_DMA, s,                                                                                 \
+                hipLaunchKernelGGL((mlp2_dact_dma_kernel<ACT, true>), grid, dim3(512), kLdsBytes, s, dy, a.dy_index, \
+                                   a.dy_scale, a.off, a.map, a.d, a.f, w2, (const bf16_t*)a.h, dh, act,            \
+                                   a.row_part, (long)a.B, row_counters(a.sched, a.E, 0), clock_slot(CS_MLP2_DACT)))
+        XMOE_DISPATCH_ACT(a.act, XMOE_CALL);
+#undef XMOE_CALL
+    } else {
+#define XMOE_CALL(ACT)                                                                                              \
+    XMOE_LAUNCH(K_MLP2_DACT_DMA, s,                                                                                 \
+                hipLaunchKernelGGL((mlp2_dact_dma_kernel<ACT, false>), grid, dim3(512), kLdsBytes, s, dy, nullptr,  \
+                                   nullptr, a.off, a.map, a.d, a.f, w2, (const bf16_t*)a.h, dh, act,               \
+                                   a.row_part, (long)a.B, row_counters(a.sched, a.E, 0), clock_slot(CS_MLP2_DACT)))
+        XMOE_DISPATCH_ACT(a.act, XMOE_CALL);
+#undef XMOE_CALL
+    }
+    if (a.row_grad) {
+        st = launch_row_grad_reduce(a.row_part, 4 * ntf, a.B, a.row_grad, s);
+        if (st != XMOE_OK) return st;
+    }
+    return bwd_rest(a, max_tiles, s);
+}
+
+int mlp2_bwd_wgrads_dma(const Mlp2Args& a, hipStream_t s) {
+    Mlp2Args w = a;
+    w.dxd = nullptr;
+    const int st = init_device();
+    return st != XMOE_OK ? st : bwd_rest(w, 0, s);
 }
 
 }  // namespace xmoe

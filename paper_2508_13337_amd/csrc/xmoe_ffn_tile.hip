@@ -93,25 +93,6 @@ int launch_row_grad_reduce(const float* row_part, int parts, int B, float* row_g
     return XMOE_OK;
 }
 
-// A row GEMM's block: its row tile (expert and rows from the tile map) and column tile.  Blocks go to the XCDs in turn
-// (block b to XCD b % 8); each XCD takes an eighth of the tiles there are, in one run, columns fastest, so that its L2
-// fetches the rows of a tile once for all columns and an expert's weights once for all its row tiles.
-struct RowTile {
-    int e, row0, rows, col;   // rows: valid rows of the tile, may exceed the tile
-    __device__ __forceinline__ bool init(const int32_t* __restrict__ off, const int32_t* __restrict__ map, int cols) {
-        const int total = map[0] * cols, per = (total + 7) / 8, s = blockIdx.x >> 3;
-        const int t = (blockIdx.x & 7) * per + s;
-        if (s >= per || t >= total) return false;
-        const int i = t / cols;
-        col = t - i * cols;
-        e = map[4 + 2 * i];
-        row0 = map[4 + 2 * i + 1];
-        rows = off[e + 1] - row0;
-        return true;
-    }
-};
-static inline dim3 row_grid(int max_tiles, int cols) { return dim3(((long long)max_tiles * cols + 7) / 8 * 8); }
-
 #define XMOE_TILE_BOUNDS __launch_bounds__(TileShape<BIG>::kThreads, 2)
 
 // ---------------------------------------------------------------------------------------------------------
@@ -128,7 +109,7 @@ __global__ XMOE_TILE_BOUNDS void ffn_gateup_mfma_kernel(const T* __restrict__ xd
     using S = TileShape<BIG>;
     __shared__ __align__(16) char smem[S::kLds];
     RowTile t;
-    if (!t.init(off, map, (f + S::kN / 2 - 1) / (S::kN / 2))) return;
+    if (!t.init(off, map, (f + S::kN / 2 - 1) / (S::kN / 2), S::kM)) return;
     const int n0 = t.col * (S::kN / 2);
     RowSrc<T, S::kThreads> a;
     ColSrc<T, S::kThreads, false> b;
@@ -182,7 +163,7 @@ __global__ XMOE_TILE_BOUNDS void ffn_down_mfma_kernel(const T* __restrict__ A, c
     using S = TileShape<BIG>;
     __shared__ __align__(16) char smem[S::kLds];
     RowTile t;
-    if (!t.init(off, map, (d + S::kN - 1) / S::kN)) return;
+    if (!t.init(off, map, (d + S::kN - 1) / S::kN, S::kM)) return;
     const int n0 = t.col * S::kN;
     RowSrc<T, S::kThreads> a;
     ColSrc<T, S::kThreads, false> b;
@@ -208,7 +189,7 @@ __device__ __forceinline__ void dact_tile(const T* __restrict__ dY, const int32_
     using S = TileShape<BIG>;
     __shared__ __align__(16) char smem[S::kLds];
     RowTile t;
-    if (!t.init(off, map, (f + S::kN - 1) / S::kN)) return;
+    if (!t.init(off, map, (f + S::kN - 1) / S::kN, S::kM)) return;
     const int n0 = t.col * S::kN;
     RowSrc<T, S::kThreads> a, b;
     a.init(dy_index ? dY : dY + (size_t)t.row0 * d, d, t.rows, dy_index ? dy_index + t.row0 : nullptr);
@@ -312,7 +293,7 @@ __global__ XMOE_TILE_BOUNDS void ffn_dx_mfma_kernel(const T* __restrict__ dG, co
     using S = TileShape<BIG>;
     __shared__ __align__(16) char smem[S::kLds];
     RowTile t;
-    if (!t.init(off, map, (d + S::kN - 1) / S::kN)) return;
+    if (!t.init(off, map, (d + S::kN - 1) / S::kN, S::kM)) return;
     const int n0 = t.col * S::kN;
     tile_f32x16_t acc[S::kMI][2];
     tile_zero<BIG>(acc);
@@ -390,7 +371,7 @@ __global__ XMOE_TILE_BOUNDS void mlp2_up_mfma_kernel(const T* __restrict__ xd,
     using S = TileShape<BIG>;
     __shared__ __align__(16) char smem[S::kLds];
     RowTile t;
-    if (!t.init(off, map, (f + S::kN - 1) / S::kN)) return;
+    if (!t.init(off, map, (f + S::kN - 1) / S::kN, S::kM)) return;
     const int n0 = t.col * S::kN;
     RowSrc<T, S::kThreads> a;
     ColSrc<T, S::kThreads, false> b;
@@ -458,6 +439,21 @@ static int launch_wgrad(WgradJobs<T> jobs, int n_jobs, int E, int d, int f, cons
     return XMOE_OK;
 }
 
+template <typename T>
+static int wgrad_call(const FfnArgs& a, hipStream_t s) {
+    WgradJobs<T> jobs = {{{(const T*)a.act, (const T*)a.dy, nullptr, a.dy_index, a.f, a.d, 0, (T*)a.dwd},
+                          {(const T*)a.xd, (const T*)a.dg, a.row_index, nullptr, a.d, a.f, 0, (T*)a.dwg},
+                          {(const T*)a.xd, (const T*)a.du, a.row_index, nullptr, a.d, a.f, 0, (T*)a.dwu}}};
+    return launch_wgrad<T>(jobs, 3, a.E, a.d, a.f, a.off, a.sched, s);
+}
+template <typename T>
+static int wgrad_call(const Mlp2Args& a, hipStream_t s) {
+    WgradJobs<T> jobs = {{{(const T*)a.a_buf, (const T*)a.dy, nullptr, a.dy_index, a.f, a.d, 0, (T*)a.dw2},
+                          {(const T*)a.xd, (const T*)a.dh, a.row_index, nullptr, a.d, a.f, 0, (T*)a.dw1},
+                          {}}};
+    return launch_wgrad<T>(jobs, 2, a.E, a.d, a.f, a.off, a.sched, s);
+}
+
 template <typename T, bool BIG>
 static int fwd_tile(const FfnArgs& a, hipStream_t s) {
     using S = TileShape<BIG>;
@@ -476,7 +472,7 @@ static int fwd_tile(const FfnArgs& a, hipStream_t s) {
 }
 
 template <typename T, bool BIG>
-static int bwd_tile(const FfnArgs& a, hipStream_t s) {
+static int bwd_rows_tile(const FfnArgs& a, hipStream_t s) {
     using S = TileShape<BIG>;
     const int max_tiles = ffn_max_tiles(a.B, a.E, S::kM);
     int st = launch_tile_map(a.off, a.E, S::kM, max_tiles, a.map, a.sched, s);
@@ -494,10 +490,7 @@ static int bwd_tile(const FfnArgs& a, hipStream_t s) {
                 hipLaunchKernelGGL((ffn_dx_mfma_kernel<T, BIG>), row_grid(max_tiles, ceil_div(a.d, S::kN)),
                                    dim3(S::kThreads), 0, s, (const T*)a.dg, (const T*)a.du, a.off, a.map, a.d, a.f,
                                    (const T*)a.wg, (const T*)a.wu, (T*)a.dxd));
-    WgradJobs<T> jobs = {{{(const T*)a.act, (const T*)a.dy, nullptr, a.dy_index, a.f, a.d, 0, (T*)a.dwd},
-                          {(const T*)a.xd, (const T*)a.dg, a.row_index, nullptr, a.d, a.f, 0, (T*)a.dwg},
-                          {(const T*)a.xd, (const T*)a.du, a.row_index, nullptr, a.d, a.f, 0, (T*)a.dwu}}};
-    return launch_wgrad<T>(jobs, 3, a.E, a.d, a.f, a.off, a.sched, s);
+    return XMOE_OK;
 }
 
 template <typename T, bool BIG>
@@ -520,7 +513,7 @@ static int mlp2_fwd_tile(const Mlp2Args& a, hipStream_t s) {
 }
 
 template <typename T, bool BIG>
-static int mlp2_bwd_tile(const Mlp2Args& a, hipStream_t s) {
+static int mlp2_bwd_rows_tile(const Mlp2Args& a, hipStream_t s) {
     using S = TileShape<BIG>;
     const int max_tiles = ffn_max_tiles(a.B, a.E, S::kM);
     int st = launch_tile_map(a.off, a.E, S::kM, max_tiles, a.map, a.sched, s);
@@ -541,20 +534,52 @@ static int mlp2_bwd_tile(const Mlp2Args& a, hipStream_t s) {
                 hipLaunchKernelGGL((ffn_dx_mfma_kernel<T, BIG>), row_grid(max_tiles, ceil_div(a.d, S::kN)),
                                    dim3(S::kThreads), 0, s, (const T*)a.dh, (const T*)nullptr, a.off, a.map, a.d, a.f,
                                    (const T*)a.w1, (const T*)nullptr, (T*)a.dxd));
-    WgradJobs<T> jobs = {{{(const T*)a.a_buf, (const T*)a.dy, nullptr, a.dy_index, a.f, a.d, 0, (T*)a.dw2},
-                          {(const T*)a.xd, (const T*)a.dh, a.row_index, nullptr, a.d, a.f, 0, (T*)a.dw1},
-                          {}}};
-    return launch_wgrad<T>(jobs, 2, a.E, a.d, a.f, a.off, a.sched, s);
+    return XMOE_OK;
 }
 
-// runs CALL<T, BIG>(a, s) for the call's element type and tile
-#define XMOE_TILE_CALL(CALL)                                                                       \
-    if (a.dt == XMOE_F32) return big_tiles(a.B, a.E, a.d, a.f, a.dt) ? CALL<float, true>(a, s) : CALL<float, false>(a, s); \
-    return big_tiles(a.B, a.E, a.d, a.f, a.dt) ? CALL<bf16_t, true>(a, s) : CALL<bf16_t, false>(a, s)
+// Widths that are multiples of 8 (bf16): the forward's row products always take the direct-to-LDS tiles, whatever the
+// number of rows (staged small tiles | direct, us: E 24 d 1000 f 712, 16 rows per expert 40 | 33; E 16 d 2040 f 1480, 40
+// rows 96 | 78; E 4 d 1496 f 208, 1500 rows 61 | 40), the backward's where the staged tiles would be the big ones (E 8 d
+// 1000 f 1000, backward, 96 rows 90 | 96; big ones: T 3001 d 1000 f 712 E 24+1, staged | direct: dAct 82 | 58, dX 78 | 75).
+//
+// Their weight gradients take the 256-row kernels (whose operands are K-strided, so that widths only have to be whole
+// 16-byte pieces) where those have two tiles per CU and the experts rows enough for their main loop, or many tiles.  Whole
+// backward with the staged weight gradients | those, us: E 24 d 1000 f 712 (900 tiles) 40 rows 127 | 144, 96 rows 139 | 134,
+// 375 rows 244 | 195; E 16 d 2040 f 1480 (2304) 4 rows 245 | 261, 16 rows 284 | 271, 375 rows 600 | 442; E 256 d 328 f 200
+// (1536) 4 rows 125 | 143, 16 rows 153 | 149, 96 rows 187 | 157; E 8 d 1000 f 1000 (384) 375 rows 118 | 137, 1500 rows
+// 282 | 259; E 128 d 176 f 320 (640) 96 rows 105 | 106, 375 rows 180 | 173.
+static inline bool dma_wgrads(int B, int E, int d, int f, bool dual) {
+    const long long n = (long long)E * (ceil_div(f, 256) * ceil_div(d, 256) + ceil_div(d, 256) * ceil_div(f, dual ? 128 : 256));
+    return (B >= 96ll * E && n >= 512) || (B >= 16ll * E && n >= 1536);
+}
 
-int ffn_fwd_tile(const FfnArgs& a, hipStream_t s) { XMOE_TILE_CALL(fwd_tile); }
-int ffn_bwd_tile(const FfnArgs& a, hipStream_t s) { XMOE_TILE_CALL(bwd_tile); }
-int mlp2_fwd_tile(const Mlp2Args& a, hipStream_t s) { XMOE_TILE_CALL(mlp2_fwd_tile); }
-int mlp2_bwd_tile(const Mlp2Args& a, hipStream_t s) { XMOE_TILE_CALL(mlp2_bwd_tile); }
+#define XMOE_TILE_CALL(CALL)                                                              \
+    (a.dt == XMOE_F32 ? (big ? CALL<float, true>(a, s) : CALL<float, false>(a, s))        \
+                      : (big ? CALL<bf16_t, true>(a, s) : CALL<bf16_t, false>(a, s)))
+
+int ffn_fwd_tile(const FfnArgs& a, hipStream_t s) {
+    if (direct_supported(a)) return ffn_fwd_direct(a, s);
+    const bool big = big_tiles(a.B, a.E, a.d, a.f, a.dt);
+    return XMOE_TILE_CALL(fwd_tile);
+}
+int mlp2_fwd_tile(const Mlp2Args& a, hipStream_t s) {
+    if (direct_supported(a)) return mlp2_fwd_direct(a, s);
+    const bool big = big_tiles(a.B, a.E, a.d, a.f, a.dt);
+    return XMOE_TILE_CALL(mlp2_fwd_tile);
+}
+int ffn_bwd_tile(const FfnArgs& a, hipStream_t s) {
+    const bool big = big_tiles(a.B, a.E, a.d, a.f, a.dt), direct = direct_supported(a);
+    const int st = big && direct ? ffn_bwd_rows_direct(a, s) : XMOE_TILE_CALL(bwd_rows_tile);
+    if (st != XMOE_OK) return st;
+    if (direct && dma_wgrads(a.B, a.E, a.d, a.f, true)) return ffn_bwd_wgrads_dma(a, s);
+    return a.dt == XMOE_F32 ? wgrad_call<float>(a, s) : wgrad_call<bf16_t>(a, s);
+}
+int mlp2_bwd_tile(const Mlp2Args& a, hipStream_t s) {
+    const bool big = big_tiles(a.B, a.E, a.d, a.f, a.dt), direct = direct_supported(a);
+    const int st = big && direct ? mlp2_bwd_rows_direct(a, s) : XMOE_TILE_CALL(mlp2_bwd_rows_tile);
+    if (st != XMOE_OK) return st;
+    if (direct && dma_wgrads(a.B, a.E, a.d, a.f, false)) return mlp2_bwd_wgrads_dma(a, s);
+    return a.dt == XMOE_F32 ? wgrad_call<float>(a, s) : wgrad_call<bf16_t>(a, s);
+}
 
 }  // namespace xmoe

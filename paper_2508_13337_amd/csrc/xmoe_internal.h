@@ -56,6 +56,12 @@ enum KernelId : int {
     K_FFN_GATEUP_FEW,
     K_FFN_DOWN_FEW,
     K_MLP2_UP_FEW,
+    K_FFN_GATEUP_DIRECT,
+    K_FFN_DOWN_DIRECT,
+    K_FFN_DACT_DIRECT,
+    K_FFN_DX_DIRECT,
+    K_MLP2_UP_DIRECT,
+    K_MLP2_DACT_DIRECT,
     K_COUNT
 };
 

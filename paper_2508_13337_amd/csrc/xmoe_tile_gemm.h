@@ -468,4 +468,31 @@ __device__ __forceinline__ float tile_sum_over_cols(float (&part)[16]) {
     return part[0] + __shfl_xor(part[0], 1, 64);
 }
 
+// A row GEMM's block: its row tile (expert and rows from the tile map) and column tile.  Blocks go to the XCDs in turn
+// (block b to XCD b % 8); each XCD takes an eighth of the tiles there are, in one run.  An expert's tiles are numbered in
+// bands of eight row tiles, down the rows of a band first: the blocks of an XCD then work on few experts at a time, and its
+// L2 fetches a panel of weights once for the rows of a band and the rows once for all columns.
+constexpr int kTileBand = 8;
+struct RowTile {
+    int e, row0, rows, col;   // rows: valid rows of the tile, may exceed the tile
+    __device__ __forceinline__ bool init(const int32_t* __restrict__ off, const int32_t* __restrict__ map, int cols,
+                                         int tile_rows) {
+        const int total = map[0] * cols, per = (total + 7) / 8, s = blockIdx.x >> 3;
+        const int t = (blockIdx.x & 7) * per + s;
+        if (s >= per || t >= total) return false;
+        const int i = t / cols;
+        e = map[4 + 2 * i];
+        const int lo = off[e], hi = off[e + 1];
+        const int first = i - (map[4 + 2 * i + 1] - lo) / tile_rows;   // the expert's first row tile
+        const int tiles = (hi - lo + tile_rows - 1) / tile_rows;
+        const int u = t - first * cols, band = u / (kTileBand * cols), v = u - band * kTileBand * cols;
+        const int in_band = tiles - band * kTileBand < kTileBand ? tiles - band * kTileBand : kTileBand;
+        col = v / in_band;
+        row0 = lo + (band * kTileBand + v - col * in_band) * tile_rows;
+        rows = hi - row0;
+        return true;
+    }
+};
+static inline dim3 row_grid(int max_tiles, int cols) { return dim3((unsigned)(((long long)max_tiles * cols + 7) / 8 * 8)); }
+
 }  // namespace xmoe

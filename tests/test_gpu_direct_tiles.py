@@ -1,0 +1,177 @@
+"""The 128 x 128 tiles with direct-to-LDS loads (xmoe_ffn_direct.hip): segments at the edges of their row blocks, K of
+less than one 64-wide unit and with ragged ends, output tiles of every 8-column remainder, both sides of the rules that
+choose them, and the bits of the 256-row kernels.
+
+Tolerance: every stored result is one float32-accumulated product of bf16 operands, rounded once (2^-9 relative).  The
+reference rounds the stored factors (A, dG, dU) as the kernels do, so that an odd rounding of a factor is all they differ
+by.  Results are held to 2^-6 of the row's (weight gradients: the matrix's) root mean square
+or of the value itself; the row scales' gradient is a float32 sum."""
+import pytest
+import torch
+
+from gpu_util import launched
+
+pytestmark = pytest.mark.gpu
+
+ROWS = [1, 0, 31, 32, 33, 63, 64, 65, 127, 128, 129, 200, 7]
+
+
+def inputs(rows, d, f, matrices):
+    g = torch.Generator().manual_seed(sum(rows) + d + 3 * f + matrices)
+    E, B, T = len(rows), sum(rows), 61
+    off = torch.tensor([0] + list(torch.tensor(rows).cumsum(0)), dtype=torch.int32)
+    x, dout = (torch.randn((T, d), generator=g).bfloat16() for _ in range(2))
+    idx = torch.randint(0, T, (B,), generator=g, dtype=torch.int32)
+    scale = torch.rand(B, generator=g)
+    w = [(torch.randn((E, f, d) if i == matrices - 1 else (E, d, f), generator=g) * (f if i == matrices - 1 else d) ** -0.5)
+         .bfloat16() for i in range(matrices)]
+    return off, x, dout, idx, scale, w
+
+
+def run(m, rows, d, f, expert, gathered=True, scaled=True):
+    """Forward and backward: {name: tensor} on the host, and the kernels launched by either."""
+    off, x, dout, idx, scale, w = inputs(rows, d, f, 3 if expert == "swiglu" else 2)
+    B, E = sum(rows), len(rows)
+    X, D = (t if gathered else t[idx.long()] for t in (x, dout))
+    new = lambda *s: torch.full(s, 7.0, dtype=torch.bfloat16, device="cuda")
+    t = {"y": new(B + 1, d), "dxd": new(B + 1, d)}
+    t.update({n: new(B + 1, f) for n in (("g", "u") if expert == "swiglu" else ("h",))})
+    t.update({"dw%d" % i: new(*a.shape) for i, a in enumerate(w)})
+    t["rg"] = torch.full((B + 1,), 7.0, device="cuda")
+    o = {n: a[:B] if a.shape[0] == B + 1 else a for n, a in t.items()}
+    two = expert != "swiglu"
+    ws = m.alloc_workspace(max(m.xmoe_workspace_bytes(op, B, d, E, 1, f, m.XMOE_BF16)
+                               for op in ((m.WS_MLP2_FWD, m.WS_MLP2_BWD) if two else (m.WS_FFN_FWD, m.WS_FFN_BWD))))
+    xc, dc, oc, wc, ic = X.cuda(), D.cuda(), off.cuda(), [a.cuda() for a in w], idx.cuda() if gathered else None
+    kw = dict(row_index=ic, dy_row_index=ic, dy_row_scale=scale.cuda() if gathered and scaled else None,
+              dy_row_scale_grad=o["rg"])
+    if two:
+        k1 = launched(m, lambda: m.xmoe_expert_mlp2_fwd(xc, oc, *wc, expert, o["h"], o["y"], ws, row_index=ic))
+        k2 = launched(m, lambda: m.xmoe_expert_mlp2_bwd(xc, o["h"], dc, oc, *wc, expert, o["dxd"], o["dw0"], o["dw1"], ws,
+                                                        **kw))
+    else:
+        k1 = launched(m, lambda: m.xmoe_expert_ffn_fwd(xc, oc, *wc, o["g"], o["u"], o["y"], ws, row_index=ic))
+        k2 = launched(m, lambda: m.xmoe_expert_ffn_bwd(xc, o["g"], o["u"], dc, oc, *wc, o["dxd"], o["dw0"], o["dw1"],
+                                                       o["dw2"], ws, **kw))
+    host = {n: a.cpu() for n, a in t.items()}
+    assert all(bool((a[B] == 7.0).all()) for n, a in host.items() if a.shape[0] == B + 1)   # nothing behind the last row
+    return {n: a[:B] if a.shape[0] == B + 1 else a for n, a in host.items()}, k1, k2
+
+
+def close(name, got, want, dims=-1, tol=2.0 ** -6):
+    rms = want.pow(2).mean(dim=dims, keepdim=True).sqrt()
+    err = ((got.double() - want).abs() / torch.maximum(want.abs(), rms).clamp_min(1e-30)).max()
+    assert float(err) <= tol, (name, float(err))
+
+
+def act64(name, h):
+    if name == "identity":
+        return h, torch.ones_like(h)
+    if name == "gelu":
+        cdf = 0.5 * torch.erfc(-h / 2 ** 0.5)
+        return h * cdf, cdf + h * torch.exp(-0.5 * h * h) / (2 * torch.pi) ** 0.5
+    s = torch.sigmoid(h)
+    return h * s, s * (1 + h * (1 - s))
+
+
+def check(rows, d, f, expert, o, gathered=True, scaled=True):
+    off, x, dout, idx, scale, w = inputs(rows, d, f, 3 if expert == "swiglu" else 2)
+    c = scale.double() if gathered and scaled else torch.ones(sum(rows), dtype=torch.float64)
+    for e, n in enumerate(rows):
+        s = slice(int(off[e]), int(off[e + 1]))
+        if n == 0:
+            assert not any(bool(o["dw%d" % i][e].any()) for i in range(len(w)))
+            continue
+        X, D, cs = x[idx[s].long()].double(), dout[idx[s].long()].double(), c[s][:, None]
+        W = [a[e].double() for a in w]
+        if expert == "swiglu":
+            close("g", o["g"][s], X @ W[0])
+            close("u", o["u"][s], X @ W[1])
+            G, U = o["g"][s].double(), o["u"][s].double()     # the backward starts from the stored activations
+            S, dS = act64("silu", G)
+            A, back = S * U, lambda dA: [dA * U * dS, dA * S]
+            S1, _ = act64("silu", X @ W[0])
+            A1 = S1 * (X @ W[1])
+        else:
+            close("h", o["h"][s], X @ W[0])
+            A, dS = act64(expert, o["h"][s].double())
+            A1, back = act64(expert, X @ W[0])[0], lambda dA: [dA * dS]
+        close("y", o["y"][s], A1.bfloat16().double() @ W[-1])
+        P = D @ W[-1].t()
+        close("rg", o["rg"][s], (P * A).sum(1), dims=0, tol=1e-4)
+        g = [v.bfloat16().double() for v in back(cs * P)]
+        close("dxd", o["dxd"][s], sum(v @ a.t() for v, a in zip(g, W)))
+        close("dw last", o["dw%d" % (len(w) - 1)][e], (cs * A).bfloat16().double().t() @ D, dims=(0, 1))
+        for i, v in enumerate(g):
+            close("dw%d" % i, o["dw%d" % i][e], X.t() @ v, dims=(0, 1))
+
+
+@pytest.mark.parametrize("expert,gathered,scaled", [("swiglu", True, True), ("swiglu", False, False), ("swiglu", True, False),
+                                                    ("gelu", True, True), ("silu", False, False), ("identity", True, True)])
+@pytest.mark.parametrize("d,f", [(256, 256), (448, 320)])
+def test_multiples_of_64(d, f, expert, gathered, scaled):
+    import paper_2508_13337_amd as m
+    o, k1, k2 = run(m, ROWS, d, f, expert, gathered, scaled)
+    up = "ffn_gateup" if expert == "swiglu" else "mlp2_up"
+    da = "ffn_dact" if expert == "swiglu" else "mlp2_dact"
+    assert k1 == {"tile_map_kernel", up + "_direct_kernel", "ffn_down_direct_kernel"}, k1
+    assert {da + "_direct_kernel", "ffn_dx_direct_kernel"} <= k2 and any("ffn_bwd_rest" in k or "wgrad" in k for k in k2), k2
+    check(ROWS, d, f, expert, o, gathered, scaled)
+
+
+# K of less than a unit, ending inside its first and second half and inside a K-strided tile; one, two and more output tiles
+@pytest.mark.parametrize("expert", ["swiglu", "gelu"])
+@pytest.mark.parametrize("d,f", [(8, 8), (8, 136), (72, 40), (104, 328), (264, 120), (328, 200)])
+@pytest.mark.parametrize("rows", [ROWS, [300, 0, 1000, 129] + [96] * 12], ids=["few", "many"])
+def test_multiples_of_8(rows, d, f, expert):
+    import paper_2508_13337_amd as m
+    o, _, _ = run(m, rows, d, f, expert)
+    check(rows, d, f, expert, o)
+
+
+def test_weight_gradients_of_the_256_row_kernels():
+    """Widths that are no multiple of 64, with enough tiles of 256 for them."""
+    import paper_2508_13337_amd as m
+    rows = [97, 0, 300, 64] + [100] * 82
+    for d, f, expert in ((264, 392, "swiglu"), (520, 776, "gelu")):
+        o, _, k2 = run(m, rows, d, f, expert)
+        assert any("ffn_bwd_rest" in k or "wgrad_dma" in k for k in k2), k2
+        check(rows, d, f, expert, o)
+
+
+def test_bits_of_the_256_row_kernels():
+    """The same rows in a call of few tiles and among so many that the 256-row kernels take it."""
+    import paper_2508_13337_amd as m
+    d, f, few, many = 320, 256, [70, 1, 0, 129], [6000, 5000, 4097, 8000]
+    g = torch.Generator().manual_seed(3)
+    x = torch.randn((61, d), generator=g).bfloat16().cuda()
+    w = [(torch.randn(s, generator=g) * 0.06).bfloat16().cuda() for s in ((64, d, f), (64, d, f), (64, f, d))]
+    long = [torch.randint(0, 61, (n,), generator=g, dtype=torch.int32) for n in many]
+    outs = []
+    for rows in (few, many):
+        rows64 = rows + [0 if rows is few else 4500] * 60
+        idx = torch.cat([i[:n] for i, n in zip(long, rows)] + [torch.zeros(sum(rows64[4:]), dtype=torch.int32)])
+        off = torch.tensor([0] + list(torch.tensor(rows64).cumsum(0)), dtype=torch.int32)
+        # few rows on average would take the few-row kernels: the first four experts alone
+        E = 4 if rows is few else 64
+        B = int(off[E])
+        o = [torch.empty((B, n), dtype=torch.bfloat16, device="cuda") for n in (f, f, d)]
+        ws = m.alloc_workspace(m.xmoe_workspace_bytes(m.WS_FFN_FWD, B, d, E, 1, f, m.XMOE_BF16))
+        k = launched(m, lambda: m.xmoe_expert_ffn_fwd(x, off[:E + 1].cuda(), *(a[:E] for a in w), *o, ws,
+                                                      row_index=idx[:B].cuda()))
+        outs.append((off.tolist(), [t.cpu() for t in o], k))
+    assert "ffn_gateup_direct_kernel" in outs[0][2] and "ffn_gateup_dma_kernel" in outs[1][2], (outs[0][2], outs[1][2])
+    for p, q in zip(outs[0][1], outs[1][1]):
+        for e, n in enumerate(few):
+            assert torch.equal(p[outs[0][0][e]:][:n], q[outs[1][0][e]:][:n]), e
+
+
+@pytest.mark.parametrize("E,d,f,rows,fwd,bwd", [(4, 256, 256, 129, True, True), (4, 192, 256, 129, False, False),
+                                                (4, 256, 192, 129, False, False), (64, 256, 256, 64 * 800, False, False),
+                                                (64, 256, 256, 64 * 90, True, True), (64, 256, 512, 64 * 90, True, False)])
+def test_both_sides_of_the_rules(E, d, f, rows, fwd, bwd):
+    import paper_2508_13337_amd as m
+    count = [rows // E + (e < rows % E) for e in range(E)]
+    _, k1, k2 = run(m, count, d, f, "swiglu")
+    assert ("ffn_gateup_direct_kernel" in k1) == fwd and ("ffn_gateup_dma_kernel" in k1) != fwd, k1
+    assert ("ffn_dact_direct_kernel" in k2) == bwd and ("ffn_rowgemm_dma_kernel<true>" in k2) != bwd, k2
