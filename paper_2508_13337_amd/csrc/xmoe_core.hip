@@ -70,6 +70,7 @@ const char* const kKernelNames[K_COUNT] = {
     "ffn_dx_direct_kernel",
     "mlp2_up_direct_kernel",
     "mlp2_dact_direct_kernel",
+    "ffn_wgrad_direct_kernel",
 };
 
 hipEvent_t get_event() {

@@ -117,13 +117,17 @@ int mlp2_fwd_few(const Mlp2Args& a, hipStream_t s);
 // 128-row tiles with direct-to-LDS loads (bf16, d % 8 == 0, f % 8 == 0 and 16-byte aligned operands): the whole forward, and
 // the backward's row products (tile map, dAct with the row scales' gradient, dX) without the weight gradients
 bool direct_fwd(int B, int E, int d, int f);   // whether they take a call's row products from the 256-row kernels
-bool direct_bwd(int B, int E, int d, int f);
+bool direct_bwd(int B, int E, int d, int f, int matrices);       // matrices of an expert: 3, or 2 (mlp2)
+bool direct_wgrads(int B, int E, int d, int f, int matrices);    // and, behind direct_bwd, its weight gradients
+long long wgrad_tiles_256(int E, int d, int f, int matrices);    // tiles of the 256-row weight-gradient kernels
 bool direct_supported(const FfnArgs& a);
 bool direct_supported(const Mlp2Args& a);
 int ffn_fwd_direct(const FfnArgs& a, hipStream_t s);
 int ffn_bwd_rows_direct(const FfnArgs& a, hipStream_t s);
+int ffn_bwd_wgrads_direct(const FfnArgs& a, hipStream_t s);   // the weight gradients, behind the row products
 int mlp2_fwd_direct(const Mlp2Args& a, hipStream_t s);
 int mlp2_bwd_rows_direct(const Mlp2Args& a, hipStream_t s);
+int mlp2_bwd_wgrads_direct(const Mlp2Args& a, hipStream_t s);
 
 int mlp2_fwd_tile(const Mlp2Args& a, hipStream_t s);
 int mlp2_bwd_tile(const Mlp2Args& a, hipStream_t s);

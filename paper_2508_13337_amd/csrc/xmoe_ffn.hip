@@ -85,9 +85,10 @@ int xmoe_expert_ffn_bwd(const void* xd, const int32_t* row_index, const void* g_
     a.row_part = (float*)p;   // the partial sums are always written (the matrix-core kernel has no branch for them)
     hipStream_t s = (hipStream_t)stream;
     if (!ffn_dma_supported(a)) return ffn_bwd_tile(a, s);
-    if (!direct_bwd(B, E, d, f)) return ffn_bwd_dma(a, s);
+    if (!direct_bwd(B, E, d, f, 3)) return ffn_bwd_dma(a, s);
     st = ffn_bwd_rows_direct(a, s);
-    return st != XMOE_OK ? st : ffn_bwd_wgrads_dma(a, s);
+    if (st != XMOE_OK) return st;
+    return direct_wgrads(B, E, d, f, 3) ? ffn_bwd_wgrads_direct(a, s) : ffn_bwd_wgrads_dma(a, s);
 }
 
 int xmoe_expert_mlp2_fwd(const void* xd, const int32_t* row_index, const int32_t* expert_offsets, int B, int E,
@@ -151,9 +152,10 @@ int xmoe_expert_mlp2_bwd(const void* xd, const int32_t* row_index, const void* h
     a.row_part = (float*)p;   // always written, as for the SwiGLU expert
     hipStream_t s = (hipStream_t)stream;
     if (!mlp2_dma_supported(a)) return mlp2_bwd_tile(a, s);
-    if (!direct_bwd(B, E, d, f)) return mlp2_bwd_dma(a, s);
+    if (!direct_bwd(B, E, d, f, 2)) return mlp2_bwd_dma(a, s);
     st = mlp2_bwd_rows_direct(a, s);
-    return st != XMOE_OK ? st : mlp2_bwd_wgrads_dma(a, s);
+    if (st != XMOE_OK) return st;
+    return direct_wgrads(B, E, d, f, 2) ? mlp2_bwd_wgrads_direct(a, s) : mlp2_bwd_wgrads_dma(a, s);
 }
 
 }  // extern "C"

@@ -1,12 +1,12 @@
-// Row products of the expert MLP on 128 x 128 bf16 tiles with direct-to-LDS loads (xmoe_tile_direct.h):
+// Products of the expert MLP on 128 x 128 bf16 tiles with direct-to-LDS loads (xmoe_tile_direct.h):
 //   - widths that are multiples of 8 but not of 64, in place of the register-staged tiles (the launch profiler counts them
 //     under those tiles' names);
 //   - widths that are multiples of 64 where the 256 x 256 tiles of the direct-to-LDS kernels are too few for the chip, or
-//     half empty (direct_fwd, direct_bwd below).
+//     half empty (direct_fwd, direct_bwd, direct_wgrads below).
 //
 // Measured (MI355X): T 3001 d 1000 f 712, 24 experts + 1 shared, register-staged | these: gate/up 96 | 72 us, dAct 82 | 58,
 // down 51 | 47, dX 78 | 75; 509 tokens, 64 experts + 2 shared, d 2048 f 1408, 256-row tiles | these: gate/up 180 | 172,
-// down 120 | 86; 8 experts of 200 rows, d 2048 f 1408: forward 119 | 57, backward 215 | 166.
+// down 120 | 86; 8 experts of 200 rows, d 2048 f 1408: forward 119 | 57; weight gradients of the first of these 166 | 103.
 //
 // Bound: a 128 x 128 tile takes in 64 bytes per clock and CU at the full rate of the matrix cores, about what a CU's load
 // path delivers at best; they reach 15 to 30 % of it where K is long, a third less than the 256 x 256 tiles, which is why
@@ -225,6 +225,48 @@ XMOE_DIRECT_KERNEL ffn_dx_direct_kernel(const bf16_t* __restrict__ dG, const bf1
     dir_store(acc, smem, dXd + (size_t)t.row0 * d + n0, d, t.rows, d - n0);
 }
 
+// Weight gradients dW_e[m, n] = sum over the expert's rows r of P[r, m] * Q[r, n], all of a call's in one launch, the
+// experts with the most rows first; a matrix's tiles are cut into at most eight runs, dealt to the XCDs in turn.
+struct DirectWgrad {
+    const bf16_t *P, *Q;
+    const int32_t *p_index, *q_index;   // or NULL; at most one
+    int M, N, tiles_m;
+    bf16_t* dW;
+};
+struct DirectWgrads {
+    DirectWgrad job[3];
+    int n_jobs, tiles, run, runs;   // tiles of a matrix, tiles of a run, runs of a matrix
+};
+template <bool GP, bool GQ>
+__device__ __forceinline__ void wgrad_direct_tile(const DirectWgrad& j, int u, int e, int lo, int K, char* smem) {
+    const int m0 = (u % j.tiles_m) * 128, n0 = (u / j.tiles_m) * 128;
+    tile_f32x16_t acc[2][2];
+    tile_zero<true>(acc);
+    if (K > 0) {
+        DirColsK<GP> a;
+        DirColsK<GQ> b;
+        a.init(j.P + m0 + (GP ? 0 : (size_t)lo * j.M), j.M, j.M - m0, GP ? j.p_index + lo : nullptr, K);
+        b.init(j.Q + n0 + (GQ ? 0 : (size_t)lo * j.N), j.N, j.N - n0, GQ ? j.q_index + lo : nullptr, K);
+        dir_mainloop_cc<GP, GQ>(acc, a, b, K, j.M - m0, j.N - n0, smem);
+    }
+    dir_store(acc, smem, j.dW + (size_t)e * j.M * j.N + (size_t)m0 * j.N + n0, j.N, j.M - m0, j.N - n0);
+}
+XMOE_DIRECT_KERNEL ffn_wgrad_direct_kernel(DirectWgrads jobs, int E, const int32_t* __restrict__ off,
+                                           const int32_t* __restrict__ sched) {
+    __shared__ __align__(16) char smem[kDirLds];
+    const int s = blockIdx.x >> 3, r = (s / jobs.run) * 8 + (blockIdx.x & 7);   // run r of all
+    const int m = r / jobs.runs, u = (r - m * jobs.runs) * jobs.run + s % jobs.run;
+    if (m >= jobs.n_jobs * E || u >= jobs.tiles) return;
+    const DirectWgrad j = jobs.job[m % jobs.n_jobs];
+    const int e = sched[m / jobs.n_jobs], lo = off[e], K = off[e + 1] - lo;
+    if (j.p_index)
+        wgrad_direct_tile<true, false>(j, u, e, lo, K, smem);
+    else if (j.q_index)
+        wgrad_direct_tile<false, true>(j, u, e, lo, K, smem);
+    else
+        wgrad_direct_tile<false, false>(j, u, e, lo, K, smem);
+}
+
 template <class Args>
 inline int tile_map_direct(const Args& a, hipStream_t s) {
     return launch_tile_map(a.off, a.E, 128, ffn_max_tiles(a.B, a.E, 128), a.map, a.sched, s);
@@ -264,25 +306,37 @@ bool direct_fwd(int B, int E, int d, int f) {
     if (row_tiles * ((f + 127) / 128 + (d + 255) / 256) <= 640) return true;
     return (B <= 96ll * E && weights <= 160000000) || (B <= 72ll * E && weights <= 200000000 && (long long)d * f <= 1 << 22);
 }
-// The backward's dAct and dX (the weight gradients stay a launch of the 256-row kernels, which without dX of their own is
-// longer at its end).  Whole backward, us, 256-row | these:
-//   few tiles: rows per expert       40           200          400          800          1600
-//     4 experts, 2048 x 1408        167 | 141    198 | 146    212 | 162    250 | 208    340 | 347    (24, 24, 48, 96, 168 of dAct)
-//     8 experts, 2048 x 1408        172 | 146    215 | 166    205 | 214    327 | 320    535 | 579    (48, 48, 96, 192, 336)
-//     8 experts, 4096 x 1024        233 | 162    293 | 201    368 | 273    401 | 435                 (32, 32, 64, 128)
-//     8 experts, 1024 x 704         139 | 112    155 | 120    163 | 130    175 | 144    237 | 232    (24, 24, 48, 96, 168)
-//    16 experts, 1024 x 704         146 | 126    164 | 130    134 | 147    219 | 209    335 | 344    (48, 48, 96, 192, 336)
-//   half-empty tiles: rows            4           32           64           96
-//    16 experts, 2048 x 1408        228 | 186    219 | 186    225 | 190    192 | 202
-//    64 experts, 1024 x 704         197 | 166    202 | 165    224 | 187    204 | 194
-//    64 experts, 2048 x 1408        504 | 471    530 | 505    562 | 541    601 | 589   (96 of routed and 2 x 1021 rows: 679 | 757)
-//    32 experts, 4096 x 1024        372 | 364    379 | 370    406 | 399    430 | 428   (1 row: 320 | 330)
-//    32 experts, 7168 x 2048       1070 | 1002  1124 | 1042  1203 | 1136  1297 | 1246
-//   256 experts, 2048 x 512         695 | 680    776 | 770    852 | 845    907 | 902
-bool direct_bwd(int B, int E, int d, int f) {
+// The backward.  Its weight gradients take the 128 x 128 tiles where the 256-row kernels have few tiles of them and the
+// experts are not long; dAct and dX do with them, and where a launch of theirs has few or half-empty tiles of 256 rows (the
+// weight gradients are then a launch of the 256-row kernels without dX).  Whole backward, us, all 256-row | dAct and dX
+// 128-row | all 128-row (- : not measured):
+//     rows per expert                        40                100               400                  1600
+//     4 experts, 512 x 256 (24 tiles)     79 | 55 | 34      82 | 60 | 35     104 | 72 | 39      161 | 132 | 56
+//     4 experts, 2048 x 1408 (544)       167 | 141 | 93    175 | 149 | 98    212 | 162 | 123    340 | 347 | 314
+//     8 experts, 1024 x 704 (288)        139 | 112 | 59    136 | 111 | 62    163 | 130 | 79     237 | 232 | 184
+//     8 experts, 2048 x 1408 (1088)      172 | 146 | 115   175 | 151 | 120   205 | 214 | 196    535 | 579 | 578
+//     8 experts, 4096 x 1024 (1536)      233 | 162 | 141   246 | 169 | 147   368 | 273 | 267    746 | 767 | 813
+//    16 experts, 1024 x 704 (576)        146 | 126 | 72    139 | 118 | 75    134 | 147 | 120    335 | 344 | 339
+//    16 experts, 2048 x 1408 (2176)      234 | 206 | 183   196 | 210 | 193   380 | 375 | 388   1000 | 1086 | 1183
+//    64 experts, 1024 x 704 (2304)       215 | 169 | 173   204 | 194 | 195   369 | - | 432
+//    64 experts, 2048 x 1408 (8704)      542 | 520 | 676   601 | 589 | 738  1171 | - | 1540
+//   256 experts, 1024 x 256 (3072)       253 | 238 | 264   280 | 270 | 312
+//    32 experts, 7168 x 2048 (14336)    1166 | 1090 | -   1297 | 1246 | -
+//   256 experts, 2048 x 512             810 | 812 | -      907 | 902 | -
+// dAct and dX by rows per expert: 64 experts, 2048 x 1408: 4 rows 504 | 471, 64 rows 562 | 541, 96 of routed and 2 x 1021
+// rows 679 | 757; 16 experts, 2048 x 1408: 64 rows 225 | 190, 96 rows 192 | 202.
+long long wgrad_tiles_256(int E, int d, int f, int matrices) {
+    const long long td = (d + 255) / 256;
+    return E * td * ((f + 255) / 256 + (matrices == 3 ? (f + 127) / 128 : (f + 255) / 256));
+}
+bool direct_wgrads(int B, int E, int d, int f, int matrices) {
+    const long long n = wgrad_tiles_256(E, d, f, matrices);
+    return n <= 2200 && n * B <= 600000ll * E;
+}
+bool direct_bwd(int B, int E, int d, int f, int matrices) {
     if (d < 256 || f < 256) return false;
     const long long row_tiles = E * ((B + 256ll * E - 1) / (256ll * E));
-    return B <= 80ll * E || row_tiles * ((f + 255) / 256) <= 64;
+    return B <= 80ll * E || row_tiles * ((f + 255) / 256) <= 64 || direct_wgrads(B, E, d, f, matrices);
 }
 
 bool direct_supported(const FfnArgs& a) {
@@ -338,6 +392,31 @@ static int bwd_rows_direct(const FfnArgs& a, hipStream_t s) {
 }
 int ffn_bwd_rows_direct(const FfnArgs& a, hipStream_t s) {
     return fast_act(a.d, a.f) ? bwd_rows_direct<true>(a, s) : bwd_rows_direct<false>(a, s);
+}
+
+static int launch_wgrads(DirectWgrads w, int n_jobs, int kid, int E, int d, int f, const int32_t* off, const int32_t* sched,
+                         hipStream_t s) {
+    for (int i = 0; i < n_jobs; ++i) w.job[i].tiles_m = (w.job[i].M + 127) / 128;
+    w.n_jobs = n_jobs;
+    w.tiles = ((d + 127) / 128) * ((f + 127) / 128);
+    w.run = (w.tiles + 7) / 8;
+    w.runs = (w.tiles + w.run - 1) / w.run;
+    const dim3 grid((unsigned)(((long long)n_jobs * E * w.runs + 7) / 8 * 8 * w.run));
+    XMOE_LAUNCH(kid, s, hipLaunchKernelGGL(ffn_wgrad_direct_kernel, grid, dim3(256), 0, s, w, E, off, sched));
+    return XMOE_OK;
+}
+int ffn_bwd_wgrads_direct(const FfnArgs& a, hipStream_t s) {
+    DirectWgrads w = {};
+    w.job[0] = {(const bf16_t*)a.act, (const bf16_t*)a.dy, nullptr, a.dy_index, a.f, a.d, 0, (bf16_t*)a.dwd};
+    w.job[1] = {(const bf16_t*)a.xd, (const bf16_t*)a.dg, a.row_index, nullptr, a.d, a.f, 0, (bf16_t*)a.dwg};
+    w.job[2] = {(const bf16_t*)a.xd, (const bf16_t*)a.du, a.row_index, nullptr, a.d, a.f, 0, (bf16_t*)a.dwu};
+    return launch_wgrads(w, 3, fast_act(a.d, a.f) ? K_FFN_WGRAD_DIRECT : K_FFN_WGRAD_MFMA, a.E, a.d, a.f, a.off, a.sched, s);
+}
+int mlp2_bwd_wgrads_direct(const Mlp2Args& a, hipStream_t s) {
+    DirectWgrads w = {};
+    w.job[0] = {(const bf16_t*)a.a_buf, (const bf16_t*)a.dy, nullptr, a.dy_index, a.f, a.d, 0, (bf16_t*)a.dw2};
+    w.job[1] = {(const bf16_t*)a.xd, (const bf16_t*)a.dh, a.row_index, nullptr, a.d, a.f, 0, (bf16_t*)a.dw1};
+    return launch_wgrads(w, 2, fast_act(a.d, a.f) ? K_FFN_WGRAD_DIRECT : K_FFN_WGRAD_MFMA, a.E, a.d, a.f, a.off, a.sched, s);
 }
 
 template <bool FAST>

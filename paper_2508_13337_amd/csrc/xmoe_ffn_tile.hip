@@ -542,15 +542,24 @@ static int mlp2_bwd_rows_tile(const Mlp2Args& a, hipStream_t s) {
 // rows 96 | 78; E 4 d 1496 f 208, 1500 rows 61 | 40), the backward's where the staged tiles would be the big ones (E 8 d
 // 1000 f 1000, backward, 96 rows 90 | 96; big ones: T 3001 d 1000 f 712 E 24+1, staged | direct: dAct 82 | 58, dX 78 | 75).
 //
-// Their weight gradients take the 256-row kernels (whose operands are K-strided, so that widths only have to be whole
-// 16-byte pieces) where those have two tiles per CU and the experts rows enough for their main loop, or many tiles.  Whole
-// backward with the staged weight gradients | those, us: E 24 d 1000 f 712 (900 tiles) 40 rows 127 | 144, 96 rows 139 | 134,
-// 375 rows 244 | 195; E 16 d 2040 f 1480 (2304) 4 rows 245 | 261, 16 rows 284 | 271, 375 rows 600 | 442; E 256 d 328 f 200
-// (1536) 4 rows 125 | 143, 16 rows 153 | 149, 96 rows 187 | 157; E 8 d 1000 f 1000 (384) 375 rows 118 | 137, 1500 rows
-// 282 | 259; E 128 d 176 f 320 (640) 96 rows 105 | 106, 375 rows 180 | 173.
-static inline bool dma_wgrads(int B, int E, int d, int f, bool dual) {
-    const long long n = (long long)E * (ceil_div(f, 256) * ceil_div(d, 256) + ceil_div(d, 256) * ceil_div(f, dual ? 128 : 256));
-    return (B >= 96ll * E && n >= 512) || (B >= 16ll * E && n >= 1536);
+// Their weight gradients take the direct-to-LDS 128 x 128 tiles; the staged ones where the experts have hardly any rows (a
+// 64 x 64 tile of nothing but its stores), the 256-row kernels (K-strided operands only have to be whole 16-byte pieces)
+// where there are rows and tiles enough for them.  Whole backward, us, staged | direct | 256-row:
+//   rows per expert             1             16                  96                  375                  1500
+//   E 24 d 1000 f 712 (900)   83 | 100 | 129  118 | 104 | 142   139 | 113 | 134   244 | 189 | 195    697 | 585 | 552
+//   E 16 d 2040 f 1480 (2304) 208 | 204 | 232 284 | 235 | 271   341 | 256 | 276   601 | 451 | 442   1642 | 1432 | 1277
+//   E 256 d 328 f 200 (1536)  91 | 103 | 133  153 | 124 | 149   187 | 145 | 157   392 |     | 311
+//   E 8 d 1000 f 1000 (384)   64 | 69 | 114    80 | 76 | 125     91 | 82 | 112    118 | 104 | 137    282 | 241 | 259
+//   E 4 d 1496 f 208 (72)     40 | 40 | 59     52 | 43 | 62      59 | 46 | 68      72 | 57 | 85      131 | 102 | 164
+// A long expert among short ones (E 24 of 375 rows and one of 3001, d 1000 f 712) keeps the 256-row kernels' launch waiting
+// for its few tiles: weight gradients alone 166 | 103 | 200.
+template <class Args>
+static int wgrads_any_width(const Args& a, int matrices, int (*direct)(const Args&, hipStream_t),
+                            int (*dma)(const Args&, hipStream_t), hipStream_t s) {
+    if (a.dt == XMOE_F32) return wgrad_call<float>(a, s);
+    if (!direct_supported(a) || a.B < 12ll * a.E) return wgrad_call<bf16_t>(a, s);
+    if (a.B >= 1000ll * a.E && wgrad_tiles_256(a.E, a.d, a.f, matrices) >= 512) return dma(a, s);
+    return direct(a, s);
 }
 
 #define XMOE_TILE_CALL(CALL)                                                              \
@@ -568,18 +577,14 @@ int mlp2_fwd_tile(const Mlp2Args& a, hipStream_t s) {
     return XMOE_TILE_CALL(mlp2_fwd_tile);
 }
 int ffn_bwd_tile(const FfnArgs& a, hipStream_t s) {
-    const bool big = big_tiles(a.B, a.E, a.d, a.f, a.dt), direct = direct_supported(a);
-    const int st = big && direct ? ffn_bwd_rows_direct(a, s) : XMOE_TILE_CALL(bwd_rows_tile);
-    if (st != XMOE_OK) return st;
-    if (direct && dma_wgrads(a.B, a.E, a.d, a.f, true)) return ffn_bwd_wgrads_dma(a, s);
-    return a.dt == XMOE_F32 ? wgrad_call<float>(a, s) : wgrad_call<bf16_t>(a, s);
+    const bool big = big_tiles(a.B, a.E, a.d, a.f, a.dt);
+    const int st = big && direct_supported(a) ? ffn_bwd_rows_direct(a, s) : XMOE_TILE_CALL(bwd_rows_tile);
+    return st != XMOE_OK ? st : wgrads_any_width(a, 3, ffn_bwd_wgrads_direct, ffn_bwd_wgrads_dma, s);
 }
 int mlp2_bwd_tile(const Mlp2Args& a, hipStream_t s) {
-    const bool big = big_tiles(a.B, a.E, a.d, a.f, a.dt), direct = direct_supported(a);
-    const int st = big && direct ? mlp2_bwd_rows_direct(a, s) : XMOE_TILE_CALL(mlp2_bwd_rows_tile);
-    if (st != XMOE_OK) return st;
-    if (direct && dma_wgrads(a.B, a.E, a.d, a.f, false)) return mlp2_bwd_wgrads_dma(a, s);
-    return a.dt == XMOE_F32 ? wgrad_call<float>(a, s) : wgrad_call<bf16_t>(a, s);
+    const bool big = big_tiles(a.B, a.E, a.d, a.f, a.dt);
+    const int st = big && direct_supported(a) ? mlp2_bwd_rows_direct(a, s) : XMOE_TILE_CALL(mlp2_bwd_rows_tile);
+    return st != XMOE_OK ? st : wgrads_any_width(a, 2, mlp2_bwd_wgrads_direct, mlp2_bwd_wgrads_dma, s);
 }
 
 }  // namespace xmoe

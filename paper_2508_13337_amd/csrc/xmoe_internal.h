@@ -62,6 +62,7 @@ enum KernelId : int {
     K_FFN_DX_DIRECT,
     K_MLP2_UP_DIRECT,
     K_MLP2_DACT_DIRECT,
+    K_FFN_WGRAD_DIRECT,
     K_COUNT
 };
 

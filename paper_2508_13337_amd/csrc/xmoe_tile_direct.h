@@ -15,6 +15,8 @@
 // row (tile_row and tile_col do not apply).  K is added in the same ascending steps of 16 as everywhere else.
 #pragma once
 
+#include <type_traits>
+
 #include "xmoe_ffn.h"
 #include "xmoe_tile_gemm.h"
 
@@ -303,6 +305,138 @@ __device__ __forceinline__ void dir_mainloop_rc(tile_f32x16_t (&acc)[2][2], DirR
             sb ^= 2;
         }
     }
+    dir_wait_and_barrier<0>();
+}
+
+// ---- both operands K-strided (weight gradients): five stages of a tile of either, four of them on their way.
+// GATHER: k-row k is row index[k] of the matrix.  The index of a piece is an ordinary load, issued with the stage four
+// before the piece's own: the wait for that stage covers it, so that it never makes the ring wait.  The waits count the
+// direct-to-LDS loads of three stages and not the index loads among them: right whatever the compiler makes of those.
+constexpr int kDirStage = 2 * kDirTile;
+template <bool GATHER>
+struct DirColsK {
+    const bf16_t* p[2];            // GATHER: the piece's column in row 0, else of the tile issued next
+    int limit[2];
+    size_t step;                   // GATHER: the leading dimension
+    const int32_t* index;
+    int last;                      // K - 1
+    int row[GATHER ? 4 : 1][2];    // source rows of the pieces of tile t: row[t & 3]
+    __device__ __forceinline__ static int k_row(int i) {
+        return (int)(threadIdx.x >> 6) * 8 + i * 4 + (int)((threadIdx.x & 63) >> 4);
+    }
+    __device__ __forceinline__ void init(const bf16_t* p0, size_t ld, int cols, const int32_t* index_, int K) {
+        index = index_;
+        last = K - 1;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int kr = k_row(i);
+            int n = 8 * ((int)(threadIdx.x & 15) ^ ((kr & 3) << 2));
+            if (n >= cols) n = 0;
+            p[i] = p0 + (GATHER ? 0 : (size_t)kr * ld) + n;
+            limit[i] = (K - kr + 31) / 32;
+        }
+        step = GATHER ? ld : 32 * ld;
+    }
+    template <int S>
+    __device__ __forceinline__ void fetch(int t) {   // the rows of tile t, t & 3 == S
+        if (!GATHER) return;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int k = 32 * t + k_row(i);
+            row[GATHER ? S : 0][i] = index[k < last ? k : last];
+        }
+    }
+    template <int S>
+    __device__ __forceinline__ void issue(char* __restrict__ tile, int t) {
+        const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const bf16_t* a = GATHER ? p[i] + (size_t)row[GATHER ? S : 0][i] * step : p[i];
+            a = t < limit[i] ? a : reinterpret_cast<const bf16_t*>(kDirZero);
+            __builtin_amdgcn_global_load_lds(XMOE_GLB_PTR(a), XMOE_LDS_PTR(tile + wave * 2048 + i * 1024), 16, 0, 0);
+            if (!GATHER) p[i] += step;
+        }
+    }
+};
+template <bool GA, bool GB, int MI, int S>
+__device__ __forceinline__ void dir_step_cc(tile_f32x16_t (&acc)[2][2], DirFrags<MI ? MI : 1>& f0, DirFrags<MI ? MI : 1>& f1,
+                                            DirColsK<GA>& a, DirColsK<GB>& b, int i, char* __restrict__ next,
+                                            const char* __restrict__ cur) {
+    constexpr int M = MI ? MI : 1;
+    a.template issue<S>(next, i + 4);
+    b.template issue<S>(next + kDirTile, i + 4);
+    a.template fetch<S>(i + 8);
+    b.template fetch<S>(i + 8);
+    if (MI > 0) {
+        const int wm = threadIdx.x >> 7;
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+            DirFrags<M>& f = ks ? f1 : f0;
+#pragma unroll
+            for (int ni = 0; ni < 2; ++ni) f.b[ni] = dir_frag_col(cur + kDirTile, dir_col<false>(ni), ks);
+#pragma unroll
+            for (int mi = 0; mi < M; ++mi) f.a[mi] = dir_frag_col(cur, wm * 64 + mi * 32, ks);
+            dir_mma<M>(acc, ks ? f0 : f1);
+        }
+    }
+    dir_wait_and_barrier<12>();
+}
+template <bool GA, bool GB, int MI>
+__device__ __forceinline__ void dir_loop_cc(tile_f32x16_t (&acc)[2][2], DirColsK<GA>& a, DirColsK<GB>& b, int n, char* smem) {
+    DirFrags<MI ? MI : 1> f0, f1;
+    dir_clear(f1);
+    // whole rounds of four: an exit from between the steps would cost a copy of every accumulator (stages past the end of K
+    // hold zeros)
+    char *cur = smem, *next = smem + 4 * kDirStage, *const end = smem + 5 * kDirStage;
+    auto step = [&](auto S, int i) {
+        dir_step_cc<GA, GB, MI, S.value>(acc, f0, f1, a, b, i, next, cur);
+        next = cur;
+        cur = cur + kDirStage < end ? cur + kDirStage : smem;
+    };
+    for (int i = 0; i < n; i += 4) {
+        step(std::integral_constant<int, 0>{}, i);
+        step(std::integral_constant<int, 1>{}, i + 1);
+        step(std::integral_constant<int, 2>{}, i + 2);
+        step(std::integral_constant<int, 3>{}, i + 3);
+    }
+    if (MI > 0) dir_mma<MI ? MI : 1>(acc, f1);
+}
+// acc += A B over K >= 1; rows, cols: valid ones of the tile.  At most one of the operands is gathered.
+template <bool GA, bool GB>
+__device__ __forceinline__ void dir_mainloop_cc(tile_f32x16_t (&acc)[2][2], DirColsK<GA>& a, DirColsK<GB>& b, int K, int rows,
+                                                int cols, char* smem) {
+    static_assert(!(GA && GB), "the wait counts");
+    const int n = (K + 31) / 32;
+    auto fetch = [&](auto S, int t) {
+        a.template fetch<S.value>(t);
+        b.template fetch<S.value>(t);
+    };
+    auto first = [&](auto S) {
+        a.template issue<S.value>(smem + S.value * kDirStage, S.value);
+        b.template issue<S.value>(smem + S.value * kDirStage + kDirTile, S.value);
+        fetch(S, S.value + 4);
+    };
+    constexpr std::integral_constant<int, 0> S0{};
+    constexpr std::integral_constant<int, 1> S1{};
+    constexpr std::integral_constant<int, 2> S2{};
+    constexpr std::integral_constant<int, 3> S3{};
+    fetch(S0, 0);
+    fetch(S1, 1);
+    fetch(S2, 2);
+    fetch(S3, 3);
+    first(S0);
+    first(S1);
+    first(S2);
+    first(S3);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int mi_n = cols > (wave & 1) * 64 ? (rows - (wave >> 1) * 64 + 31) / 32 : 0;
+    dir_wait_and_barrier<12>();
+    if (mi_n >= 2)
+        dir_loop_cc<GA, GB, 2>(acc, a, b, n, smem);
+    else if (mi_n == 1)
+        dir_loop_cc<GA, GB, 1>(acc, a, b, n, smem);
+    else
+        dir_loop_cc<GA, GB, 0>(acc, a, b, n, smem);
     dir_wait_and_barrier<0>();
 }
 

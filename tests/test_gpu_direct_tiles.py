@@ -115,7 +115,7 @@ def test_multiples_of_64(d, f, expert, gathered, scaled):
     up = "ffn_gateup" if expert == "swiglu" else "mlp2_up"
     da = "ffn_dact" if expert == "swiglu" else "mlp2_dact"
     assert k1 == {"tile_map_kernel", up + "_direct_kernel", "ffn_down_direct_kernel"}, k1
-    assert {da + "_direct_kernel", "ffn_dx_direct_kernel"} <= k2 and any("ffn_bwd_rest" in k or "wgrad" in k for k in k2), k2
+    assert {da + "_direct_kernel", "ffn_dx_direct_kernel", "ffn_wgrad_direct_kernel"} <= k2, k2
     check(ROWS, d, f, expert, o, gathered, scaled)
 
 
@@ -129,14 +129,16 @@ def test_multiples_of_8(rows, d, f, expert):
     check(rows, d, f, expert, o)
 
 
-def test_weight_gradients_of_the_256_row_kernels():
-    """Widths that are no multiple of 64, with enough tiles of 256 for them."""
+@pytest.mark.parametrize("expert", ["swiglu", "identity"])
+@pytest.mark.parametrize("rows", [[1200, 0, 1001, 63] * 12 + [3000] * 16, [1700, 1, 0, 2300]], ids=["256-row", "direct"])
+def test_long_segments(rows, expert):
+    """Weight gradients of widths that are no multiple of 64: long segments, with enough tiles for the 256-row kernels
+    and with too few."""
     import paper_2508_13337_amd as m
-    rows = [97, 0, 300, 64] + [100] * 82
-    for d, f, expert in ((264, 392, "swiglu"), (520, 776, "gelu")):
-        o, _, k2 = run(m, rows, d, f, expert)
-        assert any("ffn_bwd_rest" in k or "wgrad_dma" in k for k in k2), k2
-        check(rows, d, f, expert, o)
+    d, f = (264, 392) if expert == "swiglu" else (520, 392)
+    o, _, k2 = run(m, rows, d, f, expert)
+    assert any("ffn_bwd_rest" in k or "wgrad_dma" in k for k in k2) == (len(rows) > 4), k2
+    check(rows, d, f, expert, o)
 
 
 def test_bits_of_the_256_row_kernels():
@@ -166,12 +168,14 @@ def test_bits_of_the_256_row_kernels():
             assert torch.equal(p[outs[0][0][e]:][:n], q[outs[1][0][e]:][:n]), e
 
 
-@pytest.mark.parametrize("E,d,f,rows,fwd,bwd", [(4, 256, 256, 129, True, True), (4, 192, 256, 129, False, False),
-                                                (4, 256, 192, 129, False, False), (64, 256, 256, 64 * 800, False, False),
-                                                (64, 256, 256, 64 * 90, True, True), (64, 256, 512, 64 * 90, True, False)])
-def test_both_sides_of_the_rules(E, d, f, rows, fwd, bwd):
+@pytest.mark.parametrize("E,d,f,rows,fwd,bwd,wgrads", [
+    (4, 256, 256, 129, True, True, True), (4, 192, 256, 129, False, False, False), (4, 256, 192, 129, False, False, False),
+    (64, 256, 256, 64 * 800, False, True, True), (64, 256, 256, 64 * 3200, False, False, False),
+    (8, 2048, 2048, 8 * 60, True, True, True), (10, 2048, 2560, 600, True, True, False)])
+def test_both_sides_of_the_rules(E, d, f, rows, fwd, bwd, wgrads):
     import paper_2508_13337_amd as m
     count = [rows // E + (e < rows % E) for e in range(E)]
     _, k1, k2 = run(m, count, d, f, "swiglu")
     assert ("ffn_gateup_direct_kernel" in k1) == fwd and ("ffn_gateup_dma_kernel" in k1) != fwd, k1
     assert ("ffn_dact_direct_kernel" in k2) == bwd and ("ffn_rowgemm_dma_kernel<true>" in k2) != bwd, k2
+    assert ("ffn_wgrad_direct_kernel" in k2) == wgrads, k2
