@@ -93,7 +93,8 @@ __device__ __forceinline__ void act_fast_grad(float h, float& a, float& g) {
     }
 }
 
-int launch_tile_map(const int32_t* off, int E, int tile_rows, int max_tiles, int32_t* map, int32_t* sched,
+// rank: the experts' order too (the backward's weight gradients)
+int launch_tile_map(const int32_t* off, int E, int tile_rows, int max_tiles, int32_t* map, int32_t* sched, bool rank,
                     hipStream_t s);
 
 // row_grad[i] = sum over p < parts of row_part[p * B + i], p ascending (fixed order: the result is reproducible)

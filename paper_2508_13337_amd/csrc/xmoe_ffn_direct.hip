@@ -268,8 +268,8 @@ XMOE_DIRECT_KERNEL ffn_wgrad_direct_kernel(DirectWgrads jobs, int E, const int32
 }
 
 template <class Args>
-inline int tile_map_direct(const Args& a, hipStream_t s) {
-    return launch_tile_map(a.off, a.E, 128, ffn_max_tiles(a.B, a.E, 128), a.map, a.sched, s);
+inline int tile_map_direct(const Args& a, bool rank, hipStream_t s) {
+    return launch_tile_map(a.off, a.E, 128, ffn_max_tiles(a.B, a.E, 128), a.map, a.sched, rank, s);
 }
 template <class Args>
 inline dim3 grid_direct(const Args& a, int n, int cols) {
@@ -356,7 +356,7 @@ bool direct_supported(const Mlp2Args& a) {
 
 template <bool FAST>
 static int fwd_direct(const FfnArgs& a, hipStream_t s) {
-    int st = tile_map_direct(a, s);
+    int st = tile_map_direct(a, false, s);
     if (st != XMOE_OK) return st;
     XMOE_LAUNCH(FAST ? K_FFN_GATEUP_DIRECT : K_FFN_GATEUP_MFMA, s,
                 hipLaunchKernelGGL((ffn_gateup_direct_kernel<FAST>), grid_direct(a, a.f, 64), dim3(256), 0, s,
@@ -373,7 +373,7 @@ int ffn_fwd_direct(const FfnArgs& a, hipStream_t s) {
 
 template <bool FAST>
 static int bwd_rows_direct(const FfnArgs& a, hipStream_t s) {
-    int st = tile_map_direct(a, s);
+    int st = tile_map_direct(a, true, s);
     if (st != XMOE_OK) return st;
     XMOE_LAUNCH(FAST ? K_FFN_DACT_DIRECT : K_FFN_DACT_MFMA, s,
                 hipLaunchKernelGGL((ffn_dact_direct_kernel<FAST>), grid_direct(a, a.f, 128), dim3(256), 0, s,
@@ -421,7 +421,7 @@ int mlp2_bwd_wgrads_direct(const Mlp2Args& a, hipStream_t s) {
 
 template <bool FAST>
 static int mlp2_fwd_direct_as(const Mlp2Args& a, hipStream_t s) {
-    int st = tile_map_direct(a, s);
+    int st = tile_map_direct(a, false, s);
     if (st != XMOE_OK) return st;
 #define XMOE_CALL(ACT)                                                                                                    \
     XMOE_LAUNCH(FAST ? K_MLP2_UP_DIRECT : K_MLP2_UP_MFMA, s,                                                              \
@@ -441,7 +441,7 @@ int mlp2_fwd_direct(const Mlp2Args& a, hipStream_t s) {
 
 template <bool FAST>
 static int mlp2_bwd_rows_direct_as(const Mlp2Args& a, hipStream_t s) {
-    int st = tile_map_direct(a, s);
+    int st = tile_map_direct(a, true, s);
     if (st != XMOE_OK) return st;
 #define XMOE_CALL(ACT)                                                                                                    \
     XMOE_LAUNCH(FAST ? K_MLP2_DACT_DIRECT : K_MLP2_DACT_MFMA, s,                                                          \

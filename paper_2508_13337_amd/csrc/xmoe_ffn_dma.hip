@@ -1959,7 +1959,7 @@ int ffn_fwd_dma(const FfnArgs& a, hipStream_t s) {
     int st = init_device();
     if (st != XMOE_OK) return st;
     const int max_tiles = ffn_max_tiles(a.B, a.E, TM);
-    st = launch_tile_map(a.off, a.E, TM, max_tiles, a.map, a.sched, s);
+    st = launch_tile_map(a.off, a.E, TM, max_tiles, a.map, a.sched, false, s);
     if (st != XMOE_OK) return st;
     const bf16_t *xd = (const bf16_t*)a.xd, *wg = (const bf16_t*)a.wg, *wu = (const bf16_t*)a.wu,
                  *wd = (const bf16_t*)a.wd;
@@ -2043,7 +2043,7 @@ int ffn_bwd_dma(const FfnArgs& a, hipStream_t s) {
     int st = init_device();
     if (st != XMOE_OK) return st;
     const int max_tiles = ffn_max_tiles(a.B, a.E, TM);
-    st = launch_tile_map(a.off, a.E, TM, max_tiles, a.map, a.sched, s);
+    st = launch_tile_map(a.off, a.E, TM, max_tiles, a.map, a.sched, true, s);
     if (st != XMOE_OK) return st;
     const bf16_t *wd = (const bf16_t*)a.wd, *dy = (const bf16_t*)a.dy;
     bf16_t *dg = (bf16_t*)a.dg, *du = (bf16_t*)a.du, *act = (bf16_t*)a.act;
@@ -2087,7 +2087,7 @@ int mlp2_fwd_dma(const Mlp2Args& a, hipStream_t s) {
     int st = init_device();
     if (st != XMOE_OK) return st;
     const int max_tiles = ffn_max_tiles(a.B, a.E, TM);
-    st = launch_tile_map(a.off, a.E, TM, max_tiles, a.map, a.sched, s);
+    st = launch_tile_map(a.off, a.E, TM, max_tiles, a.map, a.sched, false, s);
     if (st != XMOE_OK) return st;
     const bf16_t *xd = (const bf16_t*)a.xd, *w1 = (const bf16_t*)a.w1, *w2 = (const bf16_t*)a.w2;
     const int ntf = (a.f + TN - 1) / TN, ntd = (a.d + TN - 1) / TN;
@@ -2180,7 +2180,7 @@ int mlp2_bwd_dma(const Mlp2Args& a, hipStream_t s) {
     int st = init_device();
     if (st != XMOE_OK) return st;
     const int max_tiles = ffn_max_tiles(a.B, a.E, TM);
-    st = launch_tile_map(a.off, a.E, TM, max_tiles, a.map, a.sched, s);
+    st = launch_tile_map(a.off, a.E, TM, max_tiles, a.map, a.sched, true, s);
     if (st != XMOE_OK) return st;
     const bf16_t *w2 = (const bf16_t*)a.w2, *dy = (const bf16_t*)a.dy;
     bf16_t *dh = (bf16_t*)a.dh, *act = (bf16_t*)a.a_buf;

@@ -243,7 +243,7 @@ bool few_rows(int B, int E) { return B <= 32ll * E; }
 
 int ffn_fwd_few(const FfnArgs& a, hipStream_t s) {
     const int max_tiles = ffn_max_tiles(a.B, a.E, kFewRows);
-    int st = launch_tile_map(a.off, a.E, kFewRows, max_tiles, a.map, a.sched, s);
+    int st = launch_tile_map(a.off, a.E, kFewRows, max_tiles, a.map, a.sched, false, s);
     if (st != XMOE_OK) return st;
     const FewOut o1 = {(bf16_t*)a.g, (bf16_t*)a.u, (bf16_t*)a.act}, o2 = {(bf16_t*)a.y, nullptr, nullptr};
     XMOE_LAUNCH(K_FFN_GATEUP_FEW, s,
@@ -258,7 +258,7 @@ int ffn_fwd_few(const FfnArgs& a, hipStream_t s) {
 
 int mlp2_fwd_few(const Mlp2Args& a, hipStream_t s) {
     const int max_tiles = ffn_max_tiles(a.B, a.E, kFewRows);
-    int st = launch_tile_map(a.off, a.E, kFewRows, max_tiles, a.map, a.sched, s);
+    int st = launch_tile_map(a.off, a.E, kFewRows, max_tiles, a.map, a.sched, false, s);
     if (st != XMOE_OK) return st;
     const FewOut o1 = {(bf16_t*)a.h, (bf16_t*)a.a_buf, nullptr}, o2 = {(bf16_t*)a.y, nullptr, nullptr};
 #define XMOE_CALL(ACT)                                                                                               \
