@@ -325,6 +325,12 @@ int xmoe_dispatch_bwd(const void* dxd, const int32_t* row_of_slot, const void* s
 int xmoe_route_bwd(const float* logits, const int32_t* topk_idx, const float* dw, int T, int E, int k,
                    float* dlogits, void* stream);
 
+/* xmoe_combine_bwd_weights and xmoe_route_bwd in one pass: dw[t,j] = row_grad[row_of_slot[t*k+j]] (0 for a dropped entry),
+ * and dlogits from it.  dw [T,k], dlogits [T,E] float32 (out).
+ */
+int xmoe_route_bwd_rows(const float* logits, const int32_t* topk_idx, const float* row_grad, const int32_t* row_of_slot,
+                        int T, int E, int k, float* dw, float* dlogits, void* stream);
+
 /* Backward of the gate projection:  dw_router = x^T dlogits  [d,E] dt;  dx_gate = dlogits w_router^T  [T,d] dt.
  * ws: XMOE_WS_GATE_BWD bytes.
  */

@@ -21,7 +21,7 @@ ACT_CODES = {"identity": 0, "gelu": 1, "silu": 2}   # xmoe_act
 __all__ = [
     "XMoEError", "xmoe_version", "xmoe_workspace_bytes", "xmoe_gate_logits", "xmoe_route", "xmoe_build_eri",
     "xmoe_dispatch", "xmoe_expert_ffn_fwd", "xmoe_expert_ffn_bwd", "xmoe_combine", "xmoe_combine_bwd",
-    "xmoe_dispatch_bwd", "xmoe_route_bwd", "xmoe_gate_logits_bwd", "xmoe_prof_enable", "xmoe_prof_reset",
+    "xmoe_dispatch_bwd", "xmoe_route_bwd", "xmoe_route_bwd_rows", "xmoe_gate_logits_bwd", "xmoe_prof_enable", "xmoe_prof_reset",
     "xmoe_prof_read", "xmoe_prof_copy", "xmoe_prof_shader_clocks", "dtype_code", "alloc_workspace",
     "XMOE_F32", "XMOE_BF16", "WS_BUILD_ERI", "WS_FFN_FWD", "WS_FFN_BWD", "WS_GATE_BWD", "WS_BUILD_ERI_CAPPED", "xmoe_build_eri_capped",
     "xmoe_expert_mlp2_fwd", "xmoe_expert_mlp2_bwd", "WS_MLP2_FWD", "WS_MLP2_BWD", "ACT_CODES",
@@ -347,6 +347,18 @@ def xmoe_route_bwd(logits, topk_idx, dw, dlogits) -> None:
     _check(lib().xmoe_route_bwd(_ptr(logits, torch.float32, "logits"), _ptr(topk_idx, torch.int32, "topk_idx"),
                                 _ptr(dw, torch.float32, "dw"), T, E, k, _ptr(dlogits, torch.float32, "dlogits"),
                                 _stream()), "xmoe_route_bwd")
+
+
+def xmoe_route_bwd_rows(logits, topk_idx, row_grad, row_of_slot, dw, dlogits) -> None:
+    """xmoe_combine_bwd_weights and xmoe_route_bwd in one pass."""
+    T, E = logits.shape
+    k = topk_idx.shape[1]
+    assert row_of_slot.numel() == T * k and tuple(dw.shape) == (T, k) and tuple(dlogits.shape) == (T, E)
+    _check(lib().xmoe_route_bwd_rows(_ptr(logits, torch.float32, "logits"), _ptr(topk_idx, torch.int32, "topk_idx"),
+                                     _ptr(row_grad, torch.float32, "row_grad"),
+                                     _ptr(row_of_slot, torch.int32, "row_of_slot"), T, E, k,
+                                     _ptr(dw, torch.float32, "dw"), _ptr(dlogits, torch.float32, "dlogits"),
+                                     _stream()), "xmoe_route_bwd_rows")
 
 
 def xmoe_gate_logits_bwd(x, w_router, dlogits, dw_router, dx_gate, ws) -> None:

@@ -25,7 +25,7 @@ class XMoELayer:
     [B,d] copy of the tokens exists.  The backward of combine is fused the same way (fuse_combine_bwd, the default):
     the MLP's backward reads dOut through token_ids and scales by combine_weights, so no [B,d] gradient of the expert
     outputs exists, and it also returns the gradient of every row's combine weight (dy_row_scale_grad), which
-    xmoe_combine_bwd_weights puts into slot order: the expert outputs Y are then read by the forward combine only
+    xmoe_route_bwd_rows takes from there: the expert outputs Y are then read by the forward combine only
     and nothing but G and U is held between forward and backward.  (Without fuse_combine_bwd, xmoe_combine_bwd
     reads Y back for the weights' gradient and writes dY, and xmoe_dispatch copies dOut into the shared experts'
     dY rows.)
@@ -127,7 +127,7 @@ class XMoELayer:
                                     self.dxd, grads["dwg"], grads["dwu"], grads["dwd"], self.ws,
                                     row_index=self.token_ids_all, dy_row_index=self.token_ids_all,
                                     dy_row_scale=self.combine_weights_all, dy_row_scale_grad=self.row_grad)
-            api.xmoe_combine_bwd_weights(self.row_grad, self.row_of_slot, self.dw)
+            api.xmoe_route_bwd_rows(self.logits, self.topk_idx, self.row_grad, self.row_of_slot, self.dw, self.dlogits)
         else:
             if self.E_s > 0:   # dY of a shared expert's rows is dout itself
                 if self.max_token_count is None:
@@ -138,7 +138,7 @@ class XMoELayer:
             api.xmoe_expert_ffn_bwd(x, self.g, self.u, self.dy, self.offsets_all, w["wg"], w["wu"], w["wd"],
                                     self.dxd, grads["dwg"], grads["dwu"], grads["dwd"], self.ws,
                                     row_index=self.token_ids_all)
-        api.xmoe_route_bwd(self.logits, self.topk_idx, self.dw, self.dlogits)
+            api.xmoe_route_bwd(self.logits, self.topk_idx, self.dw, self.dlogits)
         api.xmoe_gate_logits_bwd(x, w["w_router"], self.dlogits, grads["dw_router"], self.dx_gate, self.ws)
         dxd, dxd_shared, kw = self._row_args(self.dxd)
         api.xmoe_dispatch_bwd(dxd, self.row_of_slot, dxd_shared, self.dx_gate, self.k, self.dx, **kw)
@@ -221,12 +221,12 @@ class XMoE2Layer:
                                      grads["dw1"], grads["dw2"], self.ws, row_index=self.token_ids,
                                      dy_row_index=self.token_ids, dy_row_scale=self.combine_weights,
                                      dy_row_scale_grad=self.row_grad)
-            api.xmoe_combine_bwd_weights(self.row_grad, self.row_of_slot, self.dw)
+            api.xmoe_route_bwd_rows(self.logits, self.topk_idx, self.row_grad, self.row_of_slot, self.dw, self.dlogits)
         else:
             api.xmoe_combine_bwd(dout, self.y, self.row_of_slot, self.topk_w, self.dy, self.dw)
             api.xmoe_expert_mlp2_bwd(x, self.h, self.dy, self.expert_offsets, w["w1"], w["w2"], self.act, self.dxd,
                                      grads["dw1"], grads["dw2"], self.ws, row_index=self.token_ids)
-        api.xmoe_route_bwd(self.logits, self.topk_idx, self.dw, self.dlogits)
+            api.xmoe_route_bwd(self.logits, self.topk_idx, self.dw, self.dlogits)
         api.xmoe_gate_logits_bwd(x, w["w_router"], self.dlogits, grads["dw_router"], self.dx_gate, self.ws)
         api.xmoe_dispatch_bwd(self.dxd, self.row_of_slot, None, self.dx_gate, self.k, self.dx)
         return self.dx
