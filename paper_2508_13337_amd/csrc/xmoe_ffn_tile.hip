@@ -168,6 +168,11 @@ __global__ XMOE_TILE_BOUNDS void ffn_gateup_mfma_kernel(const T* __restrict__ xd
     tile_f32x16_t acc[S::kMI][2];
     tile_zero<BIG>(acc);
     tile_mainloop<T, BIG, true, false>(acc, d, t.rows, f - n0, a, b, smem);
+    if constexpr (std::is_same<T, float>::value)
+        tile_recover<BIG, true>(acc, d, 1, [&](int, int ni) {
+            return PlainPair{{row_index ? xd : xd + (size_t)t.row0 * d, (size_t)d, 1, row_index ? row_index + t.row0 : nullptr, nullptr, t.rows},
+                             {(ni ? wu : wg) + (size_t)t.e * d * f + n0, 1, (size_t)f, nullptr, nullptr, f - n0}};
+        });
     const int n = n0 + tile_col<BIG, true>(0);
     if (n >= f) return;
 #pragma unroll
@@ -222,6 +227,11 @@ __global__ XMOE_TILE_BOUNDS void ffn_down_mfma_kernel(const T* __restrict__ A, c
     tile_f32x16_t acc[S::kMI][2];
     tile_zero<BIG>(acc);
     tile_mainloop<T, BIG, false, false>(acc, f, t.rows, d - n0, a, b, smem);
+    if constexpr (std::is_same<T, float>::value)
+        tile_recover<BIG, false>(acc, f, 1, [&](int, int) {
+            return PlainPair{{A + (size_t)t.row0 * f, (size_t)f, 1, nullptr, nullptr, t.rows},
+                             {wd + (size_t)t.e * f * d + n0, 1, (size_t)d, nullptr, nullptr, d - n0}};
+        });
     tile_store<T, BIG>(acc, Y + (size_t)t.row0 * d + n0, d, t.rows, d - n0);
 }
 
@@ -247,6 +257,11 @@ __device__ __forceinline__ void dact_tile(const T* __restrict__ dY, const int32_
     tile_f32x16_t acc[S::kMI][2];
     tile_zero<BIG>(acc);
     tile_mainloop<T, BIG, false, false>(acc, d, t.rows, f - n0, a, b, smem);
+    if constexpr (std::is_same<T, float>::value)
+        tile_recover<BIG, false>(acc, d, 1, [&](int, int) {
+            return PlainPair{{dy_index ? dY : dY + (size_t)t.row0 * d, (size_t)d, 1, dy_index ? dy_index + t.row0 : nullptr, nullptr, t.rows},
+                             {w + ((size_t)t.e * f + n0) * d, (size_t)d, 1, nullptr, nullptr, f - n0}};
+        });
     const bool scaled = dy_index && dy_scale;
 #pragma unroll
     for (int mi = 0; mi < S::kMI; ++mi) {
@@ -353,6 +368,11 @@ __global__ XMOE_TILE_BOUNDS void ffn_dx_mfma_kernel(const T* __restrict__ dG, co
         b.init((set ? wu : wg) + ((size_t)t.e * d + n0) * f, f, d - n0, nullptr);
         tile_mainloop<T, BIG, false, false>(acc, f, t.rows, d - n0, a, b, smem);
     }
+    if constexpr (std::is_same<T, float>::value)
+        tile_recover<BIG, false>(acc, f, dU ? 2 : 1, [&](int set, int) {
+            return PlainPair{{(set ? dU : dG) + (size_t)t.row0 * f, (size_t)f, 1, nullptr, nullptr, t.rows},
+                             {(set ? wu : wg) + ((size_t)t.e * d + n0) * f, (size_t)f, 1, nullptr, nullptr, d - n0}};
+        });
     tile_store<T, BIG>(acc, dXd + (size_t)t.row0 * d + n0, d, t.rows, d - n0);
 }
 
@@ -387,6 +407,11 @@ __device__ __forceinline__ void wgrad_tile(const WgradJob<T>& j, int u, int e, i
     tile_f32x16_t acc[S::kMI][2];
     tile_zero<BIG>(acc);
     tile_mainloop<T, BIG, false, true>(acc, K, j.M - m0, j.N - n0, a, b, smem);
+    if constexpr (std::is_same<T, float>::value)
+        tile_recover<BIG, false>(acc, K, 1, [&](int, int) {
+            return PlainPair{{j.P + m0 + (GP ? 0 : (size_t)lo * j.M), 1, (size_t)j.M, nullptr, GP ? j.p_index + lo : nullptr, j.M - m0},
+                             {j.Q + n0 + (GQ ? 0 : (size_t)lo * j.N), 1, (size_t)j.N, nullptr, GQ ? j.q_index + lo : nullptr, j.N - n0}};
+        });
     tile_store<T, BIG>(acc, j.dW + (size_t)e * j.M * j.N + (size_t)m0 * j.N + n0, j.N, j.M - m0, j.N - n0);
 }
 
@@ -430,6 +455,11 @@ __global__ XMOE_TILE_BOUNDS void mlp2_up_mfma_kernel(const T* __restrict__ xd,
     tile_f32x16_t acc[S::kMI][2];
     tile_zero<BIG>(acc);
     tile_mainloop<T, BIG, false, false>(acc, d, t.rows, f - n0, a, b, smem);
+    if constexpr (std::is_same<T, float>::value)
+        tile_recover<BIG, false>(acc, d, 1, [&](int, int) {
+            return PlainPair{{row_index ? xd : xd + (size_t)t.row0 * d, (size_t)d, 1, row_index ? row_index + t.row0 : nullptr, nullptr, t.rows},
+                             {w1 + (size_t)t.e * d * f + n0, 1, (size_t)f, nullptr, nullptr, f - n0}};
+        });
 #pragma unroll
     for (int ni = 0; ni < 2; ++ni) {
         const int n = n0 + tile_col<BIG, false>(ni);

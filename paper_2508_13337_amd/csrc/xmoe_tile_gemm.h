@@ -11,7 +11,9 @@
 // (v_mfma_f32_32x32x2_f32) takes 512.  The largest product left out is 2^-23 of the whole at worst and 2^-26 on average,
 // below what one float32 addition of the sum rounds off, and a sum has six roundings per 16 k instead of eight: against
 // float64 the results are nearer than those of the float32 instruction (training step, f32 cases: 1.2e-6 -> 1.0e-6 and
-// 3.9e-7 -> 3.5e-7).  A non-finite input gives NaN in the results it reaches (an infinity has no finite parts).
+// 3.9e-7 -> 3.5e-7).  An infinity has no finite parts, and the parts of a product that overflows may do so with either
+// sign: what comes out as NaN is computed again from the floats themselves (tile_recover).  The parts reach down to 2^-133: an
+// operand below 2^-110 (1e-33) is taken with an absolute error of 2^-134.
 //
 // K is stepped by 64 bf16 (both operand tiles lie in LDS as [row or column][128 bytes of k]) or 16 floats ([row or
 // column][three parts of 32 bytes]), so that one 16-byte LDS read is a fragment of a matrix instruction.  The operands
@@ -435,6 +437,54 @@ __device__ __forceinline__ void tile_mainloop(tile_f32x16_t (&acc)[TileShape<BIG
         compute(P1, RAGGED ? K - (i + 1) * kK : kK);
         if (i + 2 < n) store(P0, P0);
     }
+}
+
+// float32: results that the parts lose.  A 32 x 32 block of accumulators that holds a NaN is multiplied again with the
+// float32 instruction, straight from memory, and its NaNs take what comes out: an infinity where the floats give one, NaN
+// where they do.  Finite operands whose products don't overflow never come here, so nothing is done for speed.
+// One operand: element (i, k) of the tile, i its row (of A) or column (of B), n of them valid.
+struct PlainOp {
+    const float* p;
+    size_t stride_i, stride_k;
+    const int32_t* index_i;
+    const int32_t* index_k;
+    int n;
+    __device__ __forceinline__ float at(int i, int k) const {
+        i = i < n ? i : n - 1;
+        return p[(size_t)(index_i ? index_i[i] : i) * stride_i + (size_t)(index_k ? index_k[k] : k) * stride_k];
+    }
+};
+struct PlainPair {
+    PlainOp a, b;
+};
+// pairs(set, ni): the operands of product `set` of the sum; DUAL: b is the matrix of column block ni
+template <bool BIG, bool DUAL, class Pairs>
+__device__ __forceinline__ void tile_recover(tile_f32x16_t (&acc)[TileShape<BIG>::kMI][2], int K, int sets, Pairs&& pairs) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+    for (int mi = 0; mi < TileShape<BIG>::kMI; ++mi)
+#pragma unroll
+        for (int ni = 0; ni < 2; ++ni) {
+            bool lost = false;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) lost |= acc[mi][ni][v] != acc[mi][ni][v];
+            if (!__any(lost)) continue;
+            const int i = (BIG ? (wave >> 1) * 64 : wave * 32) + mi * 32 + (lane & 31);
+            const int j = tile_col<BIG, DUAL>(DUAL ? 0 : ni);
+            tile_f32x16_t x;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) x[v] = 0.f;
+            for (int set = 0; set < sets; ++set) {
+                const PlainPair q = pairs(set, ni);
+                for (int k0 = 0; k0 < K; k0 += 2) {   // both halves of the wave go round together
+                    const int k = k0 + (lane >> 5);
+                    const float a = k < K ? q.a.at(i, k) : 0.f, b = k < K ? q.b.at(j, k) : 0.f;
+                    x = __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, x, 0, 0, 0);
+                }
+            }
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[mi][ni][v] = acc[mi][ni][v] != acc[mi][ni][v] ? x[v] : acc[mi][ni][v];
+        }
 }
 
 template <bool BIG>
