@@ -266,28 +266,25 @@ __global__ __launch_bounds__(256) void eri_direct_kernel(const int32_t* __restri
 // Block e < E handles expert e: a three-pass radix select over the order-preserving bit pattern of the weights
 // finds the C-th largest weight, then the segment is compacted in row order.  Blocks >= E write the sentinels of
 // the rows behind the last retained one.  No floating-point arithmetic takes part in the decision.
+//
+// Bound: one CU per expert, and the fullest expert's block is the launch: latency of its loads, its barriers, and the LDS
+// atomics of the first pass, whose bins (sign, exponent, two bits) the weights of a softmax share.  So 16 waves, a window
+// of 8192 rows with eight loads in flight per thread (a segment that fits one is read once for the three passes), four
+// copies of the histogram, and one barrier per window of the compaction: a row's place is the number of heavier rows in
+// front of it plus the number of equal ones, as far as they are kept, so both prefixes come from the same ballots.
+// T 8192, E 64, k 6, C 960, Zipf-like load: 256 threads, a row each per step | this: 62 | 16 us.
 // ---------------------------------------------------------------------------------------------------------
+constexpr int kCapThreads = 1024, kCapWaves = kCapThreads / 64;
+constexpr int kCapRows = 8;                              // rows per thread and window
+constexpr int kCapWindow = kCapThreads * kCapRows;
+constexpr int kCapCopies = 4;
 __device__ __forceinline__ uint32_t weight_key(float w) {
     uint32_t u = __float_as_uint(w);
     if (u == 0x80000000u) u = 0u;                          // -0.0 ties with +0.0
     return (u & 0x80000000u) ? ~u : (u | 0x80000000u);   // ascending in w
 }
 
-// exclusive prefix of `flag` over the block's 256 threads in thread order; total in *total
-__device__ __forceinline__ int block_excl_count(bool flag, int* wave_tot, int* total) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const unsigned long long bal = __ballot(flag);
-    const int in_wave = __popcll(bal & ((1ull << lane) - 1ull));
-    __syncthreads();   // wave_tot may still be read from the previous call
-    if (lane == 0) wave_tot[wave] = __popcll(bal);
-    __syncthreads();
-    int before = 0;
-    for (int w = 0; w < wave; ++w) before += wave_tot[w];
-    *total = wave_tot[0] + wave_tot[1] + wave_tot[2] + wave_tot[3];
-    return before + in_wave;
-}
-
-// exclusive prefix of `v` over the block's 256 threads in thread order; total in *total
+// exclusive prefix of `v` over the block's threads in thread order; total in *total
 __device__ __forceinline__ int block_excl_sum(int v, int* wave_tot, int* total) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     int inc = v;
@@ -299,13 +296,18 @@ __device__ __forceinline__ int block_excl_sum(int v, int* wave_tot, int* total) 
     __syncthreads();   // wave_tot may still be read from the previous call
     if (lane == 63) wave_tot[wave] = inc;
     __syncthreads();
-    int before = 0;
-    for (int w = 0; w < wave; ++w) before += wave_tot[w];
-    *total = wave_tot[0] + wave_tot[1] + wave_tot[2] + wave_tot[3];
+    int before = 0, all = 0;
+#pragma unroll
+    for (int w = 0; w < kCapWaves; ++w) {
+        const int t = wave_tot[w];
+        before += w < wave ? t : 0;
+        all += t;
+    }
+    *total = all;
     return before + inc - v;
 }
 
-__global__ __launch_bounds__(256) void eri_cap_kernel(const int32_t* __restrict__ off0,      // dropless offsets [E+1]
+__global__ __launch_bounds__(kCapThreads) void eri_cap_kernel(const int32_t* __restrict__ off0,      // dropless offsets [E+1]
                                                       const int32_t* __restrict__ flat0,     // flat entry of row [B]
                                                       const float* __restrict__ w0,          // weight of row [B]
                                                       int B, int E, int k, int C,
@@ -315,15 +317,17 @@ __global__ __launch_bounds__(256) void eri_cap_kernel(const int32_t* __restrict_
                                                       int32_t* __restrict__ expert_ids,
                                                       float* __restrict__ combine_weights,
                                                       int32_t* __restrict__ row_of_slot) {
-    __shared__ int hist[2048];
-    __shared__ int wave_tot[4];
+    __shared__ int4 hist[2048];               // one int per copy
+    static_assert(kCapCopies == 4, "");
+    __shared__ int wave_tot[kCapWaves];
+    __shared__ int2 wave_cnt[2][kCapWaves];   // heavier, equal rows of a wave's part of the window
     __shared__ uint32_t s_prefix, s_mask;
     __shared__ int s_remaining, s_new_lo, s_kept_total;
     const int tid = threadIdx.x;
     // retained rows before this block's expert, and in total: every block recomputes the short prefix it needs
     {
         int before_me = 0, all = 0;
-        for (int i = tid; i < E; i += 256) {
+        for (int i = tid; i < E; i += kCapThreads) {
             const int n = off0[i + 1] - off0[i];
             const int c = n < C ? n : C;
             all += c;
@@ -342,7 +346,7 @@ __global__ __launch_bounds__(256) void eri_cap_kernel(const int32_t* __restrict_
     if ((int)blockIdx.x >= E) {
         // rows behind the last retained one
         const int base = ((int)blockIdx.x - E) * kEriChunk;
-        for (int r = base + tid; r < base + kEriChunk && r < B; r += 256) {
+        for (int r = base + tid; r < base + kEriChunk && r < B; r += kCapThreads) {
             if (r >= kept_total) {
                 token_ids[r] = -1;
                 expert_ids[r] = E;
@@ -360,42 +364,69 @@ __global__ __launch_bounds__(256) void eri_cap_kernel(const int32_t* __restrict_
         expert_offsets[e] = new_lo;
         if (e == E - 1) expert_offsets[E] = kept_total;
     }
+    // Row r of a thread's kCapRows of the window at `base`: a wave's 64 lanes hold consecutive rows, a wave the next
+    // kCapRows groups of 64, so that ballots and the waves' totals give prefixes in row order
+    const int lane = tid & 63, wave = tid >> 6;
+    uint32_t key[kCapRows];
+    float w[kCapRows];
+    const uint32_t un = (uint32_t)n;   // unsigned: the last window may reach past 2^31
+    auto row_at = [&](uint32_t base, int r) { return base + (wave * kCapRows + r) * 64 + lane; };
+    auto load = [&](uint32_t base) {
+#pragma unroll
+        for (int r = 0; r < kCapRows; ++r) {
+            const uint32_t i = row_at(base, r);
+            w[r] = w0[lo + (i < un ? i : 0)];
+        }
+#pragma unroll
+        for (int r = 0; r < kCapRows; ++r) key[r] = weight_key(w[r]);
+    };
+    if (n == 0) return;   // the same for the whole block
+    load(0);
     // the C-th largest key of the segment (only needed when something is dropped)
     uint32_t vstar = 0;
     int need_eq = 0;   // how many rows with key == vstar are kept
-    if (n > C && C > 0) {
+    const bool select = n > C && C > 0;
+    if (select) {
         if (tid == 0) {
             s_prefix = 0;
             s_mask = 0;
             s_remaining = C;
         }
         const int shifts[3] = {21, 10, 0}, widths[3] = {11, 11, 10};
+#pragma unroll
         for (int p = 0; p < 3; ++p) {
             const int shift = shifts[p], nb = 1 << widths[p];
-            for (int i = tid; i < nb; i += 256) hist[i] = 0;
+            for (int i = tid; i < nb; i += kCapThreads) hist[i] = make_int4(0, 0, 0, 0);
             __syncthreads();
             const uint32_t prefix = s_prefix, mask = s_mask;
-            for (int i = tid; i < n; i += 256) {
-                const uint32_t key = weight_key(w0[lo + i]);
-                if ((key & mask) == prefix) atomicAdd(&hist[(key >> shift) & (nb - 1)], 1);
+            for (uint32_t base = 0; base < un; base += kCapWindow) {
+                if (n > kCapWindow) load(base);
+#pragma unroll
+                for (int r = 0; r < kCapRows; ++r)
+                    if (row_at(base, r) < un && (key[r] & mask) == prefix)
+                        atomicAdd(reinterpret_cast<int*>(&hist[(key[r] >> shift) & (nb - 1)]) + (tid & (kCapCopies - 1)), 1);
             }
             __syncthreads();
             // which bin holds the `remaining`-th largest key: thread t owns the bins nb-1 - t*bpt .. (downwards);
             // an exclusive prefix of the threads' sums, then the one thread whose range the target falls into
             // walks its few bins
             {
-                const int bpt = nb / 256;
+                const int bpt = nb / kCapThreads;
                 const int hi = nb - 1 - tid * bpt;
+                auto bin = [&](int i) {
+                    const int4 h = hist[i];
+                    return (h.x + h.y) + (h.z + h.w);
+                };
                 int mine = 0;
-                for (int j = 0; j < bpt; ++j) mine += hist[hi - j];
+                for (int j = 0; j < bpt; ++j) mine += bin(hi - j);
                 int tot_unused;
                 const int before = block_excl_sum(mine, wave_tot, &tot_unused);
                 const int remaining = s_remaining;
                 __syncthreads();   // everyone has read s_remaining before the owner overwrites it
                 if (before < remaining && remaining <= before + mine) {
                     int rem = remaining - before, b = hi;
-                    while (hist[b] < rem) {
-                        rem -= hist[b];
+                    while (bin(b) < rem) {
+                        rem -= bin(b);
                         --b;
                     }
                     s_remaining = rem;
@@ -408,43 +439,56 @@ __global__ __launch_bounds__(256) void eri_cap_kernel(const int32_t* __restrict_
         vstar = s_prefix;
         need_eq = s_remaining;
     }
-    // compaction in row order
-    int eq_seen = 0, kept_seen = 0;
-    for (int base = 0; base < n; base += 256) {
-        const int i = base + tid;
-        const bool in = i < n;
-        uint32_t key = 0;
-        int flat = 0;
-        float w = 0.f;
-        if (in) {
-            w = w0[lo + i];
-            flat = flat0[lo + i];
-            key = weight_key(w);
+    // compaction in row order: rows heavier than vstar stay, and the first need_eq of those equal to it
+    int gt_seen = 0, eq_seen = 0;
+    for (uint32_t base = 0; base < un; base += kCapWindow) {
+        if (n > kCapWindow) load(base);
+        int flat[kCapRows];
+#pragma unroll
+        for (int r = 0; r < kCapRows; ++r) {
+            const uint32_t i = row_at(base, r);
+            flat[r] = flat0[lo + (i < un ? i : 0)];
         }
-        bool keep;
-        if (n <= C) {
-            keep = in;
-        } else if (C <= 0) {
-            keep = false;
-        } else {
-            const bool eq = in && key == vstar;
-            int eq_total;
-            const int eq_rank = eq_seen + block_excl_count(eq, wave_tot, &eq_total);
-            eq_seen += eq_total;
-            keep = in && (key > vstar || (eq && eq_rank < need_eq));
+        unsigned long long gt[kCapRows], eq[kCapRows];
+        int2 mine = make_int2(0, 0);
+#pragma unroll
+        for (int r = 0; r < kCapRows; ++r) {
+            const bool in = row_at(base, r) < un;
+            gt[r] = __ballot(in && (n <= C || (select && key[r] > vstar)));
+            eq[r] = __ballot(in && select && key[r] == vstar);
+            mine.x += __popcll(gt[r]);
+            mine.y += __popcll(eq[r]);
         }
-        int kept_total_chunk;
-        const int pos = kept_seen + block_excl_count(keep, wave_tot, &kept_total_chunk);
-        kept_seen += kept_total_chunk;
-        if (in) {
+        // two sets of totals: one is written while slower waves still read the other
+        int2* cnt = wave_cnt[(base / kCapWindow) & 1];
+        if (lane == 0) cnt[wave] = mine;
+        __syncthreads();
+        int g = gt_seen, q = eq_seen;
+#pragma unroll
+        for (int v = 0; v < kCapWaves; ++v) {
+            const int2 t = cnt[v];
+            g += v < wave ? t.x : 0;
+            q += v < wave ? t.y : 0;
+            gt_seen += t.x;
+            eq_seen += t.y;
+        }
+#pragma unroll
+        for (int r = 0; r < kCapRows; ++r) {
+            const unsigned long long below = (1ull << lane) - 1ull;
+            const int g_at = g + __popcll(gt[r] & below), q_at = q + __popcll(eq[r] & below);
+            const bool is_eq = (eq[r] >> lane) & 1ull;
+            const bool keep = ((gt[r] >> lane) & 1ull) || (is_eq && q_at < need_eq);
+            g += __popcll(gt[r]);
+            q += __popcll(eq[r]);
+            if (row_at(base, r) >= un) continue;
             if (keep) {
-                const int row = new_lo + pos;
-                token_ids[row] = flat / k;
+                const int row = new_lo + g_at + (q_at < need_eq ? q_at : need_eq);
+                token_ids[row] = flat[r] / k;
                 expert_ids[row] = e;
-                combine_weights[row] = w;
-                row_of_slot[flat] = row;
+                combine_weights[row] = w[r];
+                row_of_slot[flat[r]] = row;
             } else {
-                row_of_slot[flat] = -1;
+                row_of_slot[flat[r]] = -1;
             }
         }
     }
@@ -623,7 +667,7 @@ extern "C" int xmoe_build_eri_capped(const int32_t* topk_idx, const float* topk_
                                        (size_t)kSubPerChunk * E * sizeof(int), s, topk_idx, topk_w, B, E, k, ebits,
                                        counts, off0, flat0, nullptr, w0, nullptr));
     XMOE_LAUNCH(K_ERI_CAP, s,
-                hipLaunchKernelGGL(eri_cap_kernel, dim3(E + nchunks), dim3(256), 0, s, off0, flat0, w0, B, E, k,
+                hipLaunchKernelGGL(eri_cap_kernel, dim3(E + nchunks), dim3(kCapThreads), 0, s, off0, flat0, w0, B, E, k,
                                    max_token_count, tokens_per_expert, expert_offsets, token_ids, expert_ids,
                                    combine_weights, row_of_slot));
     return XMOE_OK;
