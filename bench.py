@@ -96,7 +96,7 @@ def kernel_work(cfg, materialise_dy=False):
             "row_grad_reduce_kernel": ((f + 255) // 256 * 4 + 1) * B * 4,
             "combine_bwd_weights_kernel": B * 12,
             "route_kernel": T * E * 4 + T * k * 8,
-            "route_bwd_kernel": 2 * T * E * 4 + T * k * 8,
+            "route_bwd_kernel": 2 * T * E * 4 + T * k * 16,
         }
         gemm_bytes = {"up": R * d * s + W + 2 * R * f * s, "down": R * f * s + W + R * d * s,
                       "dact": R * d * s + W + 3 * R * f * s, "dx": R * f * s + W + R * d * s,
@@ -117,7 +117,7 @@ def kernel_work(cfg, materialise_dy=False):
         "row_grad_reduce_kernel": ((f + 255) // 256 * 4 + 1) * (B + Ts) * 4,
         "combine_bwd_weights_kernel": B * 12,
         "route_kernel": T * E * 4 + T * k * 8,
-        "route_bwd_kernel": 2 * T * E * 4 + T * k * 8,
+        "route_bwd_kernel": 2 * T * E * 4 + T * k * 16,
     }
     # algorithmic bytes of the GEMM kernels: every operand read once, every result written once
     R, W = B + Ts, (E + cfg.E_s) * d * f * s
@@ -137,7 +137,7 @@ GEMM_WORK = {
     "ffn_wgrad_dma_kernel<false>": "wgrad_wd", "ffn_wgrad_dma_kernel<true>": "wgrad_wg_wu",
     "ffn_bwd_rest_dma_kernel": "bwd_rest", "ffn_gateup_few_kernel": "gateup", "ffn_down_few_kernel": "down",
 }
-for _fam in ("mfma",):
+for _fam in ("mfma", "direct"):
     for _k in ("gateup", "down", "dact", "dx", "wgrad"):
         GEMM_WORK[f"ffn_{_k}_{_fam}_kernel"] = _k
 # the two-matrix expert shares the down, dX and weight-gradient kernels (both weight gradients are one launch, except
@@ -147,7 +147,8 @@ GEMM_WORK_MLP2 = {
     "ffn_dx_dma_kernel": "dx", "ffn_wgrad_dma_kernel<false>": "wgrad", "ffn_bwd_rest_dma_kernel": "bwd_rest",
     "mlp2_up_mfma_kernel": "up", "ffn_down_mfma_kernel": "down", "mlp2_dact_mfma_kernel": "dact",
     "ffn_dx_mfma_kernel": "dx", "ffn_wgrad_mfma_kernel": "wgrad", "mlp2_up_few_kernel": "up",
-    "ffn_down_few_kernel": "down",
+    "ffn_down_few_kernel": "down", "mlp2_up_direct_kernel": "up", "ffn_down_direct_kernel": "down",
+    "mlp2_dact_direct_kernel": "dact", "ffn_dx_direct_kernel": "dx", "ffn_wgrad_direct_kernel": "wgrad",
 }
 
 def load_measured_traffic(workload):

@@ -1,12 +1,13 @@
 // Expert MLP over ragged segments (paper: Listing 1 mlp(); Appendix B.4 "Sequential GeMM"), general version: serves
-// float32 workloads and every bf16 shape the direct-to-LDS kernels do not take, on the tiles of xmoe_tile_gemm.h.
+// float32 workloads and every bf16 shape the direct-to-LDS kernels (256 x 256, 128 x 128) do not take, on the tiles of
+// xmoe_tile_gemm.h.
 // One launch covers every expert: a tile map built on the device says which expert and which rows each row tile
 // belongs to, so there is no host round trip on tokens_per_expert and no per-expert launch.
 //
-// Measured (MI355X, one training step of the layer; float32: with the float32 matrix instruction -> now; both: row tiles
-// numbered down the segments -> runs of neighbouring tiles per XCD):
-//   float32 T 2048 d 1024 f 704, 16 experts + 1 shared, k 4:   1602 -> 1130 us, the products at 85 to 156 TFLOP/s
-//   bf16    T 3001 d 1000 f 712, 24 experts + 1 shared, k 3:    627 ->  558 us, the products at 200 to 435 TFLOP/s
+// Measured (MI355X, one training step of the layer, row tiles numbered down the segments -> runs of neighbouring tiles per
+// XCD; float32: with the float32 matrix instruction -> as three bf16 parts as well):
+//   float32 T 2048 d 1024 f 704, 16 experts + 1 shared, k 4:   1602 -> 1055 us, the products at 86 to 154 TFLOP/s
+//   bf16    T 3001 d 1000 f 712, 24 experts + 1 shared, k 3:    627 ->  558 us (417 on the 128 x 128 direct tiles)
 #include "xmoe_ffn.h"
 #include "xmoe_tile_gemm.h"
 

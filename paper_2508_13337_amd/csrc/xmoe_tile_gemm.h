@@ -1,6 +1,6 @@
 // A GEMM tile on the matrix cores for any shape, stride and alignment, in float32 and in bf16, with float32 accumulators.
-// It serves the float32 workloads and the bf16 shapes whose d or f is no multiple of 64, for which the direct-to-LDS
-// kernels have no loads.
+// It serves the float32 workloads and the bf16 shapes for which the direct-to-LDS kernels have no loads (d or f no multiple
+// of 8, operands not 16-byte aligned) or are the slower ones (weight gradients of few rows per expert).
 //
 //   BIG:   128 x 128 outputs, 256 threads = 4 waves (2 x 2), wave tile 64 x 64, 64 KiB of LDS: two blocks per CU
 //   small:  64 x  64 outputs, 128 threads = 2 waves (2 x 1), wave tile 32 x 64, 32 KiB of LDS
