@@ -269,8 +269,9 @@ __global__ __launch_bounds__(256) void route_kernel(const float* __restrict__ lo
     if (t >= Tn) return;
     const float* row = logits + (size_t)t * E;
     float l[PER_LANE];
-    // order-preserving bits of the logits; 0 is below every logit's and stands for a column that does not exist or has
-    // been selected.  The largest key wins, and among equal ones the lowest expert, i.e. the first lane of the first j.
+    // order-preserving bits of the logits; 0 stands for a column that does not exist or has been selected, and is the key of
+    // one logit, the NaN of all ones.  The largest key wins, and among equal ones the lowest expert, i.e. the first lane of
+    // the first j.
     uint32_t key[PER_LANE];
 #pragma unroll
     for (int j = 0; j < PER_LANE; ++j) {
@@ -295,7 +296,9 @@ __global__ __launch_bounds__(256) void route_kernel(const float* __restrict__ lo
 
     int my_idx = 0;
     float my_w = 0.f;
-    for (int slot = 0; slot < k; ++slot) {
+    int slot = 0;
+    for (; slot < k; ++slot) {
+        if (best == 0u) break;   // wave-uniform, as `best` is
         int e = 0;
         bool found = false;
 #pragma unroll
@@ -313,6 +316,20 @@ __global__ __launch_bounds__(256) void route_kernel(const float* __restrict__ lo
             my_w = expf(logit_of(best) - m) * inv;
         }
         if (slot + 1 < k) best = wave_best();
+    }
+    // only NaNs of all ones are left: by ascending expert
+    for (int last = -1; slot < k; ++slot) {
+        int e = E;
+#pragma unroll
+        for (int j = PER_LANE - 1; j >= 0; --j) {
+            const unsigned long long who = __ballot(__float_as_uint(l[j]) == 0xffffffffu && lane + 64 * j > last);
+            if (who) e = __ffsll((long long)who) - 1 + 64 * j;
+        }
+        last = e;
+        if (lane == slot) {
+            my_idx = e;
+            my_w = logit_of(0u);
+        }
     }
     if (lane < k) {
         topk_idx[(size_t)t * k + lane] = my_idx;

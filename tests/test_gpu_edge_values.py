@@ -1,5 +1,5 @@
 """Edges of the small passes and of the products: infinities in the operands of the expert products, segments longer than
-the window of the token-dropping pass, the merged pass over the combine weights' gradient, tile maps of many experts.
+the window of the token-dropping pass, the merged pass over the combine weights' gradient, routing over NaNs, tile maps of many experts.
 
 Integers, copies and what an infinity does not reach are compared bit for bit; the many-experts products as in
 test_gpu_direct_tiles.py's reasoning for float32: sums of at most 64 terms of order one, 2^-24 each, held to 2^-16."""
@@ -132,6 +132,26 @@ def test_route_bwd_rows_is_both_passes(E, k):
     m.xmoe_route_bwd(logits, idx, dw, dl)
     m.xmoe_route_bwd_rows(logits, idx, rg, ros, dw2, dl2)
     assert torch.equal(dw, dw2) and torch.equal(dl, dl2)
+
+
+@pytest.mark.parametrize("E,k", [(8, 8), (40, 7), (64, 64), (65, 8), (200, 8), (512, 64)])
+def test_route_selects_every_expert_once(E, k):
+    """NaNs of all bit patterns, -1 (all ones) among them, take their place in the order of the bits, as infinities do."""
+    import paper_2508_13337_amd as m
+    rng = np.random.default_rng(E + k)
+    odd = np.array([0xffffffff, 0xfffffffe, 0x7fffffff, 0x7fc00000, 0xffc00000, 0xff800000, 0x7f800000, 0x80000000, 0], np.uint32)
+    bits = rng.standard_normal((67, E)).astype(np.float32).view(np.uint32)
+    bits[0:40] = rng.choice(odd, (40, E))
+    bits[40:44] = 0xffffffff
+    bits[44:48, 1:] = 0xffffffff
+    bits[48:52, :E - 1] = 0xffffffff
+    b = np.where(bits == 0x80000000, np.uint32(0), bits)          # the zeros are one number
+    key = np.where(b >> 31, ~b, b | np.uint32(0x80000000)).astype(np.int64)
+    want = np.argsort(-key, axis=1, kind="stable")[:, :k]
+    logits = torch.from_numpy(bits.view(np.float32)).cuda()
+    idx = torch.full((67, k), -1, dtype=torch.int32, device="cuda")
+    m.xmoe_route(logits, k, idx, torch.empty((67, k), device="cuda"))
+    assert np.array_equal(idx.cpu().numpy(), want)
 
 
 @pytest.mark.parametrize("E", [64, 65, 127, 129, 256, 257, 512])
