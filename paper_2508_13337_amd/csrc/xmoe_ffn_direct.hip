@@ -128,8 +128,8 @@ XMOE_DIRECT_KERNEL mlp2_up_direct_kernel(const bf16_t* __restrict__ xd, const in
     }
 }
 
-// dA = dY W^T (W = Wd or W2) and what follows from it; in, out: arrays [B, f], EPI as in dir_dact_rounds
-template <int NIN, int NOUT, class Epi>
+// dA = dY W^T (W = Wd or W2) and what follows from it; in, out: arrays [B, f], CHAIN and EPI as in dir_dact_rounds
+template <bool CHAIN, int NIN, int NOUT, class Epi>
 __device__ __forceinline__ void dact_direct(const bf16_t* __restrict__ dY, const int32_t* __restrict__ dy_index,
                                             const float* __restrict__ dy_scale, const int32_t* __restrict__ off,
                                             const int32_t* __restrict__ map, int d, int f, const bf16_t* __restrict__ w,
@@ -156,9 +156,9 @@ __device__ __forceinline__ void dact_direct(const bf16_t* __restrict__ dY, const
     float* part = row_part + (size_t)(t.col * 2 + wn) * B + t.row0;
     const float* scale = dy_index && dy_scale ? dy_scale + t.row0 : nullptr;
     if (t.rows >= wm * 64 + 64 && f - n0 >= wn * 64 + 64)
-        dir_dact_rounds<true, NIN, NOUT>(acc, smem, tin, tout, f, scale, part, t.rows, f - n0, epi);
+        dir_dact_rounds<true, CHAIN, NIN, NOUT>(acc, smem, tin, tout, f, scale, part, t.rows, f - n0, epi);
     else
-        dir_dact_rounds<false, NIN, NOUT>(acc, smem, tin, tout, f, scale, part, t.rows, f - n0, epi);
+        dir_dact_rounds<false, CHAIN, NIN, NOUT>(acc, smem, tin, tout, f, scale, part, t.rows, f - n0, epi);
 }
 
 // dG = dA * U * silu'(G), dU = dA * silu(G), A = silu(G) * U
@@ -171,7 +171,7 @@ XMOE_DIRECT_KERNEL ffn_dact_direct_kernel(const bf16_t* __restrict__ dY, const i
                                           bf16_t* __restrict__ A, float* __restrict__ row_part, int B) {
     const bf16_t* in[2] = {G, U};
     bf16_t* out[3] = {dG, dU, A};
-    dact_direct<2, 3>(dY, dy_index, dy_scale, off, map, d, f, wd, row_part, B, in, out,
+    dact_direct<FAST, 2, 3>(dY, dy_index, dy_scale, off, map, d, f, wd, row_part, B, in, out,
                       [](float da0, float sc, const float(&x)[2], float(&y)[3]) {
                           const float g = x[0], u = x[1], da = da0 * sc, sg = dir_sigmoid<FAST>(g), sl = g * sg;
                           const float a1 = sl * u;
@@ -192,7 +192,7 @@ XMOE_DIRECT_KERNEL mlp2_dact_direct_kernel(const bf16_t* __restrict__ dY, const 
                                            int B) {
     const bf16_t* in[1] = {H};
     bf16_t* out[2] = {dH, A};
-    dact_direct<1, 2>(dY, dy_index, dy_scale, off, map, d, f, w2, row_part, B, in, out,
+    dact_direct<FAST, 1, 2>(dY, dy_index, dy_scale, off, map, d, f, w2, row_part, B, in, out,
                       [](float da0, float sc, const float(&x)[1], float(&y)[2]) {
                           float a, g;
                           if (FAST)

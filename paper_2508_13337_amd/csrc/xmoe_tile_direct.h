@@ -500,10 +500,13 @@ __device__ __forceinline__ void dir_store(const tile_f32x16_t (&acc)[2][2], char
 // EPI(pa, sc, in, out): one element from the unscaled product pa, the row's scale sc and in[NIN]; fills out[NOUT] and
 // returns the unscaled activation, whose product with pa is summed over the wave's 64 columns into row_part (one part
 // per 64 columns; part: the tile's first row of the wave's part).  row_scale: of the tile's first row, or NULL.
+// CHAIN: the order of that sum.  A call's row count selects between these tiles and the 256-row ones (CHAIN: a lane's 16
+// columns of a 32-column block in turn) or the register-staged ones (otherwise: columns n and n + 32, then halving over the
+// 32), and a row's gradient has the same bits from either.
 // The inputs of a 32 x 32 block are fetched as whole 64-byte pieces of rows, one block ahead, and turned into the
 // accumulators' layout through LDS.  FULL: the wave's 64 x 64 block is entirely valid, and no load or store stands inside
 // a branch: the compiler then leaves them outstanding where it would otherwise wait for all of them.
-template <bool FULL, int NIN, int NOUT, class Epi>
+template <bool FULL, bool CHAIN, int NIN, int NOUT, class Epi>
 __device__ __forceinline__ void dir_dact_rounds(const tile_f32x16_t (&acc)[2][2], char* smem, const bf16_t* const (&in)[NIN],
                                                 bf16_t* const (&out)[NOUT], size_t f, const float* row_scale, float* part,
                                                 int rows, int cols, Epi epi) {
@@ -543,7 +546,7 @@ __device__ __forceinline__ void dir_dact_rounds(const tile_f32x16_t (&acc)[2][2]
         }
     };
     fetch(0, w[0]);
-    float rowpart = 0.f;
+    float rowpart = 0.f, pcol[16];   // pcol: not CHAIN, this lane's columns n and n + 32
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         const int mi = r >> 1, ni = r & 1;
@@ -573,17 +576,32 @@ __device__ __forceinline__ void dir_dact_rounds(const tile_f32x16_t (&acc)[2][2]
 #pragma unroll
                 for (int a = 0; a < NIN; ++a)
                     x[a] = __uint_as_float((j & 1) ? (iw[a][j >> 1] & 0xffff0000u) : (iw[a][j >> 1] << 16));
-                const float pa = acc[mi][ni][4 * q + j];
-                p = fmaf(pa, epi(pa, sc[mi], x, y), p);
+                const float pa = acc[mi][ni][4 * q + j], a = epi(pa, sc[mi], x, y);
+                if (CHAIN) {
+                    p = fmaf(pa, a, p);
+                } else {
+                    pcol[4 * q + j] = fmaf(pa, a, ni == 0 ? 0.f : pcol[4 * q + j]);
+                }
 #pragma unroll
                 for (int b = 0; b < NOUT; ++b) o[b][j] = y[b];
             }
 #pragma unroll
             for (int b = 0; b < NOUT; ++b) dir_put4(strip, 16 * b + 8 * ni, q, o[b][0], o[b][1], o[b][2], o[b][3]);
         }
-        rowpart = ni == 0 ? p : rowpart + p;
+        if (CHAIN) rowpart = ni == 0 ? p : rowpart + p;
         if (ni == 1) {
-            const float tot = rowpart + __shfl_xor(rowpart, 32, 64);
+            float tot;
+            if (CHAIN) {
+                tot = rowpart + __shfl_xor(rowpart, 32, 64);
+            } else {   // the halving of tile_sum_over_cols: columns 16, 8, 4 (the other half of the wave), 2 and 1 apart
+                float h[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    h[j] = (pcol[j] + pcol[8 + j]) + (pcol[4 + j] + pcol[12 + j]);
+                    h[j] += __shfl_xor(h[j], 32, 64);
+                }
+                tot = (h[0] + h[2]) + (h[1] + h[3]);
+            }
             if (FULL || (lane < 32 && mi * 32 + m < rows && cols > 0)) part[wm * 64 + mi * 32 + m] = tot;
             dir_strip_sync();
 #pragma unroll

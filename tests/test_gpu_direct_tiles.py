@@ -168,6 +168,46 @@ def test_bits_of_the_256_row_kernels():
             assert torch.equal(p[outs[0][0][e]:][:n], q[outs[1][0][e]:][:n]), e
 
 
+@pytest.mark.parametrize("expert", ["swiglu", "gelu"])
+@pytest.mark.parametrize("d,f,E", [(320, 256, 64), (328, 200, 4)])
+def test_backward_bits_of_the_other_kernels(d, f, E, expert):
+    """A row's gradient, and that of its scale, from both sides of the rules: widths of 64, few tiles of 128 rows and many of
+    256; widths of 8, the register-staged tiles and these."""
+    import paper_2508_13337_amd as m
+    few, many = [70, 1, 0, 129], [6000, 5000, 4097, 8000]
+    g = torch.Generator().manual_seed(d)
+    r = lambda *s: torch.randn(s, generator=g).bfloat16()
+    n_mat = 3 if expert == "swiglu" else 2
+    w = [(r(E, f, d) if i == n_mat - 1 else r(E, d, f)) * 0.06 for i in range(n_mat)]
+    w = [a.cuda() for a in w]
+    x, dy = r(61, d).cuda(), r(61, d).cuda()
+    idx = [torch.randint(0, 61, (n,), generator=g, dtype=torch.int32) for n in many]
+    scale, acts = [torch.rand(n, generator=g) for n in many], [[r(n, f) for n in many] for _ in range(n_mat - 1)]
+    outs = []
+    for rows in (few, many):
+        n_e = E if rows is many else 4
+        rest = [4500] * (n_e - 4)
+        B = sum(rows) + sum(rest)
+        off = torch.tensor([0] + list(torch.tensor(rows + rest).cumsum(0)), dtype=torch.int32)
+        rows_of = lambda t: torch.cat([a[:n] for a, n in zip(t, rows)] + [a[:1].expand(sum(rest), *a.shape[1:]) for a in t[:1]])
+        ic, sc, *saved = (rows_of(t).cuda() for t in (idx, scale, *acts))
+        o = [torch.empty((B, d), dtype=torch.bfloat16, device="cuda")] + [torch.empty_like(a[:n_e]) for a in w]
+        rg = torch.empty(B, device="cuda")
+        kw = dict(row_index=ic, dy_row_index=ic, dy_row_scale=sc, dy_row_scale_grad=rg)
+        op = m.WS_FFN_BWD if expert == "swiglu" else m.WS_MLP2_BWD
+        ws = m.alloc_workspace(m.xmoe_workspace_bytes(op, B, d, n_e, 1, f, m.XMOE_BF16))
+        wc = [a[:n_e] for a in w]
+        if expert == "swiglu":
+            k = launched(m, lambda: m.xmoe_expert_ffn_bwd(x, *saved, dy, off.cuda(), *wc, *o, ws, **kw))
+        else:
+            k = launched(m, lambda: m.xmoe_expert_mlp2_bwd(x, *saved, dy, off.cuda(), *wc, expert, *o, ws, **kw))
+        outs.append((off.tolist(), o[0].cpu(), rg.cpu(), k))
+    (o1, dx1, rg1, k1), (o2, dx2, rg2, k2) = outs
+    for e, n in enumerate(few):
+        assert torch.equal(dx1[o1[e]:][:n], dx2[o2[e]:][:n]), e
+        assert torch.equal(rg1[o1[e]:][:n], rg2[o2[e]:][:n]), e
+
+
 @pytest.mark.parametrize("E,d,f,rows,fwd,bwd,wgrads", [
     (4, 256, 256, 129, True, True, True), (4, 192, 256, 129, False, False, False), (4, 256, 192, 129, False, False, False),
     (64, 256, 256, 64 * 800, False, True, True), (64, 256, 256, 64 * 3200, False, False, False),
