@@ -579,8 +579,9 @@ __device__ __forceinline__ void dir_dact_rounds(const tile_f32x16_t (&acc)[2][2]
                 const float pa = acc[mi][ni][4 * q + j], a = epi(pa, sc[mi], x, y);
                 if (CHAIN) {
                     p = fmaf(pa, a, p);
-                } else {
-                    pcol[4 * q + j] = fmaf(pa, a, ni == 0 ? 0.f : pcol[4 * q + j]);
+                } else {   // a column past the last one holds a copy of another's product, which may be infinite
+                    const float c = ni == 0 ? 0.f : pcol[4 * q + j];
+                    pcol[4 * q + j] = FULL || ni * 32 + 8 * q + 4 * (lane >> 5) + j < cols ? fmaf(pa, a, c) : c;
                 }
 #pragma unroll
                 for (int b = 0; b < NOUT; ++b) o[b][j] = y[b];

@@ -208,6 +208,33 @@ def test_backward_bits_of_the_other_kernels(d, f, E, expert):
         assert torch.equal(rg1[o1[e]:][:n], rg2[o2[e]:][:n]), e
 
 
+@pytest.mark.parametrize("expert", ["swiglu", "identity"])
+@pytest.mark.parametrize("f", [200, 264])
+def test_an_infinite_last_column_is_counted_once(f, expert):
+    """An infinite weight of the last valid column makes the gradients of the row scales infinite, not NaN: the columns behind
+    it, which repeat it, take no part in them."""
+    import paper_2508_13337_amd as m
+    rows, d = [3000, 129, 0, 4000], 264
+    E, B, g = 4, sum(rows), torch.Generator().manual_seed(f)
+    r = lambda *s: torch.randn(s, generator=g).bfloat16()
+    off = torch.tensor([0] + list(torch.tensor(rows).cumsum(0)), dtype=torch.int32).cuda()
+    n_mat = 3 if expert == "swiglu" else 2
+    w = [r(E, f, d) if i == n_mat - 1 else r(E, d, f) for i in range(n_mat)]
+    w[-1][:, f - 1, 7] = float("inf")
+    dy, acts = r(B, d), [r(B, f) for _ in range(n_mat - 1)]
+    o = [torch.empty((B, d), dtype=torch.bfloat16, device="cuda")] + [torch.empty_like(a, device="cuda") for a in w]
+    rg, ic = torch.empty(B, device="cuda"), torch.arange(B, dtype=torch.int32, device="cuda")
+    ws = m.alloc_workspace(m.xmoe_workspace_bytes(m.WS_FFN_BWD if n_mat == 3 else m.WS_MLP2_BWD, B, d, E, 1, f, m.XMOE_BF16))
+    kw = dict(row_index=ic, dy_row_index=ic, dy_row_scale_grad=rg)
+    args = [a.cuda() for a in acts] + [dy.cuda(), off] + [a.cuda() for a in w]
+    if expert == "swiglu":
+        k = launched(m, lambda: m.xmoe_expert_ffn_bwd(r(B, d).cuda(), *args, *o, ws, **kw))
+    else:
+        k = launched(m, lambda: m.xmoe_expert_mlp2_bwd(r(B, d).cuda(), *args, expert, *o, ws, **kw))
+    sign = dy[:, 7].float().sign() * torch.stack([a[:, f - 1].float().sign() for a in acts]).prod(0)
+    assert torch.equal(rg.cpu(), float("inf") * sign)
+
+
 @pytest.mark.parametrize("E,d,f,rows,fwd,bwd,wgrads", [
     (4, 256, 256, 129, True, True, True), (4, 192, 256, 129, False, False, False), (4, 256, 192, 129, False, False, False),
     (64, 256, 256, 64 * 800, False, True, True), (64, 256, 256, 64 * 3200, False, False, False),
