@@ -6,14 +6,20 @@
 //   small:  64 x  64 outputs, 128 threads = 2 waves (2 x 1), wave tile 32 x 64, 32 KiB of LDS
 //
 // The matrix instruction is v_mfma_f32_32x32x16_bf16 for both types.  A float is the exact sum of three bf16 numbers (hi +
-// mid + lo, 8 bits each), a product of two floats the sum of nine products of bf16 numbers, each exact in float32; the six
-// of them that reach 2^-24 of the whole are taken: 192 clocks of the matrix cores per 16 k, where the float32 instruction
-// (v_mfma_f32_32x32x2_f32) takes 512.  The largest product left out is 2^-23 of the whole at worst and 2^-26 on average,
-// below what one float32 addition of the sum rounds off, and a sum has six roundings per 16 k instead of eight: against
-// float64 the results are nearer than those of the float32 instruction (training step, f32 cases: 1.2e-6 -> 1.0e-6 and
-// 3.9e-7 -> 3.5e-7).  An infinity has no finite parts, and the parts of a product that overflows may do so with either
-// sign: what comes out as NaN is computed again from the floats themselves (tile_recover).  The parts reach down to 2^-133: an
-// operand below 2^-110 (1e-33) is taken with an absolute error of 2^-134.
+// mid + lo, 8 bits each; the splitting of G. Henry, P. Tang, A. Heinecke, "Leveraging the bfloat16 artificial intelligence
+// datatype for higher-precision computations", 2019), a product of two floats the sum of nine products of bf16 numbers, each
+// exact in float32.  Six of them take 192 clocks of the matrix cores per 16 k, where the float32 instruction
+// (v_mfma_f32_32x32x2_f32) takes 512.  Left out are lo x lo, at most 2^-32 of the whole, and mid x lo and lo x mid, 2^-23
+// each at worst and 2^-26 on average: up to four times what a float32 product rounds off.  What makes up for it is that a sum
+// has an eighth of a float32 chain's roundings: per 16 k, hi x hi is added to it once and the five small products once,
+// summed among themselves before (added one by one they would each be cut off at the sum's last bit: this instruction
+// truncates).  Sums of up to kPlainK terms, which would lose by it, are the float32 instruction's.  Error against float64,
+// rms in 2^-24 of the sum of the terms' magnitudes, float32 instruction | this, for normal operands and for operands just
+// above 1 whose mid and lo are the largest: K 10 0.46 | 0.29 and 0.93 | 0.68, K 17 0.47 | 0.30 and 1.11 | 0.85, K 64 0.47 |
+// 0.21 and 1.81 | 1.07, K 1024 0.47 | 0.19 and 30.8 | 1.98; training steps 1.2e-6 -> 0.5e-6 and 4.0e-7 -> 2.5e-7.
+// An infinity has no finite parts, and the parts of a product that overflows may do so with either sign: what comes out as
+// NaN is computed again from the floats themselves (tile_recover).  The parts reach down to 2^-133: an operand below 2^-110
+// (1e-33) is taken with an absolute error of 2^-134.
 //
 // K is stepped by 64 bf16 (both operand tiles lie in LDS as [row or column][128 bytes of k]) or 16 floats ([row or
 // column][three parts of 32 bytes]), so that one 16-byte LDS read is a fragment of a matrix instruction.  The operands
@@ -318,8 +324,7 @@ __device__ __forceinline__ int tile_col(int ni) { return tile_col_base<BIG, DUAL
 // One K-step of the first MI 32-row blocks of the wave; k: valid k of the step, behind which there are zeros only.
 // Consecutive matrix instructions go to different accumulators.
 template <bool BIG, bool DUAL, int MI, int N>
-__device__ __forceinline__ void tile_compute(tile_f32x16_t (&acc)[N][2], const char* ta, const char* tb, int k,
-                                             const bf16_t*) {
+__device__ __forceinline__ void tile_compute(tile_f32x16_t (&acc)[N][2], const char* ta, const char* tb, int k) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int ra = (BIG ? (wave >> 1) * 64 : wave * 32) + (lane & 31);
 #pragma unroll
@@ -338,30 +343,44 @@ __device__ __forceinline__ void tile_compute(tile_f32x16_t (&acc)[N][2], const c
             for (int ni = 0; ni < 2; ++ni) acc[mi][ni] = tile_mfma(fa[mi], fb[ni], acc[mi][ni]);
     }
 }
-// float32: the six products of the parts that reach 2^-24 of the whole, the smallest first
+// float32: six products of the parts in ascending size, hi x hi into the sum, the others among themselves and then into the
+// sum
 template <bool BIG, bool DUAL, int MI, int N>
-__device__ __forceinline__ void tile_compute(tile_f32x16_t (&acc)[N][2], const char* ta, const char* tb, int,
-                                             const float*) {
+__device__ __forceinline__ void tile_compute_split(tile_f32x16_t (&acc)[N][2], const char* ta, const char* tb) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, c = lane >> 5;
     const int ra = (BIG ? (wave >> 1) * 64 : wave * 32) + (lane & 31);
-    uint4 fa[MI][3], fb[2][3];
+    uint4 fb[2][3];
 #pragma unroll
-    for (int p = 0; p < 3; ++p) {
-#pragma unroll
-        for (int mi = 0; mi < MI; ++mi)
-            fa[mi][p] = *reinterpret_cast<const uint4*>(ta + split_addr(ra + mi * 32, p, c));
+    for (int p = 0; p < 3; ++p)
 #pragma unroll
         for (int ni = 0; ni < 2; ++ni)
             fb[ni][p] = *reinterpret_cast<const uint4*>(tb + split_addr(tile_col<BIG, DUAL>(ni), p, c));
+    constexpr int kPa[5] = {0, 2, 1, 0, 1}, kPb[5] = {2, 0, 1, 1, 0};
+#pragma unroll
+    for (int mi = 0; mi < MI; ++mi) {
+        uint4 fa[3];
+#pragma unroll
+        for (int p = 0; p < 3; ++p) fa[p] = *reinterpret_cast<const uint4*>(ta + split_addr(ra + mi * 32, p, c));
+        tile_f32x16_t x[2];
+#pragma unroll
+        for (int ni = 0; ni < 2; ++ni)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) x[ni][v] = 0.f;
+#pragma unroll
+        for (int t = 0; t < 5; ++t)
+#pragma unroll
+            for (int ni = 0; ni < 2; ++ni) x[ni] = tile_mfma(fa[kPa[t]], fb[ni][kPb[t]], x[ni]);
+#pragma unroll
+        for (int ni = 0; ni < 2; ++ni) acc[mi][ni] = tile_mfma(fa[0], fb[ni][0], acc[mi][ni]);
+#pragma unroll
+        for (int ni = 0; ni < 2; ++ni)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[mi][ni][v] += x[ni][v];
     }
-    constexpr int kPa[6] = {0, 2, 1, 0, 1, 0}, kPb[6] = {2, 0, 1, 1, 0, 0};
-#pragma unroll
-    for (int t = 0; t < 6; ++t)
-#pragma unroll
-        for (int mi = 0; mi < MI; ++mi)
-#pragma unroll
-            for (int ni = 0; ni < 2; ++ni) acc[mi][ni] = tile_mfma(fa[mi][kPa[t]], fb[ni][kPb[t]], acc[mi][ni]);
 }
+
+// Sums of up to this many terms are float32's own: in them the products that are left out weigh as much as the roundings
+constexpr int kPlainK = 8;
 
 // acc += A B over K; smem holds TileShape<BIG>::kLds bytes; rows, cols: valid ones of the tile (may exceed it).  Every
 // thread of the block calls it.  A wave multiplies only its 32-row blocks that hold a valid row, and nothing if no
@@ -374,17 +393,23 @@ __device__ __forceinline__ void tile_mainloop(tile_f32x16_t (&acc)[TileShape<BIG
     constexpr int kBOff = TileShape<BIG>::kM * TileElem<T>::kRowBytes;
     constexpr int kBuf = kBOff + TileShape<BIG>::kN * TileElem<T>::kRowBytes;
     static_assert(2 * kBuf <= TileShape<BIG>::kLds, "two buffers");
-    if (K <= 0) return;   // block-uniform
+    if (K <= (std::is_same<T, float>::value ? kPlainK : 0)) return;   // block-uniform; float32: tile_recover's sums
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wcol = BIG ? (wave & 1) * (DUAL ? 32 : 64) : 0;
     const int mi_n = cols > wcol ? (rows - (BIG ? (wave >> 1) * 64 : wave * 32) + 31) / 32 : 0;
     const int n = (K + kK - 1) / kK, n_full = a.wide() && b.wide() ? K / kK : 0;
     auto compute = [&](auto P, int k) {
         const char* t = smem + P.value * kBuf;
+        auto blocks = [&](auto M) {
+            if constexpr (std::is_same<T, float>::value)
+                tile_compute_split<BIG, DUAL, M.value>(acc, t, t + kBOff);
+            else
+                tile_compute<BIG, DUAL, M.value>(acc, t, t + kBOff, k);
+        };
         if (mi_n >= MI)
-            tile_compute<BIG, DUAL, MI>(acc, t, t + kBOff, k, (const T*)nullptr);
+            blocks(std::integral_constant<int, MI>{});
         else if (MI == 2 && mi_n == 1)
-            tile_compute<BIG, DUAL, 1>(acc, t, t + kBOff, k, (const T*)nullptr);
+            blocks(std::integral_constant<int, 1>{});
     };
     auto load_whole = [&](auto S, int i) {
         a.advance(i * kK, K);
@@ -439,9 +464,9 @@ __device__ __forceinline__ void tile_mainloop(tile_f32x16_t (&acc)[TileShape<BIG
     }
 }
 
-// float32: results that the parts lose.  A 32 x 32 block of accumulators that holds a NaN is multiplied again with the
-// float32 instruction, straight from memory, and its NaNs take what comes out: an infinity where the floats give one, NaN
-// where they do.  Finite operands whose products don't overflow never come here, so nothing is done for speed.
+// float32: results that the parts lose, and sums of at most kPlainK terms.  A 32 x 32 block of accumulators that holds a NaN
+// is multiplied again with the float32 instruction, straight from memory, and its NaNs take what comes out: an infinity
+// where the floats give one, NaN where they do.  Finite operands whose products don't overflow never come here.
 // One operand: element (i, k) of the tile, i its row (of A) or column (of B), n of them valid.
 struct PlainOp {
     const float* p;
@@ -465,7 +490,7 @@ __device__ __forceinline__ void tile_recover(tile_f32x16_t (&acc)[TileShape<BIG>
     for (int mi = 0; mi < TileShape<BIG>::kMI; ++mi)
 #pragma unroll
         for (int ni = 0; ni < 2; ++ni) {
-            bool lost = false;
+            bool lost = K <= kPlainK;
 #pragma unroll
             for (int v = 0; v < 16; ++v) lost |= acc[mi][ni][v] != acc[mi][ni][v];
             if (!__any(lost)) continue;
@@ -476,14 +501,21 @@ __device__ __forceinline__ void tile_recover(tile_f32x16_t (&acc)[TileShape<BIG>
             for (int v = 0; v < 16; ++v) x[v] = 0.f;
             for (int set = 0; set < sets; ++set) {
                 const PlainPair q = pairs(set, ni);
-                for (int k0 = 0; k0 < K; k0 += 2) {   // both halves of the wave go round together
-                    const int k = k0 + (lane >> 5);
-                    const float a = k < K ? q.a.at(i, k) : 0.f, b = k < K ? q.b.at(j, k) : 0.f;
-                    x = __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, x, 0, 0, 0);
+                for (int k0 = 0; k0 < K; k0 += kPlainK) {   // both halves of the wave go round together
+                    float a[kPlainK / 2], b[kPlainK / 2];
+#pragma unroll
+                    for (int t = 0; t < kPlainK / 2; ++t) {
+                        const int k = k0 + 2 * t + (lane >> 5);
+                        a[t] = k < K ? q.a.at(i, k) : 0.f;
+                        b[t] = k < K ? q.b.at(j, k) : 0.f;
+                    }
+#pragma unroll
+                    for (int t = 0; t < kPlainK / 2; ++t) x = __builtin_amdgcn_mfma_f32_32x32x2f32(a[t], b[t], x, 0, 0, 0);
                 }
             }
 #pragma unroll
-            for (int v = 0; v < 16; ++v) acc[mi][ni][v] = acc[mi][ni][v] != acc[mi][ni][v] ? x[v] : acc[mi][ni][v];
+            for (int v = 0; v < 16; ++v)
+                acc[mi][ni][v] = K <= kPlainK || acc[mi][ni][v] != acc[mi][ni][v] ? x[v] : acc[mi][ni][v];
         }
 }
 

@@ -1,5 +1,6 @@
 """Edges of the small passes and of the products: infinities in the operands of the expert products, segments longer than
-the window of the token-dropping pass, the merged pass over the combine weights' gradient, routing over NaNs, tile maps of many experts.
+the window of the token-dropping pass, the merged pass over the combine weights' gradient, routing over NaNs, the bits of the
+float32 products, tile maps of many experts.
 
 Integers, copies and what an infinity does not reach are compared bit for bit; the many-experts products as in
 test_gpu_direct_tiles.py's reasoning for float32: sums of at most 64 terms of order one, 2^-24 each, held to 2^-16."""
@@ -104,6 +105,30 @@ def test_largest_floats():
             want = x[s].double() @ a[e].double()
             err = (o[name][s].double() - want).abs() / want.pow(2).mean(1, keepdim=True).sqrt()
             assert float(err.max()) < 2.0 ** -16, (name, float(err.max()))
+
+
+def product(m, x, w):
+    """x @ w for float32 [B, K] and [K, N]: the first product of the two-matrix expert with no activation."""
+    (B, K), N = x.shape, w.shape[1]
+    h, y = torch.empty((B, N), device="cuda"), torch.empty((B, K), device="cuda")
+    ws = m.alloc_workspace(m.xmoe_workspace_bytes(m.WS_MLP2_FWD, B, K, 1, 1, N, m.XMOE_F32))
+    off = torch.tensor([0, B], dtype=torch.int32, device="cuda")
+    m.xmoe_expert_mlp2_fwd(x.cuda(), off, w[None].contiguous().cuda(), torch.zeros((1, N, K), device="cuda"), "identity", h, y, ws)
+    return h.cpu()
+
+
+@pytest.mark.parametrize("K", [1, 2, 3, 4, 7, 8, 9, 15, 16, 17, 33, 100])
+@pytest.mark.parametrize("B", [70, 3000])
+def test_float32_products_round_no_more_than_float32(B, K):
+    """A chain of float32 additions rounds each of its K sums by at most 2^-24 of the sum of the terms' magnitudes.  Operands
+    of all bits, and ones whose last 16 bits are as large as they can be."""
+    import paper_2508_13337_amd as m
+    g = torch.Generator().manual_seed(B + K)
+    last16 = lambda *s: 1 + 2.0 ** -7 - torch.randint(1, 300, s, generator=g).float() * 2.0 ** -23
+    for new in (lambda *s: torch.randn(s, generator=g), last16):
+        x, w = new(B, K), new(K, 96)
+        err = (product(m, x, w).double() - x.double() @ w.double()).abs()
+        assert float((err / (x.double().abs() @ w.double().abs())).max()) <= K * 2.0 ** -24
 
 
 # one expert with one, two and three windows of 8192 rows, ties across them; capacities at the windows' edges
