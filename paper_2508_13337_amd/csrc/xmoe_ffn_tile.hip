@@ -401,19 +401,29 @@ template <typename T, bool BIG, bool GP, bool GQ>
 __device__ __forceinline__ void wgrad_tile(const WgradJob<T>& j, int u, int e, int lo, int K, char* smem) {
     using S = TileShape<BIG>;
     const int m0 = (u % j.tiles_m) * S::kM, n0 = (u / j.tiles_m) * S::kN;
-    ColSrc<T, S::kThreads, GP> a;
-    ColSrc<T, S::kThreads, GQ> b;
-    a.init(j.P + m0 + (GP ? 0 : (size_t)lo * j.M), nullptr, j.M, j.M - m0, GP ? j.p_index + lo : nullptr, K);
-    b.init(j.Q + n0 + (GQ ? 0 : (size_t)lo * j.N), nullptr, j.N, j.N - n0, GQ ? j.q_index + lo : nullptr, K);
+    const T *P = j.P + m0 + (GP ? 0 : (size_t)lo * j.M), *Q = j.Q + n0 + (GQ ? 0 : (size_t)lo * j.N);
+    const int32_t *pi = GP ? j.p_index + lo : nullptr, *qi = GQ ? j.q_index + lo : nullptr;
+    T* dW = j.dW + (size_t)e * j.M * j.N + (size_t)m0 * j.N + n0;
     tile_f32x16_t acc[S::kMI][2];
     tile_zero<BIG>(acc);
+    if constexpr (std::is_same<T, float>::value) {
+        const PlainPair q = {{P, 1, (size_t)j.M, nullptr, pi, j.M - m0}, {Q, 1, (size_t)j.N, nullptr, qi, j.N - n0}};
+        if (K <= kPlainK) {   // few rows are usual here
+            tile_plain<BIG>(acc, K, q);
+            tile_store<T, BIG>(acc, dW, j.N, j.M - m0, j.N - n0);
+            return;
+        }
+    }
+    ColSrc<T, S::kThreads, GP> a;
+    ColSrc<T, S::kThreads, GQ> b;
+    a.init(P, nullptr, j.M, j.M - m0, pi, K);
+    b.init(Q, nullptr, j.N, j.N - n0, qi, K);
     tile_mainloop<T, BIG, false, true>(acc, K, j.M - m0, j.N - n0, a, b, smem);
     if constexpr (std::is_same<T, float>::value)
         tile_recover<BIG, false>(acc, K, 1, [&](int, int) {
-            return PlainPair{{j.P + m0 + (GP ? 0 : (size_t)lo * j.M), 1, (size_t)j.M, nullptr, GP ? j.p_index + lo : nullptr, j.M - m0},
-                             {j.Q + n0 + (GQ ? 0 : (size_t)lo * j.N), 1, (size_t)j.N, nullptr, GQ ? j.q_index + lo : nullptr, j.N - n0}};
+            return PlainPair{{P, 1, (size_t)j.M, nullptr, pi, j.M - m0}, {Q, 1, (size_t)j.N, nullptr, qi, j.N - n0}};
         });
-    tile_store<T, BIG>(acc, j.dW + (size_t)e * j.M * j.N + (size_t)m0 * j.N + n0, j.N, j.M - m0, j.N - n0);
+    tile_store<T, BIG>(acc, dW, j.N, j.M - m0, j.N - n0);
 }
 
 template <typename T, bool BIG>

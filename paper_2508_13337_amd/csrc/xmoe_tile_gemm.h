@@ -482,6 +482,35 @@ struct PlainOp {
 struct PlainPair {
     PlainOp a, b;
 };
+// K <= kPlainK: acc += the product of the pair, its loads in flight together
+template <bool BIG>
+__device__ __forceinline__ void tile_plain(tile_f32x16_t (&acc)[TileShape<BIG>::kMI][2], int K, const PlainPair& q) {
+    constexpr int MI = TileShape<BIG>::kMI, NT = kPlainK / 2;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    float a[MI][NT], b[2][NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+        const int k = 2 * t + (lane >> 5);
+#pragma unroll
+        for (int mi = 0; mi < MI; ++mi) a[mi][t] = 0.f;
+        b[0][t] = b[1][t] = 0.f;
+        if (k >= K) continue;
+#pragma unroll
+        for (int mi = 0; mi < MI; ++mi)
+            a[mi][t] = q.a.at((BIG ? (wave >> 1) * 64 : wave * 32) + mi * 32 + (lane & 31), k);
+#pragma unroll
+        for (int ni = 0; ni < 2; ++ni) b[ni][t] = q.b.at(tile_col<BIG, false>(ni), k);
+    }
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+        if (2 * t >= K) break;   // both halves of the wave go on together
+#pragma unroll
+        for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+            for (int ni = 0; ni < 2; ++ni)
+                acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[mi][t], b[ni][t], acc[mi][ni], 0, 0, 0);
+    }
+}
 // pairs(set, ni): the operands of product `set` of the sum; DUAL: b is the matrix of column block ni
 template <bool BIG, bool DUAL, class Pairs>
 __device__ __forceinline__ void tile_recover(tile_f32x16_t (&acc)[TileShape<BIG>::kMI][2], int K, int sets, Pairs&& pairs) {
@@ -501,16 +530,16 @@ __device__ __forceinline__ void tile_recover(tile_f32x16_t (&acc)[TileShape<BIG>
             for (int v = 0; v < 16; ++v) x[v] = 0.f;
             for (int set = 0; set < sets; ++set) {
                 const PlainPair q = pairs(set, ni);
-                for (int k0 = 0; k0 < K; k0 += kPlainK) {   // both halves of the wave go round together
-                    float a[kPlainK / 2], b[kPlainK / 2];
+                for (int k0 = 0; k0 < K; k0 += 8) {   // both halves of the wave go round together
+                    float a[4], b[4];
 #pragma unroll
-                    for (int t = 0; t < kPlainK / 2; ++t) {
+                    for (int t = 0; t < 4; ++t) {
                         const int k = k0 + 2 * t + (lane >> 5);
                         a[t] = k < K ? q.a.at(i, k) : 0.f;
                         b[t] = k < K ? q.b.at(j, k) : 0.f;
                     }
 #pragma unroll
-                    for (int t = 0; t < kPlainK / 2; ++t) x = __builtin_amdgcn_mfma_f32_32x32x2f32(a[t], b[t], x, 0, 0, 0);
+                    for (int t = 0; t < 4; ++t) x = __builtin_amdgcn_mfma_f32_32x32x2f32(a[t], b[t], x, 0, 0, 0);
                 }
             }
 #pragma unroll
