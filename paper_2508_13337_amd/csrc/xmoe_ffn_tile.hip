@@ -170,7 +170,7 @@ __global__ XMOE_TILE_BOUNDS void ffn_gateup_mfma_kernel(const T* __restrict__ xd
     tile_zero<BIG>(acc);
     tile_mainloop<T, BIG, true, false>(acc, d, t.rows, f - n0, a, b, smem);
     if constexpr (std::is_same<T, float>::value)
-        tile_recover<BIG, true>(acc, d, 1, [&](int, int ni) {
+        tile_finish<BIG, true>(acc, d, 1, [&](int, int ni) {
             return PlainPair{{row_index ? xd : xd + (size_t)t.row0 * d, (size_t)d, 1, row_index ? row_index + t.row0 : nullptr, nullptr, t.rows},
                              {(ni ? wu : wg) + (size_t)t.e * d * f + n0, 1, (size_t)f, nullptr, nullptr, f - n0}};
         });
@@ -229,7 +229,7 @@ __global__ XMOE_TILE_BOUNDS void ffn_down_mfma_kernel(const T* __restrict__ A, c
     tile_zero<BIG>(acc);
     tile_mainloop<T, BIG, false, false>(acc, f, t.rows, d - n0, a, b, smem);
     if constexpr (std::is_same<T, float>::value)
-        tile_recover<BIG, false>(acc, f, 1, [&](int, int) {
+        tile_finish<BIG, false>(acc, f, 1, [&](int, int) {
             return PlainPair{{A + (size_t)t.row0 * f, (size_t)f, 1, nullptr, nullptr, t.rows},
                              {wd + (size_t)t.e * f * d + n0, 1, (size_t)d, nullptr, nullptr, d - n0}};
         });
@@ -259,7 +259,7 @@ __device__ __forceinline__ void dact_tile(const T* __restrict__ dY, const int32_
     tile_zero<BIG>(acc);
     tile_mainloop<T, BIG, false, false>(acc, d, t.rows, f - n0, a, b, smem);
     if constexpr (std::is_same<T, float>::value)
-        tile_recover<BIG, false>(acc, d, 1, [&](int, int) {
+        tile_finish<BIG, false>(acc, d, 1, [&](int, int) {
             return PlainPair{{dy_index ? dY : dY + (size_t)t.row0 * d, (size_t)d, 1, dy_index ? dy_index + t.row0 : nullptr, nullptr, t.rows},
                              {w + ((size_t)t.e * f + n0) * d, (size_t)d, 1, nullptr, nullptr, f - n0}};
         });
@@ -370,7 +370,7 @@ __global__ XMOE_TILE_BOUNDS void ffn_dx_mfma_kernel(const T* __restrict__ dG, co
         tile_mainloop<T, BIG, false, false>(acc, f, t.rows, d - n0, a, b, smem);
     }
     if constexpr (std::is_same<T, float>::value)
-        tile_recover<BIG, false>(acc, f, dU ? 2 : 1, [&](int set, int) {
+        tile_finish<BIG, false>(acc, f, dU ? 2 : 1, [&](int set, int) {
             return PlainPair{{(set ? dU : dG) + (size_t)t.row0 * f, (size_t)f, 1, nullptr, nullptr, t.rows},
                              {(set ? wu : wg) + ((size_t)t.e * d + n0) * f, (size_t)f, 1, nullptr, nullptr, d - n0}};
         });
@@ -420,7 +420,7 @@ __device__ __forceinline__ void wgrad_tile(const WgradJob<T>& j, int u, int e, i
     b.init(Q, nullptr, j.N, j.N - n0, qi, K);
     tile_mainloop<T, BIG, false, true>(acc, K, j.M - m0, j.N - n0, a, b, smem);
     if constexpr (std::is_same<T, float>::value)
-        tile_recover<BIG, false>(acc, K, 1, [&](int, int) {
+        tile_finish<BIG, false>(acc, K, 1, [&](int, int) {
             return PlainPair{{P, 1, (size_t)j.M, nullptr, pi, j.M - m0}, {Q, 1, (size_t)j.N, nullptr, qi, j.N - n0}};
         });
     tile_store<T, BIG>(acc, dW, j.N, j.M - m0, j.N - n0);
@@ -467,7 +467,7 @@ __global__ XMOE_TILE_BOUNDS void mlp2_up_mfma_kernel(const T* __restrict__ xd,
     tile_zero<BIG>(acc);
     tile_mainloop<T, BIG, false, false>(acc, d, t.rows, f - n0, a, b, smem);
     if constexpr (std::is_same<T, float>::value)
-        tile_recover<BIG, false>(acc, d, 1, [&](int, int) {
+        tile_finish<BIG, false>(acc, d, 1, [&](int, int) {
             return PlainPair{{row_index ? xd : xd + (size_t)t.row0 * d, (size_t)d, 1, row_index ? row_index + t.row0 : nullptr, nullptr, t.rows},
                              {w1 + (size_t)t.e * d * f + n0, 1, (size_t)f, nullptr, nullptr, f - n0}};
         });

@@ -17,9 +17,10 @@
 // rms in 2^-24 of the sum of the terms' magnitudes, float32 instruction | this, for normal operands and for operands just
 // above 1 whose mid and lo are the largest: K 10 0.46 | 0.29 and 0.93 | 0.68, K 17 0.47 | 0.30 and 1.11 | 0.85, K 64 0.47 |
 // 0.21 and 1.81 | 1.07, K 1024 0.47 | 0.19 and 30.8 | 1.98; training steps 1.2e-6 -> 0.5e-6 and 4.0e-7 -> 2.5e-7.
-// An infinity has no finite parts, and the parts of a product that overflows may do so with either sign: what comes out as
-// NaN is computed again from the floats themselves (tile_recover).  The parts reach down to 2^-133: an operand below 2^-110
-// (1e-33) is taken with an absolute error of 2^-134.
+// The parts are taken of 2^24 times each operand, so that the bits of the smallest floats too are parts in bf16's normal
+// range, and a sum is multiplied by 2^-48 at its end: both exact but for results below 2^-126.  What is not finite then (an
+// infinity or an operand from 2^104 on has no finite parts, a sum from 2^80 on overflows) is computed again from the floats
+// themselves (tile_finish).
 //
 // K is stepped by 64 bf16 (both operand tiles lie in LDS as [row or column][128 bytes of k]) or 16 floats ([row or
 // column][three parts of 32 bytes]), so that one 16-byte LDS read is a fragment of a matrix instruction.  The operands
@@ -90,13 +91,15 @@ __device__ __forceinline__ int split_addr(int r, int p, int c) {
     return r * 96 + p * 32 + ((c ^ (((r >> 2) ^ (r >> 3)) & 1)) << 4);
 }
 
-// The three bf16 parts of four floats, x = hi + mid + lo exactly (8 bits each; hi is cut off, so that the largest
-// finite floats stay finite, mid and lo are rounded to nearest)
+// The three bf16 parts of four floats, x kPartScale = hi + mid + lo exactly (8 bits each; hi is cut off, mid and lo are
+// rounded to nearest); kUnscale takes the scales of a product's operands off
+constexpr float kPartScale = 0x1p24f, kUnscale = 0x1p-48f;
 __device__ __forceinline__ void split4(const uint32_t (&x)[4], uint2 (&part)[3]) {
     uint32_t h[2], m[2], l[2];
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-        const uint32_t a = x[2 * i], b = x[2 * i + 1];
+        const uint32_t a = __float_as_uint(__uint_as_float(x[2 * i]) * kPartScale);
+        const uint32_t b = __float_as_uint(__uint_as_float(x[2 * i + 1]) * kPartScale);
         h[i] = __builtin_amdgcn_perm(b, a, 0x07060302u);
         const float ra = __uint_as_float(a) - __uint_as_float(a & 0xffff0000u);
         const float rb = __uint_as_float(b) - __uint_as_float(b & 0xffff0000u);
@@ -393,7 +396,7 @@ __device__ __forceinline__ void tile_mainloop(tile_f32x16_t (&acc)[TileShape<BIG
     constexpr int kBOff = TileShape<BIG>::kM * TileElem<T>::kRowBytes;
     constexpr int kBuf = kBOff + TileShape<BIG>::kN * TileElem<T>::kRowBytes;
     static_assert(2 * kBuf <= TileShape<BIG>::kLds, "two buffers");
-    if (K <= (std::is_same<T, float>::value ? kPlainK : 0)) return;   // block-uniform; float32: tile_recover's sums
+    if (K <= (std::is_same<T, float>::value ? kPlainK : 0)) return;   // block-uniform; float32: tile_finish's sums
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wcol = BIG ? (wave & 1) * (DUAL ? 32 : 64) : 0;
     const int mi_n = cols > wcol ? (rows - (BIG ? (wave >> 1) * 64 : wave * 32) + 31) / 32 : 0;
@@ -464,9 +467,10 @@ __device__ __forceinline__ void tile_mainloop(tile_f32x16_t (&acc)[TileShape<BIG
     }
 }
 
-// float32: results that the parts lose, and sums of at most kPlainK terms.  A 32 x 32 block of accumulators that holds a NaN
-// is multiplied again with the float32 instruction, straight from memory, and its NaNs take what comes out: an infinity
-// where the floats give one, NaN where they do.  Finite operands whose products don't overflow never come here.
+// float32: what stands between the sums of products of parts and the results: the parts' scale, the results that the parts
+// lose, and sums of at most kPlainK terms.  A 32 x 32 block of accumulators that holds an infinity or a NaN is multiplied
+// again with the float32 instruction, straight from memory, and these take what comes out: an infinity where the floats give
+// one, NaN where they do.
 // One operand: element (i, k) of the tile, i its row (of A) or column (of B), n of them valid.
 struct PlainOp {
     const float* p;
@@ -513,7 +517,7 @@ __device__ __forceinline__ void tile_plain(tile_f32x16_t (&acc)[TileShape<BIG>::
 }
 // pairs(set, ni): the operands of product `set` of the sum; DUAL: b is the matrix of column block ni
 template <bool BIG, bool DUAL, class Pairs>
-__device__ __forceinline__ void tile_recover(tile_f32x16_t (&acc)[TileShape<BIG>::kMI][2], int K, int sets, Pairs&& pairs) {
+__device__ __forceinline__ void tile_finish(tile_f32x16_t (&acc)[TileShape<BIG>::kMI][2], int K, int sets, Pairs&& pairs) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
     for (int mi = 0; mi < TileShape<BIG>::kMI; ++mi)
@@ -521,8 +525,12 @@ __device__ __forceinline__ void tile_recover(tile_f32x16_t (&acc)[TileShape<BIG>
         for (int ni = 0; ni < 2; ++ni) {
             bool lost = K <= kPlainK;
 #pragma unroll
-            for (int v = 0; v < 16; ++v) lost |= acc[mi][ni][v] != acc[mi][ni][v];
-            if (!__any(lost)) continue;
+            for (int v = 0; v < 16; ++v) lost |= !(fabsf(acc[mi][ni][v]) < INFINITY);
+            if (!__any(lost)) {
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[mi][ni][v] *= kUnscale;
+                continue;
+            }
             const int i = (BIG ? (wave >> 1) * 64 : wave * 32) + mi * 32 + (lane & 31);
             const int j = tile_col<BIG, DUAL>(DUAL ? 0 : ni);
             tile_f32x16_t x;
@@ -544,7 +552,7 @@ __device__ __forceinline__ void tile_recover(tile_f32x16_t (&acc)[TileShape<BIG>
             }
 #pragma unroll
             for (int v = 0; v < 16; ++v)
-                acc[mi][ni][v] = K <= kPlainK || acc[mi][ni][v] != acc[mi][ni][v] ? x[v] : acc[mi][ni][v];
+                acc[mi][ni][v] = K > kPlainK && fabsf(acc[mi][ni][v]) < INFINITY ? acc[mi][ni][v] * kUnscale : x[v];
         }
 }
 

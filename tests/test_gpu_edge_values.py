@@ -131,6 +131,21 @@ def test_float32_products_round_no_more_than_float32(B, K):
         assert float((err / (x.double().abs() @ w.double().abs())).max()) <= K * 2.0 ** -24
 
 
+@pytest.mark.parametrize("K", [7, 40])
+@pytest.mark.parametrize("ex,ew", [(-120, 100), (-126, 110), (-140, 120), (-100, -20), (-110, -33), (103, 20), (104, -20), (126, -60),
+                                   (40, 39), (41, 40), (60, 60)])
+def test_float32_products_of_small_and_large_operands(ex, ew, K):
+    """The whole range of float32, subnormal operands and results included: rounded as any other product (as above; a result
+    below 2^-126 by half of 2^-149 once more)."""
+    import paper_2508_13337_amd as m
+    g = torch.Generator().manual_seed(K)
+    x, w = ((torch.rand(s, generator=g) + 0.5) * torch.randint(0, 2, s, generator=g).mul(2).sub(1) for s in ((300, K), (K, 96)))
+    x, w = (torch.ldexp(t.double(), torch.tensor(e)).float() for t, e in ((x, ex), (w, ew)))
+    want = x.double() @ w.double()
+    bound = K * 2.0 ** -24 * (x.double().abs() @ w.double().abs()) + (K + 1) * 2.0 ** -150
+    assert bool(((product(m, x, w).double() - want).abs() <= bound).all())
+
+
 # one expert with one, two and three windows of 8192 rows, ties across them; capacities at the windows' edges
 @pytest.mark.parametrize("T,cap", [(8192, 8191), (8193, 8192), (16385, 8193), (16385, 16384), (20000, 3), (20000, 12000)])
 def test_token_dropping_of_long_segments(T, cap):
