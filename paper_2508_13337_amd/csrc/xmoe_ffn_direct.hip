@@ -1,6 +1,5 @@
 // Products of the expert MLP on 128 x 128 bf16 tiles with direct-to-LDS loads (xmoe_tile_direct.h):
-//   - widths that are multiples of 8 but not of 64, in place of the register-staged tiles (the launch profiler counts them
-//     under those tiles' names);
+//   - widths that are multiples of 8 but not of 64, in place of the register-staged tiles;
 //   - widths that are multiples of 64 where the 256 x 256 tiles of the direct-to-LDS kernels are too few for the chip, or
 //     half empty (direct_fwd, direct_bwd, direct_wgrads below).
 //
@@ -358,11 +357,11 @@ template <bool FAST>
 static int fwd_direct(const FfnArgs& a, hipStream_t s) {
     int st = tile_map_direct(a, false, s);
     if (st != XMOE_OK) return st;
-    XMOE_LAUNCH(FAST ? K_FFN_GATEUP_DIRECT : K_FFN_GATEUP_MFMA, s,
+    XMOE_LAUNCH(K_FFN_GATEUP_DIRECT, s,
                 hipLaunchKernelGGL((ffn_gateup_direct_kernel<FAST>), grid_direct(a, a.f, 64), dim3(256), 0, s,
                                    (const bf16_t*)a.xd, a.row_index, a.off, a.map, a.d, a.f, (const bf16_t*)a.wg,
                                    (const bf16_t*)a.wu, (bf16_t*)a.g, (bf16_t*)a.u, (bf16_t*)a.act));
-    XMOE_LAUNCH(FAST ? K_FFN_DOWN_DIRECT : K_FFN_DOWN_MFMA, s,
+    XMOE_LAUNCH(K_FFN_DOWN_DIRECT, s,
                 hipLaunchKernelGGL(ffn_down_direct_kernel, grid_direct(a, a.d, 128), dim3(256), 0, s, (const bf16_t*)a.act,
                                    a.off, a.map, a.d, a.f, (const bf16_t*)a.wd, (bf16_t*)a.y));
     return XMOE_OK;
@@ -375,7 +374,7 @@ template <bool FAST>
 static int bwd_rows_direct(const FfnArgs& a, hipStream_t s) {
     int st = tile_map_direct(a, true, s);
     if (st != XMOE_OK) return st;
-    XMOE_LAUNCH(FAST ? K_FFN_DACT_DIRECT : K_FFN_DACT_MFMA, s,
+    XMOE_LAUNCH(K_FFN_DACT_DIRECT, s,
                 hipLaunchKernelGGL((ffn_dact_direct_kernel<FAST>), grid_direct(a, a.f, 128), dim3(256), 0, s,
                                    (const bf16_t*)a.dy, a.dy_index, a.dy_scale, a.off, a.map, a.d, a.f, (const bf16_t*)a.wd,
                                    (const bf16_t*)a.g, (const bf16_t*)a.u, (bf16_t*)a.dg, (bf16_t*)a.du, (bf16_t*)a.act,
@@ -384,7 +383,7 @@ static int bwd_rows_direct(const FfnArgs& a, hipStream_t s) {
         st = launch_row_grad_reduce(a.row_part, (a.f + 63) / 64, a.B, a.row_grad, s);
         if (st != XMOE_OK) return st;
     }
-    XMOE_LAUNCH(FAST ? K_FFN_DX_DIRECT : K_FFN_DX_MFMA, s,
+    XMOE_LAUNCH(K_FFN_DX_DIRECT, s,
                 hipLaunchKernelGGL((ffn_dx_direct_kernel<true>), grid_direct(a, a.d, 128), dim3(256), 0, s,
                                    (const bf16_t*)a.dg, (const bf16_t*)a.du, a.off, a.map, a.d, a.f, (const bf16_t*)a.wg,
                                    (const bf16_t*)a.wu, (bf16_t*)a.dxd));
@@ -394,7 +393,7 @@ int ffn_bwd_rows_direct(const FfnArgs& a, hipStream_t s) {
     return fast_act(a.d, a.f) ? bwd_rows_direct<true>(a, s) : bwd_rows_direct<false>(a, s);
 }
 
-static int launch_wgrads(DirectWgrads w, int n_jobs, int kid, int E, int d, int f, const int32_t* off, const int32_t* sched,
+static int launch_wgrads(DirectWgrads w, int n_jobs, int E, int d, int f, const int32_t* off, const int32_t* sched,
                          hipStream_t s) {
     for (int i = 0; i < n_jobs; ++i) w.job[i].tiles_m = (w.job[i].M + 127) / 128;
     w.n_jobs = n_jobs;
@@ -402,7 +401,7 @@ static int launch_wgrads(DirectWgrads w, int n_jobs, int kid, int E, int d, int 
     w.run = (w.tiles + 7) / 8;
     w.runs = (w.tiles + w.run - 1) / w.run;
     const dim3 grid((unsigned)(((long long)n_jobs * E * w.runs + 7) / 8 * 8 * w.run));
-    XMOE_LAUNCH(kid, s, hipLaunchKernelGGL(ffn_wgrad_direct_kernel, grid, dim3(256), 0, s, w, E, off, sched));
+    XMOE_LAUNCH(K_FFN_WGRAD_DIRECT, s, hipLaunchKernelGGL(ffn_wgrad_direct_kernel, grid, dim3(256), 0, s, w, E, off, sched));
     return XMOE_OK;
 }
 int ffn_bwd_wgrads_direct(const FfnArgs& a, hipStream_t s) {
@@ -410,13 +409,13 @@ int ffn_bwd_wgrads_direct(const FfnArgs& a, hipStream_t s) {
     w.job[0] = {(const bf16_t*)a.act, (const bf16_t*)a.dy, nullptr, a.dy_index, a.f, a.d, 0, (bf16_t*)a.dwd};
     w.job[1] = {(const bf16_t*)a.xd, (const bf16_t*)a.dg, a.row_index, nullptr, a.d, a.f, 0, (bf16_t*)a.dwg};
     w.job[2] = {(const bf16_t*)a.xd, (const bf16_t*)a.du, a.row_index, nullptr, a.d, a.f, 0, (bf16_t*)a.dwu};
-    return launch_wgrads(w, 3, fast_act(a.d, a.f) ? K_FFN_WGRAD_DIRECT : K_FFN_WGRAD_MFMA, a.E, a.d, a.f, a.off, a.sched, s);
+    return launch_wgrads(w, 3, a.E, a.d, a.f, a.off, a.sched, s);
 }
 int mlp2_bwd_wgrads_direct(const Mlp2Args& a, hipStream_t s) {
     DirectWgrads w = {};
     w.job[0] = {(const bf16_t*)a.a_buf, (const bf16_t*)a.dy, nullptr, a.dy_index, a.f, a.d, 0, (bf16_t*)a.dw2};
     w.job[1] = {(const bf16_t*)a.xd, (const bf16_t*)a.dh, a.row_index, nullptr, a.d, a.f, 0, (bf16_t*)a.dw1};
-    return launch_wgrads(w, 2, fast_act(a.d, a.f) ? K_FFN_WGRAD_DIRECT : K_FFN_WGRAD_MFMA, a.E, a.d, a.f, a.off, a.sched, s);
+    return launch_wgrads(w, 2, a.E, a.d, a.f, a.off, a.sched, s);
 }
 
 template <bool FAST>
@@ -424,13 +423,13 @@ static int mlp2_fwd_direct_as(const Mlp2Args& a, hipStream_t s) {
     int st = tile_map_direct(a, false, s);
     if (st != XMOE_OK) return st;
 #define XMOE_CALL(ACT)                                                                                                    \
-    XMOE_LAUNCH(FAST ? K_MLP2_UP_DIRECT : K_MLP2_UP_MFMA, s,                                                              \
+    XMOE_LAUNCH(K_MLP2_UP_DIRECT, s,                                                              \
                 hipLaunchKernelGGL((mlp2_up_direct_kernel<ACT, FAST>), grid_direct(a, a.f, 128), dim3(256), 0, s,          \
                                    (const bf16_t*)a.xd, a.row_index, a.off, a.map, a.d, a.f, (const bf16_t*)a.w1,          \
                                    (bf16_t*)a.h, (bf16_t*)a.a_buf))
     XMOE_DISPATCH_ACT(a.act, XMOE_CALL);
 #undef XMOE_CALL
-    XMOE_LAUNCH(FAST ? K_FFN_DOWN_DIRECT : K_FFN_DOWN_MFMA, s,
+    XMOE_LAUNCH(K_FFN_DOWN_DIRECT, s,
                 hipLaunchKernelGGL(ffn_down_direct_kernel, grid_direct(a, a.d, 128), dim3(256), 0, s,
                                    (const bf16_t*)a.a_buf, a.off, a.map, a.d, a.f, (const bf16_t*)a.w2, (bf16_t*)a.y));
     return XMOE_OK;
@@ -444,7 +443,7 @@ static int mlp2_bwd_rows_direct_as(const Mlp2Args& a, hipStream_t s) {
     int st = tile_map_direct(a, true, s);
     if (st != XMOE_OK) return st;
 #define XMOE_CALL(ACT)                                                                                                    \
-    XMOE_LAUNCH(FAST ? K_MLP2_DACT_DIRECT : K_MLP2_DACT_MFMA, s,                                                          \
+    XMOE_LAUNCH(K_MLP2_DACT_DIRECT, s,                                                          \
                 hipLaunchKernelGGL((mlp2_dact_direct_kernel<ACT, FAST>), grid_direct(a, a.f, 128), dim3(256), 0, s,        \
                                    (const bf16_t*)a.dy, a.dy_index, a.dy_scale, a.off, a.map, a.d, a.f,                    \
                                    (const bf16_t*)a.w2, (const bf16_t*)a.h, (bf16_t*)a.dh, (bf16_t*)a.a_buf, a.row_part,   \
@@ -455,7 +454,7 @@ static int mlp2_bwd_rows_direct_as(const Mlp2Args& a, hipStream_t s) {
         st = launch_row_grad_reduce(a.row_part, (a.f + 63) / 64, a.B, a.row_grad, s);
         if (st != XMOE_OK) return st;
     }
-    XMOE_LAUNCH(FAST ? K_FFN_DX_DIRECT : K_FFN_DX_MFMA, s,
+    XMOE_LAUNCH(K_FFN_DX_DIRECT, s,
                 hipLaunchKernelGGL((ffn_dx_direct_kernel<false>), grid_direct(a, a.d, 128), dim3(256), 0, s,
                                    (const bf16_t*)a.dh, (const bf16_t*)nullptr, a.off, a.map, a.d, a.f,
                                    (const bf16_t*)a.w1, (const bf16_t*)nullptr, (bf16_t*)a.dxd));

@@ -122,10 +122,17 @@ def test_multiples_of_64(d, f, expert, gathered, scaled):
 # K of less than a unit, ending inside its first and second half and inside a K-strided tile; one, two and more output tiles
 @pytest.mark.parametrize("expert", ["swiglu", "gelu"])
 @pytest.mark.parametrize("d,f", [(8, 8), (8, 136), (72, 40), (104, 328), (264, 120), (328, 200)])
-@pytest.mark.parametrize("rows", [ROWS, [300, 0, 1000, 129] + [96] * 12], ids=["few", "many"])
+@pytest.mark.parametrize("rows", [[1, 0, 30, 1, 3, 2], ROWS, [300, 0, 1000, 129] + [96] * 12, [6200, 0, 6000, 129]],
+                         ids=["scarce", "few", "many", "large"])
 def test_multiples_of_8(rows, d, f, expert):
     import paper_2508_13337_amd as m
-    o, _, _ = run(m, rows, d, f, expert)
+    o, k1, k2 = run(m, rows, d, f, expert)
+    up, da = ("ffn_gateup", "ffn_dact") if expert == "swiglu" else ("mlp2_up", "mlp2_dact")
+    assert k1 == {"tile_map_kernel", up + "_direct_kernel", "ffn_down_direct_kernel"}, k1
+    B, E = sum(rows), len(rows)
+    rows_by = "direct" if B >= 96 * E and -(-B // 128) * -(-min(d, f) // 128) >= 96 else "mfma"
+    assert {da + "_%s_kernel" % rows_by, "ffn_dx_%s_kernel" % rows_by,
+            "ffn_wgrad_%s_kernel" % ("direct" if B >= 12 * E else "mfma")} <= k2, k2
     check(rows, d, f, expert, o)
 
 
@@ -138,6 +145,7 @@ def test_long_segments(rows, expert):
     d, f = (264, 392) if expert == "swiglu" else (520, 392)
     o, _, k2 = run(m, rows, d, f, expert)
     assert any("ffn_bwd_rest" in k or "wgrad_dma" in k for k in k2) == (len(rows) > 4), k2
+    assert ("ffn_wgrad_direct_kernel" in k2) == (len(rows) <= 4) and "ffn_dx_direct_kernel" in k2, k2
     check(rows, d, f, expert, o)
 
 

@@ -1,4 +1,5 @@
-"""The general matrix-core tiles (float32, and bf16 widths that are no multiple of 64) at the sizes where they can go
+"""The general matrix-core tiles (float32, and bf16 widths that are no multiple of 8 or operands that are not 16-byte aligned;
+bf16 rows start two bytes behind such an address here) at the sizes where they can go
 wrong: K of less than one step, one past a step and one element past a 16-byte vector; columns that end inside a
 four-column load or are fewer than four; row segments on both sides of every 32-row block and of both tile heights;
 leading dimensions of every residue, so that loads start unaligned.  Expert MLP forward and backward with gathered
@@ -33,6 +34,14 @@ def guarded(shape, dtype):
     return buf[256:256 + n].view(shape), check
 
 
+def to_dev_unaligned(a, dtype):
+    t = to_dev(a, dtype)
+    if dtype == "f32":
+        return t
+    u = torch.empty(t.numel() + 1, dtype=t.dtype, device="cuda")[1:].view(t.shape)
+    return u.copy_(t)
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("d,f,rows", [(1, 1, SHORT), (3, 5, SHORT), (7, 2, SHORT), (31, 33, SHORT), (66, 127, SHORT),
                                       (130, 61, SHORT), (129, 200, SHORT), (72, 8, SHORT), (517, 645, LONG),
@@ -60,7 +69,7 @@ def test_expert_ffn_any_width(d, f, rows, dtype):
                                                dwd=(E, f, d)).items()}
     row_grad, row_ok = guarded((B,), torch.float32)
     t = {n: v[0] for n, v in out.items()}
-    xt, dt_, wgt, wut, wdt = (to_dev(a, dtype) for a in (x, dout, wg, wu, wd))
+    xt, dt_, wgt, wut, wdt = to_dev_unaligned(x, dtype), *(to_dev(a, dtype) for a in (dout, wg, wu, wd))
     m.xmoe_prof_reset()
     m.xmoe_prof_enable(True)
     m.xmoe_expert_ffn_fwd(xt, to, wgt, wut, wdt, t["g"], t["u"], t["y"], ws, row_index=ti)
@@ -71,7 +80,8 @@ def test_expert_ffn_any_width(d, f, rows, dtype):
     launched = set(m.xmoe_prof_read())
     m.xmoe_prof_enable(False)
     m.xmoe_prof_reset()
-    assert {"ffn_gateup_mfma_kernel", "ffn_dact_mfma_kernel", "ffn_wgrad_mfma_kernel"} <= launched, launched
+    assert {"ffn_gateup_mfma_kernel", "ffn_down_mfma_kernel", "ffn_dact_mfma_kernel", "ffn_dx_mfma_kernel",
+            "ffn_wgrad_mfma_kernel"} <= launched, launched
     for _, check in out.values():
         check()
     row_ok()
@@ -146,7 +156,7 @@ def test_expert_mlp2_any_width(d, f, rows, dtype, act):
     out = {n: guarded(s, tdt) for n, s in dict(h=(B, f), y=(B, d), dxd=(B, d), dw1=(E, d, f), dw2=(E, f, d)).items()}
     row_grad, row_ok = guarded((B,), torch.float32)
     t = {n: v[0] for n, v in out.items()}
-    xt, dt_, w1t, w2t = (to_dev(a, dtype) for a in (x, dout, w1, w2))
+    xt, dt_, w1t, w2t = to_dev_unaligned(x, dtype), *(to_dev(a, dtype) for a in (dout, w1, w2))
 
     def call():
         m.xmoe_expert_mlp2_fwd(xt, to, w1t, w2t, act, t["h"], t["y"], ws, row_index=ti)
