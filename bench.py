@@ -135,7 +135,8 @@ GEMM_WORK = {
     "ffn_gateup_dma_kernel": "gateup", "ffn_rowgemm_dma_kernel<false>": "down",
     "ffn_rowgemm_dma_kernel<true>": "dact", "ffn_dx_dma_kernel": "dx",
     "ffn_wgrad_dma_kernel<false>": "wgrad_wd", "ffn_wgrad_dma_kernel<true>": "wgrad_wg_wu",
-    "ffn_bwd_rest_dma_kernel": "bwd_rest", "ffn_gateup_few_kernel": "gateup", "ffn_down_few_kernel": "down",
+    "ffn_bwd_rest_dma_kernel": "bwd_rest", "ffn_bwd_wgrads_dma_kernel": "wgrad",   # the latter: behind another dX
+    "ffn_gateup_few_kernel": "gateup", "ffn_down_few_kernel": "down",
 }
 for _fam in ("mfma", "direct"):
     for _k in ("gateup", "down", "dact", "dx", "wgrad"):
@@ -145,7 +146,7 @@ for _fam in ("mfma", "direct"):
 GEMM_WORK_MLP2 = {
     "mlp2_up_dma_kernel": "up", "ffn_rowgemm_dma_kernel<false>": "down", "mlp2_dact_dma_kernel": "dact",
     "ffn_dx_dma_kernel": "dx", "ffn_wgrad_dma_kernel<false>": "wgrad", "ffn_bwd_rest_dma_kernel": "bwd_rest",
-    "mlp2_up_mfma_kernel": "up", "ffn_down_mfma_kernel": "down", "mlp2_dact_mfma_kernel": "dact",
+    "ffn_bwd_wgrads_dma_kernel": "wgrad", "mlp2_up_mfma_kernel": "up", "ffn_down_mfma_kernel": "down", "mlp2_dact_mfma_kernel": "dact",
     "ffn_dx_mfma_kernel": "dx", "ffn_wgrad_mfma_kernel": "wgrad", "mlp2_up_few_kernel": "up",
     "ffn_down_few_kernel": "down", "mlp2_up_direct_kernel": "up", "ffn_down_direct_kernel": "down",
     "mlp2_dact_direct_kernel": "dact", "ffn_dx_direct_kernel": "dx", "ffn_wgrad_direct_kernel": "wgrad",

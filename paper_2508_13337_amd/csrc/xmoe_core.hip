@@ -71,6 +71,7 @@ const char* const kKernelNames[K_COUNT] = {
     "mlp2_up_direct_kernel",
     "mlp2_dact_direct_kernel",
     "ffn_wgrad_direct_kernel",
+    "ffn_bwd_wgrads_dma_kernel",
 };
 
 hipEvent_t get_event() {

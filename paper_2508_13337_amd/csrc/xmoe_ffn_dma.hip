@@ -67,7 +67,7 @@ __device__ const float kOneF = 1.0f;
 // constant 100 MHz counter when it starts and when it leaves (it is persistent, so that spans the launch); the
 // ratio is the clock the kernel really ran at (xmoe_prof_shader_clock).  One slot per kernel of the family.
 enum ClockSlot { CS_GATEUP = 0, CS_DOWN, CS_DACT, CS_DX, CS_WGRAD, CS_WGRAD_DUAL, CS_MLP2_UP, CS_MLP2_DACT, CS_BWD_REST,
-                 CS_COUNT };
+                 CS_BWD_WGRADS, CS_COUNT };
 __device__ unsigned long long g_clock_probe[CS_COUNT][4];
 // clk: the kernel's slot of g_clock_probe while the launch profiler is enabled, else NULL (nothing is written then,
 // so launches on different streams share no device memory outside their arguments)
@@ -1994,12 +1994,12 @@ static int bwd_rest(const FfnArgs& a, int max_tiles, hipStream_t s) {
         const long tiles = (long)max_tiles * ntd + (long)a.E * mtf * ntd + (long)a.E * mtd * ntf2;
         const dim3 grid(round_up8(tiles));
 #define XMOE_REST(G, DYG)                                                                                             \
-    XMOE_LAUNCH(K_FFN_BWD_REST_DMA, s,                                                                                \
+    XMOE_LAUNCH(a.dxd ? K_FFN_BWD_REST_DMA : K_FFN_BWD_WGRADS_DMA, s,                                                 \
                 hipLaunchKernelGGL((ffn_bwd_rest_dma_kernel<true, G, DYG>), grid, dim3(512), kLdsBytes, s, dg, du,    \
                                    act, dy, a.dy_index, a.dy_index, xd, a.row_index, a.row_index, a.off, a.map,       \
                                    a.sched, row_counters(a.sched, a.E, 1), a.sched + a.E, a.sched + a.E + kNumXcd,    \
                                    a.E, wgrad_one_xcd(a), a.d, a.f, wg, wu, (bf16_t*)a.dxd, (bf16_t*)a.dwd, (bf16_t*)a.dwg,             \
-                                   (bf16_t*)a.dwu, clock_slot(CS_BWD_REST)))
+                                   (bf16_t*)a.dwu, clock_slot(a.dxd ? CS_BWD_REST : CS_BWD_WGRADS)))
         if (a.row_index && a.dy_index) XMOE_REST(true, true);
         else if (a.row_index) XMOE_REST(true, false);
         else if (a.dy_index) XMOE_REST(false, true);
@@ -2128,13 +2128,13 @@ static int bwd_rest(const Mlp2Args& a, int max_tiles, hipStream_t s) {
         const long tiles = (long)max_tiles * ntd + (long)a.E * mtf * ntd + (long)a.E * mtd * ntf;
         const dim3 grid_rest(round_up8(tiles));
 #define XMOE_REST(G, DYG)                                                                                             \
-    XMOE_LAUNCH(K_FFN_BWD_REST_DMA, s,                                                                                \
+    XMOE_LAUNCH(a.dxd ? K_FFN_BWD_REST_DMA : K_FFN_BWD_WGRADS_DMA, s,                                                 \
                 hipLaunchKernelGGL((ffn_bwd_rest_dma_kernel<false, G, DYG>), grid_rest, dim3(512), kLdsBytes, s, dh,  \
                                    nullptr, act, dy, a.dy_index, a.dy_index, xd, a.row_index, a.row_index, a.off,     \
                                    a.map, a.sched, row_counters(a.sched, a.E, 1), a.sched + a.E,                      \
                                    a.sched + a.E + kNumXcd, a.E, wgrad_one_xcd(a), a.d, a.f, w1, nullptr,             \
                                    (bf16_t*)a.dxd,                                                                    \
-                                   (bf16_t*)a.dw2, (bf16_t*)a.dw1, nullptr, clock_slot(CS_BWD_REST)))
+                                   (bf16_t*)a.dw2, (bf16_t*)a.dw1, nullptr, clock_slot(a.dxd ? CS_BWD_REST : CS_BWD_WGRADS)))
         if (a.row_index && a.dy_index) XMOE_REST(true, true);
         else if (a.row_index) XMOE_REST(true, false);
         else if (a.dy_index) XMOE_REST(false, true);
@@ -2229,6 +2229,7 @@ extern "C" int xmoe_prof_shader_clock(int kernel_id, double* ghz) {
         case xmoe::K_FFN_WGRAD_DMA: slot = xmoe::CS_WGRAD; break;
         case xmoe::K_FFN_WGRAD_DUAL_DMA: slot = xmoe::CS_WGRAD_DUAL; break;
         case xmoe::K_FFN_BWD_REST_DMA: slot = xmoe::CS_BWD_REST; break;
+        case xmoe::K_FFN_BWD_WGRADS_DMA: slot = xmoe::CS_BWD_WGRADS; break;
         case xmoe::K_MLP2_UP_DMA: slot = xmoe::CS_MLP2_UP; break;
         case xmoe::K_MLP2_DACT_DMA: slot = xmoe::CS_MLP2_DACT; break;
         default: break;

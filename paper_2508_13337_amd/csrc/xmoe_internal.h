@@ -63,6 +63,7 @@ enum KernelId : int {
     K_MLP2_UP_DIRECT,
     K_MLP2_DACT_DIRECT,
     K_FFN_WGRAD_DIRECT,
+    K_FFN_BWD_WGRADS_DMA,   // ffn_bwd_rest_dma_kernel without dX
     K_COUNT
 };
 

@@ -144,7 +144,7 @@ def test_long_segments(rows, expert):
     import paper_2508_13337_amd as m
     d, f = (264, 392) if expert == "swiglu" else (520, 392)
     o, _, k2 = run(m, rows, d, f, expert)
-    assert any("ffn_bwd_rest" in k or "wgrad_dma" in k for k in k2) == (len(rows) > 4), k2
+    assert any("ffn_bwd_wgrads" in k or "wgrad_dma" in k for k in k2) == (len(rows) > 4), k2
     assert ("ffn_wgrad_direct_kernel" in k2) == (len(rows) <= 4) and "ffn_dx_direct_kernel" in k2, k2
     check(rows, d, f, expert, o)
 
@@ -253,4 +253,6 @@ def test_both_sides_of_the_rules(E, d, f, rows, fwd, bwd, wgrads):
     _, k1, k2 = run(m, count, d, f, "swiglu")
     assert ("ffn_gateup_direct_kernel" in k1) == fwd and ("ffn_gateup_dma_kernel" in k1) != fwd, k1
     assert ("ffn_dact_direct_kernel" in k2) == bwd and ("ffn_rowgemm_dma_kernel<true>" in k2) != bwd, k2
-    assert ("ffn_wgrad_direct_kernel" in k2) == wgrads, k2
+    # dX is part of the weight gradients' launch only where no kernel of its own computes it
+    assert ("ffn_wgrad_direct_kernel" in k2) == wgrads and ("ffn_dx_direct_kernel" in k2) == bwd, k2
+    assert ("ffn_bwd_wgrads_dma_kernel" in k2) == (bwd and not wgrads) and ("ffn_bwd_rest_dma_kernel" in k2) != bwd, k2
