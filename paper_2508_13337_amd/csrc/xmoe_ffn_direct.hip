@@ -287,23 +287,33 @@ inline bool fast_act(int d, int f) { return d % 64 == 0 && f % 64 == 0; }
 //     8 experts, 4096 x 1024  147 | 56     143 | 113    188 | 204    354 | 386                  (384, 768 from 400)
 //    16 experts, 1024 x 704    65 | 30      95 | 53     102 | 88     161 | 157                  (320, 640, 1120 from 400)
 //    32 experts, 2048 x 704   103 | 78     185 | 183    294 | 318                               (896, 1792 from 400)
-//   one half-empty tile per expert:
-//     rows per expert         33-40        64           96           128
-//    64 experts, 1024 x 704    97 | 64      93 | 70      97 | 77
-//    96 experts, 2048 x 704   216 | 177    212 | 189    220 | 205
-//   512 experts, 1024 x 256   243 | 210    255 | 222    269 | 241    288 | 278
-//    32 experts, 4096 x 1024  183 | 175    180 | 180    186 | 189    196 | 242     (Zipf 64: 240 | 194)
-//    64 experts, 2048 x 1408  244 | 232    247 | 242    259 | 260    268 | 313     (Zipf 64: 293 | 267)
-//    32 experts, 2048 x 2560  223 | 219    226 | 234    236 | 247
-//   256 experts, 2048 x 512   353 | 359    368 | 374    390 | 400    424 | 475
-//   128 experts, 5120 x 1536 1143 | 1216  1166 | 1289  1214 | 1383  1367 | 1600
-// Many large weights keep the chip full and their stream long, and then the larger tile's fewer requests count.  Below 256
-// columns the products are launch-bound either way.
+//   one half-empty tile per expert (Z: Zipf-like load of the mean above it):
+//     rows per expert              34           48           64           80           96           120
+//    48 experts, 2048 x 1024   163 | 137    161 | 141    160 | 146    165 | 151    168 | 155    178 | 169   Z 48: 162 | 148
+//   256 experts,  512 x 768    184 | 144    200 | 152    200 | 159    212 | 166    215 | 174    218 | 194   Z 48: 204 | 167
+//    64 experts, 1536 x 1536   212 | 193    219 | 200    221 | 208    227 | 216    231 | 224    241 | 252   Z 48: 235 | 220
+//   300 experts,  512 x 1024   267 | 219    274 | 242    277 | 242    283 | 248    300 | 267    323 | 287   Z 48: 274 | 250
+//                                                                      72
+//    32 experts, 2048 x 2560   220 | 219    223 | 225    229 | 233    235 | 235                             Z 64: 268 | 267
+//    96 experts, 1024 x 1792   260 | 232    262 | 235    264 | 249    271 | 254                             Z 64: 275 | 272
+//    16 experts, 4096 x 2816   243 | 221    250 | 224    248 | 228    255 | 228                             Z 64: 259 | 278
+//    64 experts, 2048 x 1408   244 | 217    244 | 229    245 | 238    250 | 244    (128: 268 | 313)         Z 64: 259 | 263
+//    80 experts, 2048 x 1152   241 | 220    243 | 225    249 | 235    253 | 239                             Z 64: 255 | 262
+//   512 experts,  512 x 704    315 | 247    335 | 263    334 | 274    335 | 285                             Z 64: 346 | 298
+//                                                                      80
+//    64 experts, 2048 x 1792   292 | 278    299 | 290    299 | 307    304 | 310    309 | 320    318 | 370   Z 48: 308 | 318
+//   128 experts, 2048 x 1024   338 | 330    341 | 345    351 | 350    361 | 364    362 | 372    374 | 409   Z 48: 368 | 368
+//    32 experts, 4096 x 2048   311 | 320    313 | 329    312 | 336    322 | 346    323 | 356    336 | 404   Z 48: 364 | 349
+//    96 experts, 2048 x 2048   470 | 478    473 | 503    478 | 517    488 | 531    497 | 550    521 | 614   Z 48: 519 | 531
+//   256 experts, 2048 x 1408   830 | 874    853 | 907    865 | 952    876 | 993    900 | 1003   964 | 1100  Z 48: 915 | 985
+//   128 experts, 5120 x 1536  1143 | 1216              1166 | 1289                            1214 | 1383  (128: 1367 | 1600)
+// Many weights keep the chip full and their stream long, and then the larger tile's fewer requests count: from 235 million
+// elements of a matrix on (E d f) the two are level at best.  Below 256 columns the products are launch-bound either way.
 bool direct_fwd(int B, int E, int d, int f) {
     if (d < 256 || f < 256) return false;
     const long long row_tiles = E * ((B + 256ll * E - 1) / (256ll * E)), weights = (long long)E * d * f;
     if (row_tiles * ((f + 127) / 128 + (d + 255) / 256) <= 640) return true;
-    return (B <= 96ll * E && weights <= 160000000) || (B <= 72ll * E && weights <= 200000000 && (long long)d * f <= 1 << 22);
+    return weights <= 200000000 && B <= (weights <= 160000000 ? 96ll : 72ll) * E;
 }
 // The backward.  Its weight gradients take the 128 x 128 tiles where the 256-row kernels have few tiles of them and the
 // experts are not long; dAct and dX do with them, and where a launch of theirs has few or half-empty tiles of 256 rows (the

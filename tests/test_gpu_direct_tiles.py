@@ -256,3 +256,17 @@ def test_both_sides_of_the_rules(E, d, f, rows, fwd, bwd, wgrads):
     # dX is part of the weight gradients' launch only where no kernel of its own computes it
     assert ("ffn_wgrad_direct_kernel" in k2) == wgrads and ("ffn_dx_direct_kernel" in k2) == bwd, k2
     assert ("ffn_bwd_wgrads_dma_kernel" in k2) == (bwd and not wgrads) and ("ffn_bwd_rest_dma_kernel" in k2) != bwd, k2
+
+
+@pytest.mark.parametrize("E,d,f,mean,direct", [(32, 2048, 2560, 40, True), (32, 2048, 2560, 73, False), (80, 2048, 1152, 72, True),
+                                               (64, 2048, 1792, 40, False), (64, 1536, 1536, 96, True), (64, 1536, 1536, 97, False)])
+def test_forward_rule_for_half_empty_tiles(E, d, f, mean, direct):
+    """By the size of the weights and the mean row count alone."""
+    import paper_2508_13337_amd as m
+    B = E * mean
+    off = torch.arange(0, B + 1, mean, dtype=torch.int32).cuda()
+    new = lambda *s: torch.zeros(s, dtype=torch.bfloat16, device="cuda")
+    ws = m.alloc_workspace(m.xmoe_workspace_bytes(m.WS_FFN_FWD, B, d, E, 1, f, m.XMOE_BF16))
+    w = new(E, d, f), new(E, d, f), new(E, f, d)
+    k = launched(m, lambda: m.xmoe_expert_ffn_fwd(new(B, d), off, *w, new(B, f), new(B, f), new(B, d), ws))
+    assert ("ffn_gateup_direct_kernel" in k) == direct and ("ffn_gateup_dma_kernel" in k) != direct, k
