@@ -120,7 +120,6 @@ int mlp2_fwd_few(const Mlp2Args& a, hipStream_t s);
 bool direct_fwd(int B, int E, int d, int f);   // whether they take a call's row products from the 256-row kernels
 bool direct_bwd(int B, int E, int d, int f, int matrices);       // matrices of an expert: 3, or 2 (mlp2)
 bool direct_wgrads(int B, int E, int d, int f, int matrices);    // and, behind direct_bwd, its weight gradients
-long long wgrad_tiles_256(int E, int d, int f, int matrices);    // tiles of the 256-row weight-gradient kernels
 bool direct_supported(const FfnArgs& a);
 bool direct_supported(const Mlp2Args& a);
 int ffn_fwd_direct(const FfnArgs& a, hipStream_t s);

@@ -334,12 +334,9 @@ bool direct_fwd(int B, int E, int d, int f) {
 //   256 experts, 2048 x 512             810 | 812 | -      907 | 902 | -
 // dAct and dX by rows per expert: 64 experts, 2048 x 1408: 4 rows 504 | 471, 64 rows 562 | 541, 96 of routed and 2 x 1021
 // rows 679 | 757; 16 experts, 2048 x 1408: 64 rows 225 | 190, 96 rows 192 | 202.
-long long wgrad_tiles_256(int E, int d, int f, int matrices) {
-    const long long td = (d + 255) / 256;
-    return E * td * ((f + 255) / 256 + (matrices == 3 ? (f + 127) / 128 : (f + 255) / 256));
-}
 bool direct_wgrads(int B, int E, int d, int f, int matrices) {
-    const long long n = wgrad_tiles_256(E, d, f, matrices);
+    const long long td = (d + 255) / 256;   // n: tiles of the 256-row weight-gradient kernels
+    const long long n = E * td * ((f + 255) / 256 + (matrices == 3 ? (f + 127) / 128 : (f + 255) / 256));
     return n <= 2200 && n * B <= 600000ll * E;
 }
 bool direct_bwd(int B, int E, int d, int f, int matrices) {

@@ -633,24 +633,32 @@ static int mlp2_bwd_rows_tile(const Mlp2Args& a, hipStream_t s) {
 // rows 96 | 78; E 4 d 1496 f 208, 1500 rows 61 | 40), the backward's where the staged tiles would be the big ones (E 8 d
 // 1000 f 1000, backward, 96 rows 90 | 96; big ones: T 3001 d 1000 f 712 E 24+1, staged | direct: dAct 82 | 58, dX 78 | 75).
 //
-// Their weight gradients take the direct-to-LDS 128 x 128 tiles; the staged ones where the experts have hardly any rows (a
-// 64 x 64 tile of nothing but its stores), the 256-row kernels (K-strided operands only have to be whole 16-byte pieces)
-// where there are rows and tiles enough for them.  Whole backward, us, staged | direct | 256-row:
-//   rows per expert             1             16                  96                  375                  1500
-//   E 24 d 1000 f 712 (900)   83 | 100 | 129  118 | 104 | 142   139 | 113 | 134   244 | 189 | 195    697 | 585 | 552
-//   E 16 d 2040 f 1480 (2304) 208 | 204 | 232 284 | 235 | 271   341 | 256 | 276   601 | 451 | 442   1642 | 1432 | 1277
-//   E 256 d 328 f 200 (1536)  91 | 103 | 133  153 | 124 | 149   187 | 145 | 157   392 |     | 311
-//   E 8 d 1000 f 1000 (384)   64 | 69 | 114    80 | 76 | 125     91 | 82 | 112    118 | 104 | 137    282 | 241 | 259
-//   E 4 d 1496 f 208 (72)     40 | 40 | 59     52 | 43 | 62      59 | 46 | 68      72 | 57 | 85      131 | 102 | 164
-// A long expert among short ones (E 24 of 375 rows and one of 3001, d 1000 f 712) keeps the 256-row kernels' launch waiting
-// for its few tiles: weight gradients alone 166 | 103 | 200.
+// Their weight gradients take the direct-to-LDS 128 x 128 tiles as well; the staged ones where the experts have hardly any
+// rows (a 64 x 64 tile of nothing but its stores).  Whole backward, us, staged | direct:
+//   rows per expert             1          16          96          375         1500
+//   E 24 d 1000 f 712         83 | 100   118 | 104   139 | 113   244 | 189   697 | 585
+//   E 16 d 2040 f 1480       208 | 204   284 | 235   341 | 256   601 | 451  1642 | 1432
+//   E 256 d 328 f 200         91 | 103   153 | 124   183 | 144   400 | 346   988 | 957 (1200 rows)
+//   E 8 d 1000 f 1000         64 | 69     80 | 76     91 | 82    118 | 104   282 | 241
+//   E 4 d 1496 f 208          40 | 40     52 | 43     59 | 46     72 | 57    131 | 102
+// The 256-row kernels (K-strided operands only have to be whole 16-byte pieces) would take these widths too.  They are
+// ahead at many rows and even loads, and far behind where one segment is long, whose few tiles then are their launch; no
+// rule on the mean can tell the two.  Whole backward, us, direct | 256-row, even load, Zipf-like, one segment E/4 times as
+// long:
+//   E 24 d 1000 f 712,    375 rows   177 | 186     175 | 229     199 | 259
+//                        1200        447 | 439     459 | 583     549 | 709
+//   E 64 d 520 f 264,     375        159 | 162     157 | 253     185 | 385
+//                        1200        418 | 373     431 | 737     579 | 972
+//   E 64 d 1000 f 712,    375        488 | 449     505 | 524     590 | 700
+//                        1200       1276 | 1120   1273 | 1371   1541 | 1945
+//   E 256 d 328 f 200,    375        346 | 315     379 | 507     596 | 940
+//                        1200        957 | 752    1126 | 1328   1125 | 1649
+//   E 8 d 2040 f 1480,    375        206 | 221     214 | 248     219 | 236
+//                        1200        519 | 502     545 | 567     621 | 597
 template <class Args>
-static int wgrads_any_width(const Args& a, int matrices, int (*direct)(const Args&, hipStream_t),
-                            int (*dma)(const Args&, hipStream_t), hipStream_t s) {
+static int wgrads_any_width(const Args& a, int (*direct)(const Args&, hipStream_t), hipStream_t s) {
     if (a.dt == XMOE_F32) return wgrad_call<float>(a, s);
-    if (!direct_supported(a) || a.B < 12ll * a.E) return wgrad_call<bf16_t>(a, s);
-    if (a.B >= 1000ll * a.E && wgrad_tiles_256(a.E, a.d, a.f, matrices) >= 512) return dma(a, s);
-    return direct(a, s);
+    return direct_supported(a) && a.B >= 12ll * a.E ? direct(a, s) : wgrad_call<bf16_t>(a, s);
 }
 
 #define XMOE_TILE_CALL(CALL)                                                              \
@@ -669,13 +677,15 @@ int mlp2_fwd_tile(const Mlp2Args& a, hipStream_t s) {
 }
 int ffn_bwd_tile(const FfnArgs& a, hipStream_t s) {
     const bool big = big_tiles(a.B, a.E, a.d, a.f, a.dt);
-    const int st = big && direct_supported(a) ? ffn_bwd_rows_direct(a, s) : XMOE_TILE_CALL(bwd_rows_tile);
-    return st != XMOE_OK ? st : wgrads_any_width(a, 3, ffn_bwd_wgrads_direct, ffn_bwd_wgrads_dma, s);
+    const bool direct = big && direct_supported(a);
+    const int st = direct ? ffn_bwd_rows_direct(a, s) : XMOE_TILE_CALL(bwd_rows_tile);
+    return st != XMOE_OK ? st : wgrads_any_width(a, ffn_bwd_wgrads_direct, s);
 }
 int mlp2_bwd_tile(const Mlp2Args& a, hipStream_t s) {
     const bool big = big_tiles(a.B, a.E, a.d, a.f, a.dt);
-    const int st = big && direct_supported(a) ? mlp2_bwd_rows_direct(a, s) : XMOE_TILE_CALL(mlp2_bwd_rows_tile);
-    return st != XMOE_OK ? st : wgrads_any_width(a, 2, mlp2_bwd_wgrads_direct, mlp2_bwd_wgrads_dma, s);
+    const bool direct = big && direct_supported(a);
+    const int st = direct ? mlp2_bwd_rows_direct(a, s) : XMOE_TILE_CALL(mlp2_bwd_rows_tile);
+    return st != XMOE_OK ? st : wgrads_any_width(a, mlp2_bwd_wgrads_direct, s);
 }
 
 }  // namespace xmoe
