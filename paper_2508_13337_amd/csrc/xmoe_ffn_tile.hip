@@ -630,8 +630,7 @@ static int mlp2_bwd_rows_tile(const Mlp2Args& a, hipStream_t s) {
 
 // Widths that are multiples of 8 (bf16): the forward's row products always take the direct-to-LDS tiles, whatever the
 // number of rows (staged small tiles | direct, us: E 24 d 1000 f 712, 16 rows per expert 40 | 33; E 16 d 2040 f 1480, 40
-// rows 96 | 78; E 4 d 1496 f 208, 1500 rows 61 | 40), the backward's where the staged tiles would be the big ones (E 8 d
-// 1000 f 1000, backward, 96 rows 90 | 96; big ones: T 3001 d 1000 f 712 E 24+1, staged | direct: dAct 82 | 58, dX 78 | 75).
+// rows 96 | 78; E 4 d 1496 f 208, 1500 rows 61 | 40), the backward's as direct_rows says.
 //
 // Their weight gradients take the direct-to-LDS 128 x 128 tiles as well; the staged ones where the experts have hardly any
 // rows (a 64 x 64 tile of nothing but its stores).  Whole backward, us, staged | direct:
@@ -661,6 +660,24 @@ static int wgrads_any_width(const Args& a, int (*direct)(const Args&, hipStream_
     return direct_supported(a) && a.B >= 12ll * a.E ? direct(a, s) : wgrad_call<bf16_t>(a, s);
 }
 
+// dAct and dX at these widths: direct where the staged 64 x 64 tiles (row tiles of a mean segment, columns of the wider
+// product) are more than the 512 blocks that the chip holds at a time, and not for hardly any rows.  Whole backward, us,
+// staged | direct (blocks):
+//   E 16 d 1000 f 712:    45 rows   86 | 90 (256)       80 rows   92 | 92 (512)     120 rows  116 | 97 (512 to 768)
+//   E 8 d 2040 f 1480:    45       138 | 147 (256)      96       142 | 148 (512)    120       176 | 151 (512 to 768)
+//   E 32 d 2040 f 1480:   20       403 | 393 (1024)     64       533 | 429          160       610 | 579
+//   E 8 d 1000 f 1000:    80        79 | 84 (256)      160        89 | 88 (384)     200       108 | 91 (512)
+//   E 4 d 1000 f 712:    160        64 | 67 (192)      400        77 | 76 (448)     520        95 | 78 (576)
+//   E 2 d 2040 f 1480:   200        92 | 101 (256)     400       108 | 109 (448)    520       135 | 111 (576)
+//   E 3 d 2504 f 1000:   200        94 | 100 (480)     280       102 | 104 (600)    400       119 | 110 (840)
+//   E 64 d 1000 f 712:     6       250 | 254 (1024)     45       245 | 238          90        305 | 253 (2048)
+//   E 256 d 520 f 264:     6       298 | 299 (2304)     45       240 | 225          90        313 | 265 (4608)
+//   E 96 d 520 f 520:      4       167 | 171 (864)      30       145 | 144          60        177 | 154
+static inline bool direct_rows(int B, int E, int d, int f) {
+    const long long blocks = (long long)E * ceil_div(ceil_div(B, E), 64) * ceil_div(d > f ? d : f, 64);
+    return B >= 24ll * E && blocks > 512;
+}
+
 #define XMOE_TILE_CALL(CALL)                                                              \
     (a.dt == XMOE_F32 ? (big ? CALL<float, true>(a, s) : CALL<float, false>(a, s))        \
                       : (big ? CALL<bf16_t, true>(a, s) : CALL<bf16_t, false>(a, s)))
@@ -677,13 +694,13 @@ int mlp2_fwd_tile(const Mlp2Args& a, hipStream_t s) {
 }
 int ffn_bwd_tile(const FfnArgs& a, hipStream_t s) {
     const bool big = big_tiles(a.B, a.E, a.d, a.f, a.dt);
-    const bool direct = big && direct_supported(a);
+    const bool direct = direct_rows(a.B, a.E, a.d, a.f) && direct_supported(a);
     const int st = direct ? ffn_bwd_rows_direct(a, s) : XMOE_TILE_CALL(bwd_rows_tile);
     return st != XMOE_OK ? st : wgrads_any_width(a, ffn_bwd_wgrads_direct, s);
 }
 int mlp2_bwd_tile(const Mlp2Args& a, hipStream_t s) {
     const bool big = big_tiles(a.B, a.E, a.d, a.f, a.dt);
-    const bool direct = big && direct_supported(a);
+    const bool direct = direct_rows(a.B, a.E, a.d, a.f) && direct_supported(a);
     const int st = direct ? mlp2_bwd_rows_direct(a, s) : XMOE_TILE_CALL(mlp2_bwd_rows_tile);
     return st != XMOE_OK ? st : wgrads_any_width(a, mlp2_bwd_wgrads_direct, s);
 }

@@ -130,14 +130,15 @@ def test_multiples_of_8(rows, d, f, expert):
     up, da = ("ffn_gateup", "ffn_dact") if expert == "swiglu" else ("mlp2_up", "mlp2_dact")
     assert k1 == {"tile_map_kernel", up + "_direct_kernel", "ffn_down_direct_kernel"}, k1
     B, E = sum(rows), len(rows)
-    rows_by = "direct" if B >= 96 * E and -(-B // 128) * -(-min(d, f) // 128) >= 96 else "mfma"
+    blocks = E * -(-(-(-B // E)) // 64) * -(-max(d, f) // 64)
+    rows_by = "direct" if B >= 24 * E and blocks > 512 else "mfma"
     assert {da + "_%s_kernel" % rows_by, "ffn_dx_%s_kernel" % rows_by,
             "ffn_wgrad_%s_kernel" % ("direct" if B >= 12 * E else "mfma")} <= k2, k2
     check(rows, d, f, expert, o)
 
 
 @pytest.mark.parametrize("expert", ["swiglu", "identity"])
-@pytest.mark.parametrize("rows", [[1200, 0, 1001, 63] * 12 + [3000] * 16, [1700, 1, 0, 2300]], ids=["many", "few"])
+@pytest.mark.parametrize("rows", [[1200, 0, 1001, 63] * 12 + [3000] * 16, [2700, 1, 0, 2300]], ids=["many", "few"])
 def test_long_segments(rows, expert):
     """Weight gradients of widths that are no multiple of 64: long segments, with many tiles and with few."""
     import paper_2508_13337_amd as m
@@ -268,3 +269,21 @@ def test_forward_rule_for_half_empty_tiles(E, d, f, mean, direct):
     w = new(E, d, f), new(E, d, f), new(E, f, d)
     k = launched(m, lambda: m.xmoe_expert_ffn_fwd(new(B, d), off, *w, new(B, f), new(B, f), new(B, d), ws))
     assert ("ffn_gateup_direct_kernel" in k) == direct and ("ffn_gateup_dma_kernel" in k) != direct, k
+
+
+@pytest.mark.parametrize("E,d,f,B,rows,wgrads", [(87, 328, 200, 24 * 87, True, True), (87, 328, 200, 24 * 87 - 1, False, True),
+                                                 (85, 328, 200, 64 * 85, False, True), (86, 200, 328, 64 * 86, True, True),
+                                                 (9, 2040, 200, 128 * 9, True, True), (8, 2040, 200, 128 * 8, False, True),
+                                                 (200, 328, 200, 12 * 200, False, True), (200, 328, 200, 12 * 200 - 1, False, False)])
+def test_backward_rules_of_widths_of_8(E, d, f, B, rows, wgrads):
+    """Which kernels take the row products (more than 512 staged tiles, 24 rows per expert) and the weight gradients (12)."""
+    import paper_2508_13337_amd as m
+    off = torch.tensor([min(B, -(-B // E) * e) for e in range(E + 1)], dtype=torch.int32).cuda()
+    new = lambda *s: torch.zeros(s, dtype=torch.bfloat16, device="cuda")
+    ws = m.alloc_workspace(m.xmoe_workspace_bytes(m.WS_FFN_BWD, B, d, E, 1, f, m.XMOE_BF16))
+    w = new(E, d, f), new(E, d, f), new(E, f, d)
+    k = launched(m, lambda: m.xmoe_expert_ffn_bwd(new(B, d), new(B, f), new(B, f), new(B, d), off, *w, new(B, d),
+                                                  *(torch.empty_like(a) for a in w), ws))
+    for name in ("ffn_dact_%s_kernel", "ffn_dx_%s_kernel"):
+        assert (name % "direct" in k) == rows and (name % "mfma" in k) != rows, k
+    assert ("ffn_wgrad_direct_kernel" in k) == wgrads and ("ffn_wgrad_mfma_kernel" in k) != wgrads, k
