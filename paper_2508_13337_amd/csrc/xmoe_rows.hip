@@ -89,7 +89,11 @@ __global__ __launch_bounds__(256) void dispatch_kernel(const T* __restrict__ x, 
 // used.  The sum keeps the slot order j = 0 .. k-1, then the shared rows, then the addend.  An entry with
 // row_of_slot outside [0, B) (a dropped token) contributes nothing.
 // HBM-bound.  Rows are read and results written with streaming accesses: T 8192, d 2048, k 6 + 2 shared: 63.7 -> 55.3 us
-// (5.8 TB/s, what the streaming copy kernel reaches; the loads alone 56.2).
+// (5.8 TB/s, what the streaming copy kernel reaches; the loads alone 56.2).  At every size: where the rows would stay in a
+// cache the layer's next kernels have more use for the room.  Layers, us, plain | streaming below 192 MiB of rows: training
+// step T 1021 d 2048 k 6 + 2 1047 | 1039, T 512 d 1024 E 64 k 8 163 | 159, T 1500 d 768 k 2 260 | 257, T 3001 d 1000 k 3 + 1
+// 410 | 416; forward T 1021 d 2048 k 6 + 2 350 | 345, T 509 282 | 284, T 8 148 | 148.  With nothing but the rows' writer
+// and the result's reader beside it, plain is ahead: T 509 d 2048 k 6 (12 MB) 14.5 | 15.0, T 4096 (101 MB) 52.9 | 54.5.
 // =========================================================================================================
 template <typename T, bool VEC, int KU>
 __global__ __launch_bounds__(256) void combine_kernel(const T* __restrict__ y, const int32_t* __restrict__ row_of_slot,
