@@ -14,8 +14,17 @@ from test_gpu_parity import check_capped_eri, i32, run_build_eri
 pytestmark = pytest.mark.gpu
 
 
-def ffn(m, rows, x, w, dy, gu=None):
-    """Forward and backward of one call on plain rows (gu: the backward starts from these instead): name -> host tensor."""
+def gathered_rows(a):
+    """(token matrix, row index) that stand for the rows of a."""
+    p = torch.randperm(a.shape[0], generator=torch.Generator().manual_seed(a.shape[0]))
+    t = torch.empty_like(a)
+    t[p] = a
+    return t.cuda(), p.int().cuda()
+
+
+def ffn(m, rows, x, w, dy, gu=None, gathered=False):
+    """Forward and backward of one call (gu: the backward starts from these instead; gathered: rows of x and dy through an
+    index): name -> host tensor."""
     off = torch.tensor([0] + list(torch.tensor(rows).cumsum(0)), dtype=torch.int32).cuda()
     (B, d), (E, _, f), dt = x.shape, w[0].shape, x.dtype
     new = lambda *s: torch.empty(s, dtype=dt, device="cuda")
@@ -23,10 +32,11 @@ def ffn(m, rows, x, w, dy, gu=None):
          "dwd": new(E, f, d)}
     code = m.XMOE_F32 if dt == torch.float32 else m.XMOE_BF16
     ws = m.alloc_workspace(max(m.xmoe_workspace_bytes(op, B, d, E, 1, f, code) for op in (m.WS_FFN_FWD, m.WS_FFN_BWD)))
-    xc, dc, wc = x.cuda(), dy.cuda(), [a.cuda() for a in w]
-    m.xmoe_expert_ffn_fwd(xc, off, *wc, o["g"], o["u"], o["y"], ws)
+    (xc, xi), (dc, di) = (gathered_rows(a) if gathered else (a.cuda(), None) for a in (x, dy))
+    wc = [a.cuda() for a in w]
+    m.xmoe_expert_ffn_fwd(xc, off, *wc, o["g"], o["u"], o["y"], ws, row_index=xi)
     g, u = (o["g"], o["u"]) if gu is None else (t.cuda() for t in gu)
-    m.xmoe_expert_ffn_bwd(xc, g, u, dc, off, *wc, o["dxd"], o["dwg"], o["dwu"], o["dwd"], ws)
+    m.xmoe_expert_ffn_bwd(xc, g, u, dc, off, *wc, o["dxd"], o["dwg"], o["dwu"], o["dwd"], ws, row_index=xi, dy_row_index=di)
     return {n: t.float().cpu() for n, t in o.items()}
 
 
@@ -38,9 +48,13 @@ def random_ffn(rows, d, f, dt):
 
 
 @pytest.mark.parametrize("dt", [torch.float32, torch.bfloat16])
-@pytest.mark.parametrize("rows,d,f", [([70, 5, 130], 72, 40), ([70, 5, 130], 33, 129), ([0, 300, 260, 1] * 8, 328, 264)])
-def test_infinities_go_where_the_products_take_them(rows, d, f, dt):
+@pytest.mark.parametrize("gathered", [False, True])
+@pytest.mark.parametrize("rows,d,f", [([70, 5, 130], 72, 40), ([70, 5, 130], 33, 129), ([0, 300, 260, 1] * 8, 328, 264),
+                                      ([0, 3000, 5200, 1], 520, 500)])   # the last: 128 x 128 tiles of every product
+def test_infinities_go_where_the_products_take_them(rows, d, f, dt, gathered):
+    import functools
     import paper_2508_13337_amd as m
+    ffn = functools.partial(globals()["ffn"], gathered=gathered)
     x, w, dy = random_ffn(rows, d, f, dt)
     e = 2 if rows[0] else 1
     lo, hi = sum(rows[:e]), sum(rows[:e + 1])
@@ -90,6 +104,44 @@ def test_infinities_go_where_the_products_take_them(rows, d, f, dt):
     mask = torch.zeros_like(o["dxd"], dtype=torch.bool)
     mask[lo:hi, kd] = True
     assert torch.equal(o["dxd"][~mask], base["dxd"][~mask])
+
+
+@pytest.mark.parametrize("gathered", [False, True])
+@pytest.mark.parametrize("act", ["identity", "silu"])
+@pytest.mark.parametrize("rows,d,f", [([70, 5, 130], 72, 41), ([0, 3000, 5200, 1], 520, 500)])
+def test_infinities_in_the_two_matrix_expert(rows, d, f, act, gathered):
+    import paper_2508_13337_amd as m
+    x, (w1, _, w2), dy = random_ffn(rows, d, f, torch.float32)
+    off = torch.tensor([0] + list(torch.tensor(rows).cumsum(0)), dtype=torch.int32).cuda()
+    E, B, r, e, inf = len(rows), sum(rows), sum(rows[:2]) + 2, 2, float("inf")
+    x1, v2 = x.clone(), w2.clone()
+    x1[r, d - 1] = inf
+    v2[e, f - 1, 3] = inf
+    outs = []
+    for xs, ws2 in ((x, w2), (x1, w2), (x, v2)):
+        new = lambda *s: torch.empty(s, device="cuda")
+        o = {"h": new(B, f), "y": new(B, d), "dxd": new(B, d), "dw1": new(E, d, f), "dw2": new(E, f, d)}
+        (xc, xi), (dc, di) = (gathered_rows(a) if gathered else (a.cuda(), None) for a in (xs, dy))
+        ws = m.alloc_workspace(max(m.xmoe_workspace_bytes(op, B, d, E, 1, f, m.XMOE_F32) for op in (m.WS_MLP2_FWD, m.WS_MLP2_BWD)))
+        wc = w1.cuda(), ws2.cuda()
+        m.xmoe_expert_mlp2_fwd(xc, off, *wc, act, o["h"], o["y"], ws, row_index=xi)
+        m.xmoe_expert_mlp2_bwd(xc, o["h"], dc, off, *wc, act, o["dxd"], o["dw1"], o["dw2"], ws, row_index=xi, dy_row_index=di)
+        outs.append({n: t.cpu() for n, t in o.items()})
+    clean, row, weight = outs
+    # a row of x: its row of H, with the weights' signs, and no other row of anything
+    assert torch.equal(row["h"][r], inf * w1[e, d - 1].sign())
+    others = torch.arange(B) != r
+    for n in ("h", "y", "dxd"):
+        assert torch.equal(row[n][others], clean[n][others]), n
+    # a weight of W2: its column of the expert's Y, with the activations' signs
+    s = slice(sum(rows[:e]), sum(rows[:e + 1]))
+    assert torch.equal(weight["y"][s, 3], inf * clean["h"][s, f - 1].sign())
+    mask = torch.ones(B, d, dtype=torch.bool)
+    mask[s, 3] = False
+    assert torch.equal(weight["y"][mask], clean["y"][mask])
+    same = [i for i in range(E) if i != e]
+    for n in ("dw1", "dw2"):
+        assert torch.equal(weight[n][same], clean[n][same]), n
 
 
 def test_largest_floats():
