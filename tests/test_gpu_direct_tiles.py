@@ -210,6 +210,8 @@ def test_backward_bits_of_the_other_kernels(d, f, E, expert):
             k = launched(m, lambda: m.xmoe_expert_mlp2_bwd(x, *saved, dy, off.cuda(), *wc, expert, *o, ws, **kw))
         outs.append((off.tolist(), o[0].cpu(), rg.cpu(), k))
     (o1, dx1, rg1, k1), (o2, dx2, rg2, k2) = outs
+    direct = "ffn_dact_direct_kernel" if expert == "swiglu" else "mlp2_dact_direct_kernel"
+    assert (direct in k1) == (d % 64 == 0) and (direct in k2) != (d % 64 == 0), (k1, k2)
     for e, n in enumerate(few):
         assert torch.equal(dx1[o1[e]:][:n], dx2[o2[e]:][:n]), e
         assert torch.equal(rg1[o1[e]:][:n], rg2[o2[e]:][:n]), e
@@ -238,6 +240,7 @@ def test_an_infinite_last_column_is_counted_once(f, expert):
         k = launched(m, lambda: m.xmoe_expert_ffn_bwd(r(B, d).cuda(), *args, *o, ws, **kw))
     else:
         k = launched(m, lambda: m.xmoe_expert_mlp2_bwd(r(B, d).cuda(), *args, expert, *o, ws, **kw))
+    assert ("ffn_dact_direct_kernel" if expert == "swiglu" else "mlp2_dact_direct_kernel") in k, k
     sign = dy[:, 7].float().sign() * torch.stack([a[:, f - 1].float().sign() for a in acts]).prod(0)
     assert torch.equal(rg.cpu(), float("inf") * sign)
 
