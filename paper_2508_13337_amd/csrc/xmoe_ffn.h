@@ -46,6 +46,50 @@ struct Mlp2Args {
     float* row_part;
 };
 
+// Weight gradients of the 128- and 64-row kernels: dW_e[m, n] = sum over the expert's rows r of P[r, m] * Q[r, n].  All of a
+// call's are one launch, the experts with the most rows first (sched), so the long sums start early and only one tail of idle
+// CUs is left.  A matrix's tiles are cut into at most eight runs, dealt to the XCDs in turn (block b runs on XCD b % 8): the
+// tiles of a run share operand panels in one L2.
+template <typename T>
+struct WgradJob {
+    const T *P, *Q;
+    const int32_t *p_index, *q_index;   // or NULL; at most one
+    int M, N;
+    T* dW;
+};
+template <typename T>
+struct WgradJobs {
+    WgradJob<T> job[3];
+    int n_jobs, tiles, run, runs;   // tiles of a matrix, tiles of a run, runs of a matrix
+    // matrix m of all (jobs of the first expert in sched's order, of the second ...) and its tile u for this block
+    __device__ __forceinline__ bool place(int E, int& m, int& u) const {
+        const int s = blockIdx.x >> 3, r = (s / run) * 8 + (blockIdx.x & 7);   // run r of all
+        m = r / runs;
+        u = (r - m * runs) * run + s % run;
+        return m < n_jobs * E && u < tiles;
+    }
+    // tile x tile outputs per block; the launch's grid
+    dim3 cut(int E, int d, int f, int tile) {
+        tiles = ((d + tile - 1) / tile) * ((f + tile - 1) / tile);
+        run = (tiles + 7) / 8;
+        runs = (tiles + run - 1) / run;
+        return dim3((unsigned)(((long long)n_jobs * E * runs + 7) / 8 * 8 * run));
+    }
+};
+template <typename T>
+WgradJobs<T> wgrad_jobs(const FfnArgs& a) {
+    return {{{(const T*)a.act, (const T*)a.dy, nullptr, a.dy_index, a.f, a.d, (T*)a.dwd},
+             {(const T*)a.xd, (const T*)a.dg, a.row_index, nullptr, a.d, a.f, (T*)a.dwg},
+             {(const T*)a.xd, (const T*)a.du, a.row_index, nullptr, a.d, a.f, (T*)a.dwu}},
+            3};
+}
+template <typename T>
+WgradJobs<T> wgrad_jobs(const Mlp2Args& a) {
+    return {{{(const T*)a.a_buf, (const T*)a.dy, nullptr, a.dy_index, a.f, a.d, (T*)a.dw2},
+             {(const T*)a.xd, (const T*)a.dh, a.row_index, nullptr, a.d, a.f, (T*)a.dw1}},
+            2};
+}
+
 // sigmoid with the hardware exp2 and reciprocal (each good to about 1 ulp): the results are rounded to bf16, and
 // the library-grade expf and IEEE division cost as much as a quarter of a tile's main loop in the fused epilogues.
 __device__ __forceinline__ float fast_sigmoid(float g) {

@@ -224,21 +224,10 @@ XMOE_DIRECT_KERNEL ffn_dx_direct_kernel(const bf16_t* __restrict__ dG, const bf1
     dir_store(acc, smem, dXd + (size_t)t.row0 * d + n0, d, t.rows, d - n0);
 }
 
-// Weight gradients dW_e[m, n] = sum over the expert's rows r of P[r, m] * Q[r, n], all of a call's in one launch, the
-// experts with the most rows first; a matrix's tiles are cut into at most eight runs, dealt to the XCDs in turn.
-struct DirectWgrad {
-    const bf16_t *P, *Q;
-    const int32_t *p_index, *q_index;   // or NULL; at most one
-    int M, N, tiles_m;
-    bf16_t* dW;
-};
-struct DirectWgrads {
-    DirectWgrad job[3];
-    int n_jobs, tiles, run, runs;   // tiles of a matrix, tiles of a run, runs of a matrix
-};
+// Weight gradients
 template <bool GP, bool GQ>
-__device__ __forceinline__ void wgrad_direct_tile(const DirectWgrad& j, int u, int e, int lo, int K, char* smem) {
-    const int m0 = (u % j.tiles_m) * 128, n0 = (u / j.tiles_m) * 128;
+__device__ __forceinline__ void wgrad_direct_tile(const WgradJob<bf16_t>& j, int u, int e, int lo, int K, char* smem) {
+    const int tiles_m = (j.M + 127) / 128, m0 = (u % tiles_m) * 128, n0 = (u / tiles_m) * 128;
     tile_f32x16_t acc[2][2];
     tile_zero<true>(acc);
     if (K > 0) {
@@ -250,13 +239,12 @@ __device__ __forceinline__ void wgrad_direct_tile(const DirectWgrad& j, int u, i
     }
     dir_store(acc, smem, j.dW + (size_t)e * j.M * j.N + (size_t)m0 * j.N + n0, j.N, j.M - m0, j.N - n0);
 }
-XMOE_DIRECT_KERNEL ffn_wgrad_direct_kernel(DirectWgrads jobs, int E, const int32_t* __restrict__ off,
+XMOE_DIRECT_KERNEL ffn_wgrad_direct_kernel(WgradJobs<bf16_t> jobs, int E, const int32_t* __restrict__ off,
                                            const int32_t* __restrict__ sched) {
     __shared__ __align__(16) char smem[kDirLds];
-    const int s = blockIdx.x >> 3, r = (s / jobs.run) * 8 + (blockIdx.x & 7);   // run r of all
-    const int m = r / jobs.runs, u = (r - m * jobs.runs) * jobs.run + s % jobs.run;
-    if (m >= jobs.n_jobs * E || u >= jobs.tiles) return;
-    const DirectWgrad j = jobs.job[m % jobs.n_jobs];
+    int m, u;
+    if (!jobs.place(E, m, u)) return;
+    const WgradJob<bf16_t> j = jobs.job[m % jobs.n_jobs];
     const int e = sched[m / jobs.n_jobs], lo = off[e], K = off[e + 1] - lo;
     if (j.p_index)
         wgrad_direct_tile<true, false>(j, u, e, lo, K, smem);
@@ -400,30 +388,16 @@ int ffn_bwd_rows_direct(const FfnArgs& a, hipStream_t s) {
     return fast_act(a.d, a.f) ? bwd_rows_direct<true>(a, s) : bwd_rows_direct<false>(a, s);
 }
 
-static int launch_wgrads(DirectWgrads w, int n_jobs, int E, int d, int f, const int32_t* off, const int32_t* sched,
-                         hipStream_t s) {
-    for (int i = 0; i < n_jobs; ++i) w.job[i].tiles_m = (w.job[i].M + 127) / 128;
-    w.n_jobs = n_jobs;
-    w.tiles = ((d + 127) / 128) * ((f + 127) / 128);
-    w.run = (w.tiles + 7) / 8;
-    w.runs = (w.tiles + w.run - 1) / w.run;
-    const dim3 grid((unsigned)(((long long)n_jobs * E * w.runs + 7) / 8 * 8 * w.run));
-    XMOE_LAUNCH(K_FFN_WGRAD_DIRECT, s, hipLaunchKernelGGL(ffn_wgrad_direct_kernel, grid, dim3(256), 0, s, w, E, off, sched));
+template <class Args>
+static int bwd_wgrads(const Args& a, hipStream_t s) {
+    WgradJobs<bf16_t> jobs = wgrad_jobs<bf16_t>(a);
+    const dim3 grid = jobs.cut(a.E, a.d, a.f, 128);
+    XMOE_LAUNCH(K_FFN_WGRAD_DIRECT, s,
+                hipLaunchKernelGGL(ffn_wgrad_direct_kernel, grid, dim3(256), 0, s, jobs, a.E, a.off, a.sched));
     return XMOE_OK;
 }
-int ffn_bwd_wgrads_direct(const FfnArgs& a, hipStream_t s) {
-    DirectWgrads w = {};
-    w.job[0] = {(const bf16_t*)a.act, (const bf16_t*)a.dy, nullptr, a.dy_index, a.f, a.d, 0, (bf16_t*)a.dwd};
-    w.job[1] = {(const bf16_t*)a.xd, (const bf16_t*)a.dg, a.row_index, nullptr, a.d, a.f, 0, (bf16_t*)a.dwg};
-    w.job[2] = {(const bf16_t*)a.xd, (const bf16_t*)a.du, a.row_index, nullptr, a.d, a.f, 0, (bf16_t*)a.dwu};
-    return launch_wgrads(w, 3, a.E, a.d, a.f, a.off, a.sched, s);
-}
-int mlp2_bwd_wgrads_direct(const Mlp2Args& a, hipStream_t s) {
-    DirectWgrads w = {};
-    w.job[0] = {(const bf16_t*)a.a_buf, (const bf16_t*)a.dy, nullptr, a.dy_index, a.f, a.d, 0, (bf16_t*)a.dw2};
-    w.job[1] = {(const bf16_t*)a.xd, (const bf16_t*)a.dh, a.row_index, nullptr, a.d, a.f, 0, (bf16_t*)a.dw1};
-    return launch_wgrads(w, 2, a.E, a.d, a.f, a.off, a.sched, s);
-}
+int ffn_bwd_wgrads_direct(const FfnArgs& a, hipStream_t s) { return bwd_wgrads(a, s); }
+int mlp2_bwd_wgrads_direct(const Mlp2Args& a, hipStream_t s) { return bwd_wgrads(a, s); }
 
 template <bool FAST>
 static int mlp2_fwd_direct_as(const Mlp2Args& a, hipStream_t s) {

@@ -378,29 +378,13 @@ __global__ XMOE_TILE_BOUNDS void ffn_dx_mfma_kernel(const T* __restrict__ dG, co
 }
 
 // ---------------------------------------------------------------------------------------------------------
-// weight gradients: dW_e[m,n] = sum over the expert's rows r of P[r,m] * Q[r,n]   (K = ragged)
-//   dWd = A^T dY (M=f, N=d);  dWg = Xd^T dG, dWu = Xd^T dU (M=d, N=f).  Empty experts get zeros.
-// All of a call's weight gradients are one launch, the experts with the most rows first (sched), so the long sums start
-// early and only one tail of idle CUs is left.  A matrix's tiles are cut into at most eight runs, dealt to the XCDs in turn
-// (block b runs on XCD b % 8): the tiles of a run share operand panels in one L2.
+// weight gradients: dWd = A^T dY (M=f, N=d);  dWg = Xd^T dG, dWu = Xd^T dU (M=d, N=f)   (K = ragged).  Empty experts get
+// zeros.
 // ---------------------------------------------------------------------------------------------------------
-template <typename T>
-struct WgradJob {
-    const T *P, *Q;
-    const int32_t *p_index, *q_index;   // or NULL
-    int M, N, tiles_m;
-    T* dW;
-};
-template <typename T>
-struct WgradJobs {
-    WgradJob<T> job[3];
-    int n_jobs, tiles, run, runs;   // tiles of a matrix, tiles of a run, runs of a matrix
-};
-
 template <typename T, bool BIG, bool GP, bool GQ>
 __device__ __forceinline__ void wgrad_tile(const WgradJob<T>& j, int u, int e, int lo, int K, char* smem) {
     using S = TileShape<BIG>;
-    const int m0 = (u % j.tiles_m) * S::kM, n0 = (u / j.tiles_m) * S::kN;
+    const int tiles_m = (j.M + S::kM - 1) / S::kM, m0 = (u % tiles_m) * S::kM, n0 = (u / tiles_m) * S::kN;
     const T *P = j.P + m0 + (GP ? 0 : (size_t)lo * j.M), *Q = j.Q + n0 + (GQ ? 0 : (size_t)lo * j.N);
     const int32_t *pi = GP ? j.p_index + lo : nullptr, *qi = GQ ? j.q_index + lo : nullptr;
     T* dW = j.dW + (size_t)e * j.M * j.N + (size_t)m0 * j.N + n0;
@@ -430,9 +414,8 @@ template <typename T, bool BIG>
 __global__ XMOE_TILE_BOUNDS void ffn_wgrad_mfma_kernel(WgradJobs<T> jobs, int E, const int32_t* __restrict__ off,
                                                        const int32_t* __restrict__ sched) {
     __shared__ __align__(16) char smem[TileShape<BIG>::kLds];
-    const int s = blockIdx.x >> 3, r = (s / jobs.run) * 8 + (blockIdx.x & 7);   // run r of all
-    const int m = r / jobs.runs, u = (r - m * jobs.runs) * jobs.run + s % jobs.run;
-    if (m >= jobs.n_jobs * E || u >= jobs.tiles) return;
+    int m, u;
+    if (!jobs.place(E, m, u)) return;
     const WgradJob<T> j = jobs.job[m % jobs.n_jobs];
     const int e = sched[m / jobs.n_jobs];
     const int lo = off[e], K = off[e + 1] - lo;
@@ -510,39 +493,18 @@ static inline bool big_wgrad_tiles(int jobs, int E, int d, int f) {
     return (long long)jobs * E * ceil_div(d, 128) * ceil_div(f, 128) >= 512;
 }
 
-template <typename T>
-static int launch_wgrad(WgradJobs<T> jobs, int n_jobs, int E, int d, int f, const int32_t* off, const int32_t* sched,
-                        hipStream_t s) {
-    const bool big = big_wgrad_tiles(n_jobs, E, d, f);
-    const int tile = big ? 128 : 64;
-    for (int i = 0; i < n_jobs; ++i) jobs.job[i].tiles_m = ceil_div(jobs.job[i].M, tile);
-    jobs.n_jobs = n_jobs;
-    jobs.tiles = ceil_div(d, tile) * ceil_div(f, tile);
-    jobs.run = ceil_div(jobs.tiles, 8);
-    jobs.runs = ceil_div(jobs.tiles, jobs.run);
-    const dim3 grid(((long long)n_jobs * E * jobs.runs + 7) / 8 * 8 * jobs.run);
+template <typename T, class Args>
+static int wgrad_call(const Args& a, hipStream_t s) {
+    WgradJobs<T> jobs = wgrad_jobs<T>(a);
+    const bool big = big_wgrad_tiles(jobs.n_jobs, a.E, a.d, a.f);
+    const dim3 grid = jobs.cut(a.E, a.d, a.f, big ? 128 : 64);
     if (big)
         XMOE_LAUNCH(K_FFN_WGRAD_MFMA, s, hipLaunchKernelGGL((ffn_wgrad_mfma_kernel<T, true>), grid, dim3(256), 0, s, jobs,
-                                                            E, off, sched));
+                                                            a.E, a.off, a.sched));
     else
         XMOE_LAUNCH(K_FFN_WGRAD_MFMA, s, hipLaunchKernelGGL((ffn_wgrad_mfma_kernel<T, false>), grid, dim3(128), 0, s,
-                                                            jobs, E, off, sched));
+                                                            jobs, a.E, a.off, a.sched));
     return XMOE_OK;
-}
-
-template <typename T>
-static int wgrad_call(const FfnArgs& a, hipStream_t s) {
-    WgradJobs<T> jobs = {{{(const T*)a.act, (const T*)a.dy, nullptr, a.dy_index, a.f, a.d, 0, (T*)a.dwd},
-                          {(const T*)a.xd, (const T*)a.dg, a.row_index, nullptr, a.d, a.f, 0, (T*)a.dwg},
-                          {(const T*)a.xd, (const T*)a.du, a.row_index, nullptr, a.d, a.f, 0, (T*)a.dwu}}};
-    return launch_wgrad<T>(jobs, 3, a.E, a.d, a.f, a.off, a.sched, s);
-}
-template <typename T>
-static int wgrad_call(const Mlp2Args& a, hipStream_t s) {
-    WgradJobs<T> jobs = {{{(const T*)a.a_buf, (const T*)a.dy, nullptr, a.dy_index, a.f, a.d, 0, (T*)a.dw2},
-                          {(const T*)a.xd, (const T*)a.dh, a.row_index, nullptr, a.d, a.f, 0, (T*)a.dw1},
-                          {}}};
-    return launch_wgrad<T>(jobs, 2, a.E, a.d, a.f, a.off, a.sched, s);
 }
 
 template <typename T, bool BIG>

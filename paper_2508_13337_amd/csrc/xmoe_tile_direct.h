@@ -614,3 +614,6 @@ __device__ __forceinline__ void dir_dact_rounds(const tile_f32x16_t (&acc)[2][2]
 }
 
 }  // namespace xmoe
+
+#undef XMOE_LDS_PTR
+#undef XMOE_GLB_PTR
