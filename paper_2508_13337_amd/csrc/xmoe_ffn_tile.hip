@@ -6,7 +6,7 @@
 //
 // Measured (MI355X, one training step of the layer, row tiles numbered down the segments -> runs of neighbouring tiles per
 // XCD; float32: with the float32 matrix instruction -> as three bf16 parts as well):
-//   float32 T 2048 d 1024 f 704, 16 experts + 1 shared, k 4:   1602 -> 1055 us, the products at 86 to 154 TFLOP/s
+//   float32 T 2048 d 1024 f 704, 16 experts + 1 shared, k 4:   1613 -> 1108 us, the products at 85 to 147 TFLOP/s
 //   bf16    T 3001 d 1000 f 712, 24 experts + 1 shared, k 3:    627 ->  558 us (417 on the 128 x 128 direct tiles)
 #include "xmoe_ffn.h"
 #include "xmoe_tile_gemm.h"

@@ -31,9 +31,11 @@
 // 16-byte loads at the rate of aligned ones but for the lines they straddle, so an odd leading dimension costs no scalar
 // path.  Only a vector that crosses the end of K or of the columns is fetched element by element.
 //
-// Bound: float32 by the matrix cores and the split's vector instructions between them (gate/up of T 2048, d 1024, f 704, 16
-// experts + 1: 344 -> 189 us, the matrix cores busy 45 % of it); bf16 by latency (512 clocks of matrix work per step and
-// wave, 44 % of a wave's time is waits, the matrix cores are busy 15 %).
+// Bound: float32 by the matrix cores and the vector instructions of the split and of the small products' sums between them
+// (gate/up of T 2048, d 1024, f 704, 16 experts + 1: 344 -> 201 us, the matrix cores busy 40 % of it); float32 with few tiles
+// and K up to 256 by the chain of a step (T 256 d 128 f 64, 8 experts, whole step: 89 us with the float32 instruction, 94
+// now); bf16 by latency (512 clocks of matrix work per step and wave, 44 % of a wave's time is waits, the matrix cores are
+// busy 15 %).
 #pragma once
 
 #include <type_traits>
